@@ -223,7 +223,7 @@ int slapo_gemm_kernel_name(int dtype, int layout, int epilogue, int64_t M, int64
                            int weight_grad, int with_ws, char *buf, size_t len);
 
 /* Weight gradient C[M,N] (+)= A[K,M]^T B[K,N] (layout 2 with K = tokens; accumulate != 0 adds to C). When the
- * output has too few 128x128 tiles to fill the chip and K is a long multiple of 256 (at least 6144), the product is
+ * output has too few 128x128 tiles to fill the chip and K is long (at least 6144), the product is
  * computed in up to 8 K ranges at once, as fp32 partial tiles in `ws` that a second kernel adds in range order (bitwise
  * reproducible); an output with many tiles whose grid ends in a thin round uses `ws` as slapo_gemm_ex does.
  * slapo_weight_grad_workspace writes the bytes of `ws` a shape wants (0: the plain GEMM is used

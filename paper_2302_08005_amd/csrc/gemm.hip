@@ -3,8 +3,8 @@
 // derivative and residual-add epilogues applied to the fp32 accumulators in registers.
 //
 // bf16 path: 8 wavefronts in a 2x4 grid (or 2 x 2x2 with an in-block K split), each owning a block of
-// v_mfma_f32_32x32x16_bf16 tiles. K slabs go global -> LDS by direct loads into a ring of LDS stages (or,
-// for shapes with a K tail, through registers), one barrier per slab. Operands whose contraction index is
+// v_mfma_f32_32x32x16_bf16 tiles. K slabs go global -> LDS by direct loads into a ring of LDS stages, one barrier
+// per slab; a K that is no multiple of the slab ends in a zero-filled one. Operands whose contraction index is
 // contiguous in memory are read from LDS with 16-byte reads; operands whose contraction index is the
 // strided one (the "N" operand of dY*W and both operands of dY^T*X) stay in their memory order in LDS and
 // are read with the transposing ds_read_b64_tr_b16, so no transposed copy of any tensor is ever made.
@@ -87,8 +87,8 @@ __device__ __forceinline__ GateTerms gate_terms(float u, float w) {
 }
 
 // LDS layouts. Every tile sits in LDS unpadded and in memory order, 16 bytes of thread t of a slab at byte
-// 16 t of the stage, so that a slab can be brought in either through registers or by the direct
-// global -> LDS loads of gfx950 (one wave-level load fills 1 KB of consecutive LDS, lane l at byte 16 l).
+// 16 t of the stage, as the direct global -> LDS loads of gfx950 write it (one wave-level load fills 1 KB of
+// consecutive LDS, lane l at byte 16 l).
 // Bank conflicts are avoided by permuting, inside each tile row, which 16-byte chunk of global memory a
 // thread fetches. The LDS has 64 banks of 4 B: 16 lanes of a 16-byte access, and 32 lanes of a transposing
 // 8-byte read, are checked against each other for conflicts. Measured peak rates per CU with conflict-free
@@ -108,12 +108,12 @@ __device__ __forceinline__ GateTerms gate_terms(float u, float w) {
 // costs as much LDS time as reading it three times; measured on the chip, fragment reads running beside
 // register-staged stores take the sum of both times, beside direct loads the maximum.
 
-// PF: slabs of register prefetch of the register-staged path (NS == 0, two LDS stages).
-// NS: LDS stages of the direct-load path (0 = register-staged).
+// NS: LDS stages.
 // PW: extra wavefronts that do nothing but issue the direct loads (0 = every wavefront loads its share). A
 //     vector-memory instruction holds its wavefront at issue while the address unit is busy, and the 32 KB
 //     a 128x128 tile needs per slab keep that unit (64 B per clock) busy for as long as the slab's MFMAs
 //     take; with the loads on wavefronts of their own, that wait never stands in front of an MFMA.
+// KTAIL: K is no multiple of BK and an operand is contiguous along it.
 // F16: the 16-bit elements are IEEE half instead of bf16 (same data movement; MFMA and conversions differ).
 // Position of workgroup `bid` of a grid of tiles_m x tiles_n tiles. Workgroups are handed to the 8 XCDs round-robin;
 // the ids are renumbered so that each XCD (own L2) gets a run of consecutive tile ids, and the ids are ordered in
@@ -144,7 +144,7 @@ __device__ __forceinline__ TilePos tile_position(int bid, int tiles_m, int tiles
 // thin: workgroup tail_begin + r * (tiles in the tail) + t covers range r of tail tile t and leaves its fp32
 // accumulators as a full tile in hyb_ws[(t * tail_splits + r)][BM][BN]; hybrid_reduce_kernel adds the ranges in
 // order and applies the epilogue. Plain launches pass tail_begin = number of tiles.
-template <int LAYOUT, int BM, int BN, int BK, int WGM, int WGN, int KS, int PF, int NS, int PW, bool KTAIL, int EPI,
+template <int LAYOUT, int BM, int BN, int BK, int WGM, int WGN, int KS, int NS, int PW, bool KTAIL, int EPI,
           bool F16 = false, bool HYB = false>
 __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(int M, int N, int K,
                                                                   const bf16_t* __restrict__ A,
@@ -164,17 +164,14 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
   // larger wave tile).
   constexpr int NCOMP = WGM * WGN * KS * 64;         // threads that compute
   constexpr int NTHR = PW ? PW * 64 : NCOMP;         // threads that load
-  static_assert(PW == 0 || NS > 0, "loader wavefronts belong to the direct path");
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
   constexpr int A_LOADS = BM * BK / 8 / NTHR, B_LOADS = BN * BK / 8 / NTHR;
   static_assert(A_LOADS >= 1 && B_LOADS >= 1, "tile too small for the thread count");
   static_assert(BK == 32 || BK == 64 || BK == 128, "swizzles written for 64- to 256-byte tile rows");
-  static_assert(!(KTAIL && NS), "a direct load cannot zero-fill the K tail");
-  static_assert(NS == 0 || (NS >= 2 && NS <= 10), "stage count");
+  static_assert(NS >= 2 && NS <= 10, "stage count");
   constexpr int PA = A_KC ? BK : BM;        // row pitch of the A tile in elements (unpadded)
   constexpr int PB = B_KC ? BK : BN;
   constexpr int SA = BM * BK, SB = BN * BK;  // elements per stage
-  constexpr int NSTG = NS ? NS : 2;
   auto swzK = [](int row) { constexpr int RP = BK >= 128 ? 1 : 128 / BK; return (row / RP) % (BK / 8); };
   auto swzM = [](int krow, auto width) {
     constexpr int W = decltype(width)::value;
@@ -189,16 +186,15 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
     return W >= 128 ? (((q & 3) << 1) ^ ((q >> 3) & 1)) : (((q & 1) << 1) ^ ((q >> 2) & 1));
   };
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-  bf16_t* sA = smem;               // [NSTG][SA]
-  bf16_t* sB = smem + NSTG * SA;   // [NSTG][SB]
+  bf16_t* sA = smem;               // [NS][SA]
+  bf16_t* sB = smem + NS * SA;   // [NS][SB]
 
   const int tiles_n = (N + BN - 1) / BN, tiles_m = (M + BM - 1) / BM;
   const int nblk = tiles_m * tiles_n;
   // Split-K instances: `act` K ranges per tile, every (range, tile) pair a workgroup; consecutive ids walk the
   // tiles of one range, so the blocks an XCD holds still share operand panels.
   constexpr bool SPLITK = (EPI == EPI_SPLITK);
-  static_assert(!SPLITK || NS > 0, "split-K instances use the direct-load pipeline");
-  static_assert(!(HYB && SPLITK) && (!HYB || NS > 0), "hybrid launches use the direct-load pipeline");
+  static_assert(!(HYB && SPLITK), "one kind of K range at a time");
   int bid = blockIdx.x;
   bool is_tail = false;          // (uniform for the workgroup)
   int tail_range = 0, tail_tile = 0;
@@ -222,14 +218,11 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
   const int kgroup = cw / (WGM * WGN), wave = cw % (WGM * WGN);
   const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
 
-  // Each thread moves A_LOADS + B_LOADS 16-byte pieces per slab: thread t owns position t of the slab (tile
-  // row t / CA, chunk position t % CA), piece i sits NTHR positions (RSA tile rows) further. Pieces outside
-  // M or N are read from a clamped (valid) address and never reach a stored output, so only the K tail
-  // needs zero fill; all loads are unconditional, which lets the compiler keep the next slabs' loads in
-  // flight while it waits for the oldest ones only.
+  // Each loading thread moves A_LOADS + B_LOADS 16-byte pieces per slab: thread t owns position t of the slab (tile
+  // row t / CA, chunk position t % CA), piece i sits NTHR positions (RSA tile rows) further. Pieces outside M or N are
+  // whatever the buffer holds there (zero past its end) and never reach a stored output.
   constexpr int CA = A_KC ? BK / 8 : BM / 8, CB = B_KC ? BK / 8 : BN / 8;   // pieces per tile row
   constexpr int RSA = NTHR / CA, RSB = NTHR / CB;                            // tile rows between pieces
-  static_assert(NS != 0 || (RSA % 16 == 0 && RSB % 16 == 0), "the K-tail test assumes one column per thread");
   const int ar = tid / CA, br = tid / CB;
   // column (in elements) of the chunk fetched for the position in tile row r
   auto col_a = [&](int r) {
@@ -238,22 +231,7 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
   auto col_b = [&](int r) {
     return B_KC ? ((tid % CB) ^ swzK(r)) * 8 : ((tid % CB) ^ (swzM(r, std::integral_constant<int, BN>{}) << 1)) * 8;
   };
-  const int ac = col_a(ar), bc = col_b(br);
   const int lda = A_KC ? K : M, ldb = B_KC ? K : N;
-  const bf16_t* ga[A_LOADS];
-  const bf16_t* gb[B_LOADS];
-#pragma unroll
-  for (int i = 0; i < A_LOADS; ++i) {
-    const int tr = ar + i * RSA;
-    if (A_KC) { int r = m0 + tr; r = r < M ? r : M - 1; ga[i] = A + (int64_t)r * lda + col_a(tr); }
-    else { int c = m0 + col_a(tr); c = c < M ? c : M - 8; ga[i] = A + (int64_t)tr * lda + c; }
-  }
-#pragma unroll
-  for (int i = 0; i < B_LOADS; ++i) {
-    const int tr = br + i * RSB;
-    if (B_KC) { int r = n0 + tr; r = r < N ? r : N - 1; gb[i] = B + (int64_t)r * ldb + col_b(tr); }
-    else { int c = n0 + col_b(tr); c = c < N ? c : N - 8; gb[i] = B + (int64_t)tr * ldb + c; }
-  }
   const int64_t stepA = A_KC ? BK : (int64_t)BK * lda, stepB = B_KC ? BK : (int64_t)BK * ldb;
 
   // slabs of this workgroup: all of them, or the split's range (the host makes every range non-empty)
@@ -261,47 +239,7 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
   const int nk_per = (nk_all + splits - 1) / splits;
   const int ks0 = split * nk_per;   // (split = 0, splits = 1 for workgroups that walk all of K)
   const int nk = nk_all - ks0 < nk_per ? nk_all - ks0 : nk_per;
-  static_assert(PF == 1 || PF == 2, "register prefetch depth");
-  u32x4_t ra0[A_LOADS], rb0[B_LOADS], ra1[A_LOADS], rb1[B_LOADS];   // register sets: slab k lives in set k % PF
-  // Every call issues exactly A_LOADS + B_LOADS loads (slab index clamped to the last one), so the number
-  // of loads in flight is the same on every path and the oldest slab can be awaited on its own.
-  auto load_global = [&](int kstep, u32x4_t (&ra)[A_LOADS], u32x4_t (&rb)[B_LOADS]) {
-    kstep = kstep < nk ? kstep : nk - 1;
-    const int k0 = kstep * BK;
-#pragma unroll
-    for (int i = 0; i < A_LOADS; ++i) {
-      const bf16_t* p = ga[i] + kstep * stepA;
-      if (KTAIL) {  // pieces at or beyond K: read a valid address, zero the value
-        const bool ok = A_KC ? (k0 + ac < K) : (k0 + ar + i * RSA < K);
-        p = ok ? p : A;
-        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(p);
-        ra[i] = ok ? v : u32x4_t{0, 0, 0, 0};
-      } else {
-        ra[i] = *reinterpret_cast<const u32x4_t*>(p);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < B_LOADS; ++i) {
-      const bf16_t* p = gb[i] + kstep * stepB;
-      if (KTAIL) {
-        const bool ok = B_KC ? (k0 + bc < K) : (k0 + br + i * RSB < K);
-        p = ok ? p : B;
-        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(p);
-        rb[i] = ok ? v : u32x4_t{0, 0, 0, 0};
-      } else {
-        rb[i] = *reinterpret_cast<const u32x4_t*>(p);
-      }
-    }
-  };
-  auto store_lds = [&](int stage, const u32x4_t (&ra)[A_LOADS], const u32x4_t (&rb)[B_LOADS]) {
-    bf16_t* a = sA + stage * SA + tid * 8;
-    bf16_t* b = sB + stage * SB + tid * 8;
-#pragma unroll
-    for (int i = 0; i < A_LOADS; ++i) *reinterpret_cast<u32x4_t*>(a + i * NTHR * 8) = ra[i];
-#pragma unroll
-    for (int i = 0; i < B_LOADS; ++i) *reinterpret_cast<u32x4_t*>(b + i * NTHR * 8) = rb[i];
-  };
-  // Direct path: the same pieces, written by the memory system straight into LDS (wave-uniform LDS base,
+  // The pieces are written by the memory system straight into LDS (wave-uniform LDS base,
   // lane l lands 16 l bytes behind it). Completion is tracked by the vector-memory counter. The loads are
   // buffer loads: resource = the operand from the tile's origin on, per-lane byte offset fixed for the whole
   // K loop, the K step in the scalar offset. Issuing a slab then takes no vector-ALU instruction at all,
@@ -326,10 +264,24 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
     if constexpr (UNTRACKED) buffer_load_lds_16_untracked(base, bytes, lds, voffset, soffset);
     else buffer_load_lds_16(base, bytes, lds, voffset, soffset);
   };
+  // A K that is no multiple of BK ends in a partial slab. Operands whose rows run along the other dimension end with
+  // the buffer there (zeros by the bounds above); the pieces of a K-contiguous row that lie at or beyond K would read
+  // the next row, so the last slab sends them out of bounds (K % 8 == 0: a piece lies on one side as a whole). KTAIL:
+  // instances for such K of their own, because the test alone costs the others 1.5 % (loads issued by computing waves).
   auto load_direct = [&](int kstep, int stage) {
     bf16_t* a = sA + stage * SA + lw * 512;
     bf16_t* b = sB + stage * SB + lw * 512;
     const unsigned soa = (unsigned)(ks0 + kstep) * (unsigned)(stepA * 2), sob = (unsigned)(ks0 + kstep) * (unsigned)(stepB * 2);
+    const int left = K - (ks0 + kstep) * BK;   // (uniform)
+    if (KTAIL && (A_KC || B_KC) && left < BK) {
+#pragma unroll
+      for (int i = 0; i < A_LOADS; ++i)
+        dma16(base_a, bytes_a, a + i * NTHR * 8, !A_KC || col_a(ar + i * RSA) < left ? voa[i] : 0xfffffff0u, soa);
+#pragma unroll
+      for (int i = 0; i < B_LOADS; ++i)
+        dma16(base_b, bytes_b, b + i * NTHR * 8, !B_KC || col_b(br + i * RSB) < left ? vob[i] : 0xfffffff0u, sob);
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < A_LOADS; ++i) dma16(base_a, bytes_a, a + i * NTHR * 8, voa[i], soa);
 #pragma unroll
@@ -436,46 +388,19 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
     }
   };
 
-  if constexpr (NS == 0) {
-    // Register-staged pipeline: the slab of k-step k is computed from LDS stage k&1 while the global loads
-    // of the next PF slabs are in flight in registers (register set k % PF holds slab k); a slab is written
-    // to LDS right after the compute of the step before it. With PF == 2 the slab count must be even (the
-    // host falls back to PF == 1 otherwise). Loads and stores are issued on every step (slab index
-    // clamped; the last steps re-fetch the last slab into a stage nobody reads): with every step alike,
-    // the wait before an LDS store covers the oldest slab only and the newer loads stay in flight.
-    load_global(0, ra0, rb0);
-    if (PF > 1) load_global(1, ra1, rb1);
-    store_lds(0, ra0, rb0);
-    __syncthreads();
-    if (PF == 1) {
-      for (int k = 0; k < nk; ++k) {
-        load_global(k + 1, ra0, rb0);
-        compute(k & 1);
-        store_lds((k + 1) & 1, ra0, rb0);
-        __syncthreads();
-      }
-    } else {
-      for (int k = 0; k < nk; k += 2) {
-        load_global(k + 2, ra0, rb0);
-        compute(0);
-        store_lds(1, ra1, rb1);
-        __syncthreads();
-        load_global(k + 3, ra1, rb1);
-        compute(1);
-        store_lds(0, ra0, rb0);
-        __syncthreads();
-      }
-    }
-  } else {
-    // Direct pipeline over a ring of NS stages, slab j in stage j % NS (at least NS - 1 slabs). Step k issues the loads of slab k + NS - 1 into the stage that step k - 1 computed from (free
+  {
+    // Pipeline over a ring of NS stages, slab j in stage j % NS. Step k issues the loads of slab k + NS - 1
+    // into the stage that step k - 1 computed from (free
     // since the barrier that ended step k - 1), computes slab k, then waits until its own loads of slab
     // k + 1 have landed (the younger ones stay in flight) and meets the other wavefronts at the barrier.
     constexpr int LPS = A_LOADS + B_LOADS;   // loads per slab and loading wavefront
     if (is_loader) {
 #pragma unroll
-      for (int j = 0; j < NS - 1; ++j) load_direct(j, j);
+      for (int j = 0; j < NS - 1; ++j)
+        if (j < nk) load_direct(j, j);   // (uniform)
     }
-    wait_loads_and_lds<(NS - 2) * LPS>();
+    if (nk >= NS - 1) wait_loads_and_lds<(NS - 2) * LPS>();
+    else wait_loads_and_lds<0>();
     block_barrier();
     if (PW && is_loader) {
       // loader wavefronts: issue, wait for the oldest slab, meet the others; nothing else
@@ -668,7 +593,7 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
 
 template <int BM, int BN, int BK, int WGM, int WGN, int KS, int NS>
 constexpr size_t gemm_lds_bytes() {
-  constexpr size_t main_bytes = (size_t)(NS ? NS : 2) * (BM + BN) * BK * sizeof(bf16_t);
+  constexpr size_t main_bytes = (size_t)NS * (BM + BN) * BK * sizeof(bf16_t);
   constexpr size_t epi_bytes = (size_t)WGM * WGN * 32 * (BN / WGN + 4) * sizeof(float);
   constexpr size_t red_bytes = KS == 2 ? (size_t)BM * BN * sizeof(float) : 0;
   constexpr size_t m1 = main_bytes > epi_bytes ? main_bytes : epi_bytes;
@@ -732,29 +657,27 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(int M, int N, int K, cons
     }
 }
 
-// epilogue / layout pairs the layer itself uses; only these get the tuned (deep-prefetch) kernels
+// epilogue / layout pairs the layer itself uses; the others exist as 128x128 tiles only
 constexpr bool epi_used(int layout, int epi) {
   return layout == GEMM_NT ? (epi == EPI_NONE || epi == EPI_BIAS || epi == EPI_BIAS_ACT || epi == EPI_GATE)
        : layout == GEMM_NN ? (epi == EPI_NONE || epi == EPI_DACT || epi == EPI_ADD || epi == EPI_DGATE)
                            : (epi == EPI_NONE || epi == EPI_ADD);
 }
 
-template <int LAYOUT, int BM, int BN, int BK, int WGM, int WGN, int KS, int PF, int NS, int PW, bool KTAIL, bool F16>
+template <int LAYOUT, int BM, int BN, int WGM, int WGN, int KS, int NS, int PW, bool F16, bool ALL_EPI = false>
 static void launch_bf16_tile(int epi, int act, int M, int N, int K, const void* A, const void* B, void* C,
                              const void* bias, const void* aux_in, void* aux_out, hipStream_t st) {
   const int tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-  const size_t lds = gemm_lds_bytes<BM, BN, BK, WGM, WGN, KS, NS>();
+  const size_t lds = gemm_lds_bytes<BM, BN, 64, WGM, WGN, KS, NS>();
 #define SLAPO_GEMM(E)                                                                                       \
   do {                                                                                                      \
-    if constexpr (KTAIL || epi_used(LAYOUT, E)) {                                                           \
-      auto kern = gemm_bf16_kernel<LAYOUT, BM, BN, BK, WGM, WGN, KS, PF, NS, PW, KTAIL, E, F16>;                           \
+    if constexpr (ALL_EPI || epi_used(LAYOUT, E)) {                                                         \
+      auto kern = LAYOUT == GEMM_TN || K % 64 == 0 ? gemm_bf16_kernel<LAYOUT, BM, BN, 64, WGM, WGN, KS, NS, PW, false, E, F16> \
+                                                   : gemm_bf16_kernel<LAYOUT, BM, BN, 64, WGM, WGN, KS, NS, PW, LAYOUT != GEMM_TN, E, F16>; \
       (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);  \
       hipLaunchKernelGGL(kern, dim3(tiles), dim3((WGM * WGN * KS + PW) * 64), lds, st, M, N, K, (const bf16_t*)A,       \
                          (const bf16_t*)B, (bf16_t*)C, (const bf16_t*)bias, (const bf16_t*)aux_in,          \
                          (bf16_t*)aux_out, act, tiles, 1, (float*)nullptr);                                 \
-    } else {                                                                                                \
-      launch_bf16_tile<LAYOUT, 128, 128, 64, 2, 2, 1, 1, 0, 0, true, F16>(epi, act, M, N, K, A, B, C, bias, aux_in,    \
-                                                              aux_out, st);                                 \
     }                                                                                                       \
   } while (0)
   switch (epi) {
@@ -780,8 +703,8 @@ static HybridPlan hybrid_plan(int epi, int M, int N, int K) {
   const int tiles = ((M + 255) / 256) * ((N + 255) / 256);
   HybridPlan none = {tiles, 0, 1, 0}, p = none;
   static const bool disabled = debug_flag("no-hybrid");
-  if (disabled || (epi != EPI_NONE && epi != EPI_ADD) || K % 128 != 0) return none;
-  const int rem = tiles % 256, nk = K / 64;
+  if (disabled || (epi != EPI_NONE && epi != EPI_ADD)) return none;
+  const int rem = tiles % 256, nk = (K + 63) / 64;
   if (tiles <= 256 || rem == 0) return none;
   int s = 256 / rem;
   s = s > 8 ? 8 : s;
@@ -837,7 +760,8 @@ static void launch_hybrid(const HybridPlan& hp, int epi, int M, int N, int K, co
   const int grid = hp.tail_begin + hp.tail_tiles * hp.splits;
 #define SLAPO_HYB(E)                                                                                           \
   do {                                                                                                         \
-    auto kern = gemm_bf16_kernel<LAYOUT, BM, BN, 64, 2, 4, 1, 2, 2, PW, false, E, F16, true>;                  \
+    auto kern = LAYOUT == GEMM_TN || K % 64 == 0 ? gemm_bf16_kernel<LAYOUT, BM, BN, 64, 2, 4, 1, 2, PW, false, E, F16, true> \
+                                                 : gemm_bf16_kernel<LAYOUT, BM, BN, 64, 2, 4, 1, 2, PW, LAYOUT != GEMM_TN, E, F16, true>; \
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);       \
     hipLaunchKernelGGL(kern, dim3(grid), dim3((8 + PW) * 64), lds, st, M, N, K, (const bf16_t*)A, (const bf16_t*)B, \
                        (bf16_t*)C, (const bf16_t*)nullptr, (const bf16_t*)aux_in, (bf16_t*)nullptr, 0,         \
@@ -851,13 +775,12 @@ static void launch_hybrid(const HybridPlan& hp, int epi, int M, int N, int K, co
 }
 
 // Tile selection, from measurements on the layer's shapes. 256x256 tiles (8 wavefronts, 128x64 each, direct
-// loads into two stages, issued by four more wavefronts in the NT layout) when they still cover at least three quarters of the 256 CUs. Otherwise 128x128
-// tiles (8 wavefronts, 64x32 each): direct loads into a ring of four stages issued by four loader
-// wavefronts when K is a multiple of four slabs; else register-staged with two slabs of prefetch. For outputs with few tiles, 128x64
-// tiles: long K the same direct scheme with four computing wavefronts, else 128-deep slabs and two wave
-// sets splitting each slab. Other K go to the general kernel (one slab of register prefetch, zero-filled
-// tail).
-enum TileKind { TILE_256, TILE_128_SPLITSLAB, TILE_128_LOADERS, TILE_128_REGS, TILE_128x64_LOADERS, TILE_128x64_DEEP, TILE_GENERAL };
+// loads into two stages, issued by four more wavefronts in the NT layout) when they still cover at least three quarters
+// of the 256 CUs. Otherwise 128x128 tiles (8 wavefronts, 64x32 each; TN: two sets of four, 64x64 each): a ring of four
+// stages filled by four loader wavefronts. 128x64 tiles of the same form (four computing wavefronts) where all of them
+// fit one round. K needs no particular multiple: TN products with K = 2286 tokens and 768 x 3072 outputs take 18.7 us
+// (41.7 with the register-staged kernel that such K used to go to), K = 2000 and 10240 x 2560 take 107 us (170 before).
+enum TileKind { TILE_256, TILE_128_SPLITSLAB, TILE_128_LOADERS, TILE_128x64_LOADERS };
 static TileKind select_tile(int layout, int M, int N, int K, bool solo) {
   const int64_t t256 = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
   const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
@@ -868,8 +791,8 @@ static TileKind select_tile(int layout, int M, int N, int K, bool solo) {
   // 1.0; a 256x256 tile is four small ones). In the backward pass the idle CUs of a thin round are exactly where
   // the other stream's kernels run, and the same rule makes the step slower (2.7B-shaped layer: 5.39 ms against
   // 4.99 ms; on a single stream 5.06 against 5.62), so it is not applied there.
-  bool big = K % 128 == 0 && t256 >= 192;
-  if (solo && big && K % 256 == 0 && K >= 2048) {
+  bool big = t256 >= 192;
+  if (solo && big && K >= 2048) {
     const double e256 = 1.30, e128 = layout == GEMM_NT ? 1.05 : 1.0;
     const double c256 = (double)((t256 + 255) / 256) * 4.0 / e256, c128 = (double)((t128 + 255) / 256) / e128;
     big = c256 <= c128;
@@ -878,11 +801,10 @@ static TileKind select_tile(int layout, int M, int N, int K, bool solo) {
   // TN: both operands go through the transposing LDS reads (two per fragment): the 64x64 wave tile of the
   // split-slab form needs a third fewer of them per MFMA, worth 5-7 % on the weight-gradient shapes; the
   // K-contiguous layouts gain nothing from it
-  if (K % 256 == 0 && t128 >= 160) return layout == GEMM_TN ? TILE_128_SPLITSLAB : TILE_128_LOADERS;
-  if (K % 128 == 0 && (t128 >= 160 || K % 256 != 0)) return TILE_128_REGS;
-  if (K % 256 == 0 && K >= 1024) return TILE_128x64_LOADERS;
-  if (K % 256 == 0) return TILE_128x64_DEEP;
-  return TILE_GENERAL;
+  // Two rounds of 128x64 tiles are slower than one of 128x128 (768 x 3072 outputs, K = 2286: 26.8 against 18.7 us), one
+  // round is faster (2304 x 768: 14.9 against 17.4).
+  if ((int64_t)((M + 127) / 128) * ((N + 63) / 64) <= 256) return TILE_128x64_LOADERS;
+  return layout == GEMM_TN ? TILE_128_SPLITSLAB : TILE_128_LOADERS;
 }
 
 template <int LAYOUT, bool F16>
@@ -898,25 +820,20 @@ static void launch_bf16(int epi, int act, int M, int N, int K, const void* A, co
       return;
     }
   }
-  switch (select_tile(LAYOUT, M, N, K, solo)) {
+  // (epilogues that the layer never pairs with this layout come as 128x128 tiles only)
+  switch (epi_used(LAYOUT, epi) ? select_tile(LAYOUT, M, N, K, solo) : TILE_128_LOADERS) {
     case TILE_256:
       // NT: four loader wavefronts beside the eight that compute (168 registers: three wavefronts per SIMD fit; the
       // NN/TN instances need 190-230, so their wavefronts load their own shares)
-      if constexpr (LAYOUT == GEMM_NT) launch_bf16_tile<LAYOUT, 256, 256, 64, 2, 4, 1, 2, 2, 4, false, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
-      else launch_bf16_tile<LAYOUT, 256, 256, 64, 2, 4, 1, 2, 2, 0, false, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
+      launch_bf16_tile<LAYOUT, 256, 256, 2, 4, 1, 2, LAYOUT == GEMM_NT ? 4 : 0, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
       break;
     case TILE_128_SPLITSLAB:
-      launch_bf16_tile<LAYOUT, 128, 128, 64, 2, 2, 2, 2, 4, 4, false, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st); break;
+      if constexpr (LAYOUT == GEMM_TN) launch_bf16_tile<LAYOUT, 128, 128, 2, 2, 2, 4, 4, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
+      break;
     case TILE_128_LOADERS:
-      launch_bf16_tile<LAYOUT, 128, 128, 64, 2, 4, 1, 2, 4, 4, false, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st); break;
-    case TILE_128_REGS:
-      launch_bf16_tile<LAYOUT, 128, 128, 64, 2, 4, 1, 2, 0, 0, false, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st); break;
+      launch_bf16_tile<LAYOUT, 128, 128, 2, 4, 1, 4, 4, F16, true>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st); break;
     case TILE_128x64_LOADERS:
-      launch_bf16_tile<LAYOUT, 128, 64, 64, 2, 2, 1, 2, 4, 4, false, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st); break;
-    case TILE_128x64_DEEP:
-      launch_bf16_tile<LAYOUT, 128, 64, 128, 2, 2, 2, 2, 0, 0, false, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st); break;
-    default:
-      launch_bf16_tile<LAYOUT, 128, 128, 64, 2, 2, 1, 1, 0, 0, true, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st); break;
+      launch_bf16_tile<LAYOUT, 128, 64, 2, 2, 1, 4, 4, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st); break;
   }
 }
 
@@ -950,7 +867,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(int64_t chunks, int6
 // where the second kernel and the partial tiles cost more than the idle CUs).
 static int weight_grad_splits(int M, int N, int K) {
   static const bool disabled = debug_flag("no-splitk");   // A/B timing
-  if (disabled || K % 256 != 0 || N % 8 != 0) return 1;
+  if (disabled || N % 8 != 0) return 1;
   const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
   if (t128 >= 160) return 1;
   int64_t s = 256 / t128;
@@ -976,7 +893,7 @@ static void launch_splitk(int splits, int accumulate, int M, int N, int K, const
   constexpr int BM = 128, BN = 128;
   const int tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
   const size_t lds = gemm_lds_bytes<BM, BN, 64, 2, 2, 2, 4>();
-  auto kern = gemm_bf16_kernel<GEMM_TN, BM, BN, 64, 2, 2, 2, 2, 4, 4, false, EPI_SPLITK, F16>;
+  auto kern = gemm_bf16_kernel<GEMM_TN, BM, BN, 64, 2, 2, 2, 4, 4, false, EPI_SPLITK, F16>;
   (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(kern, dim3(tiles * splits), dim3((2 * 2 * 2 + 4) * 64), lds, st, M, N, K, (const bf16_t*)A,
                      (const bf16_t*)B, (bf16_t*)C, (const bf16_t*)nullptr, (const bf16_t*)nullptr,
@@ -1000,36 +917,34 @@ void launch_weight_grad(int dtype, int accumulate, int M, int N, int K, const vo
 }
 
 // The kernel instance a GEMM of this shape runs as, in the spelling of the kernel's template arguments
-// (layout, BM, BN, BK, WGM, WGN, KS, PF, NS, PW, KTAIL, epilogue, F16, HYB), as the profiler prints the symbol; for
+// (layout, BM, BN, BK, WGM, WGN, KS, NS, PW, KTAIL, epilogue, F16, HYB), as the profiler prints the symbol; for
 // the weight-gradient path (`weight_grad`) with its K ranges, if any.
 void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool solo, bool weight_grad, bool with_ws,
                    char* buf, size_t len) {
   if (dtype == DT_FP32) { snprintf(buf, len, "gemm_f32_kernel<%d>", layout); return; }
   const int f16 = dtype == DT_FP16 ? 1 : 0;
   const char* b = f16 ? "true" : "false";
+  const char* kt = layout != GEMM_TN && K % 64 != 0 ? "true" : "false";
   if (with_ws && !(weight_grad && weight_grad_splits(M, N, K) > 1) && select_tile(layout, M, N, K, false) == TILE_256) {
     const HybridPlan hp = hybrid_plan(weight_grad ? EPI_NONE : epi, M, N, K);
     if (hp.ws_bytes) {
-      snprintf(buf, len, "gemm_bf16_kernel<%d, 256, 256, 64, 2, 4, 1, 2, 2, %d, false, %d, %s, true> (%d tiles + %d tiles in %d K ranges) + hybrid_reduce_kernel",
-               layout, layout == GEMM_NT ? 4 : 0, epi, b, hp.tail_begin, hp.tail_tiles, hp.splits);
+      snprintf(buf, len, "gemm_bf16_kernel<%d, 256, 256, 64, 2, 4, 1, 2, %d, %s, %d, %s, true> (%d tiles + %d tiles in %d K ranges) + hybrid_reduce_kernel",
+               layout, layout == GEMM_NT ? 4 : 0, kt, epi, b, hp.tail_begin, hp.tail_tiles, hp.splits);
       return;
     }
   }
   if (weight_grad) {
     const int splits = weight_grad_splits(M, N, K);
     if (splits > 1) {
-      snprintf(buf, len, "gemm_bf16_kernel<2, 128, 128, 64, 2, 2, 2, 2, 4, 4, false, %d, %s, false> in %d K ranges + splitk_reduce_kernel", EPI_SPLITK, b, splits);
+      snprintf(buf, len, "gemm_bf16_kernel<2, 128, 128, 64, 2, 2, 2, 4, 4, false, %d, %s, false> in %d K ranges + splitk_reduce_kernel", EPI_SPLITK, b, splits);
       return;
     }
   }
-  static const char* const shape[] = {"256, 256, 64, 2, 4, 1, 2, 2, 0, false", "128, 128, 64, 2, 2, 2, 2, 4, 4, false",
-                                      "128, 128, 64, 2, 4, 1, 2, 4, 4, false", "128, 128, 64, 2, 4, 1, 2, 0, 0, false",
-                                      "128, 64, 64, 2, 2, 1, 2, 4, 4, false", "128, 64, 128, 2, 2, 2, 2, 0, 0, false",
-                                      "128, 128, 64, 2, 2, 1, 1, 0, 0, true"};
-  TileKind k = select_tile(layout, M, N, K, solo);
-  if (k != TILE_GENERAL && !epi_used(layout, epi)) k = TILE_GENERAL;   // epilogues the layer never pairs with this layout
-  if (k == TILE_256 && layout == GEMM_NT) snprintf(buf, len, "gemm_bf16_kernel<0, 256, 256, 64, 2, 4, 1, 2, 2, 4, false, %d, %s, false>", epi, b);
-  else snprintf(buf, len, "gemm_bf16_kernel<%d, %s, %d, %s, false>", layout, shape[(int)k], epi, b);
+  static const char* const shape[] = {"256, 256, 64, 2, 4, 1, 2, 0", "128, 128, 64, 2, 2, 2, 4, 4", "128, 128, 64, 2, 4, 1, 4, 4",
+                                      "128, 64, 64, 2, 2, 1, 4, 4"};
+  const TileKind k = epi_used(layout, epi) ? select_tile(layout, M, N, K, solo) : TILE_128_LOADERS;
+  if (k == TILE_256 && layout == GEMM_NT) snprintf(buf, len, "gemm_bf16_kernel<0, 256, 256, 64, 2, 4, 1, 2, 4, %s, %d, %s, false>", kt, epi, b);
+  else snprintf(buf, len, "gemm_bf16_kernel<%d, %s, %s, %d, %s, false>", layout, shape[(int)k], kt, epi, b);
 }
 
 void launch_gemm(int dtype, int layout, int epi, int act, int M, int N, int K, const void* A, const void* B,

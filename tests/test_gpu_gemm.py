@@ -141,3 +141,35 @@ def test_thin_last_round_in_k_ranges(dtype, layout, M, N, K):
     with pytest.raises(B.SlapoError) as e:           # a workspace that is too small is refused, not half used
         B.slapo_gemm_ex(dtype, layout, B.EPI_NONE, 0, M, N, K, A, Bm, out, ws=ws[:nbytes // 2])
     assert e.value.status == -5
+
+
+# K that is no multiple of the 64-deep slab: fewer than one slab, one element piece over, one under, odd (token counts of
+# weight gradients), against 256x256 tiles, 128x128 tiles and 128x64 tiles (all with ragged edges) and the K-range forms.
+@pytest.mark.parametrize("layout,Ks", [(B.NT, (8, 72, 200, 1016)), (B.NN, (8, 72, 200, 1016)), (B.TN, (1, 63, 65, 203, 1013))])
+@pytest.mark.parametrize("M,N", [(3592, 3336), (1664, 2056), (520, 136)])
+def test_gemm_partial_last_slab(layout, Ks, M, N):
+    for K in Ks:
+        rng = np.random.default_rng(K + M)
+        a = store(rng.standard_normal((M, K)), W.BF16)
+        b = store(rng.standard_normal((K, N)) * 0.1, W.BF16)
+        ref = a @ b                                   # fp32 on the host: far below one bf16 rounding
+        a[5] = np.nan                                 # the pieces beyond K are zeros, not the next row: only row 5 may show it
+        A = to_dev(a if layout != B.TN else a.T.copy(), W.BF16)
+        Bm = to_dev(b.T.copy() if layout == B.NT else b, W.BF16)
+        Cout = torch.empty(M, N, dtype=A.dtype, device=DEV)
+        B.slapo_gemm(W.BF16, layout, B.EPI_NONE, 0, M, N, K, A, Bm, Cout)
+        got = to_np(Cout)
+        assert np.isnan(got[5]).all()
+        got[5] = ref[5]
+        assert err(got, ref) <= 5e-3, K
+
+
+@pytest.mark.parametrize("M,N,K", [(136, 264, 8191), (4352, 4096, 1999), (1024, 1024, 12289)])
+def test_weight_gradient_in_k_ranges_of_odd_length(M, N, K):
+    rng = np.random.default_rng(K)
+    a = store(rng.standard_normal((K, M)), W.BF16)
+    b = store(rng.standard_normal((K, N)) * 0.05, W.BF16)
+    ws = torch.empty(max(B.slapo_weight_grad_workspace(W.BF16, M, N, K), 16), dtype=torch.uint8, device=DEV)
+    out = torch.empty(M, N, dtype=torch.bfloat16, device=DEV)
+    B.slapo_weight_grad(W.BF16, 0, M, N, K, to_dev(a, W.BF16), to_dev(b, W.BF16), out, ws)
+    assert err(out, a.T @ b) <= 5e-3
