@@ -55,6 +55,12 @@ template <bool F16> __device__ __forceinline__ f32x16_t mfma16(bf16x8_t a, bf16x
   else
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
+template <bool F16> __device__ __forceinline__ f32x4_t mfma16_16(bf16x8_t a, bf16x8_t b, f32x4_t c) {
+  if constexpr (F16)
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
 // acc += a b with the accumulator held in the accumulation registers (AGPRs), written out because the compiler
 // picks one MFMA form per function and takes the ordinary registers whenever everything fits into 256 of them.
 // Opaque to the compiler's hazard pass: the caller makes sure that a and b were not written by a vector-ALU

@@ -3,7 +3,9 @@
 // derivative and residual-add epilogues applied to the fp32 accumulators in registers.
 //
 // bf16 path: 8 wavefronts in a 2x4 grid (or 2 x 2x2 with an in-block K split), each owning a block of
-// v_mfma_f32_32x32x16_bf16 tiles. K slabs go global -> LDS by direct loads into a ring of LDS stages, one barrier
+// v_mfma_f32_16x16x32_bf16 tiles. That form moves half the accumulator traffic per multiply of the 32x32x16 one, and
+// under a load that is bound by power the chip holds a higher clock with it: a loop of nothing but MFMAs on random data
+// runs at 2.12 PFLOP/s (2.1 GHz) against 1.87 (1.86 GHz) with the 32x32x16 form, at the same cycle count. K slabs go global -> LDS by direct loads into a ring of LDS stages, one barrier
 // per slab; a K that is no multiple of the slab ends in a zero-filled one. Operands whose contraction index is
 // contiguous in memory are read from LDS with 16-byte reads; operands whose contraction index is the
 // strided one (the "N" operand of dY*W and both operands of dY^T*X) stay in their memory order in LDS and
@@ -109,10 +111,11 @@ __device__ __forceinline__ GateTerms gate_terms(float u, float w) {
 // register-staged stores take the sum of both times, beside direct loads the maximum.
 
 // NS: LDS stages.
-// PW: extra wavefronts that do nothing but issue the direct loads (0 = every wavefront loads its share). A
+// PW: extra wavefronts that do nothing but issue the direct loads. A
 //     vector-memory instruction holds its wavefront at issue while the address unit is busy, and the 32 KB
 //     a 128x128 tile needs per slab keep that unit (64 B per clock) busy for as long as the slab's MFMAs
 //     take; with the loads on wavefronts of their own, that wait never stands in front of an MFMA.
+//     0 = every wavefront loads its share, spread between its MFMAs (256x256 tiles, which have twice the MFMAs per byte).
 // KTAIL: K is no multiple of BK and an operand is contiguous along it.
 // F16: the 16-bit elements are IEEE half instead of bf16 (same data movement; MFMA and conversions differ).
 // Position of workgroup `bid` of a grid of tiles_m x tiles_n tiles. Workgroups are handed to the 8 XCDs round-robin;
@@ -156,7 +159,6 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
                                                                   int tail_begin, int tail_splits,
                                                                   float* __restrict__ hyb_ws) {
   constexpr bool A_KC = (LAYOUT != GEMM_TN);  // A operand contiguous along K
-  constexpr bool DBUF = (LAYOUT != GEMM_NT);  // second fragment register set (measured: +3 % TN, +2-5 % NN, -1 % NT)
   constexpr bool B_KC = (LAYOUT == GEMM_NT);
   // KS == 2: two sets of WGM x WGN wavefronts share the output tile; set g multiplies the g-th half of
   // every K slab and the two accumulator sets are added through LDS before the epilogue. This doubles the
@@ -164,15 +166,16 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
   // larger wave tile).
   constexpr int NCOMP = WGM * WGN * KS * 64;         // threads that compute
   constexpr int NTHR = PW ? PW * 64 : NCOMP;         // threads that load
-  constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
+  constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
   constexpr int A_LOADS = BM * BK / 8 / NTHR, B_LOADS = BN * BK / 8 / NTHR;
   static_assert(A_LOADS >= 1 && B_LOADS >= 1, "tile too small for the thread count");
-  static_assert(BK == 32 || BK == 64 || BK == 128, "swizzles written for 64- to 256-byte tile rows");
+  static_assert(BK == 64, "swizzles and fragment addresses written for 128-byte tile rows");
+  static_assert(TM % 2 == 0, "tile rows are multiplied in pairs");
   static_assert(NS >= 2 && NS <= 10, "stage count");
   constexpr int PA = A_KC ? BK : BM;        // row pitch of the A tile in elements (unpadded)
   constexpr int PB = B_KC ? BK : BN;
   constexpr int SA = BM * BK, SB = BN * BK;  // elements per stage
-  auto swzK = [](int row) { constexpr int RP = BK >= 128 ? 1 : 128 / BK; return (row / RP) % (BK / 8); };
+  auto swzK = [](int row) { return (row / 2) % 8; };
   auto swzM = [](int krow, auto width) {
     constexpr int W = decltype(width)::value;
     static_assert(W >= 64, "at least four 32-byte granules per tile row");
@@ -258,8 +261,9 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
   const unsigned bytes_a = records((int64_t)M * K - origin_a), bytes_b = records((int64_t)N * K - origin_b);
   const int lw = __builtin_amdgcn_readfirstlane(PW ? cw - NCOMP / 64 : cw);   // index among the loading wavefronts
   // Fragments of an operand that is not contiguous along K come through transposing reads, which the compiler would
-  // hold back behind every direct load this wavefront has in flight (common.h): those instances issue their own.
-  constexpr bool UNTRACKED = !(A_KC && B_KC) && PW == 0;
+  // hold back behind every direct load this wavefront has in flight (common.h): wavefronts that also compute issue
+  // their loads where it does not see them.
+  constexpr bool UNTRACKED = PW == 0;
   auto dma16 = [](const bf16_t* base, unsigned bytes, bf16_t* lds, unsigned voffset, unsigned soffset) {
     if constexpr (UNTRACKED) buffer_load_lds_16_untracked(base, bytes, lds, voffset, soffset);
     else buffer_load_lds_16(base, bytes, lds, voffset, soffset);
@@ -268,132 +272,171 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
   // the buffer there (zeros by the bounds above); the pieces of a K-contiguous row that lie at or beyond K would read
   // the next row, so the last slab sends them out of bounds (K % 8 == 0: a piece lies on one side as a whole). KTAIL:
   // instances for such K of their own, because the test alone costs the others 1.5 % (loads issued by computing waves).
-  auto load_direct = [&](int kstep, int stage) {
-    bf16_t* a = sA + stage * SA + lw * 512;
-    bf16_t* b = sB + stage * SB + lw * 512;
-    const unsigned soa = (unsigned)(ks0 + kstep) * (unsigned)(stepA * 2), sob = (unsigned)(ks0 + kstep) * (unsigned)(stepB * 2);
+  auto load_piece = [&](int kstep, int stage, int i) {   // piece i of the A (i < A_LOADS) or B tile of a slab
     const int left = K - (ks0 + kstep) * BK;   // (uniform)
-    if (KTAIL && (A_KC || B_KC) && left < BK) {
-#pragma unroll
-      for (int i = 0; i < A_LOADS; ++i)
-        dma16(base_a, bytes_a, a + i * NTHR * 8, !A_KC || col_a(ar + i * RSA) < left ? voa[i] : 0xfffffff0u, soa);
-#pragma unroll
-      for (int i = 0; i < B_LOADS; ++i)
-        dma16(base_b, bytes_b, b + i * NTHR * 8, !B_KC || col_b(br + i * RSB) < left ? vob[i] : 0xfffffff0u, sob);
-      return;
+    const bool last = KTAIL && (A_KC || B_KC) && left < BK;
+    if (i < A_LOADS) {
+      bf16_t* a = sA + stage * SA + lw * 512;
+      const unsigned soa = (unsigned)(ks0 + kstep) * (unsigned)(stepA * 2);
+      dma16(base_a, bytes_a, a + i * NTHR * 8, !last || !A_KC || col_a(ar + i * RSA) < left ? voa[i] : 0xfffffff0u, soa);
+    } else {
+      i -= A_LOADS;
+      bf16_t* b = sB + stage * SB + lw * 512;
+      const unsigned sob = (unsigned)(ks0 + kstep) * (unsigned)(stepB * 2);
+      dma16(base_b, bytes_b, b + i * NTHR * 8, !last || !B_KC || col_b(br + i * RSB) < left ? vob[i] : 0xfffffff0u, sob);
     }
+  };
+  auto load_direct = [&](int kstep, int stage) {
 #pragma unroll
-    for (int i = 0; i < A_LOADS; ++i) dma16(base_a, bytes_a, a + i * NTHR * 8, voa[i], soa);
-#pragma unroll
-    for (int i = 0; i < B_LOADS; ++i) dma16(base_b, bytes_b, b + i * NTHR * 8, vob[i], sob);
+    for (int i = 0; i < A_LOADS + B_LOADS; ++i) load_piece(kstep, stage, i);
   };
 
-  f32x16_t acc[TM][TN];
+  f32x4_t acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
-  // Per-lane fragment addressing (stage 0, k-step 0).
-  // K-contiguous: chunk 2*ks + lane/32 of row lane%32, stored at position (2*ks + lane/32) ^ swzK =
-  // (2*ks ^ fsw) with the low bit folded into the base.
-  const int fsw = swzK(lane & 31) & ~1;
-  const int kc_low = (((lane >> 5) ^ swzK(lane & 31)) & 1) << 3;
-  const int fa_base = (wm0 + (lane & 31)) * PA + kc_low;
-  const int fb_base = (wn0 + (lane & 31)) * PB + kc_low;
-  // M-contiguous: the lane reads 4 elements at k-row krow_l (+4 for the upper half of the fragment), column
-  // 16*((lane/16)%2) + 4*(lane%4) of the 32-wide tile; the 32-byte granule index g is stored at g ^ swzM.
-  const int krow_l = 8 * (lane >> 5) + ((lane & 15) >> 2);
+  // Per-lane fragment addressing (stage 0, k-step 0). A fragment is 16 rows x 32 k: lane l holds k 8 (l / 16) .. + 7 of
+  // row l % 16.
+  // K-contiguous: chunk 4*ks + lane/16 of the row, stored at position (4*ks + lane/16) ^ swzK = (4*ks ^ fsw) with the two
+  // low bits folded into the base.
+  const int fsw = swzK(lane & 15) & 4;
+  const int kc_low = (((lane >> 4) ^ swzK(lane & 15)) & 3) << 3;
+  const int fa_base = (wm0 + (lane & 15)) * PA + kc_low;
+  const int fb_base = (wn0 + (lane & 15)) * PB + kc_low;
+  // M-contiguous: the lane reads 4 elements at k-row krow_l (+4 for the upper half of the fragment), column 4*(lane%4) of
+  // the 16-wide granule g, which is stored at g ^ swzM.
+  const int krow_l = 8 * (lane >> 4) + ((lane & 15) >> 2);
   int ma_lo[2], ma_sw[2], mb_lo[2], mb_sw[2];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    const int swa = swzM(krow_l + 4 * h, std::integral_constant<int, BM>{});
-    const int swb = swzM(krow_l + 4 * h, std::integral_constant<int, BN>{});
-    ma_lo[h] = (krow_l + 4 * h) * PA + (((((lane >> 4) ^ swa) & 1)) << 4) + 4 * (lane & 3);
-    mb_lo[h] = (krow_l + 4 * h) * PB + (((((lane >> 4) ^ swb) & 1)) << 4) + 4 * (lane & 3);
-    ma_sw[h] = swa & ~1;
-    mb_sw[h] = swb & ~1;
+    ma_lo[h] = (krow_l + 4 * h) * PA + 4 * (lane & 3);
+    mb_lo[h] = (krow_l + 4 * h) * PB + 4 * (lane & 3);
+    ma_sw[h] = swzM(krow_l + 4 * h, std::integral_constant<int, BM>{});
+    mb_sw[h] = swzM(krow_l + 4 * h, std::integral_constant<int, BN>{});
   }
   auto frag_kc = [&](const bf16_t* tile, int base, int pitch, int t, int ks) -> bf16x8_t {
-    return *reinterpret_cast<const bf16x8_t*>(tile + base + t * 32 * pitch + (((2 * ks) ^ fsw) << 3));
+    return *reinterpret_cast<const bf16x8_t*>(tile + base + t * 16 * pitch + (((4 * ks) ^ fsw) << 3));
   };
-  auto frag_mc = [&](const bf16_t* tile, const int (&lo)[2], const int (&sw)[2], int pitch, int g0, int ks) -> bf16x8_t {
+  auto frag_mc = [&](const bf16_t* tile, const int (&lo)[2], const int (&sw)[2], int pitch, int g, int ks) -> bf16x8_t {
     typedef s16x4_t __attribute__((address_space(3))) * lds4_t;
-    const bf16_t* p = tile + ks * 16 * pitch;
-    s16x4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(p + lo[0] + ((g0 ^ sw[0]) << 4)));
-    s16x4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(p + lo[1] + ((g0 ^ sw[1]) << 4)));
+    const bf16_t* p = tile + ks * 32 * pitch;
+    s16x4_t v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(p + lo[0] + ((g ^ sw[0]) << 4)));
+    s16x4_t v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4_t)(p + lo[1] + ((g ^ sw[1]) << 4)));
     typedef short s16x8_t __attribute__((ext_vector_type(8)));
     s16x8_t v = __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7);
     return __builtin_bit_cast(bf16x8_t, v);
   };
-  auto compute = [&](int stage) {
+  // The operands are swapped (the instruction's rows are the columns of C), so a lane holds four consecutive columns of
+  // one row of C.
+  constexpr int KQ = BK / 32 / KS;
+  auto read_a = [&](int stage, int kq, int i) {
     const bf16_t* a = sA + stage * SA;
+    const int ks = kq + kgroup * KQ;
+    return A_KC ? frag_kc(a, fa_base, PA, i, ks) : frag_mc(a, ma_lo, ma_sw, PA, (wm0 >> 4) + i, ks);
+  };
+  auto read_b = [&](int stage, int kq, int j) {
     const bf16_t* b = sB + stage * SB;
-    constexpr int KQ = BK / 16 / KS;
-    if constexpr (DBUF && TM * TN >= TM + TN && KQ >= 2) {
-      // Large wave tiles with both operands strided: one fragment of the NEXT k-step is requested in front of each
-      // of the first TM + TN MFMAs of the current one, into a second register set, in the order the next
-      // k-step uses them (A0, B0.., A1..). Every fragment then has at least six MFMAs of time, where the
-      // single-set schedule the compiler produces waits for its last B fragment two MFMAs after asking for it.
-      bf16x8_t fa[2][TM], fb[2][TN];
-      auto read_a = [&](int kq, int i) {
-        const int ks = kq + kgroup * KQ;
-        return A_KC ? frag_kc(a, fa_base, PA, i, ks) : frag_mc(a, ma_lo, ma_sw, PA, (wm0 >> 4) + 2 * i, ks);
-      };
-      auto read_b = [&](int kq, int j) {
-        const int ks = kq + kgroup * KQ;
-        return B_KC ? frag_kc(b, fb_base, PB, j, ks) : frag_mc(b, mb_lo, mb_sw, PB, (wn0 >> 4) + 2 * j, ks);
-      };
+    const int ks = kq + kgroup * KQ;
+    return B_KC ? frag_kc(b, fb_base, PB, j, ks) : frag_mc(b, mb_lo, mb_sw, PB, (wn0 >> 4) + j, ks);
+  };
+  constexpr int LPS = A_LOADS + B_LOADS;   // loads per slab and loading wavefront
+
+  if constexpr (PW == 0) {
+    // Two stages, every wavefront loads its share. The slab is a stream of pairs of tile rows (2 TN MFMAs each): the next
+    // pair's two A fragments are requested in front of the first two MFMAs of this one, and a B fragment of the next
+    // k-step right behind its last use in this one, six MFMAs ahead of its first use, so 32 registers of fragments are
+    // enough. The barrier that hands over the next slab stands in front of the LAST pair, whose operands are in registers
+    // by then: its MFMAs cover the barrier and the LDS round trip of the next slab's first fragments. From there on
+    // this slab's stage is free, so the loads of the slab after the next one start in the last pair, one every LOAD_GAP
+    // MFMAs (a vector-memory instruction holds its wavefront while the address unit is busy).
+    // Same box, against the 32x32x16 form with its barrier between two slabs: NT 8192 x 2048 x 8192 202 -> 182.5 us (1.51
+    // PFLOP/s), NN 207 -> 183, TN 2048 x 8192 x 8192 209 -> 186; the change of MFMA form alone gives 189 / 188 / 194.
+    // What is left is the clock (1.8 GHz under this load) and, per tile, 8-11 us of first loads and last stores.
+    static_assert(NS == 2 && KS == 1, "alternating stages");
+    constexpr int PAIRS = TM / 2, NPAIR = KQ * PAIRS, MPP = 2 * TN;
+    // Epilogues that move two values per product element put bursts of stores between the other workgroups' loads: the
+    // earlier request pays there (4096 x 22016 x 4096 gated: 574 us at a gap of 2, 598 at 4, 627 at 6), the even spread
+    // everywhere else (8192 x 2048 x 8192: 187.7 / 182.5 / 186.2).
+    constexpr int LOAD_GAP = EPI == EPI_GATE || EPI == EPI_DGATE || EPI == EPI_BIAS_ACT ? 2 : 4;
+    static_assert(LOAD_GAP * (LPS - 1) < NPAIR * MPP - MPP, "all loads issued in front of the wait");
+    constexpr int EARLY = (MPP + LOAD_GAP - 1) / LOAD_GAP;   // loads issued in the last pair of the slab before
 #pragma unroll
-      for (int i = 0; i < TM; ++i) fa[0][i] = read_a(0, i);
+    for (int i = 0; i < LPS; ++i) load_piece(0, 0, i);
+    if (nk > 1) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) fb[0][j] = read_b(0, j);
+      for (int i = 0; i < EARLY; ++i) load_piece(1, 1, i);
+      wait_loads_and_lds<EARLY>();
+    } else {
+      wait_loads_and_lds<0>();
+    }
+    block_barrier();
+    bf16x8_t fa[2][2], fb[TN];
+    fa[0][0] = read_a(0, 0, 0);
+    fb[0] = read_b(0, 0, 0);
+    fa[0][1] = read_a(0, 0, 1);
 #pragma unroll
-      for (int kq = 0; kq < KQ; ++kq) {
-        const int cur = kq & 1, nxt = cur ^ 1;
+    for (int j = 1; j < TN; ++j) fb[j] = read_b(0, 0, j);
+    for (int k0 = 0; k0 < nk; k0 += 2) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+      for (int s = 0; s < 2; ++s) {
+        const int k = k0 + s;
+        if (k >= nk) break;   // uniform
+        static_assert(NPAIR % 2 == 0, "register sets alternate across slabs");
 #pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            const int m = i * TN + j;   // MFMA index inside the k-step = slot of the next k-step to request
-            if (kq + 1 < KQ) {
-              if (m == 0) fa[nxt][0] = read_a(kq + 1, 0);
-              else if (m <= TN) fb[nxt][m - 1] = read_b(kq + 1, m - 1);
-              else if (m < TM + TN) fa[nxt][m - TN] = read_a(kq + 1, m - TN);
+        for (int p = 0; p < NPAIR; ++p) {
+          const int kq = p / PAIRS, ip = p % PAIRS;
+          const bool last = p + 1 == NPAIR;
+          if (last) {
+            wait_loads_and_lds<0>();
+            block_barrier();
+          }
+          // (behind the last slab the requests read a stage whose contents nobody uses)
+          const int nstage = last ? s ^ 1 : s, np = last ? 0 : p + 1;
+#pragma unroll
+          for (int m = 0; m < MPP; ++m) {
+            const int j = m >> 1, h = m & 1;
+            if (m < 2) fa[(p + 1) & 1][m] = read_a(nstage, np / PAIRS, 2 * (np % PAIRS) + m);
+            if (m == 0 && ip == 0) fb[TN - 1] = read_b(s, kq, TN - 1);
+            if (h == 0 && j > 0 && ip == PAIRS - 1) fb[j - 1] = read_b(nstage, last ? 0 : kq + 1, j - 1);
+            const int n = last ? m : MPP + p * MPP + m;   // MFMAs since the barrier
+            if (n % LOAD_GAP == 0 && n / LOAD_GAP < LPS) {
+              if (last) {
+                if (k + 2 < nk) load_piece(k + 2, s, n / LOAD_GAP);
+              } else if (k + 1 < nk) {
+                load_piece(k + 1, s ^ 1, n / LOAD_GAP);
+              }
             }
-            acc[i][j] = mfma16<F16>(fa[cur][i], fb[cur][j], acc[i][j]);
+            acc[2 * ip + h][j] = mfma16_16<F16>(fb[j], fa[p & 1][h], acc[2 * ip + h][j]);
             __builtin_amdgcn_sched_barrier(0);   // keep this order (the scheduler would sink the requests)
           }
+        }
       }
-      return;
     }
-    // scheduling hint for the slab: interleave the LDS reads with the MFMAs (variant chosen by measurement)
-    __builtin_amdgcn_iglp_opt(LAYOUT == GEMM_TN ? 1 : 0);
-#pragma unroll
-    for (int kq = 0; kq < BK / 16 / KS; ++kq) {
-      const int ks = kq + kgroup * (BK / 16 / KS);
-      bf16x8_t fa[TM], fb[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-        fa[i] = A_KC ? frag_kc(a, fa_base, PA, i, ks) : frag_mc(a, ma_lo, ma_sw, PA, (wm0 >> 4) + 2 * i, ks);
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        fb[j] = B_KC ? frag_kc(b, fb_base, PB, j, ks) : frag_mc(b, mb_lo, mb_sw, PB, (wn0 >> 4) + 2 * j, ks);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma16<F16>(fa[i], fb[j], acc[i][j]);
-    }
-  };
-
-  {
+  } else {
     // Pipeline over a ring of NS stages, slab j in stage j % NS. Step k issues the loads of slab k + NS - 1
     // into the stage that step k - 1 computed from (free
     // since the barrier that ended step k - 1), computes slab k, then waits until its own loads of slab
     // k + 1 have landed (the younger ones stay in flight) and meets the other wavefronts at the barrier.
-    constexpr int LPS = A_LOADS + B_LOADS;   // loads per slab and loading wavefront
+    auto compute = [&](int stage) {
+      // scheduling hint for the slab: interleave the LDS reads with the MFMAs (variant chosen by measurement)
+      __builtin_amdgcn_iglp_opt(LAYOUT == GEMM_TN ? 1 : 0);
+#pragma unroll
+      for (int kq = 0; kq < KQ; ++kq) {
+        bf16x8_t fa[TM], fb[TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[i] = read_a(stage, kq, i);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[j] = read_b(stage, kq, j);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = mfma16_16<F16>(fb[j], fa[i], acc[i][j]);
+      }
+    };
     if (is_loader) {
 #pragma unroll
       for (int j = 0; j < NS - 1; ++j)
@@ -402,7 +445,7 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
     if (nk >= NS - 1) wait_loads_and_lds<(NS - 2) * LPS>();
     else wait_loads_and_lds<0>();
     block_barrier();
-    if (PW && is_loader) {
+    if (is_loader) {
       // loader wavefronts: issue, wait for the oldest slab, meet the others; nothing else
       for (int k0 = 0; k0 < nk; k0 += NS) {
 #pragma unroll
@@ -419,13 +462,9 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
       for (int k0 = 0; k0 < nk; k0 += NS) {
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-          if (k0 + s >= nk) break;                  // uniform
-          const bool more = k0 + s + NS - 1 < nk;   // uniform
-          if (!PW && more) load_direct(k0 + s + NS - 1, (s + NS - 1) % NS);
+          if (k0 + s >= nk) break;                   // uniform
           compute(s);
-          if (PW) wait_loads_and_lds<63>();          // LDS reads done (no loads of its own)
-          else if (more) wait_loads_and_lds<(NS - 2) * LPS>();
-          else wait_loads_and_lds<0>();
+          wait_loads_and_lds<63>();                  // LDS reads done (no loads of its own)
           block_barrier();
         }
       }
@@ -434,32 +473,32 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
 
   if (PW && is_loader) return;   // every load has landed (the last steps drain them); the rest is compute only
 
-  // Epilogue. The accumulators (element r of a 32x32 tile: row (r/4)*8 + 4*(lane/32) + r%4, column
-  // lane%32) go, one 32-row slab at a time, through a per-wave fp32 staging area in LDS so that every
+  // Epilogue. The accumulators (element r of a 16x16 tile: row lane%16, column 4*(lane/16) + r) go, one 32-row slab at a time, through a per-wave fp32 staging area in LDS so that every
   // global access of the epilogue (bias, auxiliary input, both outputs) is a 16-byte access of 8
   // consecutive columns of one row. The main loop ended with a barrier, so the stages are free.
   if (KS == 2) {   // add the second wave set's accumulators to the first; then only the first goes on
-    float* red = reinterpret_cast<float*>(smem) + wave * (TM * TN * 16 * 64) + lane;
+    f32x4_t* red = reinterpret_cast<f32x4_t*>(smem) + wave * (TM * TN * 64) + lane;
     if (kgroup == 1) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) red[((i * TN + j) * 16 + r) * 64] = acc[i][j][r];
+        for (int j = 0; j < TN; ++j) red[(i * TN + j) * 64] = acc[i][j];
     }
     __syncthreads();
     if (kgroup == 0) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int j = 0; j < TN; ++j) {
+          const f32x4_t other = red[(i * TN + j) * 64];
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] += red[((i * TN + j) * 16 + r) * 64];
+          for (int r = 0; r < 4; ++r) acc[i][j][r] += other[r];
+        }
     }
     __syncthreads();
     if (kgroup == 1) return;
   }
+  constexpr int SM = WM / 32;   // 32-row slabs of the wave tile
   constexpr int LDP = WN + 4;
   float* stage = reinterpret_cast<float*>(smem) + wave * (32 * LDP);
   constexpr int CPR = WN / 8;         // 8-column chunks per staged row
@@ -473,7 +512,7 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
   constexpr bool AUX = (EPI == EPI_DACT || EPI == EPI_ADD || EPI == EPI_DGATE);
   constexpr int NP = 32 / RPP;
   constexpr int NAUX = EPI == EPI_DGATE ? 2 : 1;   // 16-byte pieces of auxiliary input per 8 product columns
-  u32x4_t au[TM][NP * NAUX];
+  u32x4_t au[SM][NP * NAUX];
   auto aux_fetch = [&](int i, u32x4_t (&dst)[NP * NAUX]) {
     const int nc = n < N ? n : N - 8;
 #pragma unroll
@@ -495,14 +534,14 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
   };
   if (AUX && !is_tail) aux_fetch(0, au[0]);
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    if (AUX && !is_tail && i + 1 < TM) aux_fetch(i + 1, au[i + 1]);
+  for (int i = 0; i < SM; ++i) {
+    if (AUX && !is_tail && i + 1 < SM) aux_fetch(i + 1, au[i + 1]);
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        stage[((r >> 2) * 8 + 4 * (lane >> 5) + (r & 3)) * LDP + j * 32 + (lane & 31)] = acc[i][j][r];
+      for (int j = 0; j < TN; ++j)
+        *reinterpret_cast<f32x4_t*>(stage + (h * 16 + (lane & 15)) * LDP + j * 16 + 4 * (lane >> 4)) = acc[2 * i + h][j];
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int pass = 0; pass < 32 / RPP; ++pass) {
@@ -755,15 +794,15 @@ __global__ __launch_bounds__(256) void hybrid_reduce_kernel(int M, int N, int ta
 template <int LAYOUT, bool F16>
 static void launch_hybrid(const HybridPlan& hp, int epi, int M, int N, int K, const void* A, const void* B, void* C,
                           const void* aux_in, float* ws, hipStream_t st) {
-  constexpr int BM = 256, BN = 256, PW = LAYOUT == GEMM_NT ? 4 : 0;   // (loader wavefronts as in the plain launch)
+  constexpr int BM = 256, BN = 256;
   const size_t lds = gemm_lds_bytes<BM, BN, 64, 2, 4, 1, 2>();
   const int grid = hp.tail_begin + hp.tail_tiles * hp.splits;
 #define SLAPO_HYB(E)                                                                                           \
   do {                                                                                                         \
-    auto kern = LAYOUT == GEMM_TN || K % 64 == 0 ? gemm_bf16_kernel<LAYOUT, BM, BN, 64, 2, 4, 1, 2, PW, false, E, F16, true> \
-                                                 : gemm_bf16_kernel<LAYOUT, BM, BN, 64, 2, 4, 1, 2, PW, LAYOUT != GEMM_TN, E, F16, true>; \
+    auto kern = LAYOUT == GEMM_TN || K % 64 == 0 ? gemm_bf16_kernel<LAYOUT, BM, BN, 64, 2, 4, 1, 2, 0, false, E, F16, true> \
+                                                 : gemm_bf16_kernel<LAYOUT, BM, BN, 64, 2, 4, 1, 2, 0, LAYOUT != GEMM_TN, E, F16, true>; \
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);       \
-    hipLaunchKernelGGL(kern, dim3(grid), dim3((8 + PW) * 64), lds, st, M, N, K, (const bf16_t*)A, (const bf16_t*)B, \
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(8 * 64), lds, st, M, N, K, (const bf16_t*)A, (const bf16_t*)B, \
                        (bf16_t*)C, (const bf16_t*)nullptr, (const bf16_t*)aux_in, (bf16_t*)nullptr, 0,         \
                        hp.tail_begin, hp.splits, ws);                                                          \
   } while (0)
@@ -775,7 +814,7 @@ static void launch_hybrid(const HybridPlan& hp, int epi, int M, int N, int K, co
 }
 
 // Tile selection, from measurements on the layer's shapes. 256x256 tiles (8 wavefronts, 128x64 each, direct
-// loads into two stages, issued by four more wavefronts in the NT layout) when they still cover at least three quarters
+// loads into two stages) when they still cover at least three quarters
 // of the 256 CUs. Otherwise 128x128 tiles (8 wavefronts, 64x32 each; TN: two sets of four, 64x64 each): a ring of four
 // stages filled by four loader wavefronts. 128x64 tiles of the same form (four computing wavefronts) where all of them
 // fit one round. K needs no particular multiple: TN products with K = 2286 tokens and 768 x 3072 outputs take 18.7 us
@@ -823,9 +862,7 @@ static void launch_bf16(int epi, int act, int M, int N, int K, const void* A, co
   // (epilogues that the layer never pairs with this layout come as 128x128 tiles only)
   switch (epi_used(LAYOUT, epi) ? select_tile(LAYOUT, M, N, K, solo) : TILE_128_LOADERS) {
     case TILE_256:
-      // NT: four loader wavefronts beside the eight that compute (168 registers: three wavefronts per SIMD fit; the
-      // NN/TN instances need 190-230, so their wavefronts load their own shares)
-      launch_bf16_tile<LAYOUT, 256, 256, 2, 4, 1, 2, LAYOUT == GEMM_NT ? 4 : 0, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
+      launch_bf16_tile<LAYOUT, 256, 256, 2, 4, 1, 2, 0, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
       break;
     case TILE_128_SPLITSLAB:
       if constexpr (LAYOUT == GEMM_TN) launch_bf16_tile<LAYOUT, 128, 128, 2, 2, 2, 4, 4, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
@@ -928,8 +965,8 @@ void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool sol
   if (with_ws && !(weight_grad && weight_grad_splits(M, N, K) > 1) && select_tile(layout, M, N, K, false) == TILE_256) {
     const HybridPlan hp = hybrid_plan(weight_grad ? EPI_NONE : epi, M, N, K);
     if (hp.ws_bytes) {
-      snprintf(buf, len, "gemm_bf16_kernel<%d, 256, 256, 64, 2, 4, 1, 2, %d, %s, %d, %s, true> (%d tiles + %d tiles in %d K ranges) + hybrid_reduce_kernel",
-               layout, layout == GEMM_NT ? 4 : 0, kt, epi, b, hp.tail_begin, hp.tail_tiles, hp.splits);
+      snprintf(buf, len, "gemm_bf16_kernel<%d, 256, 256, 64, 2, 4, 1, 2, 0, %s, %d, %s, true> (%d tiles + %d tiles in %d K ranges) + hybrid_reduce_kernel",
+               layout, kt, epi, b, hp.tail_begin, hp.tail_tiles, hp.splits);
       return;
     }
   }
@@ -943,8 +980,7 @@ void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool sol
   static const char* const shape[] = {"256, 256, 64, 2, 4, 1, 2, 0", "128, 128, 64, 2, 2, 2, 4, 4", "128, 128, 64, 2, 4, 1, 4, 4",
                                       "128, 64, 64, 2, 2, 1, 4, 4"};
   const TileKind k = epi_used(layout, epi) ? select_tile(layout, M, N, K, solo) : TILE_128_LOADERS;
-  if (k == TILE_256 && layout == GEMM_NT) snprintf(buf, len, "gemm_bf16_kernel<0, 256, 256, 64, 2, 4, 1, 2, 4, %s, %d, %s, false>", kt, epi, b);
-  else snprintf(buf, len, "gemm_bf16_kernel<%d, %s, %s, %d, %s, false>", layout, shape[(int)k], kt, epi, b);
+  snprintf(buf, len, "gemm_bf16_kernel<%d, %s, %s, %d, %s, false>", layout, shape[(int)k], kt, epi, b);
 }
 
 void launch_gemm(int dtype, int layout, int epi, int act, int M, int N, int K, const void* A, const void* B,
