@@ -10,7 +10,7 @@
 // contiguous in memory are read from LDS with 16-byte reads; operands whose contraction index is the
 // strided one (the "N" operand of dY*W and both operands of dY^T*X) stay in their memory order in LDS and
 // are read with the transposing ds_read_b64_tr_b16, so no transposed copy of any tensor is ever made.
-// fp32 path: a plain LDS-tiled FMA kernel (correctness mode).
+// fp32 path (the mode that checks the others): fp32 MFMAs, wavefronts that share a tile along K.
 #include <stdio.h>
 #include <stdlib.h>
 #include <type_traits>
@@ -639,61 +639,123 @@ constexpr size_t gemm_lds_bytes() {
   return m1 > red_bytes ? m1 : red_bytes;
 }
 
-// fp32 correctness kernel: 64x64 tile, 16-deep slabs, each thread a 4x4 block.
+// fp32: 32x32 tiles, eight wavefronts that take the 16-deep K chunks of the tile in turn, so that a product with few
+// tiles (256 tokens, 256 columns: 64) still has 512 wavefronts' loads in flight; such products are bound by the chain of
+// load latencies, not by the 157 TFLOP/s of the fp32 MFMAs. Operands go from memory to registers in the shape of
+// v_mfma_f32_16x16x4_f32 fragments (nothing is shared between wavefronts that do not share K), the next chunk requested
+// ahead of the one that is multiplied; the partial tiles meet in LDS. Inputs, products and sums are fp32 as in a plain FMA
+// loop. (Two or four chunks ahead need 150-250 registers and lose more to the fewer wavefronts: 512 x 3072 x 768 takes 52
+// and 67 us.)
+// A fragment element belongs to k = k0 + 4 (lane/16) + s in step s for either operand; lane%16 counts rows.
+//  - contiguous along K: one 16-byte load per 16 rows gives the four steps
+//  - contiguous along rows: one 8-byte load per step gives the rows 2 (lane%16) + {0, 1} of the two 16-row tiles
+// Against one 64x64 tile of plain FMAs per workgroup: 256 x 256 x 1024 142 -> 10 us, 512 x 3072 x 768 157 -> 48 us.
+constexpr int F32_WAVES = 8;
 template <int LAYOUT>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A,
-                                                       const float* __restrict__ B, float* __restrict__ C,
-                                                       const float* __restrict__ bias, const float* aux_in,
-                                                       float* __restrict__ aux_out, int epi, int act) {
-  __shared__ float sA[16][65], sB[16][65];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int q = tid; q < 64 * 16; q += 256) {
-      const int mm = q & 63, kk = q >> 6;
-      const int m = m0 + mm, n = n0 + mm, k = k0 + kk;
-      float av = 0.f, bv = 0.f;
-      if (k < K) {
-        if (m < M) av = (LAYOUT == GEMM_TN) ? A[(int64_t)k * M + m] : A[(int64_t)m * K + k];
-        if (n < N) bv = (LAYOUT == GEMM_NT) ? B[(int64_t)n * K + k] : B[(int64_t)k * N + n];
+__global__ __launch_bounds__(F32_WAVES * 64) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A,
+                                                                  const float* __restrict__ B, float* __restrict__ C,
+                                                                  const float* __restrict__ bias, const float* aux_in,
+                                                                  float* __restrict__ aux_out, int epi, int act) {
+  constexpr bool A_KC = LAYOUT != GEMM_TN, B_KC = LAYOUT == GEMM_NT;
+  constexpr int PITCH = 36;   // floats per staged row of 32
+  __shared__ __attribute__((aligned(16))) float part[F32_WAVES][32 * PITCH];
+  const int tiles_n = (N + 31) / 32;
+  const int m0 = ((int)blockIdx.x / tiles_n) * 32, n0 = ((int)blockIdx.x % tiles_n) * 32;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15, g = lane >> 4;
+
+  struct Frag { float v[2][4]; };   // [16-row tile][step]
+  // rows beyond the operand are clamped (their products are never stored), k beyond K is zero in both operands
+  auto load = [&](auto kc, const float* X, int r0, int rows, int k0) {
+    Frag f;
+    if constexpr (decltype(kc)::value) {
+      const int k = k0 + 4 * g;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int r = r0 + 16 * t + i < rows ? r0 + 16 * t + i : rows - 1;
+        float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (k < K) w = *reinterpret_cast<const float4*>(X + (int64_t)r * K + k);   // (K % 8 == 0)
+        f.v[t][0] = w.x; f.v[t][1] = w.y; f.v[t][2] = w.z; f.v[t][3] = w.w;
       }
-      sA[kk][mm] = av;
-      sB[kk][mm] = bv;
+    } else {
+      const int r = r0 + 2 * i < rows ? r0 + 2 * i : rows - 2;                      // (rows % 8 == 0)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int k = k0 + 4 * g + s;
+        float2 w = make_float2(0.f, 0.f);
+        if (k < K) w = *reinterpret_cast<const float2*>(X + (int64_t)k * rows + r);
+        f.v[0][s] = w.x; f.v[1][s] = w.y;
+      }
     }
-    __syncthreads();
+    return f;
+  };
+  f32x4_t acc[2][2] = {};
+  const int chunks = (K + 15) / 16;
+  Frag fa[2], fb[2];
+  auto fetch = [&](int buf, int c) {
+    if (c >= chunks) return;   // (uniform)
+    fa[buf] = load(std::integral_constant<bool, A_KC>{}, A, m0, M, c * 16);
+    fb[buf] = load(std::integral_constant<bool, B_KC>{}, B, n0, N, c * 16);
+  };
+  auto multiply = [&](int buf, int c) {
+    if (c >= chunks) return;   // (uniform)
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = sA[kk][ty * 4 + i]; b[i] = sB[kk][tx * 4 + i]; }
+      for (int tm = 0; tm < 2; ++tm)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+        for (int tn = 0; tn < 2; ++tn)   // operands swapped: a lane holds four columns of one row
+          acc[tm][tn] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[buf].v[tn][s], fa[buf].v[tm][s], acc[tm][tn], 0, 0, 0);
+  };
+  fetch(0, wave);
+  for (int c = wave; c < chunks; c += 2 * F32_WAVES) {
+    fetch(1, c + F32_WAVES);
+    multiply(0, c);
+    fetch(0, c + 2 * F32_WAVES);
+    multiply(1, c + F32_WAVES);
   }
+  // element (tm, tn, r) of the lane: row i of A tile tm, row 4 g + r of B tile tn
+  float* mine = part[wave];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int tm = 0; tm < 2; ++tm) {
+    float* row = mine + (A_KC ? 16 * tm + i : 2 * i + tm) * PITCH;
+    if constexpr (B_KC) {
+#pragma unroll
+      for (int tn = 0; tn < 2; ++tn) *reinterpret_cast<f32x4_t*>(row + 16 * tn + 4 * g) = acc[tm][tn];
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) *reinterpret_cast<float2*>(row + 8 * g + 2 * r) = make_float2(acc[tm][0][r], acc[tm][1][r]);
+    }
+  }
+  __syncthreads();
+  // four columns of one row per thread, the partial tiles added in order
+  if (threadIdx.x >= 256) return;
+  const int m = m0 + (int)threadIdx.x / 8, n = n0 + ((int)threadIdx.x % 8) * 4;
+  if (m >= M || n >= N) return;
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < F32_WAVES; ++w) {
+    const float4 x = *reinterpret_cast<const float4*>(part[w] + ((int)threadIdx.x / 8) * PITCH + ((int)threadIdx.x % 8) * 4);
+    v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
+  }
+  if (epi == EPI_GATE) {          // (gate, up) pairs in adjacent columns
+#pragma unroll
+    for (int j = 0; j < 4; j += 2) {
+      const GateTerms t = gate_terms<false>(v[j], v[j + 1]);
+      C[(int64_t)m * (N / 2) + (n + j) / 2] = t.out;
+      aux_out[(int64_t)m * N + n + j] = t.dgate;
+      aux_out[(int64_t)m * N + n + j + 1] = t.dup;
+    }
+  } else if (epi == EPI_DGATE) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m >= M || n >= N) continue;
-      if (epi == EPI_GATE) {          // (gate, up) pairs in adjacent columns; the even one does the work
-        if (j & 1) continue;
-        const GateTerms g = gate_terms<false>(acc[i][j], acc[i][j + 1]);
-        C[(int64_t)m * (N / 2) + n / 2] = g.out;
-        aux_out[(int64_t)m * N + n] = g.dgate;
-        aux_out[(int64_t)m * N + n + 1] = g.dup;
-      } else if (epi == EPI_DGATE) {
-        const int64_t q = (int64_t)m * (2 * N) + 2 * n;
-        C[q] = acc[i][j] * aux_in[q];
-        C[q + 1] = acc[i][j] * aux_in[q + 1];
-      } else {
-        epilogue_store<float>(epi, act, acc[i][j], m, n, N, C, bias, aux_in, aux_out);
-      }
+      const int64_t q = (int64_t)m * (2 * N) + 2 * (n + j);
+      C[q] = v[j] * aux_in[q];
+      C[q + 1] = v[j] * aux_in[q + 1];
     }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) epilogue_store<float>(epi, act, v[j], m, n + j, N, C, bias, aux_in, aux_out);
+  }
 }
 
 // epilogue / layout pairs the layer itself uses; the others exist as 128x128 tiles only
@@ -987,9 +1049,9 @@ void launch_gemm(int dtype, int layout, int epi, int act, int M, int N, int K, c
                  void* C, const void* bias, const void* aux_in, void* aux_out, hipStream_t st, bool solo, float* ws,
                  size_t ws_bytes) {
   if (dtype == DT_FP32) {
-    dim3 grid((N + 63) / 64, (M + 63) / 64);
+    const dim3 grid((unsigned)(((M + 31) / 32) * ((N + 31) / 32)));
 #define SLAPO_F32(L)                                                                                      \
-  hipLaunchKernelGGL(gemm_f32_kernel<L>, grid, dim3(256), 0, st, M, N, K, (const float*)A, (const float*)B, \
+  hipLaunchKernelGGL(gemm_f32_kernel<L>, grid, dim3(F32_WAVES * 64), 0, st, M, N, K, (const float*)A, (const float*)B, \
                      (float*)C, (const float*)bias, (const float*)aux_in, (float*)aux_out, epi, act)
     if (layout == GEMM_NT) SLAPO_F32(GEMM_NT);
     else if (layout == GEMM_NN) SLAPO_F32(GEMM_NN);

@@ -173,3 +173,28 @@ def test_weight_gradient_in_k_ranges_of_odd_length(M, N, K):
     out = torch.empty(M, N, dtype=torch.bfloat16, device=DEV)
     B.slapo_weight_grad(W.BF16, 0, M, N, K, to_dev(a, W.BF16), to_dev(b, W.BF16), out, ws)
     assert err(out, a.T @ b) <= 5e-3
+
+
+# fp32: tiles of 32 x 32 with K in 16-deep chunks over eight wavefronts: fewer rows than a tile, one over, one piece of
+# columns over; K below one chunk, below eight, between, and odd where K runs along the rows of both operands.
+@pytest.mark.parametrize("layout,Ks", [(B.NT, (8, 24, 136, 264, 1000)), (B.NN, (8, 24, 136, 264, 1000)), (B.TN, (1, 17, 127, 129, 999))])
+@pytest.mark.parametrize("M,N", [(1, 8), (33, 40), (77, 264), (256, 1024)])
+def test_gemm_fp32_tiles(layout, Ks, M, N):
+    if layout == B.TN:
+        M = -(-M // 8) * 8
+    for K in Ks:
+        rng = np.random.default_rng(K + M)
+        a = rng.standard_normal((M, K)).astype(np.float32)
+        b = rng.standard_normal((K, N)).astype(np.float32)
+        ref, mag = a.astype(np.float64) @ b, np.abs(a).astype(np.float64) @ np.abs(b)
+        if M > 5:
+            a[5] = np.nan                             # only row 5 may show it
+        A = to_dev(a if layout != B.TN else a.T.copy(), W.FP32)
+        Bm = to_dev(b.T.copy() if layout == B.NT else b, W.FP32)
+        Cout = torch.empty(M, N, dtype=torch.float32, device=DEV)
+        B.slapo_gemm(W.FP32, layout, B.EPI_NONE, 0, M, N, K, A, Bm, Cout)
+        got = to_np(Cout).astype(np.float64)
+        if M > 5:
+            assert np.isnan(got[5]).all()
+            got[5] = ref[5]
+        assert (np.abs(got - ref) <= (K + 8) * 2.0 ** -24 * mag + 1e-30).all(), K   # K rounded additions and the 8 partial sums
