@@ -205,12 +205,13 @@ int slapo_gemm(int dtype, int layout, int epilogue, int act, int64_t M, int64_t 
  *          helper stream's weight gradients share the chip (slapo_gemm, like the forward pass, selects for a GEMM that
  *          runs alone: it may take 128x128 tiles where a grid of 256x256 tiles would end in a thin last round).
  *   ws, ws_bytes: optional device workspace (16-byte aligned; free again when the call's work is done). With it, a
- *          plain or add-epilogue GEMM (epilogue 0 or 4) whose grid of 256x256 tiles is not a multiple of the 256 CUs
- *          and whose K is long computes the tiles beyond the last full round in several K ranges (fp32 partial tiles
+ *          plain or add-epilogue GEMM (epilogue 0 or 4) whose grid of tiles is not a multiple of the 256 CUs and whose K
+ *          is long computes the tiles beyond the last full round in several K ranges (fp32 partial tiles
  *          in ws, added in range order by a second kernel: bitwise reproducible), so that the last round is short
- *          instead of thin. slapo_gemm_workspace writes the bytes a shape can use (0: it runs as slapo_gemm would);
- *          a non-NULL ws smaller than that is refused with SLAPO_ERR_WORKSPACE. The layer calls do the same with a
- *          region of their scratch buffer. */
+ *          instead of thin; layouts 0 and 1 with few tiles do so with all of them. slapo_gemm_workspace writes the bytes
+ *          a shape can use (0: it runs as slapo_gemm would); for a grid of 256x256 tiles a non-NULL ws smaller than that
+ *          is refused with SLAPO_ERR_WORKSPACE, the smaller tiles do without one that does not hold it. The layer calls
+ *          do the same with a region of their scratch buffer. */
 enum { SLAPO_GEMM_SHARED = 1 };
 int slapo_gemm_workspace(int dtype, int layout, int epilogue, int64_t M, int64_t N, int64_t K, size_t *ws_bytes);
 int slapo_gemm_ex(int dtype, int layout, int epilogue, int act, int64_t M, int64_t N, int64_t K,

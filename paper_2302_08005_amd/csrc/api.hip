@@ -225,12 +225,12 @@ ScratchLayout scratch_layout(const slapo_layer_desc* d) {
     // the same kind of workspace for the GEMMs of the forward pass and of the data-gradient chain whose tile grid
     // would end in a thin round (their last tiles are then computed in K ranges); a region of its own, because
     // the chain runs while the helper stream's weight gradients use the one above
-    size_t g = gemm_ws_bytes(d->dtype, EPI_NONE, Ti, Hi, Ai);                       // attention output projection
+    size_t g = gemm_ws_bytes(d->dtype, GEMM_NT, EPI_NONE, Ti, Hi, Ai);                       // attention output projection
     auto upto = [&](size_t v) { g = g > v ? g : v; };
-    upto(gemm_ws_bytes(d->dtype, EPI_NONE, Ti, Hi, Fi));                             // second FFN product
-    upto(gemm_ws_bytes(d->dtype, EPI_NONE, Ti, Hi, F1));                             // gradient of the FFN input
-    upto(gemm_ws_bytes(d->dtype, EPI_NONE, Ti, Ai, Hi));                             // gradient of the attention output
-    upto(gemm_ws_bytes(d->dtype, EPI_NONE, Ti, Hi, 3 * Ai));                         // gradient of the attention input
+    upto(gemm_ws_bytes(d->dtype, GEMM_NT, EPI_NONE, Ti, Hi, Fi));                             // second FFN product
+    upto(gemm_ws_bytes(d->dtype, GEMM_NN, EPI_NONE, Ti, Hi, F1));                             // gradient of the FFN input
+    upto(gemm_ws_bytes(d->dtype, GEMM_NN, EPI_NONE, Ti, Ai, Hi));                             // gradient of the attention output
+    upto(gemm_ws_bytes(d->dtype, GEMM_NN, EPI_NONE, Ti, Hi, 3 * Ai));                         // gradient of the attention input
     L.gemm_ws = g ? take(g) : 0;
     L.gemm_ws_bytes = g;
   }
@@ -661,7 +661,7 @@ static int gemm_entry(int dtype, int layout, int epilogue, int act, int64_t M, i
   if (layout == GEMM_NT && (K % 8)) return SLAPO_ERR_ALIGN;
   if (misaligned(A) || misaligned(B) || misaligned(C) || misaligned(ws)) return SLAPO_ERR_ALIGN;
   // a workspace is all or nothing: one that is too small for what the shape can use is refused, not half used
-  if (ws && ws_bytes < gemm_ws_bytes(dtype, epilogue, (int)M, (int)N, (int)K)) return SLAPO_ERR_WORKSPACE;
+  if (ws && ws_bytes < gemm_ws_least_bytes(dtype, layout, epilogue, (int)M, (int)N, (int)K)) return SLAPO_ERR_WORKSPACE;
   entry_error();
   launch_gemm(dtype, layout, epilogue, act, (int)M, (int)N, (int)K, A, B, C, bias, aux_in, aux_out,
               (hipStream_t)stream, solo, (float*)ws, ws ? ws_bytes : 0);
@@ -679,7 +679,7 @@ int slapo_gemm_workspace(int dtype, int layout, int epilogue, int64_t M, int64_t
   if (layout < GEMM_NT || layout > GEMM_TN || epilogue < EPI_NONE || epilogue > EPI_DGATE) return SLAPO_ERR_UNSUPPORTED;
   if (M <= 0 || N <= 0 || K <= 0) return SLAPO_ERR_SHAPE;
   if (M * N >= ((int64_t)1 << 31) || M * K >= ((int64_t)1 << 31) || N * K >= ((int64_t)1 << 31)) return SLAPO_ERR_UNSUPPORTED;
-  *ws_bytes = gemm_ws_bytes(dtype, epilogue, (int)M, (int)N, (int)K);
+  *ws_bytes = gemm_ws_bytes(dtype, layout, epilogue, (int)M, (int)N, (int)K);
   return SLAPO_OK;
 }
 

@@ -793,88 +793,6 @@ static void launch_bf16_tile(int epi, int act, int M, int N, int K, const void* 
 #undef SLAPO_GEMM
 }
 
-// ---- thin last rounds: the tail tiles of a 256x256 grid in several K ranges ----------------------------
-// 320 tiles on 256 CUs take two rounds for 1.25 rounds of work. With a workspace at hand, the tiles beyond the
-// last full round are cut into s = 256 / (their number) K ranges, so that the last round has about 256 workgroups
-// of 1/s the length, and a second kernel adds the ranges in order (bitwise reproducible) and applies the
-// epilogue. Worth it when the saved (1 - 1/s) of a round outweighs writing and re-reading the partial tiles,
-// i.e. for long K; plain and add epilogues only (the others have so many tiles that a thin round matters little).
-struct HybridPlan { int tail_begin, tail_tiles, splits; size_t ws_bytes; };
-static HybridPlan hybrid_plan(int epi, int M, int N, int K) {
-  const int tiles = ((M + 255) / 256) * ((N + 255) / 256);
-  HybridPlan none = {tiles, 0, 1, 0}, p = none;
-  static const bool disabled = debug_flag("no-hybrid");
-  if (disabled || (epi != EPI_NONE && epi != EPI_ADD)) return none;
-  const int rem = tiles % 256, nk = (K + 63) / 64;
-  if (tiles <= 256 || rem == 0) return none;
-  int s = 256 / rem;
-  s = s > 8 ? 8 : s;
-  while (s > 1 && ((s - 1) * ((nk + s - 1) / s) >= nk || nk / s < 8)) --s;   // every range non-empty, at least 8 slabs
-  if (s < 2) return none;
-  // a round of 64-deep slabs takes about 1.1 us per slab; the partial tiles are written and read once at ~4 TB/s
-  const double saved_us = (1.0 - 1.0 / s) * nk * 1.1;
-  const double cost_us = 2.0 * rem * s * 256.0 * 256.0 * 4.0 / 4.0e6;
-  if (saved_us < 1.5 * cost_us) return none;
-  p.tail_tiles = rem;
-  p.tail_begin = tiles - rem;
-  p.splits = s;
-  p.ws_bytes = (size_t)rem * s * 256 * 256 * sizeof(float);
-  return p;
-}
-
-// C tile of tail tile t = sum over the K ranges of hyb_ws[(t * splits + r)] (+ aux_in), eight columns per thread.
-template <bool F16>
-__global__ __launch_bounds__(256) void hybrid_reduce_kernel(int M, int N, int tail_begin, int splits,
-                                                            const float* __restrict__ ws, bf16_t* C,
-                                                            const bf16_t* aux_in) {
-  constexpr int BM = 256, BN = 256, CPT = BM * BN / 8;   // 8-column chunks per tile
-  const int tiles_n = (N + BN - 1) / BN, tiles_m = (M + BM - 1) / BM;
-  const int q = blockIdx.x * 256 + threadIdx.x;
-  const int t = q / CPT, in_tile = q - t * CPT;
-  const TilePos pos = tile_position(tail_begin + t, tiles_m, tiles_n, 1);
-  const int row = in_tile / (BN / 8), col = (in_tile % (BN / 8)) * 8;
-  const int m = pos.tile_m * BM + row, n = pos.tile_n * BN + col;
-  if (m >= M || n >= N) return;
-  const float* part = ws + ((size_t)t * splits * BM + row) * BN + col;
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int r = 0; r < splits; ++r) {
-    float v[8];
-    load8(part + (size_t)r * BM * BN, v);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] += v[e];
-  }
-  const int64_t idx = (int64_t)m * N + n;
-  if (aux_in) {
-    float v[8];
-    load8h<F16>(aux_in + idx, v);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] += v[e];
-  }
-  store8h<F16>(C + idx, acc);
-}
-
-template <int LAYOUT, bool F16>
-static void launch_hybrid(const HybridPlan& hp, int epi, int M, int N, int K, const void* A, const void* B, void* C,
-                          const void* aux_in, float* ws, hipStream_t st) {
-  constexpr int BM = 256, BN = 256;
-  const size_t lds = gemm_lds_bytes<BM, BN, 64, 2, 4, 1, 2>();
-  const int grid = hp.tail_begin + hp.tail_tiles * hp.splits;
-#define SLAPO_HYB(E)                                                                                           \
-  do {                                                                                                         \
-    auto kern = LAYOUT == GEMM_TN || K % 64 == 0 ? gemm_bf16_kernel<LAYOUT, BM, BN, 64, 2, 4, 1, 2, 0, false, E, F16, true> \
-                                                 : gemm_bf16_kernel<LAYOUT, BM, BN, 64, 2, 4, 1, 2, 0, LAYOUT != GEMM_TN, E, F16, true>; \
-    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);       \
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(8 * 64), lds, st, M, N, K, (const bf16_t*)A, (const bf16_t*)B, \
-                       (bf16_t*)C, (const bf16_t*)nullptr, (const bf16_t*)aux_in, (bf16_t*)nullptr, 0,         \
-                       hp.tail_begin, hp.splits, ws);                                                          \
-  } while (0)
-  if (epi == EPI_ADD) SLAPO_HYB(EPI_ADD); else SLAPO_HYB(EPI_NONE);
-#undef SLAPO_HYB
-  const int chunks = hp.tail_tiles * (BM * BN / 8);
-  hipLaunchKernelGGL(hybrid_reduce_kernel<F16>, dim3(chunks / 256), dim3(256), 0, st, M, N, hp.tail_begin, hp.splits,
-                     (const float*)ws, (bf16_t*)C, epi == EPI_ADD ? (const bf16_t*)aux_in : (const bf16_t*)nullptr);
-}
-
 // Tile selection, from measurements on the layer's shapes. 256x256 tiles (8 wavefronts, 128x64 each, direct
 // loads into two stages) when they still cover at least three quarters
 // of the 256 CUs. Otherwise 128x128 tiles (8 wavefronts, 64x32 each; TN: two sets of four, 64x64 each): a ring of four
@@ -908,14 +826,121 @@ static TileKind select_tile(int layout, int M, int N, int K, bool solo) {
   return layout == GEMM_TN ? TILE_128_SPLITSLAB : TILE_128_LOADERS;
 }
 
+// ---- thin last rounds: the tail tiles of a grid in several K ranges ----------------------------------
+// 320 tiles on 256 CUs take two rounds for 1.25 rounds of work. With a workspace at hand, the tiles beyond the
+// last full round are cut into s = 256 / (their number) K ranges, so that the last round has about 256 workgroups
+// of 1/s the length, and a second kernel adds the ranges in order (bitwise reproducible) and applies the
+// epilogue. Worth it when the saved (1 - 1/s) of a round outweighs writing and re-reading the partial tiles,
+// i.e. for long K; plain and add epilogues only (the others have so many tiles that a thin round matters little).
+// A grid with fewer tiles than half the CUs is all tail: 128 x 1024 outputs are 16 tiles of 128x64.
+// Same box, without / with: NT 2331 x 2048 x 8192 (304 tiles of 128x128) 98 / 83 us, 2000 x 2560 x 10240 (320) 125 / 102,
+// NN 2000 x 2560 x 7680 101 / 84; 128 x 1024 x 4096 16.3 / 10.8, K = 3072 12.9 / 10.7. Below those lengths the second
+// kernel costs what the ranges save (2331 x 2048 x 2048: 29 us either way).
+struct HybridPlan { TileKind tile; int tail_begin, tail_tiles, splits; size_t ws_bytes; };
+static HybridPlan hybrid_plan(int layout, int epi, int M, int N, int K) {
+  HybridPlan none = {TILE_256, 0, 0, 1, 0}, p = none;
+  static const bool disabled = debug_flag("no-hybrid");
+  if (disabled || (epi != EPI_NONE && epi != EPI_ADD)) return none;
+  p.tile = select_tile(layout, M, N, K, false);
+  if (p.tile == TILE_128_SPLITSLAB || (p.tile == TILE_128x64_LOADERS && layout == GEMM_TN)) return none;   // (K ranges of their own: weight_grad_splits)
+  const int bm = p.tile == TILE_256 ? 256 : 128, bn = p.tile == TILE_256 ? 256 : p.tile == TILE_128x64_LOADERS ? 64 : 128;
+  const int tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+  const int rem = tiles % 256, nk = (K + 63) / 64;
+  if (rem == 0 || (tiles < 256 && p.tile != TILE_128x64_LOADERS)) return none;
+  int s = 256 / rem;
+  s = s > 8 ? 8 : s;
+  while (s > 1 && ((s - 1) * ((nk + s - 1) / s) >= nk || nk / s < 8)) --s;   // every range non-empty, at least 8 slabs
+  if (s < 2) return none;
+  // Time of a 64-deep slab of a round, and the partial tiles written and read once at ~4 TB/s; the small tiles' rounds are
+  // short enough for the second kernel's own 4 us to count.
+  const double slab_us = p.tile == TILE_256 ? 1.1 : p.tile == TILE_128_LOADERS ? 0.37 : 0.25;
+  const double saved_us = (1.0 - 1.0 / s) * nk * slab_us;
+  const double cost_us = 2.0 * rem * s * bm * bn * 4.0 / 4.0e6;
+  if (saved_us < 1.5 * cost_us + (p.tile == TILE_256 ? 0.0 : 4.0)) return none;
+  p.tail_tiles = rem;
+  p.tail_begin = tiles - rem;
+  p.splits = s;
+  p.ws_bytes = (size_t)rem * s * bm * bn * sizeof(float);
+  return p;
+}
+
+// C tile of tail tile t = sum over the K ranges of hyb_ws[(t * splits + r)] (+ aux_in), eight columns per thread, the
+// ranges four at a time so that their loads are in flight together.
+template <int BM, int BN, bool F16>
+__global__ __launch_bounds__(256) void hybrid_reduce_kernel(int M, int N, int tail_begin, int splits,
+                                                            const float* __restrict__ ws, bf16_t* C,
+                                                            const bf16_t* aux_in) {
+  constexpr int CPT = BM * BN / 8;   // 8-column chunks per tile
+  const int tiles_n = (N + BN - 1) / BN, tiles_m = (M + BM - 1) / BM;
+  const int q = blockIdx.x * 256 + threadIdx.x;
+  const int t = q / CPT, in_tile = q - t * CPT;
+  const TilePos pos = tile_position(tail_begin + t, tiles_m, tiles_n, 1);
+  const int row = in_tile / (BN / 8), col = (in_tile % (BN / 8)) * 8;
+  const int m = pos.tile_m * BM + row, n = pos.tile_n * BN + col;
+  if (m >= M || n >= N) return;
+  const float* part = ws + ((size_t)t * splits * BM + row) * BN + col;
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int r0 = 0; r0 < splits; r0 += 4) {
+    float v[4][8];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (r0 + r < splits) load8(part + (size_t)(r0 + r) * BM * BN, v[r]);   // (uniform)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (r0 + r < splits) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] += v[r][e];
+      }
+  }
+  const int64_t idx = (int64_t)m * N + n;
+  if (aux_in) {
+    float v[8];
+    load8h<F16>(aux_in + idx, v);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] += v[e];
+  }
+  store8h<F16>(C + idx, acc);
+}
+
+template <int LAYOUT, int BM, int BN, int WGM, int WGN, int NS, int PW, bool F16>
+static void launch_hybrid_tile(const HybridPlan& hp, int epi, int M, int N, int K, const void* A, const void* B, void* C,
+                               const void* aux_in, float* ws, hipStream_t st) {
+  const size_t lds = gemm_lds_bytes<BM, BN, 64, WGM, WGN, 1, NS>();
+  const int grid = hp.tail_begin + hp.tail_tiles * hp.splits;
+#define SLAPO_HYB(E)                                                                                           \
+  do {                                                                                                         \
+    auto kern = LAYOUT == GEMM_TN || K % 64 == 0 ? gemm_bf16_kernel<LAYOUT, BM, BN, 64, WGM, WGN, 1, NS, PW, false, E, F16, true> \
+                                                 : gemm_bf16_kernel<LAYOUT, BM, BN, 64, WGM, WGN, 1, NS, PW, LAYOUT != GEMM_TN, E, F16, true>; \
+    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);       \
+    hipLaunchKernelGGL(kern, dim3(grid), dim3((WGM * WGN + PW) * 64), lds, st, M, N, K, (const bf16_t*)A, (const bf16_t*)B, \
+                       (bf16_t*)C, (const bf16_t*)nullptr, (const bf16_t*)aux_in, (bf16_t*)nullptr, 0,         \
+                       hp.tail_begin, hp.splits, ws);                                                          \
+  } while (0)
+  if (epi == EPI_ADD) SLAPO_HYB(EPI_ADD); else SLAPO_HYB(EPI_NONE);
+#undef SLAPO_HYB
+  const int chunks = hp.tail_tiles * (BM * BN / 8);
+  hipLaunchKernelGGL((hybrid_reduce_kernel<BM, BN, F16>), dim3(chunks / 256), dim3(256), 0, st, M, N, hp.tail_begin, hp.splits,
+                     (const float*)ws, (bf16_t*)C, epi == EPI_ADD ? (const bf16_t*)aux_in : (const bf16_t*)nullptr);
+}
+
+template <int LAYOUT, bool F16>
+static void launch_hybrid(const HybridPlan& hp, int epi, int M, int N, int K, const void* A, const void* B, void* C,
+                          const void* aux_in, float* ws, hipStream_t st) {
+  if (hp.tile == TILE_256) launch_hybrid_tile<LAYOUT, 256, 256, 2, 4, 2, 0, F16>(hp, epi, M, N, K, A, B, C, aux_in, ws, st);
+  else if constexpr (LAYOUT != GEMM_TN) {
+    if (hp.tile == TILE_128_LOADERS) launch_hybrid_tile<LAYOUT, 128, 128, 2, 4, 4, 4, F16>(hp, epi, M, N, K, A, B, C, aux_in, ws, st);
+    else launch_hybrid_tile<LAYOUT, 128, 64, 2, 2, 4, 4, F16>(hp, epi, M, N, K, A, B, C, aux_in, ws, st);
+  }
+}
+
 template <int LAYOUT, bool F16>
 static void launch_bf16(int epi, int act, int M, int N, int K, const void* A, const void* B, void* C,
                         const void* bias, const void* aux_in, void* aux_out, hipStream_t st, bool solo, float* ws,
                         size_t ws_bytes) {
-  if (ws && select_tile(LAYOUT, M, N, K, false) == TILE_256) {
+  if (ws) {
     // (with a workspace the thin last round in K ranges also beats the full grid of 128x128 tiles that a GEMM running
     // alone would otherwise take: 359 against 397 us for the 8192 x 2560 x 10240 NT product)
-    const HybridPlan hp = hybrid_plan(epi, M, N, K);
+    const HybridPlan hp = hybrid_plan(LAYOUT, epi, M, N, K);
     if (hp.ws_bytes && hp.ws_bytes <= ws_bytes) {
       launch_hybrid<LAYOUT, F16>(hp, epi, M, N, K, A, B, C, aux_in, ws, st);
       return;
@@ -976,14 +1001,20 @@ static int weight_grad_splits(int M, int N, int K) {
   return s < 2 ? 1 : (int)s;
 }
 
-size_t gemm_ws_bytes(int dtype, int epi, int M, int N, int K) {
-  return dtype == DT_FP32 ? 0 : hybrid_plan(epi, M, N, K).ws_bytes;
+size_t gemm_ws_bytes(int dtype, int layout, int epi, int M, int N, int K) {
+  return dtype == DT_FP32 ? 0 : hybrid_plan(layout, epi, M, N, K).ws_bytes;
+}
+
+size_t gemm_ws_least_bytes(int dtype, int layout, int epi, int M, int N, int K) {
+  if (dtype == DT_FP32) return 0;
+  const HybridPlan hp = hybrid_plan(layout, epi, M, N, K);
+  return hp.tile == TILE_256 ? hp.ws_bytes : 0;
 }
 
 size_t weight_grad_ws_bytes(int dtype, int M, int N, int K) {
   if (dtype == DT_FP32) return 0;
   const int s = weight_grad_splits(M, N, K);
-  return s > 1 ? (size_t)s * M * N * sizeof(float) : hybrid_plan(EPI_NONE, M, N, K).ws_bytes;   // (same for the add epilogue)
+  return s > 1 ? (size_t)s * M * N * sizeof(float) : hybrid_plan(GEMM_TN, EPI_NONE, M, N, K).ws_bytes;   // (same for the add epilogue)
 }
 
 template <bool F16>
@@ -1024,11 +1055,13 @@ void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool sol
   const int f16 = dtype == DT_FP16 ? 1 : 0;
   const char* b = f16 ? "true" : "false";
   const char* kt = layout != GEMM_TN && K % 64 != 0 ? "true" : "false";
-  if (with_ws && !(weight_grad && weight_grad_splits(M, N, K) > 1) && select_tile(layout, M, N, K, false) == TILE_256) {
-    const HybridPlan hp = hybrid_plan(weight_grad ? EPI_NONE : epi, M, N, K);
+  static const char* const shape[] = {"256, 256, 64, 2, 4, 1, 2, 0", "128, 128, 64, 2, 2, 2, 4, 4", "128, 128, 64, 2, 4, 1, 4, 4",
+                                      "128, 64, 64, 2, 2, 1, 4, 4"};
+  if (with_ws && !(weight_grad && weight_grad_splits(M, N, K) > 1)) {
+    const HybridPlan hp = hybrid_plan(layout, weight_grad ? EPI_NONE : epi, M, N, K);
     if (hp.ws_bytes) {
-      snprintf(buf, len, "gemm_bf16_kernel<%d, 256, 256, 64, 2, 4, 1, 2, 0, %s, %d, %s, true> (%d tiles + %d tiles in %d K ranges) + hybrid_reduce_kernel",
-               layout, kt, epi, b, hp.tail_begin, hp.tail_tiles, hp.splits);
+      snprintf(buf, len, "gemm_bf16_kernel<%d, %s, %s, %d, %s, true> (%d tiles + %d tiles in %d K ranges) + hybrid_reduce_kernel",
+               layout, shape[(int)hp.tile], kt, epi, b, hp.tail_begin, hp.tail_tiles, hp.splits);
       return;
     }
   }
@@ -1039,8 +1072,6 @@ void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool sol
       return;
     }
   }
-  static const char* const shape[] = {"256, 256, 64, 2, 4, 1, 2, 0", "128, 128, 64, 2, 2, 2, 4, 4", "128, 128, 64, 2, 4, 1, 4, 4",
-                                      "128, 64, 64, 2, 2, 1, 4, 4"};
   const TileKind k = epi_used(layout, epi) ? select_tile(layout, M, N, K, solo) : TILE_128_LOADERS;
   snprintf(buf, len, "gemm_bf16_kernel<%d, %s, %s, %d, %s, false>", layout, shape[(int)k], kt, epi, b);
 }

@@ -19,11 +19,14 @@ enum { EPI_NONE = 0, EPI_BIAS = 1, EPI_BIAS_ACT = 2, EPI_DACT = 3, EPI_ADD = 4, 
 
 // solo: nothing else runs beside this GEMM (it may then pick tiles by round count, see launch_bf16)
 // ws / ws_bytes: optional fp32 workspace (gemm_ws_bytes says how much a shape can use; 0: none). With it, a grid
-//   of 256x256 tiles that would end in a thin last round computes its last tiles in several K ranges instead.
+//   that would end in a thin last round computes its last tiles in several K ranges instead.
 void launch_gemm(int dtype, int layout, int epi, int act, int M, int N, int K, const void* A, const void* B,
                  void* C, const void* bias, const void* aux_in, void* aux_out, hipStream_t st, bool solo = false,
                  float* ws = nullptr, size_t ws_bytes = 0);
-size_t gemm_ws_bytes(int dtype, int epi, int M, int N, int K);
+size_t gemm_ws_bytes(int dtype, int layout, int epi, int M, int N, int K);
+// the smallest workspace that a caller who passes one may pass: 256x256 grids ask for all that they can use, grids of
+// smaller tiles do without one that is too small for them
+size_t gemm_ws_least_bytes(int dtype, int layout, int epi, int M, int N, int K);
 void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool solo, bool weight_grad, bool with_ws,
                    char* buf, size_t len);
 // Weight gradient C[M,N] (+)= A[K,M]^T B[K,N] (accumulate: add to C). Outputs with too few tiles to fill the

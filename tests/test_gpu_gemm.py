@@ -143,6 +143,40 @@ def test_thin_last_round_in_k_ranges(dtype, layout, M, N, K):
     assert e.value.status == -5
 
 
+# The same for the smaller tiles (NT and NN only): 272 tiles of 128x128 with 16 in the tail, 304 with ragged edges and a
+# partial last slab, and grids of 128x64 tiles that are all tail: 16 tiles in 8 ranges, 9 ragged ones in 8, one row.
+@pytest.mark.parametrize("dtype", [W.BF16, W.FP16])
+@pytest.mark.parametrize("layout", [B.NT, B.NN])
+@pytest.mark.parametrize("M,N,K", [(2176, 2048, 2048), (2331, 2040, 4104), (128, 1024, 4096), (300, 136, 6152), (1, 64, 4096)])
+def test_small_tiles_in_k_ranges(dtype, layout, M, N, K):
+    nbytes = B.slapo_gemm_workspace(dtype, layout, B.EPI_NONE, M, N, K)
+    assert nbytes > 0 and nbytes == B.slapo_gemm_workspace(dtype, layout, B.EPI_ADD, M, N, K)
+    assert B.slapo_gemm_workspace(dtype, layout, B.EPI_BIAS, M, N, K) == 0
+    assert "K ranges" in B.slapo_gemm_kernel_name(dtype, layout, B.EPI_NONE, M, N, K, with_ws=1)
+    rng = np.random.default_rng(M + N + K + layout)
+    a = store(rng.standard_normal((M, K)), dtype)
+    b = store(rng.standard_normal((K, N)) * 0.1, dtype)
+    aux = store(rng.standard_normal((M, N)), dtype)
+    ref = a.astype(np.float64) @ b.astype(np.float64)
+    A, Bm, auxd = to_dev(a, dtype), to_dev(b.T.copy() if layout == B.NT else b, dtype), to_dev(aux, dtype)
+    ws = torch.full((nbytes,), 0x7F, dtype=torch.uint8, device=DEV)
+    out = torch.empty(M, N, dtype=A.dtype, device=DEV)
+    B.slapo_gemm_ex(dtype, layout, B.EPI_NONE, 0, M, N, K, A, Bm, out, ws=ws)
+    tol = {W.BF16: 5e-3, W.FP16: 1e-3}[dtype]
+    assert err(out, ref) <= tol
+    out2 = torch.empty_like(out)
+    B.slapo_gemm_ex(dtype, layout, B.EPI_NONE, 0, M, N, K, A, Bm, out2, ws=ws)
+    assert torch.equal(out, out2)
+    acc = auxd.clone()
+    B.slapo_gemm_ex(dtype, layout, B.EPI_ADD, 0, M, N, K, A, Bm, acc, aux_in=acc, ws=ws)
+    assert err(acc, ref + aux) <= tol
+    small = torch.empty_like(out)                    # a workspace that does not hold the partial tiles is left alone
+    B.slapo_gemm_ex(dtype, layout, B.EPI_NONE, 0, M, N, K, A, Bm, small, ws=ws[:16])
+    plain = torch.empty_like(out)
+    B.slapo_gemm(dtype, layout, B.EPI_NONE, 0, M, N, K, A, Bm, plain)
+    assert torch.equal(small, plain) and err(plain, ref) <= tol
+
+
 # K that is no multiple of the 64-deep slab: fewer than one slab, one element piece over, one under, odd (token counts of
 # weight gradients), against 256x256 tiles, 128x128 tiles and 128x64 tiles (all with ragged edges) and the K-range forms.
 @pytest.mark.parametrize("layout,Ks", [(B.NT, (8, 72, 200, 1016)), (B.NN, (8, 72, 200, 1016)), (B.TN, (1, 63, 65, 203, 1013))])
