@@ -126,7 +126,8 @@ int finish() {
 // library on the same device share them: every event record and the stream wait that consumes it are issued
 // under the device's mutex, so a wait always captures the record of its own call (a wait refers to the
 // record that precedes it at the time it is issued), and the calls' helper-stream work simply queues up
-// behind each other. "single-stream" in SLAPO_DEBUG turns the helper stream off.
+// behind each other. "single-stream" in SLAPO_DEBUG turns the helper stream off; small
+// calls do without it (backward_on_one_stream).
 struct SideStream {
   hipStream_t stream = nullptr;
   hipEvent_t fork[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -160,6 +161,19 @@ SideStream* side_stream() {
     if (!ok) (void)hipGetLastError();
   }
   return s.state == 1 ? &s : nullptr;
+}
+
+// Small calls keep all of backward on the caller's stream. A fork costs the host two event calls (the ten of a layer
+// take about 100 us, as much as its 27 launches) and the GPU 5 us of idle stream each, and next to kernels of 5 to 10 us there
+// is little to fill. Multiply-adds of the layer's projections decide, with 40 tokens' worth added for the weights that each
+// call reads and writes whatever its size. Steps per call, one stream / two: hidden 1024 (feed-forward 4096) at 128 tokens
+// 160 / 214 us, 512 187 / 201, 1024 230 / 218; hidden 512 at 2048 tokens 197 / 205; 768 at 1024 195 / 204, at 2048 262 /
+// 240; 2048 at 64 201 / 204, at 128 226 / 222. fp32 multiply-adds count eightfold (hidden 768: 225 / 225 at 64 tokens, 649 /
+// 637 at 512).
+bool backward_on_one_stream(const slapo_layer_desc* d) {
+  const double T = (double)d->batch * d->seq, H = d->hidden, F = d->ffn, A = attn_width(d);
+  const double weights = 4.0 * H * A + (is_llama(d) ? 3.0 : 2.0) * H * F;
+  return weights * (T + 40.0) * (d->dtype == SLAPO_FP32 ? 8.0 : 1.0) < 8.0e9;
 }
 
 // byte offsets of the regions of `saved`
@@ -443,7 +457,7 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   const DropoutParams dp0 = make_dropout(d, 0), dp1 = make_dropout(d, 1);
   const int nrow = bdrln_bwd_blocks(T), ncol = colsum_blocks(T);
   // `st` carries the data-gradient chain; `ws` the weight / bias gradients that hang off it
-  SideStream* side = side_stream();
+  SideStream* side = backward_on_one_stream(d) ? nullptr : side_stream();
   const bool solo = side == nullptr;   // one stream: every GEMM has the chip to itself
   hipStream_t ws = side ? side->stream : st;
   auto fork = [&](int i) {   // everything issued on st so far happens before what follows on ws

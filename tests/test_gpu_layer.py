@@ -243,3 +243,18 @@ def test_layer_parity_degenerate_sizes(cfg):
     tol, stol = TOL[cfg.dtype], saved_tol(cfg)
     bad = {k: v for k, v in errs.items() if not v <= (stol if k.startswith("saved.") else tol)}
     assert not bad, (bad, errs)
+
+
+# around the size from which backward uses the helper stream: 591 tokens on one stream, 600 on two
+@pytest.mark.parametrize("seq", [197, 200])
+def test_layer_parity_on_either_side_of_the_stream_rule(seq):
+    errs, _, _ = run_case(W.LayerConfig("streams-%d" % seq, 3, seq, 1024, 16, 4096, causal=0, dropout_p=0.1, dtype=W.BF16,
+                                        len_lo=40, len_hi=seq, config_id=61))
+    assert all(v <= TOL[W.BF16] for v in errs.values()), errs
+
+
+def test_two_host_threads_share_the_helper_stream(monkeypatch):
+    """The test above at sizes whose backward forks."""
+    big = [W.LayerConfig("threads-%d" % b, b, 200, 1024, 16, 4096, causal=0, dropout_p=0.1, dtype=W.BF16, config_id=62 + b) for b in (3, 4)]
+    monkeypatch.setitem(globals(), "SMALL", [None] * 4 + big)
+    test_backward_from_two_host_threads_on_one_device()
