@@ -422,8 +422,10 @@ __global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(i
     // since the barrier that ended step k - 1), computes slab k, then waits until its own loads of slab
     // k + 1 have landed (the younger ones stay in flight) and meets the other wavefronts at the barrier.
     auto compute = [&](int stage) {
-      // scheduling hint for the slab: interleave the LDS reads with the MFMAs (variant chosen by measurement)
-      __builtin_amdgcn_iglp_opt(LAYOUT == GEMM_TN ? 1 : 0);
+      // Scheduling hint for the slab: interleave the LDS reads with the MFMAs. With two transposing reads per fragment of
+      // both operands the plain order is the faster one (same box: 2048 x 2048 x 8192 60.9 us, 64.4 and 66.0 with the
+      // interleaving and its second variant, 1024 x 4096 x 16384 115.8 / 122.3 / 125.7); elsewhere 0-3 % the other way.
+      if constexpr (LAYOUT != GEMM_TN) __builtin_amdgcn_iglp_opt(0);
 #pragma unroll
       for (int kq = 0; kq < KQ; ++kq) {
         bf16x8_t fa[TM], fb[TN];
@@ -818,12 +820,13 @@ static TileKind select_tile(int layout, int M, int N, int K, bool solo) {
   }
   if (big) return TILE_256;
   // TN: both operands go through the transposing LDS reads (two per fragment): the 64x64 wave tile of the
-  // split-slab form needs a third fewer of them per MFMA, worth 5-7 % on the weight-gradient shapes; the
-  // K-contiguous layouts gain nothing from it
+  // split-slab form needs a third fewer of them per MFMA, worth 2-7 % on the weight-gradient shapes from K = 2048 on; the
+  // K-contiguous layouts gain nothing from it. Short K pays for the sum of its two wave sets instead: 1024 x 4096 outputs
+  // at K = 128 6.8 / 6.0 us (split-slab / plain), 512 9.0 / 8.1, 1024 12.5 / 11.6, 2048 18.3 / 18.8.
   // Two rounds of 128x64 tiles are slower than one of 128x128 (768 x 3072 outputs, K = 2286: 26.8 against 18.7 us), one
   // round is faster (2304 x 768: 14.9 against 17.4).
   if ((int64_t)((M + 127) / 128) * ((N + 63) / 64) <= 256) return TILE_128x64_LOADERS;
-  return layout == GEMM_TN ? TILE_128_SPLITSLAB : TILE_128_LOADERS;
+  return layout == GEMM_TN && K > 1024 ? TILE_128_SPLITSLAB : TILE_128_LOADERS;
 }
 
 // ---- thin last rounds: the tail tiles of a grid in several K ranges ----------------------------------
