@@ -149,7 +149,8 @@ __device__ __forceinline__ TilePos tile_position(int bid, int tiles_m, int tiles
 // order and applies the epilogue. Plain launches pass tail_begin = number of tiles.
 template <int LAYOUT, int BM, int BN, int BK, int WGM, int WGN, int KS, int NS, int PW, bool KTAIL, int EPI,
           bool F16 = false, bool HYB = false>
-__global__ __launch_bounds__((WGM * WGN * KS + PW) * 64) void gemm_bf16_kernel(int M, int N, int K,
+__global__ __launch_bounds__((WGM * WGN * KS + PW) * 64, NS == 2 && PW ? 6 : 1)   // (two workgroups of twelve wavefronts per CU)
+void gemm_bf16_kernel(int M, int N, int K,
                                                                   const bf16_t* __restrict__ A,
                                                                   const bf16_t* __restrict__ B,
                                                                   bf16_t* __restrict__ C,
@@ -829,6 +830,15 @@ static TileKind select_tile(int layout, int M, int N, int K, bool solo) {
   return layout == GEMM_TN && K > 1024 ? TILE_128_SPLITSLAB : TILE_128_LOADERS;
 }
 
+// Several rounds of 128x128 tiles: two LDS stages instead of four, so that two workgroups fit a CU and one's first loads and
+// epilogue run beside the other's products. Four / two stages, same box: NT 2286 x 3072 x 768 with GeLU 24.1 / 20.7
+// us, 2331 x 8192 x 2048 101 / 93.5, 2000 x 2560 x 2560 39.2 / 34.7; NN 2048 x 4096 x 2752 44.6 / 41.9, 2331 x 2752 x
+// 4096 gated 62.9 / 57.0. Many rounds of long K gain nothing (700 x 16384 x 4096 101.6 / 104.2).
+static bool two_per_cu(int M, int N, int K) {
+  const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
+  return t128 > 256 && (t128 <= 512 || K <= 3072);
+}
+
 // ---- thin last rounds: the tail tiles of a grid in several K ranges ----------------------------------
 // 320 tiles on 256 CUs take two rounds for 1.25 rounds of work. With a workspace at hand, the tiles beyond the
 // last full round are cut into s = 256 / (their number) K ranges, so that the last round has about 256 workgroups
@@ -958,6 +968,10 @@ static void launch_bf16(int epi, int act, int M, int N, int K, const void* A, co
       if constexpr (LAYOUT == GEMM_TN) launch_bf16_tile<LAYOUT, 128, 128, 2, 2, 2, 4, 4, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
       break;
     case TILE_128_LOADERS:
+      if (two_per_cu(M, N, K)) {
+        launch_bf16_tile<LAYOUT, 128, 128, 2, 4, 1, 2, 4, F16, true>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
+        break;
+      }
       launch_bf16_tile<LAYOUT, 128, 128, 2, 4, 1, 4, 4, F16, true>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st); break;
     case TILE_128x64_LOADERS:
       launch_bf16_tile<LAYOUT, 128, 64, 2, 2, 1, 4, 4, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st); break;
@@ -1076,6 +1090,10 @@ void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool sol
     }
   }
   const TileKind k = epi_used(layout, epi) ? select_tile(layout, M, N, K, solo) : TILE_128_LOADERS;
+  if (k == TILE_128_LOADERS && two_per_cu(M, N, K)) {
+    snprintf(buf, len, "gemm_bf16_kernel<%d, 128, 128, 64, 2, 4, 1, 2, 4, %s, %d, %s, false>", layout, kt, epi, b);
+    return;
+  }
   snprintf(buf, len, "gemm_bf16_kernel<%d, %s, %s, %d, %s, false>", layout, shape[(int)k], kt, epi, b);
 }
 
