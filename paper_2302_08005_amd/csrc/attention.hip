@@ -900,7 +900,33 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_bf16_kernel(AttnShape sh, con
 }
 
 // =================================== fp32 / generic simple kernels ===============================
-// One wavefront per query row; lane <-> key for the scores, lane <-> head-dim column for the output.
+// One wavefront per query row; lane <-> key for the scores, lane <-> head-dim column for the output. Both loops are
+// chains of load latencies: the row of a key is read 16 bytes at a time, and the rows behind an output column eight at a
+// time (added in row order). Small fp32 encoder layer (2 x 128 tokens, 4 heads of 64), against one float at a time:
+// forward 18.1 -> 12.7 us, dQ 15.1 -> 14.0, dK/dV 24.4 -> 18.0, the same bits.
+__host__ __device__ constexpr int padded4(int n) { return (n + 3) / 4 * 4; }   // LDS rows start at 16 bytes
+template <int D>
+__device__ __forceinline__ float row_dot(const float* a, const float* __restrict__ b, float s) {   // s + a . b, in order
+#pragma unroll 8
+  for (int d = 0; d < D; d += 4) {
+    const float4 x = *reinterpret_cast<const float4*>(a + d), y = *reinterpret_cast<const float4*>(b + d);
+    s = fmaf(x.x, y.x, s); s = fmaf(x.y, y.y, s); s = fmaf(x.z, y.z, s); s = fmaf(x.w, y.w, s);
+  }
+  return s;
+}
+// acc + sum over rows first <= j < end of w[j] * x[j * stride], in order
+__device__ __forceinline__ float rows_sum(const float* w, const float* __restrict__ x, int64_t stride, int first, int end, float acc) {
+  int j = first;
+  for (; j + 8 <= end; j += 8) {
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = x[(j + e) * stride];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc = fmaf(w[j + e], v[e], acc);
+  }
+  for (; j < end; ++j) acc = fmaf(w[j], x[j * stride], acc);
+  return acc;
+}
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_fwd_simple_kernel(AttnShape sh, const T* __restrict__ qkv,
                                                               const int32_t* __restrict__ seqlens,
@@ -908,7 +934,7 @@ __global__ __launch_bounds__(256) void attn_fwd_simple_kernel(AttnShape sh, cons
   extern __shared__ float fsm[];  // per wave: q[D], p[S]
   const int S = sh.seq, H = sh.hidden, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int b = blockIdx.z, a = blockIdx.y, i = blockIdx.x * 4 + wave;
-  float* qs = fsm + wave * (D + S);
+  float* qs = fsm + wave * (D + padded4(S));
   float* ps = qs + D;
   if (i >= S) return;  // no block-wide barrier below
   const int64_t rs = 3 * (int64_t)H;
@@ -920,10 +946,7 @@ __global__ __launch_bounds__(256) void attn_fwd_simple_kernel(AttnShape sh, cons
   __builtin_amdgcn_wave_barrier();
   float mx = -INFINITY;
   for (int j = lane; j < kv_end; j += 64) {
-    const T* kr = base + H + j * rs;
-    float s = 0.f;
-    for (int dd = 0; dd < D; ++dd) s = fmaf(qs[dd], to_f32(kr[dd]), s);
-    s *= scale;
+    const float s = row_dot<D>(qs, base + H + j * rs, 0.f) * scale;
     ps[j] = s;
     mx = fmaxf(mx, s);
   }
@@ -940,8 +963,7 @@ __global__ __launch_bounds__(256) void attn_fwd_simple_kernel(AttnShape sh, cons
   __builtin_amdgcn_wave_barrier();
   const float inv = sum > 0.f ? sh.drop.scale / sum : 0.f;
   for (int dd = lane; dd < D; dd += 64) {
-    float acc = 0.f;
-    for (int j = 0; j < kv_end; ++j) acc = fmaf(ps[j], to_f32(base[2 * H + j * rs + dd]), acc);
+    const float acc = rows_sum(ps, base + 2 * H + dd, rs, 0, kv_end, 0.f);
     from_f32(out[((int64_t)b * S + i) * H + a * D + dd], acc * inv);
   }
   if (lane == 0) lse[((int64_t)b * sh.heads + a) * S + i] = sum > 0.f ? mx + __logf(sum) : -INFINITY;
@@ -957,7 +979,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_simple_kernel(AttnShape sh, c
   extern __shared__ float fsm[];  // per wave: q[D], do[D], ds[S]
   const int S = sh.seq, H = sh.hidden, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int b = blockIdx.z, a = blockIdx.y, i = blockIdx.x * 4 + wave;
-  float* qs = fsm + wave * (2 * D + S);
+  float* qs = fsm + wave * (2 * D + padded4(S));
   float* dos = qs + D;
   float* ds = dos + D;
   if (i >= S) return;
@@ -974,18 +996,15 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_simple_kernel(AttnShape sh, c
   }
   __builtin_amdgcn_wave_barrier();
   for (int j = lane; j < kv_end; j += 64) {
-    const T* kr = base + H + j * rs;
-    const T* vr = base + 2 * H + j * rs;
-    float s = 0.f, dp = 0.f;
-    for (int dd = 0; dd < D; ++dd) { s = fmaf(qs[dd], to_f32(kr[dd]), s); dp = fmaf(dos[dd], to_f32(vr[dd]), dp); }
+    const float s = row_dot<D>(qs, base + H + j * rs, 0.f);
+    float dp = row_dot<D>(dos, base + 2 * H + j * rs, 0.f);
     const float p = __expf(s * scale - my_lse);
     if (sh.drop.thr != 0) dp = dropout_keep1(sh.drop, e_row + j) ? dp * sh.drop.scale : 0.f;
     ds[j] = p * (dp - my_delta);
   }
   __builtin_amdgcn_wave_barrier();
   for (int dd = lane; dd < D; dd += 64) {
-    float acc = 0.f;
-    for (int j = 0; j < kv_end; ++j) acc = fmaf(ds[j], to_f32(base[H + j * rs + dd]), acc);
+    const float acc = rows_sum(ds, base + H + dd, rs, 0, kv_end, 0.f);
     from_f32(dqkv[((int64_t)b * S + i) * rs + a * D + dd], acc * scale);
   }
 }
@@ -1000,10 +1019,10 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_simple_kernel(AttnShape sh,
   extern __shared__ float fsm[];  // per wave: k[D], v[D], p[S], ds[S]
   const int S = sh.seq, H = sh.hidden, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int b = blockIdx.z, a = blockIdx.y, j = blockIdx.x * 4 + wave;
-  float* ks = fsm + wave * (2 * D + 2 * S);
+  float* ks = fsm + wave * (2 * D + 2 * padded4(S));
   float* vs = ks + D;
   float* ps = vs + D;
-  float* ds = ps + S;
+  float* ds = ps + padded4(S);
   if (j >= S) return;
   const int64_t rs = 3 * (int64_t)H;
   const T* base = qkv + (int64_t)b * S * rs + a * D;
@@ -1013,10 +1032,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_simple_kernel(AttnShape sh,
   for (int dd = lane; dd < D; dd += 64) { ks[dd] = to_f32(base[H + j * rs + dd]); vs[dd] = to_f32(base[2 * H + j * rs + dd]); }
   __builtin_amdgcn_wave_barrier();
   for (int i = i_first + lane; i < S; i += 64) {
-    const T* qr = base + i * rs;
-    const T* dr = dout + ((int64_t)b * S + i) * H + a * D;
-    float s = 0.f, dp = 0.f;
-    for (int dd = 0; dd < D; ++dd) { s = fmaf(to_f32(qr[dd]), ks[dd], s); dp = fmaf(to_f32(dr[dd]), vs[dd], dp); }
+    const float s = row_dot<D>(ks, base + i * rs, 0.f);
+    float dp = row_dot<D>(vs, dout + ((int64_t)b * S + i) * H + a * D, 0.f);
     const float p = __expf(s * scale - lse[((int64_t)b * sh.heads + a) * S + i]);
     float pv = p;   // what multiplies V in the forward pass
     if (sh.drop.thr != 0) {
@@ -1029,11 +1046,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_simple_kernel(AttnShape sh,
   }
   __builtin_amdgcn_wave_barrier();
   for (int dd = lane; dd < D; dd += 64) {
-    float dk = 0.f, dv = 0.f;
-    for (int i = i_first; i < S; ++i) {
-      dk = fmaf(ds[i], to_f32(base[i * rs + dd]), dk);
-      dv = fmaf(ps[i], to_f32(dout[((int64_t)b * S + i) * H + a * D + dd]), dv);
-    }
+    const float dk = rows_sum(ds, base + dd, rs, i_first, S, 0.f);
+    const float dv = rows_sum(ps, dout + (int64_t)b * S * H + a * D + dd, H, i_first, S, 0.f);
     from_f32(dqkv[((int64_t)b * S + j) * rs + H + a * D + dd], dk * scale);
     from_f32(dqkv[((int64_t)b * S + j) * rs + 2 * H + a * D + dd], dv);
   }
@@ -1050,7 +1064,7 @@ static void fwd_bf16(const AttnShape& s, const void* qkv, const int32_t* seqlens
 }
 template <int D>
 static void fwd_f32(const AttnShape& s, const void* qkv, const int32_t* seqlens, void* out, float* lse, hipStream_t st) {
-  const size_t lds = (size_t)4 * (D + s.seq) * sizeof(float);
+  const size_t lds = (size_t)4 * (D + padded4(s.seq)) * sizeof(float);
   auto kern = attn_fwd_simple_kernel<float, D>;
   (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(kern, dim3((s.seq + 3) / 4, s.heads, s.batch), dim3(256), lds, st, s, (const float*)qkv, seqlens,
@@ -1102,14 +1116,14 @@ static void bwd_f32(const AttnShape& s, const void* qkv, const int32_t* seqlens,
                      (const float*)out, (const float*)dout, delta);
   dim3 grid((s.seq + 3) / 4, s.heads, s.batch);
   {
-    const size_t lds = (size_t)4 * (2 * D + s.seq) * sizeof(float);
+    const size_t lds = (size_t)4 * (2 * D + padded4(s.seq)) * sizeof(float);
     auto kern = attn_bwd_dq_simple_kernel<float, D>;
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, s, (const float*)qkv, seqlens, (const float*)dout, lse,
                        (const float*)delta, (float*)dqkv);
   }
   {
-    const size_t lds = (size_t)4 * (2 * D + 2 * s.seq) * sizeof(float);
+    const size_t lds = (size_t)4 * (2 * D + 2 * padded4(s.seq)) * sizeof(float);
     auto kern = attn_bwd_dkdv_simple_kernel<float, D>;
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, s, (const float*)qkv, seqlens, (const float*)dout, lse,
