@@ -642,7 +642,7 @@ constexpr size_t gemm_lds_bytes() {
   return m1 > red_bytes ? m1 : red_bytes;
 }
 
-// fp32: 32x32 tiles, eight wavefronts that take the 16-deep K chunks of the tile in turn, so that a product with few
+// fp32: 32x32 tiles (W = 2), or 16x16 (W = 1) where the larger ones would leave half of the CUs idle, eight wavefronts that take the 16-deep K chunks of the tile in turn, so that a product with few
 // tiles (256 tokens, 256 columns: 64) still has 512 wavefronts' loads in flight; such products are bound by the chain of
 // load latencies, not by the 157 TFLOP/s of the fp32 MFMAs. Operands go from memory to registers in the shape of
 // v_mfma_f32_16x16x4_f32 fragments (nothing is shared between wavefronts that do not share K), the next chunk requested
@@ -651,47 +651,51 @@ constexpr size_t gemm_lds_bytes() {
 // and 67 us.)
 // A fragment element belongs to k = k0 + 4 (lane/16) + s in step s for either operand; lane%16 counts rows.
 //  - contiguous along K: one 16-byte load per 16 rows gives the four steps
-//  - contiguous along rows: one 8-byte load per step gives the rows 2 (lane%16) + {0, 1} of the two 16-row tiles
-// Against one 64x64 tile of plain FMAs per workgroup: 256 x 256 x 1024 142 -> 10 us, 512 x 3072 x 768 157 -> 48 us.
+//  - contiguous along rows: one load of W floats per step gives the rows W (lane%16) .. + W - 1 of the W 16-row tiles
+// Against one 64x64 tile of plain FMAs per workgroup: 256 x 256 x 1024 142 -> 6 us, 512 x 3072 x 768 157 -> 48 us.
 constexpr int F32_WAVES = 8;
-template <int LAYOUT>
+template <int LAYOUT, int W>
 __global__ __launch_bounds__(F32_WAVES * 64) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A,
                                                                   const float* __restrict__ B, float* __restrict__ C,
                                                                   const float* __restrict__ bias, const float* aux_in,
                                                                   float* __restrict__ aux_out, int epi, int act) {
   constexpr bool A_KC = LAYOUT != GEMM_TN, B_KC = LAYOUT == GEMM_NT;
-  constexpr int PITCH = 36;   // floats per staged row of 32
-  __shared__ __attribute__((aligned(16))) float part[F32_WAVES][32 * PITCH];
-  const int tiles_n = (N + 31) / 32;
-  const int m0 = ((int)blockIdx.x / tiles_n) * 32, n0 = ((int)blockIdx.x % tiles_n) * 32;
+  constexpr int TILE = 16 * W, PITCH = TILE + 4;   // floats per staged row
+  __shared__ __attribute__((aligned(16))) float part[F32_WAVES][TILE * PITCH];
+  const int tiles_n = (N + TILE - 1) / TILE;
+  const int m0 = ((int)blockIdx.x / tiles_n) * TILE, n0 = ((int)blockIdx.x % tiles_n) * TILE;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i = lane & 15, g = lane >> 4;
 
-  struct Frag { float v[2][4]; };   // [16-row tile][step]
+  struct Frag { float v[W][4]; };   // [16-row tile][step]
   // rows beyond the operand are clamped (their products are never stored), k beyond K is zero in both operands
   auto load = [&](auto kc, const float* X, int r0, int rows, int k0) {
     Frag f;
     if constexpr (decltype(kc)::value) {
       const int k = k0 + 4 * g;
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
+      for (int t = 0; t < W; ++t) {
         const int r = r0 + 16 * t + i < rows ? r0 + 16 * t + i : rows - 1;
         float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
         if (k < K) w = *reinterpret_cast<const float4*>(X + (int64_t)r * K + k);   // (K % 8 == 0)
         f.v[t][0] = w.x; f.v[t][1] = w.y; f.v[t][2] = w.z; f.v[t][3] = w.w;
       }
     } else {
-      const int r = r0 + 2 * i < rows ? r0 + 2 * i : rows - 2;                      // (rows % 8 == 0)
+      const int r = r0 + W * i < rows ? r0 + W * i : rows - W;                      // (rows % 8 == 0)
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         const int k = k0 + 4 * g + s;
-        float2 w = make_float2(0.f, 0.f);
-        if (k < K) w = *reinterpret_cast<const float2*>(X + (int64_t)k * rows + r);
-        f.v[0][s] = w.x; f.v[1][s] = w.y;
+        if constexpr (W == 2) {
+          float2 w = make_float2(0.f, 0.f);
+          if (k < K) w = *reinterpret_cast<const float2*>(X + (int64_t)k * rows + r);
+          f.v[0][s] = w.x; f.v[1][s] = w.y;
+        } else {
+          f.v[0][s] = k < K ? X[(int64_t)k * rows + r] : 0.f;
+        }
       }
     }
     return f;
   };
-  f32x4_t acc[2][2] = {};
+  f32x4_t acc[W][W] = {};
   const int chunks = (K + 15) / 16;
   Frag fa[2], fb[2];
   auto fetch = [&](int buf, int c) {
@@ -704,9 +708,9 @@ __global__ __launch_bounds__(F32_WAVES * 64) void gemm_f32_kernel(int M, int N, 
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int tm = 0; tm < 2; ++tm)
+      for (int tm = 0; tm < W; ++tm)
 #pragma unroll
-        for (int tn = 0; tn < 2; ++tn)   // operands swapped: a lane holds four columns of one row
+        for (int tn = 0; tn < W; ++tn)   // operands swapped: a lane holds four columns of one row
           acc[tm][tn] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[buf].v[tn][s], fa[buf].v[tm][s], acc[tm][tn], 0, 0, 0);
   };
   fetch(0, wave);
@@ -719,25 +723,28 @@ __global__ __launch_bounds__(F32_WAVES * 64) void gemm_f32_kernel(int M, int N, 
   // element (tm, tn, r) of the lane: row i of A tile tm, row 4 g + r of B tile tn
   float* mine = part[wave];
 #pragma unroll
-  for (int tm = 0; tm < 2; ++tm) {
-    float* row = mine + (A_KC ? 16 * tm + i : 2 * i + tm) * PITCH;
+  for (int tm = 0; tm < W; ++tm) {
+    float* row = mine + (A_KC ? 16 * tm + i : W * i + tm) * PITCH;
     if constexpr (B_KC) {
 #pragma unroll
-      for (int tn = 0; tn < 2; ++tn) *reinterpret_cast<f32x4_t*>(row + 16 * tn + 4 * g) = acc[tm][tn];
+      for (int tn = 0; tn < W; ++tn) *reinterpret_cast<f32x4_t*>(row + 16 * tn + 4 * g) = acc[tm][tn];
     } else {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) *reinterpret_cast<float2*>(row + 8 * g + 2 * r) = make_float2(acc[tm][0][r], acc[tm][1][r]);
+      for (int tn = 0; tn < W; ++tn)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) row[W * (4 * g + r) + tn] = acc[tm][tn][r];
     }
   }
   __syncthreads();
   // four columns of one row per thread, the partial tiles added in order
-  if (threadIdx.x >= 256) return;
-  const int m = m0 + (int)threadIdx.x / 8, n = n0 + ((int)threadIdx.x % 8) * 4;
+  constexpr int TPR = TILE / 4;   // threads per row
+  if (threadIdx.x >= TILE * TPR) return;
+  const int row = (int)threadIdx.x / TPR, col = ((int)threadIdx.x % TPR) * 4, m = m0 + row, n = n0 + col;
   if (m >= M || n >= N) return;
   float v[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int w = 0; w < F32_WAVES; ++w) {
-    const float4 x = *reinterpret_cast<const float4*>(part[w] + ((int)threadIdx.x / 8) * PITCH + ((int)threadIdx.x % 8) * 4);
+    const float4 x = *reinterpret_cast<const float4*>(part[w] + row * PITCH + col);
     v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
   }
   if (epi == EPI_GATE) {          // (gate, up) pairs in adjacent columns
@@ -760,6 +767,10 @@ __global__ __launch_bounds__(F32_WAVES * 64) void gemm_f32_kernel(int M, int N, 
     for (int j = 0; j < 4; ++j) epilogue_store<float>(epi, act, v[j], m, n + j, N, C, bias, aux_in, aux_out);
   }
 }
+
+// 64 tiles of 32x32 at 256 x 256 x 1024 take 10.3 us, 256 of 16x16 6.1; 75 tiles (77 x 776 x 520) 6.0 / 3.7; 192 tiles
+// (256 x 768 x 256) 5.3 / 5.6; 1536 tiles 48 / 69.
+static bool f32_wide(int M, int N) { return (int64_t)((M + 31) / 32) * ((N + 31) / 32) > 128; }
 
 // epilogue / layout pairs the layer itself uses; the others exist as 128x128 tiles only
 constexpr bool epi_used(int layout, int epi) {
@@ -1068,7 +1079,7 @@ void launch_weight_grad(int dtype, int accumulate, int M, int N, int K, const vo
 // the weight-gradient path (`weight_grad`) with its K ranges, if any.
 void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool solo, bool weight_grad, bool with_ws,
                    char* buf, size_t len) {
-  if (dtype == DT_FP32) { snprintf(buf, len, "gemm_f32_kernel<%d>", layout); return; }
+  if (dtype == DT_FP32) { snprintf(buf, len, "gemm_f32_kernel<%d, %d>", layout, f32_wide(M, N) ? 2 : 1); return; }
   const int f16 = dtype == DT_FP16 ? 1 : 0;
   const char* b = f16 ? "true" : "false";
   const char* kt = layout != GEMM_TN && K % 64 != 0 ? "true" : "false";
@@ -1101,14 +1112,18 @@ void launch_gemm(int dtype, int layout, int epi, int act, int M, int N, int K, c
                  void* C, const void* bias, const void* aux_in, void* aux_out, hipStream_t st, bool solo, float* ws,
                  size_t ws_bytes) {
   if (dtype == DT_FP32) {
-    const dim3 grid((unsigned)(((M + 31) / 32) * ((N + 31) / 32)));
-#define SLAPO_F32(L)                                                                                      \
-  hipLaunchKernelGGL(gemm_f32_kernel<L>, grid, dim3(F32_WAVES * 64), 0, st, M, N, K, (const float*)A, (const float*)B, \
+    const bool wide = f32_wide(M, N);
+    const int tile = wide ? 32 : 16;
+    const dim3 grid((unsigned)(((M + tile - 1) / tile) * ((N + tile - 1) / tile)));
+#define SLAPO_F32W(L, W)                                                                                  \
+  hipLaunchKernelGGL((gemm_f32_kernel<L, W>), grid, dim3(F32_WAVES * 64), 0, st, M, N, K, (const float*)A, (const float*)B, \
                      (float*)C, (const float*)bias, (const float*)aux_in, (float*)aux_out, epi, act)
+#define SLAPO_F32(L) do { if (wide) SLAPO_F32W(L, 2); else SLAPO_F32W(L, 1); } while (0)
     if (layout == GEMM_NT) SLAPO_F32(GEMM_NT);
     else if (layout == GEMM_NN) SLAPO_F32(GEMM_NN);
     else SLAPO_F32(GEMM_TN);
 #undef SLAPO_F32
+#undef SLAPO_F32W
     return;
   }
 #define SLAPO_H(F)                                                                                          \
