@@ -141,6 +141,9 @@ __device__ __forceinline__ TilePos tile_position(int bid, int tiles_m, int tiles
   return t;
 }
 
+// Byte offset behind the last piece of any operand: fewer than 2^31 elements, a multiple of 8 of them.
+constexpr unsigned BEYOND_OPERANDS = 0xfffffff0u;
+
 // HYB: a grid whose tile count is not a multiple of the 256 CUs ends in a thin round that costs a full one. A
 // hybrid launch runs the tiles of the full rounds as usual (workgroups below tail_begin) and cuts each tile of
 // the remainder into tail_splits K ranges, one workgroup each, so that the last round is short instead of
@@ -250,11 +253,17 @@ void gemm_bf16_kernel(int M, int N, int K,
   // which matters because the vector ALU is where the MFMAs run: address arithmetic of a loading wavefront
   // queues behind the MFMAs of the wavefronts that share its SIMD (measured: 64-bit per-lane addresses make
   // load time and MFMA time add up; this form overlaps them). Reads beyond the operand's end return zero.
+  // A row beyond K may lie more than 32 bits of bytes away (rows of over 34 million elements): its offset stops at one
+  // that is beyond the end of every operand, instead of wrapping back into it.
+  auto byte_offset = [](int row, int ld, int col) {
+    const uint64_t b = 2 * ((uint64_t)row * ld + col);
+    return b < BEYOND_OPERANDS ? (unsigned)b : BEYOND_OPERANDS;
+  };
   unsigned voa[A_LOADS], vob[B_LOADS];
 #pragma unroll
-  for (int i = 0; i < A_LOADS; ++i) voa[i] = (unsigned)(((ar + i * RSA) * lda + col_a(ar + i * RSA)) * 2);
+  for (int i = 0; i < A_LOADS; ++i) voa[i] = byte_offset(ar + i * RSA, lda, col_a(ar + i * RSA));
 #pragma unroll
-  for (int i = 0; i < B_LOADS; ++i) vob[i] = (unsigned)(((br + i * RSB) * ldb + col_b(br + i * RSB)) * 2);
+  for (int i = 0; i < B_LOADS; ++i) vob[i] = byte_offset(br + i * RSB, ldb, col_b(br + i * RSB));
   const int64_t origin_a = A_KC ? (int64_t)m0 * lda : m0, origin_b = B_KC ? (int64_t)n0 * ldb : n0;
   auto records = [](int64_t elems) { const int64_t b = elems * 2; return (unsigned)(b < 0xffffffffll ? b : 0xffffffffll); };
   const bf16_t* base_a = A + origin_a;
@@ -279,12 +288,12 @@ void gemm_bf16_kernel(int M, int N, int K,
     if (i < A_LOADS) {
       bf16_t* a = sA + stage * SA + lw * 512;
       const unsigned soa = (unsigned)(ks0 + kstep) * (unsigned)(stepA * 2);
-      dma16(base_a, bytes_a, a + i * NTHR * 8, !last || !A_KC || col_a(ar + i * RSA) < left ? voa[i] : 0xfffffff0u, soa);
+      dma16(base_a, bytes_a, a + i * NTHR * 8, !last || !A_KC || col_a(ar + i * RSA) < left ? voa[i] : BEYOND_OPERANDS, soa);
     } else {
       i -= A_LOADS;
       bf16_t* b = sB + stage * SB + lw * 512;
       const unsigned sob = (unsigned)(ks0 + kstep) * (unsigned)(stepB * 2);
-      dma16(base_b, bytes_b, b + i * NTHR * 8, !last || !B_KC || col_b(br + i * RSB) < left ? vob[i] : 0xfffffff0u, sob);
+      dma16(base_b, bytes_b, b + i * NTHR * 8, !last || !B_KC || col_b(br + i * RSB) < left ? vob[i] : BEYOND_OPERANDS, sob);
     }
   };
   auto load_direct = [&](int kstep, int stage) {

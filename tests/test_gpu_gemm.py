@@ -232,3 +232,24 @@ def test_gemm_fp32_tiles(layout, Ks, M, N):
             assert np.isnan(got[5]).all()
             got[5] = ref[5]
         assert (np.abs(got - ref) <= (K + 8) * 2.0 ** -24 * mag + 1e-30).all(), K   # K rounded additions and the 8 partial sums
+
+
+# Operands whose contraction index is strided, with rows so long that the byte offset of a slab's row beyond K leaves 32
+# bits (less than one slab of K), or comes close to it in front of the slab's own offset (one row over a slab). The rows
+# beyond K are zeros in the other operand: only an element that does not belong there, here a NaN, shows them.
+@pytest.mark.parametrize("layout,long,K", [(B.TN, 40_000_000, 8), (B.NN, 40_000_000, 8), (B.TN, 33_000_000, 65), (B.NN, 29_000_000, 72)])
+def test_gemm_rows_of_more_than_2_gib(layout, long, K):
+    M, N = (long, 8) if layout == B.TN else (8, long)
+    wide = torch.ones(K, long, dtype=torch.bfloat16, device=DEV)
+    cols = torch.tensor([5, 13_000_000, 20_000_008, 25_032_704, long - 1], device=DEV)
+    wide[:, cols] = float("nan")
+    other = torch.arange(8 * K, device=DEV).remainder(5).to(torch.bfloat16)   # small whole numbers: exact sums
+    other = other.view(K, 8) if layout == B.TN else other.view(8, K)
+    out = torch.empty(M, N, dtype=torch.bfloat16, device=DEV)
+    B.slapo_gemm(W.BF16, layout, B.EPI_NONE, 0, M, N, K, *((wide, other) if layout == B.TN else (other, wide)), out)
+    want = other.float().sum(0 if layout == B.TN else 1)
+    got = out if layout == B.TN else out.t()                                  # [long, 8]
+    assert torch.equal(torch.isnan(got).any(1).nonzero().flatten(), cols)
+    clean = torch.ones(long, dtype=torch.bool, device=DEV)
+    clean[cols] = False
+    assert bool((got[clean] == want.to(torch.bfloat16)).all())
