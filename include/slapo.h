@@ -209,9 +209,10 @@ int slapo_gemm(int dtype, int layout, int epilogue, int act, int64_t M, int64_t 
  *          is long computes the tiles beyond the last full round in several K ranges (fp32 partial tiles
  *          in ws, added in range order by a second kernel: bitwise reproducible), so that the last round is short
  *          instead of thin; layouts 0 and 1 with few tiles do so with all of them. slapo_gemm_workspace writes the bytes
- *          a shape can use (0: it runs as slapo_gemm would); for a grid of 256x256 tiles a non-NULL ws smaller than that
- *          is refused with SLAPO_ERR_WORKSPACE, the smaller tiles do without one that does not hold it. The layer calls
- *          do the same with a region of their scratch buffer. */
+ *          a shape can use (0: it runs as slapo_gemm would). For a grid of 256x256 tiles and K a multiple of 128 a
+ *          non-NULL ws smaller than that is refused with SLAPO_ERR_WORKSPACE; other K and the smaller tiles leave a ws
+ *          that does not hold them alone and run without. The layer calls do the same with a region of their
+ *          scratch buffer. */
 enum { SLAPO_GEMM_SHARED = 1 };
 int slapo_gemm_workspace(int dtype, int layout, int epilogue, int64_t M, int64_t N, int64_t K, size_t *ws_bytes);
 int slapo_gemm_ex(int dtype, int layout, int epilogue, int act, int64_t M, int64_t N, int64_t K,

@@ -674,7 +674,7 @@ static int gemm_entry(int dtype, int layout, int epilogue, int act, int64_t M, i
   if (layout == GEMM_TN ? (M % 8) : (K % 8)) return SLAPO_ERR_ALIGN;   // A's contiguous dimension
   if (layout == GEMM_NT && (K % 8)) return SLAPO_ERR_ALIGN;
   if (misaligned(A) || misaligned(B) || misaligned(C) || misaligned(ws)) return SLAPO_ERR_ALIGN;
-  // a workspace is all or nothing: one that is too small for what the shape can use is refused, not half used
+  // a workspace that is too small for what the shape can use is never half used: it is refused or left alone
   if (ws && ws_bytes < gemm_ws_least_bytes(dtype, layout, epilogue, (int)M, (int)N, (int)K)) return SLAPO_ERR_WORKSPACE;
   entry_error();
   launch_gemm(dtype, layout, epilogue, act, (int)M, (int)N, (int)K, A, B, C, bias, aux_in, aux_out,

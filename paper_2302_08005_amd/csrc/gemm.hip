@@ -1045,7 +1045,7 @@ size_t gemm_ws_bytes(int dtype, int layout, int epi, int M, int N, int K) {
 size_t gemm_ws_least_bytes(int dtype, int layout, int epi, int M, int N, int K) {
   if (dtype == DT_FP32) return 0;
   const HybridPlan hp = hybrid_plan(layout, epi, M, N, K);
-  return hp.tile == TILE_256 ? hp.ws_bytes : 0;
+  return hp.tile == TILE_256 && K % 128 == 0 ? hp.ws_bytes : 0;
 }
 
 size_t weight_grad_ws_bytes(int dtype, int M, int N, int K) {

@@ -24,8 +24,8 @@ void launch_gemm(int dtype, int layout, int epi, int act, int M, int N, int K, c
                  void* C, const void* bias, const void* aux_in, void* aux_out, hipStream_t st, bool solo = false,
                  float* ws = nullptr, size_t ws_bytes = 0);
 size_t gemm_ws_bytes(int dtype, int layout, int epi, int M, int N, int K);
-// the smallest workspace that a caller who passes one may pass: 256x256 grids ask for all that they can use, grids of
-// smaller tiles do without one that is too small for them
+// the smallest workspace that a caller who passes one may pass: 256x256 grids whose K is a multiple of 128 have always
+// asked for all that they can use; other K and grids of smaller tiles do without one that is too small for them
 size_t gemm_ws_least_bytes(int dtype, int layout, int epi, int M, int N, int K);
 void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool solo, bool weight_grad, bool with_ws,
                    char* buf, size_t len);

@@ -253,3 +253,18 @@ def test_gemm_rows_of_more_than_2_gib(layout, long, K):
     clean = torch.ones(long, dtype=torch.bool, device=DEV)
     clean[cols] = False
     assert bool((got[clean] == want.to(torch.bfloat16)).all())
+
+
+# K no multiple of 128 under a grid of 256x256 tiles with a thin last round: the K ranges are an offer there, and a
+# workspace that does not hold them is left alone. (K multiples of 128 refuse one: test_thin_last_round_in_k_ranges.)
+@pytest.mark.parametrize("layout", [B.NT, B.NN, B.TN])
+def test_small_workspace_is_left_alone_where_k_ranges_are_an_offer(layout):
+    M, N, K = 4296, 4200, 3000
+    assert B.slapo_gemm_workspace(W.BF16, layout, B.EPI_NONE, M, N, K) > 16
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    A = torch.randn((K, M) if layout == B.TN else (M, K), device=DEV, generator=gen).to(torch.bfloat16)
+    Bm = torch.randn((N, K) if layout == B.NT else (K, N), device=DEV, generator=gen).to(torch.bfloat16)
+    small, plain = (torch.empty(M, N, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    B.slapo_gemm_ex(W.BF16, layout, B.EPI_NONE, 0, M, N, K, A, Bm, small, ws=torch.empty(16, dtype=torch.uint8, device=DEV), flags=B.GEMM_SHARED)
+    B.slapo_gemm_ex(W.BF16, layout, B.EPI_NONE, 0, M, N, K, A, Bm, plain, flags=B.GEMM_SHARED)
+    assert torch.equal(small, plain)
