@@ -228,8 +228,9 @@ int slapo_gemm_kernel_name(int dtype, int layout, int epilogue, int64_t M, int64
  * output has too few 128x128 tiles to fill the chip and K is long (at least 6144), the product is
  * computed in up to 8 K ranges at once, as fp32 partial tiles in `ws` that a second kernel adds in range order (bitwise
  * reproducible); an output with many tiles whose grid ends in a thin round uses `ws` as slapo_gemm_ex does.
- * slapo_weight_grad_workspace writes the bytes of `ws` a shape wants (0: the plain GEMM is used
- * and ws may be NULL; also for SLAPO_FP32). ws: device, 16-byte aligned, free again when the call's work is done.
+ * slapo_weight_grad_workspace writes the bytes of `ws` a shape wants (0: the plain GEMM is used; also for SLAPO_FP32).
+ * ws: device, of that size, 16-byte aligned, free again when the call's work is done. NULL is accepted where the shape
+ * wants none, and where K is no multiple of 256 (few tiles) or 128 (thin round): the plain GEMM is used there without it.
  * slapo_layer_bwd uses this path for its four weight gradients with a region of its scratch buffer. */
 int slapo_weight_grad_workspace(int dtype, int64_t M, int64_t N, int64_t K, size_t *ws_bytes);
 int slapo_weight_grad(int dtype, int accumulate, int64_t M, int64_t N, int64_t K, const void *A, const void *B,

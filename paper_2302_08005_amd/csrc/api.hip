@@ -738,7 +738,7 @@ int slapo_weight_grad(int dtype, int accumulate, int64_t M, int64_t N, int64_t K
   const int rc = check_weight_grad_shape(dtype, M, N, K);
   if (rc) return rc;
   if (!A || !B || !C) return SLAPO_ERR_NULL;
-  if (!ws && weight_grad_ws_bytes(dtype, (int)M, (int)N, (int)K)) return SLAPO_ERR_NULL;
+  if (!ws && weight_grad_ws_least_bytes(dtype, (int)M, (int)N, (int)K)) return SLAPO_ERR_NULL;
   if (misaligned(A) || misaligned(B) || misaligned(C) || misaligned(ws)) return SLAPO_ERR_ALIGN;
   entry_error();
   launch_weight_grad(dtype, accumulate ? 1 : 0, (int)M, (int)N, (int)K, A, B, C, (float*)ws, (hipStream_t)stream);

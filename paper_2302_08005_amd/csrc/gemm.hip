@@ -1054,6 +1054,11 @@ size_t weight_grad_ws_bytes(int dtype, int M, int N, int K) {
   return s > 1 ? (size_t)s * M * N * sizeof(float) : hybrid_plan(GEMM_TN, EPI_NONE, M, N, K).ws_bytes;   // (same for the add epilogue)
 }
 
+size_t weight_grad_ws_least_bytes(int dtype, int M, int N, int K) {
+  if (weight_grad_splits(M, N, K) > 1) return K % 256 == 0 ? weight_grad_ws_bytes(dtype, M, N, K) : 0;
+  return gemm_ws_least_bytes(dtype, GEMM_TN, EPI_NONE, M, N, K);
+}
+
 template <bool F16>
 static void launch_splitk(int splits, int accumulate, int M, int N, int K, const void* A, const void* B, void* C,
                           float* ws, hipStream_t st) {

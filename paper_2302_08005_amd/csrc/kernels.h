@@ -34,6 +34,9 @@ void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool sol
 // kernel: deterministic), outputs whose tile grid ends in a thin round have their last tiles cut into K ranges
 // (launch_gemm); weight_grad_ws_bytes says how much workspace a shape wants (0: none, plain GEMM).
 size_t weight_grad_ws_bytes(int dtype, int M, int N, int K);
+// what a caller has to bring: the same where K is a multiple of 256 (K ranges of few tiles) or 128 (thin last rounds), as
+// ever; other K run as one plain GEMM without a workspace
+size_t weight_grad_ws_least_bytes(int dtype, int M, int N, int K);
 void launch_weight_grad(int dtype, int accumulate, int M, int N, int K, const void* A, const void* B, void* C,
                         float* ws, hipStream_t st, bool solo = false);
 

@@ -268,3 +268,20 @@ def test_small_workspace_is_left_alone_where_k_ranges_are_an_offer(layout):
     B.slapo_gemm_ex(W.BF16, layout, B.EPI_NONE, 0, M, N, K, A, Bm, small, ws=torch.empty(16, dtype=torch.uint8, device=DEV), flags=B.GEMM_SHARED)
     B.slapo_gemm_ex(W.BF16, layout, B.EPI_NONE, 0, M, N, K, A, Bm, plain, flags=B.GEMM_SHARED)
     assert torch.equal(small, plain)
+
+
+# Shapes that can use a workspace but whose K used to keep them off it run without one: thin last rounds of 256x256 tiles
+# with K no multiple of 128, and few output tiles with K no multiple of 256.
+OFFERED = [(4296, 4200, 3000), (7680, 2560, 4000), (264, 136, 8191), (1024, 1024, 16384 - 128)]
+
+
+@pytest.mark.parametrize("accumulate", [0, 1])
+@pytest.mark.parametrize("M,N,K", OFFERED)
+def test_weight_gradient_without_the_offered_workspace(M, N, K, accumulate):
+    assert B.slapo_weight_grad_workspace(W.BF16, M, N, K) > 0
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    A, Bm, C0 = (torch.randn(*s, device=DEV, generator=gen).to(torch.bfloat16) for s in ((K, M), (K, N), (M, N)))
+    out, plain = C0.clone(), C0.clone()
+    B.slapo_weight_grad(W.BF16, accumulate, M, N, K, A, Bm, out, None)
+    B.slapo_gemm_ex(W.BF16, B.TN, B.EPI_ADD if accumulate else B.EPI_NONE, 0, M, N, K, A, Bm, plain, aux_in=plain if accumulate else None, flags=B.GEMM_SHARED)
+    assert torch.equal(out, plain)
