@@ -238,13 +238,15 @@ int slapo_weight_grad(int dtype, int accumulate, int64_t M, int64_t N, int64_t K
 
 /* slapo_weight_grad for callers that cannot allocate device memory or hand over a workspace: code under HIP graph
  * capture, tight serving / training loops, harnesses that forbid allocation. Same arguments without `ws`, same
- * results bit for bit. The fp32 partial tiles of the K-range path live in a fixed 16 MiB array in device memory that
- * is part of the library's code object (one copy per GPU the library runs on, held until the process ends); the call
- * allocates and frees nothing. A shape whose partial tiles would not fit returns SLAPO_ERR_WORKSPACE before anything
- * is launched (with the current rule - at most 256 partial tiles of 128x128 - every shape fits; the check guards the
- * array). The array keeps the last call's contents and nothing in it needs clearing: every partial tile a call reads
- * it has written itself. All calls on one GPU share the array, so two calls whose work may overlap in time on one GPU
- * (different streams, different host threads) race on it: order them, or use slapo_weight_grad with a workspace each.
+ * results bit for bit (as without a workspace where the shape's does not fit). The fp32 partial tiles of the K-range
+ * path live in a fixed 16 MiB array in device memory that is part of the library's code object (one copy per GPU the
+ * library runs on, held until the process ends); the call allocates and frees nothing. Outputs with few tiles always
+ * fit (at most 256 partial tiles of 128x128). The tiles of a thin last round may not: the call then runs as one plain
+ * GEMM, except for K a multiple of 128, which returns SLAPO_ERR_WORKSPACE before anything is launched (7680 x 2560
+ * outputs: K = 3400 runs, K = 3456 is refused). The array keeps the last call's contents and nothing in it needs
+ * clearing: every partial tile a call reads it has written itself. All calls on one GPU share the array, so two calls
+ * whose work may overlap in time on one GPU (different streams, different host threads) race on it: order them, or use
+ * slapo_weight_grad with a workspace each.
  * The device address of the array is looked up on the first call on each device; make that call outside any graph
  * capture. At most 16 devices per process. */
 int slapo_weight_grad_static(int dtype, int accumulate, int64_t M, int64_t N, int64_t K, const void *A, const void *B,

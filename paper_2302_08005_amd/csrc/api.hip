@@ -785,10 +785,10 @@ int slapo_weight_grad_static(int dtype, int accumulate, int64_t M, int64_t N, in
   if (rc) return rc;
   if (!A || !B || !C) return SLAPO_ERR_NULL;
   if (misaligned(A) || misaligned(B) || misaligned(C)) return SLAPO_ERR_ALIGN;
-  const size_t need = weight_grad_ws_bytes(dtype, (int)M, (int)N, (int)K);
-  if (need > STATIC_SCRATCH_BYTES) return SLAPO_ERR_WORKSPACE;
+  if (weight_grad_ws_least_bytes(dtype, (int)M, (int)N, (int)K) > STATIC_SCRATCH_BYTES) return SLAPO_ERR_WORKSPACE;
+  const size_t wants = weight_grad_ws_bytes(dtype, (int)M, (int)N, (int)K);
   float* ws = nullptr;
-  if (need) {   // shapes that run as one plain GEMM touch no scratch at all
+  if (wants && wants <= STATIC_SCRATCH_BYTES) {   // shapes that run as one plain GEMM touch no scratch at all
     int st = SLAPO_OK;
     ws = static_scratch(&st);
     if (!ws) return st;

@@ -40,3 +40,21 @@ def test_static_scratch_weight_gradient_matches_workspace_variant(dtype):
             assert torch.equal(got, want), (accumulate, M, N, K)
             ref = a.astype(np.float64).T @ b.astype(np.float64) + (c0 if accumulate else 0.0)
             assert err(got, ref) <= TOL[dtype], (accumulate, M, N, K)
+
+
+# K ranges beyond the array (41, 55, 32 MiB) with K no multiple of 128: the plain GEMM, as slapo_weight_grad without a
+# workspace. With K a multiple of 128 such a shape is refused.
+@pytest.mark.parametrize("accumulate", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(4296, 4200, 3000), (7680, 2560, 3400), (4352, 4096, 8191)])
+def test_static_scratch_weight_gradient_beyond_the_array(M, N, K, accumulate):
+    assert B.slapo_weight_grad_workspace(W.BF16, M, N, K) > 16 << 20
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    A, Bm, C0 = (torch.randn(*s, device=DEV, generator=gen).to(torch.bfloat16) for s in ((K, M), (K, N), (M, N)))
+    got, want = C0.clone(), C0.clone()
+    B.slapo_weight_grad_static(W.BF16, accumulate, M, N, K, A, Bm, got)
+    B.slapo_weight_grad(W.BF16, accumulate, M, N, K, A, Bm, want, None)
+    assert torch.equal(got, want)
+    K = K // 128 * 128
+    with pytest.raises(B.SlapoError) as e:
+        B.slapo_weight_grad_static(W.BF16, accumulate, M, N, K, A, Bm, got)
+    assert e.value.status == -5
