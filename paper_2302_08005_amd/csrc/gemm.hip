@@ -875,7 +875,7 @@ static HybridPlan hybrid_plan(int layout, int epi, int M, int N, int K) {
   static const bool disabled = debug_flag("no-hybrid");
   if (disabled || (epi != EPI_NONE && epi != EPI_ADD)) return none;
   p.tile = select_tile(layout, M, N, K, false);
-  if (p.tile == TILE_128_SPLITSLAB || (p.tile == TILE_128x64_LOADERS && layout == GEMM_TN)) return none;   // (K ranges of their own: weight_grad_splits)
+  if (layout == GEMM_TN && p.tile != TILE_256) return none;   // (K ranges of their own: weight_grad_splits)
   const int bm = p.tile == TILE_256 ? 256 : 128, bn = p.tile == TILE_256 ? 256 : p.tile == TILE_128x64_LOADERS ? 64 : 128;
   const int tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
   const int rem = tiles % 256, nk = (K + 63) / 64;
@@ -959,11 +959,17 @@ static void launch_hybrid_tile(const HybridPlan& hp, int epi, int M, int N, int 
 template <int LAYOUT, bool F16>
 static void launch_hybrid(const HybridPlan& hp, int epi, int M, int N, int K, const void* A, const void* B, void* C,
                           const void* aux_in, float* ws, hipStream_t st) {
-  if (hp.tile == TILE_256) launch_hybrid_tile<LAYOUT, 256, 256, 2, 4, 2, 0, F16>(hp, epi, M, N, K, A, B, C, aux_in, ws, st);
-  else if constexpr (LAYOUT != GEMM_TN) {
-    if (hp.tile == TILE_128_LOADERS) launch_hybrid_tile<LAYOUT, 128, 128, 2, 4, 4, 4, F16>(hp, epi, M, N, K, A, B, C, aux_in, ws, st);
-    else launch_hybrid_tile<LAYOUT, 128, 64, 2, 2, 4, 4, F16>(hp, epi, M, N, K, A, B, C, aux_in, ws, st);
+  if constexpr (LAYOUT != GEMM_TN) {   // (TN plans are for 256x256 tiles only)
+    if (hp.tile == TILE_128_LOADERS) {
+      launch_hybrid_tile<LAYOUT, 128, 128, 2, 4, 4, 4, F16>(hp, epi, M, N, K, A, B, C, aux_in, ws, st);
+      return;
+    }
+    if (hp.tile == TILE_128x64_LOADERS) {
+      launch_hybrid_tile<LAYOUT, 128, 64, 2, 2, 4, 4, F16>(hp, epi, M, N, K, A, B, C, aux_in, ws, st);
+      return;
+    }
   }
+  launch_hybrid_tile<LAYOUT, 256, 256, 2, 4, 2, 0, F16>(hp, epi, M, N, K, A, B, C, aux_in, ws, st);
 }
 
 template <int LAYOUT, bool F16>

@@ -202,6 +202,19 @@ def test_gemm_workspace_rules_on_the_host():
     assert B.status_string(-5).startswith("shape needs more workspace")
 
 
+def test_weight_gradient_plans_are_for_the_tiles_that_have_them():
+    """Layout TN has K-range forms of 256x256 tiles (thin last rounds) and of split-slab 128x128 tiles (few tiles) only."""
+    forms = set()
+    for M in (8, 264, 1024, 2752, 4296, 5120, 11008):
+        for N in (64, 136, 1024, 1280, 2560, 4200):
+            for K in (64, 200, 512, 1000, 1024, 1032, 2048, 3000, 6144, 8191, 16384):
+                for weight_grad in (0, 1):
+                    name = B.slapo_gemm_kernel_name(B.BF16, B.TN, B.EPI_NONE, M, N, K, weight_grad=weight_grad, with_ws=1)
+                    if "K ranges" in name:
+                        forms.add((name.split("<2, ")[1].split(", 64,")[0], name.split(" + ")[-1]))
+    assert forms == {("256, 256", "hybrid_reduce_kernel"), ("128, 128", "splitk_reduce_kernel")}
+
+
 def test_debug_switches_shrink_the_reported_workspaces():
     """SLAPO_DEBUG is read once per process: a child with the switches set reports no K-range workspaces."""
     import subprocess
