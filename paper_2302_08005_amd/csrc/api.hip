@@ -163,17 +163,27 @@ SideStream* side_stream() {
   return s.state == 1 ? &s : nullptr;
 }
 
-// Small calls keep all of backward on the caller's stream. A fork costs the host two event calls (the ten of a layer
-// take about 100 us, as much as its 27 launches) and the GPU 5 us of idle stream each, and next to kernels of 5 to 10 us there
-// is little to fill. Multiply-adds of the layer's projections decide, with 40 tokens' worth added for the weights that each
-// call reads and writes whatever its size. Steps per call, one stream / two: hidden 1024 (feed-forward 4096) at 128 tokens
-// 160 / 214 us, 512 187 / 201, 1024 230 / 218; hidden 512 at 2048 tokens 197 / 205; 768 at 1024 195 / 204, at 2048 262 /
-// 240; 2048 at 64 201 / 204, at 128 226 / 222. fp32 multiply-adds count eightfold (hidden 768: 225 / 225 at 64 tokens, 649 /
-// 637 at 512).
+// Small calls keep all of backward on the caller's stream. The forks and the join of two streams cost the host about as
+// much as the layer's 27 launches (a step's calls take 150-210 us instead of 85-130, by machine and moment), so two streams
+// pay where the step keeps the GPU busy for about that long and the weight gradients, whose few workgroups walk all tokens,
+// leave the chip to the data gradients beside them. The rule estimates the GPU's time for a step on one stream, in us:
+// launches; multiply-adds of the projections, with 300 tokens' worth for the weights that each call reads and writes
+// whatever its size (fp32 products take eight times as long); row work and the weight gradients' walk, per token, at a third
+// more than their time because two streams win that back; attention's walk over the keys, which lengthens with the head
+// width. Steps per call of classic layers (feed-forward 4 x hidden, 64-wide heads), one stream / two, on machines of
+// either speed, with the estimate (two machines where the answer differs):
+//   hidden 256   1024 tokens in sequences of 128: 135 / 169 us (151), of 1024: 184 / 173, 185 / 197 (191); 1536 of 128:
+//                147 / 170 (168); 2048 of 128: 158 / 161, 160 / 197 (185), of 512: 178 / 214 (202), of 2048: 263 / 241
+//                (271); 2560 of 128: 174 / 163 (202); 4096 of 2048: 312 / 272 (339); 8192 of 512: 289 / 255 (407)
+//   hidden 384   1024 of 128: 145 / 195 (156); 1536 of 128: 163 / 148 (175); 2048 of 128: 174 / 152, 174 / 200 (195)
+//   hidden 512   1024 of 128: 156 / 161 (164); 1536 of 128: 177 / 159 (186); 2048 of 128: 194 / 165, 193 / 206 (208)
+//   hidden 768   512 of 128: 174 / 191 (155); 1024 of 128: 193 / 180 (186), of 1024: 242 / 227 (226)
+//   hidden 1024  128: 157 / 200 (142); 512 of 128: 185 / 201 (174); 1024 of 128: 230 / 218 (216)
 bool backward_on_one_stream(const slapo_layer_desc* d) {
   const double T = (double)d->batch * d->seq, H = d->hidden, F = d->ffn, A = attn_width(d);
   const double weights = 4.0 * H * A + (is_llama(d) ? 3.0 : 2.0) * H * F;
-  return weights * (T + 40.0) * (d->dtype == SLAPO_FP32 ? 8.0 : 1.0) < 8.0e9;
+  const double products = 4.2e-9 * weights * (T * (d->dtype == SLAPO_FP32 ? 8.0 : 1.0) + 300.0);
+  return 110.0 + products + 0.03 * T + 7e-4 * (A / d->heads) * d->seq < 184.0;
 }
 
 // byte offsets of the regions of `saved`

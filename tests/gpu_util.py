@@ -1,4 +1,6 @@
 """Helpers for the GPU parity tests: host <-> device conversion and the error metric."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -35,3 +37,18 @@ def err(got, ref):
 
 # fp16 keeps 3 more mantissa bits than bf16 (2^-11 against 2^-8 per rounding): an eighth of the bf16 bar, doubled
 TOL = {W.FP32: 1e-4, W.BF16: 2e-2, W.FP16: 2.5e-3}
+
+
+def forks(step):
+    """True if the work that `step` enqueues branches off the caller's stream: captured, it is then no mere chain."""
+    step()                                          # (first-call set-up stays outside the capture)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        step()
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(l.split()[-1] for l in f if "libamdhip64" in l))
+    raw, nodes, edges = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(nodes)) == 0 and nodes.value > 1
+    assert hip.hipGraphGetEdges(raw, None, None, ctypes.byref(edges)) == 0
+    return edges.value != nodes.value - 1

@@ -6,7 +6,7 @@ import torch
 import workloads as W
 from oracle import layer as L
 from paper_2302_08005_amd import binding as B
-from gpu_util import DEV, TOL, err, to_np
+from gpu_util import DEV, TOL, err, forks, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -258,3 +258,18 @@ def test_two_host_threads_share_the_helper_stream(monkeypatch):
     big = [W.LayerConfig("threads-%d" % b, b, 200, 1024, 16, 4096, causal=0, dropout_p=0.1, dtype=W.BF16, config_id=62 + b) for b in (3, 4)]
     monkeypatch.setitem(globals(), "SMALL", [None] * 4 + big)
     test_backward_from_two_host_threads_on_one_device()
+
+
+# (tokens, sequence, hidden, heads, type): few tokens stay on the caller's stream; many fork, however narrow the layer; on
+# either side of the line at hidden 1024
+@pytest.mark.parametrize("batch,seq,hidden,heads,dtype,two", [
+    (1, 128, 1024, 16, W.BF16, False), (8, 128, 256, 4, W.BF16, False), (2, 128, 256, 4, W.FP32, False),
+    (16, 512, 256, 4, W.BF16, True), (1, 4096, 256, 2, W.BF16, True), (16, 128, 512, 8, W.FP16, True), (8, 512, 1024, 16, W.BF16, True),
+    (3, 197, 1024, 16, W.BF16, False), (3, 200, 1024, 16, W.BF16, True)])
+def test_which_calls_fork_onto_the_helper_stream(batch, seq, hidden, heads, dtype, two):
+    cfg = W.LayerConfig("forks", batch, seq, hidden, heads, 4 * hidden, causal=0, dropout_p=0.1, dtype=dtype, config_id=71)
+    layer = B.Layer(cfg, W.make_params(cfg))
+    x, dy = (torch.randn(batch, seq, hidden, device=DEV).to(layer.dt) for _ in range(2))
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    B.slapo_layer_fwd(layer.desc, layer.params, x, None, y, layer.saved, layer.scratch)
+    assert forks(lambda: B.slapo_layer_bwd(layer.desc, layer.params, x, None, dy, layer.saved, dx, layer.grads, layer.scratch)) == two
