@@ -157,7 +157,9 @@ def test_weight_gradient_workspace_rule():
     assert B.slapo_weight_grad_workspace(B.BF16, 1024, 1024, 4096) == 0                         # too short to cut up
     assert B.slapo_weight_grad_workspace(B.BF16, 128, 128, 65536) == 8 * 128 * 128 * 4          # never more than 8
     assert B.slapo_weight_grad_workspace(B.BF16, 1024, 4096, 4096) == 0                         # a full round of tiles
-    assert B.slapo_weight_grad_workspace(B.BF16, 1024, 1024, 4000) == 0                         # K no multiple of 256
+    assert B.slapo_weight_grad_workspace(B.BF16, 1024, 1024, 4000) == 0
+    assert B.slapo_weight_grad_workspace(B.BF16, 1024, 1024, 6143) == 0                         # one short of two ranges
+    assert B.slapo_weight_grad_workspace(B.BF16, 1024, 1024, 6145) == 2 * 1024 * 1024 * 4      # any K from there on
     assert B.slapo_weight_grad_workspace(B.FP32, 1024, 1024, 4096) == 0
     lib = B.lib()
     assert lib.slapo_weight_grad(0, 0, 1024, 1024, 16384, 4096, 4096, 4096, None, None) == -1   # wants a workspace
@@ -166,8 +168,9 @@ def test_weight_gradient_workspace_rule():
 
 
 def test_static_scratch_bound_and_argument_checks():
-    """slapo_weight_grad_static keeps its partial tiles in a fixed 16 MiB array: the K-range rule never asks for more
-    (at most 256 partial tiles of 128 x 128 floats), and its argument checks come before any device work."""
+    """slapo_weight_grad_static keeps its partial tiles in a fixed 16 MiB array: the K-range rule for few tiles never asks
+    for more (at most 256 partial tiles of 128 x 128 floats), thin last rounds of 256 x 256 tiles may, and are refused where
+    K is a multiple of 128 (the others run without, on the GPU); argument checks come before any device work."""
     lib = B.lib()
     worst = 0
     for M in (8, 136, 1024, 1536, 2048, 2560, 4096, 12288):
@@ -176,6 +179,10 @@ def test_static_scratch_bound_and_argument_checks():
                 if M * K < 2 ** 31 and N * K < 2 ** 31:
                     worst = max(worst, B.slapo_weight_grad_workspace(B.BF16, M, N, K))
     assert 0 < worst <= 16 << 20
+    for M, N, K in ((7680, 2560, 3456), (4296, 4200, 3072), (22016, 4096, 6016)):
+        assert B.slapo_weight_grad_workspace(B.BF16, M, N, K) > 16 << 20
+        assert lib.slapo_weight_grad_static(0, 0, M, N, K, 4096, 4096, 4096, None) == -5
+        assert lib.slapo_weight_grad(0, 0, M, N, K, 4096, 4096, 4096, None, None) == -1
     assert lib.slapo_weight_grad_static(0, 0, 1024, 1024, 16384, None, 4096, 4096, None) == -1
     assert lib.slapo_weight_grad_static(0, 0, 1024, 1024, 16384, 4096 + 2, 4096, 4096, None) == -4
     assert lib.slapo_weight_grad_static(0, 0, 1024, 1020, 16384, 4096, 4096, 4096, None) == -4

@@ -285,3 +285,61 @@ def test_weight_gradient_without_the_offered_workspace(M, N, K, accumulate):
     B.slapo_weight_grad(W.BF16, accumulate, M, N, K, A, Bm, out, None)
     B.slapo_gemm_ex(W.BF16, B.TN, B.EPI_ADD if accumulate else B.EPI_NONE, 0, M, N, K, A, Bm, plain, aux_in=plain if accumulate else None, flags=B.GEMM_SHARED)
     assert torch.equal(out, plain)
+
+
+# Every epilogue in every tile form, with ragged edges, without and with a partial last slab: 256x256 tiles, 128x128 with
+# four LDS stages (layout TN: split slabs from K > 1024 on) and with two, 128x64. Pairs of layout and epilogue that no
+# layer uses come as 128x128 tiles only. Bound: rounding of the stored result (2^-9 of it in bf16, 2^-12 in half) and of
+# the sums, doubled.
+FORMS = {"256x256": (3592, 3344, "256, 256, 64, 2, 4, 1, 2, 0"), "128x128-4": (1664, 2064, "128, 128, 64, 2, 4, 1, 4, 4"),
+         "128x128-2": (2336, 2064, "128, 128, 64, 2, 4, 1, 2, 4"), "128x64": (520, 144, "128, 64, 64, 2, 2, 1, 4, 4")}
+PAIRED = {B.NT: (B.EPI_NONE, B.EPI_BIAS, B.EPI_BIAS_ACT, B.EPI_GATE), B.NN: (B.EPI_NONE, B.EPI_DACT, B.EPI_ADD, B.EPI_DGATE),
+          B.TN: (B.EPI_NONE, B.EPI_ADD)}
+
+
+@pytest.mark.parametrize("dtype", [W.BF16, W.FP16])
+@pytest.mark.parametrize("layout", [B.NT, B.NN, B.TN])
+@pytest.mark.parametrize("form", list(FORMS))
+def test_epilogues_of_every_tile_form(form, layout, dtype):
+    M, N, name = FORMS[form]
+    tol = {W.BF16: 4e-3, W.FP16: 5e-4}[dtype]
+    for K in (192, 203 if layout == B.TN else 200) + ((1088, 2286) if form == "128x128-4" and layout == B.TN else ()):
+        if K > 1024:
+            name = "128, 128, 64, 2, 2, 2, 4, 4"
+        rng = np.random.default_rng(M + K + layout)
+        a = store(rng.standard_normal((M, K)), dtype)
+        b = store(rng.standard_normal((K, N)) * K ** -0.5, dtype)
+        bias, aux = store(rng.standard_normal(N), dtype), store(rng.standard_normal((M, 2 * N)), dtype)
+        acc = (torch.from_numpy(a) @ torch.from_numpy(b)).double().numpy()
+        A = to_dev(a.T.copy() if layout == B.TN else a, dtype)
+        Bm = to_dev(b.T.copy() if layout == B.NT else b, dtype)
+        bd, auxd, aux1 = to_dev(bias, dtype), to_dev(aux, dtype), to_dev(aux[:, :N].copy(), dtype)
+
+        def run(epi, act=W.GELU, width=N, aux_in=None, aux_out=None):
+            got = B.slapo_gemm_kernel_name(dtype, layout, epi, M, N, K)
+            assert name in got or epi not in PAIRED[layout] and "128, 128, 64, 2, 4, 1, %d, 4" % (2 if form in ("256x256", "128x128-2") else 4) in got, (epi, got)
+            out = torch.full((M, width), 7.0, dtype=A.dtype, device=DEV)
+            B.slapo_gemm(dtype, layout, epi, act, M, N, K, A, Bm, out, bias=bd, aux_in=aux_in, aux_out=aux_out)
+            return out
+
+        pre, keep = acc + bias, torch.empty(M, N, dtype=A.dtype, device=DEV)
+        errs = {"none": err(run(B.EPI_NONE), acc), "bias": err(run(B.EPI_BIAS), pre), "add": err(run(B.EPI_ADD, aux_in=aux1), acc + aux[:, :N]),
+                "dgelu": err(run(B.EPI_DACT, aux_in=aux1), acc * aux[:, :N]),
+                "drelu": err(run(B.EPI_DACT, W.RELU, aux_in=aux1), acc * (aux[:, :N] > 0)),
+                "dgate": err(run(B.EPI_DGATE, width=2 * N, aux_in=auxd), np.repeat(acc, 2, 1) * aux),
+                "relu": err(run(B.EPI_BIAS_ACT, W.RELU), np.maximum(pre, 0)),
+                "gelu": err(run(B.EPI_BIAS_ACT, aux_out=keep), _act(pre, W.GELU))}
+        errs["gelu'"] = err(keep, _dact(pre, W.GELU))
+        gate, up = acc[:, ::2], acc[:, 1::2]
+        sig = 1 / (1 + np.exp(-gate))
+        errs["gate"] = err(run(B.EPI_GATE, width=N // 2, aux_out=keep), gate * sig * up)
+        errs["gate'"] = err(keep, np.stack([up * sig * (1 + gate * (1 - sig)), gate * sig], 2).reshape(M, N))
+        assert all(v <= tol for v in errs.values()), (K, errs)
+
+
+# layout TN from K > 1024 on (split slabs), and short K in several rounds (two LDS stages)
+@pytest.mark.parametrize("M,N,Ks,name", [(768, 3072, (1025, 1087, 2286), "2, 2, 2, 4, 4"), (5120, 1280, (7, 65, 1000), "2, 4, 1, 2, 4")])
+def test_gemm_partial_last_slab_tn(M, N, Ks, name):
+    for K in Ks:
+        assert name in B.slapo_gemm_kernel_name(W.BF16, B.TN, B.EPI_NONE, M, N, K)
+    test_gemm_partial_last_slab(B.TN, Ks, M, N)

@@ -129,9 +129,9 @@ def test_layer_is_deterministic_and_accumulates():
 def test_backward_from_two_host_threads_on_one_device():
     """Two host threads, each with its own layer, buffers and stream, run forward + backward at the same time.
 
-    Backward forks its weight gradients onto the device's one helper stream with events that the threads
-    share; every record and the wait that consumes it are issued under a lock, so each call waits for its own
-    records. The results must be the bits of the same calls made one after the other.
+    Larger calls (test_two_host_threads_share_the_helper_stream below) fork their weight gradients onto the device's one
+    helper stream with events that the threads share; every record and the wait that consumes it are issued under a lock,
+    so each call waits for its own records. The results must be the bits of the same calls made one after the other.
     """
     import threading
     cfgs = [SMALL[4], SMALL[5]]
@@ -273,3 +273,21 @@ def test_which_calls_fork_onto_the_helper_stream(batch, seq, hidden, heads, dtyp
     y, dx = torch.empty_like(x), torch.empty_like(x)
     B.slapo_layer_fwd(layer.desc, layer.params, x, None, y, layer.saved, layer.scratch)
     assert forks(lambda: B.slapo_layer_bwd(layer.desc, layer.params, x, None, dy, layer.saved, dx, layer.grads, layer.scratch)) == two
+
+
+# the same checks at sizes whose backward forks: gradient accumulation, and checkpoint against plain for either wiring
+FORKING = [
+    W.LayerConfig("two-streams-postln-bf16", 4, 512, 512, 8, 1024, causal=0, dropout_p=0.1, dtype=W.BF16, len_lo=200, len_hi=512, config_id=72),
+    W.LayerConfig("two-streams-preln-fp16-d128", 4, 512, 512, 4, 1024, causal=1, dropout_p=0.1, dtype=W.FP16, pre_ln=1, config_id=73),
+]
+
+
+@pytest.mark.parametrize("cfg", FORKING, ids=lambda c: c.name)
+def test_two_streams_accumulate_and_recompute(cfg, monkeypatch):
+    layer = B.Layer(cfg, W.make_params(cfg))
+    x = torch.zeros(cfg.batch, cfg.seq, cfg.hidden, dtype=layer.dt, device=DEV)
+    layer.forward(x, None)
+    assert forks(lambda: layer.backward(x, None, x))
+    monkeypatch.setitem(globals(), "SMALL", [cfg] * 5)
+    test_layer_is_deterministic_and_accumulates()
+    test_checkpoint_mode_recomputes_to_the_same_bits(0)

@@ -13,7 +13,7 @@ import workloads as W
 from oracle import layer as L
 from oracle import llama_layer as LL
 from paper_2302_08005_amd import binding as B
-from gpu_util import DEV, TOL, err
+from gpu_util import DEV, TOL, err, forks
 
 pytestmark = pytest.mark.gpu
 
@@ -192,3 +192,19 @@ def test_full_size_24_layer_stack_layers_0_1_12_23():
         print(f"C5 layer {l}: worst {max(errs.values()):.3e}", flush=True)
         bad = {k: v for k, v in errs.items() if not v <= tol}
         assert not bad, (l, bad, errs)
+
+
+# Stacks whose backward forks: each pre-LN layer then hands the branch gradient of the layer below over from one stream to
+# the other (two alternating buffers that the weight gradients of the helper stream read too).
+@pytest.mark.parametrize("cfg", [
+    W.LayerConfig("two-streams-stack-preln-bf16", 4, 512, 512, 8, 1024, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, config_id=25),
+    W.LayerConfig("two-streams-stack-llama-bf16", 4, 512, 256, 2, 688, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, ln_eps=1e-6,
+                  arch=W.LLAMA, config_id=26),
+    W.LayerConfig("two-streams-stack-postln-fp16", 5, 400, 512, 8, 1024, causal=0, dropout_p=0.1, dtype=W.FP16, len_lo=100, len_hi=400, config_id=27),
+], ids=lambda c: c.name)
+def test_stack_on_two_streams(cfg):
+    st = B.Stack(cfg, [W.make_params(cfg, layer_id=l) for l in range(N_LAYERS)])
+    x = torch.zeros(cfg.batch, cfg.seq, cfg.hidden, dtype=st.dt, device=DEV)
+    st.forward(x, None)
+    assert forks(lambda: st.backward(x, None, x))
+    test_stack_matches_oracle_chain_and_single_layer_calls(cfg)
