@@ -5,8 +5,10 @@
 // bf16 path: 8 wavefronts in a 2x4 grid (or 2 x 2x2 with an in-block K split), each owning a block of
 // v_mfma_f32_16x16x32_bf16 tiles. That form moves half the accumulator traffic per multiply of the 32x32x16 one, and
 // under a load that is bound by power the chip holds a higher clock with it: a loop of nothing but MFMAs on random data
-// runs at 2.12 PFLOP/s (2.1 GHz) against 1.87 (1.86 GHz) with the 32x32x16 form, at the same cycle count. K slabs go global -> LDS by direct loads into a ring of LDS stages, one barrier
-// per slab; a K that is no multiple of the slab ends in a zero-filled one. Operands whose contraction index is
+// runs at 2.12 PFLOP/s (2.1 GHz) against 1.87 (1.86 GHz) with the 32x32x16 form, at the same cycle count (another box 1.94
+// / 1.73; on zeros or one repeated value, which draw less power, both run at 2.42-2.45).
+// K slabs go global -> LDS by direct loads into a ring of LDS stages, one barrier per slab; a K that is no multiple of
+// the slab ends in a zero-filled one. Operands whose contraction index is
 // contiguous in memory are read from LDS with 16-byte reads; operands whose contraction index is the
 // strided one (the "N" operand of dY*W and both operands of dY^T*X) stay in their memory order in LDS and
 // are read with the transposing ds_read_b64_tr_b16, so no transposed copy of any tensor is ever made.
@@ -102,9 +104,10 @@ __device__ __forceinline__ GateTerms gate_terms(float u, float w) {
 //    fragment address is a per-lane base plus (2*ks ^ per-lane constant).
 //  - M-contiguous tile [BK][W]: position p of k-row r holds chunk p ^ (swzM(r) << 1), i.e. 32-byte granules
 //    are permuted by swzM(r) (defined in the kernel). A transposing 8-byte read is served 32 lanes at a time:
-//    4 consecutive k-rows x 2 adjacent granules, whose 8 pieces the permutation spreads over the 8 bank
-//    groups (the conflict counter read 49 % of the LDS cycles with a permutation that only separated the
-//    four rows, 1 % of the K-contiguous level with this one).
+//    one granule of four consecutive k-rows and of the four that lie 8 further, whose 8 pieces the permutation
+//    spreads over the 8 bank groups.
+//  The conflict counter reads 1-4 % of the LDS cycles in all three layouts (6 % where K = 1024 leaves the epilogue's
+//  staging a larger share).
 //
 // Why direct loads: a ds_write moves 64 B per clock and keeps the LDS busy meanwhile, so writing a slab
 // costs as much LDS time as reading it three times; measured on the chip, fragment reads running beside
@@ -185,11 +188,10 @@ void gemm_bf16_kernel(int M, int N, int K,
     static_assert(W >= 64, "at least four 32-byte granules per tile row");
     constexpr int RPM = W >= 128 ? 1 : 128 / W;   // k-rows per 256 bytes of LDS
     const int q = krow / RPM;
-    // One transposing read covers, per group of 32 lanes, four consecutive k-rows x two adjacent granules
-    // (an even one and its successor): eight 32-byte pieces that must land in eight different bank groups.
-    // The k-row picks bits 1-2 of the granule position (bit 1 only for 64-wide tiles, whose rows alternate
-    // between the two halves of the 256 bytes by themselves), so the granule's own low bit still tells
-    // the two halves apart; rows 8 apart (the other 32 lanes) differ in bit 0.
+    // One transposing read covers, per group of 32 lanes, one granule of k-rows r..r+3 and r+8..r+11: eight 32-byte
+    // pieces that must land in eight different bank groups. The k-row picks bits 1-2 of the granule position (bit 1
+    // only for 64-wide tiles, whose rows alternate between the two halves of the 256 bytes by themselves); rows 8 apart
+    // differ in bit 0.
     return W >= 128 ? (((q & 3) << 1) ^ ((q >> 3) & 1)) : (((q & 1) << 1) ^ ((q >> 2) & 1));
   };
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
@@ -485,9 +487,11 @@ void gemm_bf16_kernel(int M, int N, int K,
 
   if (PW && is_loader) return;   // every load has landed (the last steps drain them); the rest is compute only
 
-  // Epilogue. The accumulators (element r of a 16x16 tile: row lane%16, column 4*(lane/16) + r) go, one 32-row slab at a time, through a per-wave fp32 staging area in LDS so that every
-  // global access of the epilogue (bias, auxiliary input, both outputs) is a 16-byte access of 8
-  // consecutive columns of one row. The main loop ended with a barrier, so the stages are free.
+  // Epilogue. The accumulators (element r of a 16x16 tile: row lane%16, column 4*(lane/16) + r) go, one 32-row slab at a
+  // time, through a per-wave fp32 staging area in LDS so that every global access of the epilogue (bias, auxiliary
+  // input, both outputs) is a 16-byte access of 8 consecutive columns of one row. The stages are free: every wavefront
+  // has met the others behind its last read that counts (alternating stages: the reads behind the last slab's barrier
+  // fetch what nobody uses).
   if (KS == 2) {   // add the second wave set's accumulators to the first; then only the first goes on
     f32x4_t* red = reinterpret_cast<f32x4_t*>(smem) + wave * (TM * TN * 64) + lane;
     if (kgroup == 1) {
@@ -651,9 +655,10 @@ constexpr size_t gemm_lds_bytes() {
   return m1 > red_bytes ? m1 : red_bytes;
 }
 
-// fp32: 32x32 tiles (W = 2), or 16x16 (W = 1) where the larger ones would leave half of the CUs idle, eight wavefronts that take the 16-deep K chunks of the tile in turn, so that a product with few
-// tiles (256 tokens, 256 columns: 64) still has 512 wavefronts' loads in flight; such products are bound by the chain of
-// load latencies, not by the 157 TFLOP/s of the fp32 MFMAs. Operands go from memory to registers in the shape of
+// fp32: 32x32 tiles (W = 2), or 16x16 (W = 1) where the larger ones would leave half of the CUs idle, eight wavefronts
+// that take the 16-deep K chunks of the tile in turn, so that a product with few tiles (256 tokens, 256 columns: 64) still
+// has 512 wavefronts' loads in flight; such products are bound by the chain of load latencies, not by the 157 TFLOP/s of
+// the fp32 MFMAs. Operands go from memory to registers in the shape of
 // v_mfma_f32_16x16x4_f32 fragments (nothing is shared between wavefronts that do not share K), the next chunk requested
 // ahead of the one that is multiplied; the partial tiles meet in LDS. Inputs, products and sums are fp32 as in a plain FMA
 // loop. (Two or four chunks ahead need 150-250 registers and lose more to the fewer wavefronts: 512 x 3072 x 768 takes 52
@@ -829,10 +834,10 @@ static TileKind select_tile(int layout, int M, int N, int K, bool solo) {
   // A grid of 256x256 tiles runs in rounds of 256 (one workgroup per CU) and a thin last round costs a full one:
   // 320 tiles take two rounds for 1.25 rounds of work. A GEMM that has the chip to itself (`solo`: the forward
   // pass, the exported building block) therefore takes 128x128 tiles when their round count is the cheaper one,
-  // at the long-K rates of the two kernels (PFLOP/s: 1.30 for all three layouts against 1.05 / 1.0 /
-  // 1.0; a 256x256 tile is four small ones). In the backward pass the idle CUs of a thin round are exactly where
-  // the other stream's kernels run, and the same rule makes the step slower (2.7B-shaped layer: 5.39 ms against
-  // 4.99 ms; on a single stream 5.06 against 5.62), so it is not applied there.
+  // at the long-K rates that the two kernels had when the rule was measured (PFLOP/s: 1.30 for all three layouts against
+  // 1.05 / 1.0 / 1.0; 256x256 tiles reach 1.51 now; one is four small ones). In the backward pass the idle CUs of a thin
+  // round are exactly where the other stream's kernels run, and the same rule makes the step slower (2.7B-shaped layer:
+  // 5.39 ms against 4.99 ms; on a single stream 5.06 against 5.62), so it is not applied there.
   bool big = t256 >= 192;
   if (solo && big && K >= 2048) {
     const double e256 = 1.30, e128 = layout == GEMM_NT ? 1.05 : 1.0;
@@ -884,8 +889,9 @@ static HybridPlan hybrid_plan(int layout, int epi, int M, int N, int K) {
   s = s > 8 ? 8 : s;
   while (s > 1 && ((s - 1) * ((nk + s - 1) / s) >= nk || nk / s < 8)) --s;   // every range non-empty, at least 8 slabs
   if (s < 2) return none;
-  // Time of a 64-deep slab of a round, and the partial tiles written and read once at ~4 TB/s; the small tiles' rounds are
-  // short enough for the second kernel's own 4 us to count.
+  // Time of a 64-deep slab of a round (256x256: a lower bound, the matrix cores' own time at 1.95 PFLOP/s; the kernel takes
+  // 1.35 us), and the partial tiles written and read once at ~4 TB/s; the small tiles' rounds are short enough for the
+  // second kernel's own 4 us to count.
   const double slab_us = p.tile == TILE_256 ? 1.1 : p.tile == TILE_128_LOADERS ? 0.37 : 0.25;
   const double saved_us = (1.0 - 1.0 / s) * nk * slab_us;
   const double cost_us = 2.0 * rem * s * bm * bn * 4.0 / 4.0e6;
