@@ -13,7 +13,7 @@ from gpu_util import DEV, TOL, err, store, tdtype, to_dev, to_np
 pytestmark = pytest.mark.gpu
 
 
-# the shapes reach the 256x256-tile kernel, the 128x128 kernel fed by loader wavefronts and the general kernel
+# the shapes reach 256x256 tiles, several rounds of 128x128 tiles, and 128x64 tiles with a partial last slab
 @pytest.mark.parametrize("dtype", [W.BF16, W.FP32, W.FP16])
 @pytest.mark.parametrize("M,F,K", [(2048, 6144, 128), (1664, 1664, 512), (296, 136, 200)])
 def test_gated_epilogues(dtype, M, F, K):
