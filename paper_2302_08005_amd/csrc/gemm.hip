@@ -5,7 +5,7 @@
 // bf16 path: 8 wavefronts in a 2x4 grid (or 2 x 2x2 with an in-block K split), each owning a block of
 // v_mfma_f32_16x16x32_bf16 tiles. That form moves half the accumulator traffic per multiply of the 32x32x16 one, and
 // under a load that is bound by power the chip holds a higher clock with it: a loop of nothing but MFMAs on random data
-// runs at 2.12 PFLOP/s (2.1 GHz) against 1.87 (1.86 GHz) with the 32x32x16 form, at the same cycle count (another box 1.94
+// runs at 2.12 PFLOP/s (2.1 GHz) against 1.87 (1.86 GHz) with the 32x32x16 form, at the same cycle count (another card 1.94
 // / 1.73; on zeros or one repeated value, which draw less power, both run at 2.42-2.45).
 // K slabs go global -> LDS by direct loads into a ring of LDS stages, one barrier per slab; a K that is no multiple of
 // the slab ends in a zero-filled one. Operands whose contraction index is
@@ -365,7 +365,7 @@ void gemm_bf16_kernel(int M, int N, int K,
     // by then: its MFMAs cover the barrier and the LDS round trip of the next slab's first fragments. From there on
     // this slab's stage is free, so the loads of the slab after the next one start in the last pair, one every LOAD_GAP
     // MFMAs (a vector-memory instruction holds its wavefront while the address unit is busy).
-    // Same box, against the 32x32x16 form with its barrier between two slabs: NT 8192 x 2048 x 8192 202 -> 182.5 us (1.51
+    // Same card, against the 32x32x16 form with its barrier between two slabs: NT 8192 x 2048 x 8192 202 -> 182.5 us (1.51
     // PFLOP/s), NN 207 -> 183, TN 2048 x 8192 x 8192 209 -> 186; the change of MFMA form alone gives 189 / 188 / 194.
     // What is left is the clock (1.8 GHz under this load) and, per tile, 8-11 us of first loads and last stores.
     static_assert(NS == 2 && KS == 1, "alternating stages");
@@ -435,7 +435,7 @@ void gemm_bf16_kernel(int M, int N, int K,
     // k + 1 have landed (the younger ones stay in flight) and meets the other wavefronts at the barrier.
     auto compute = [&](int stage) {
       // Scheduling hint for the slab: interleave the LDS reads with the MFMAs. With two transposing reads per fragment of
-      // both operands the plain order is the faster one (same box: 2048 x 2048 x 8192 60.9 us, 64.4 and 66.0 with the
+      // both operands the plain order is the faster one (same card: 2048 x 2048 x 8192 60.9 us, 64.4 and 66.0 with the
       // interleaving and its second variant, 1024 x 4096 x 16384 115.8 / 122.3 / 125.7); elsewhere 0-3 % the other way.
       if constexpr (LAYOUT != GEMM_TN) __builtin_amdgcn_iglp_opt(0);
 #pragma unroll
@@ -856,7 +856,7 @@ static TileKind select_tile(int layout, int M, int N, int K, bool solo) {
 }
 
 // Several rounds of 128x128 tiles: two LDS stages instead of four, so that two workgroups fit a CU and one's first loads and
-// epilogue run beside the other's products. Four / two stages, same box: NT 2286 x 3072 x 768 with GeLU 24.1 / 20.7
+// epilogue run beside the other's products. Four / two stages, same card: NT 2286 x 3072 x 768 with GeLU 24.1 / 20.7
 // us, 2331 x 8192 x 2048 101 / 93.5, 2000 x 2560 x 2560 39.2 / 34.7; NN 2048 x 4096 x 2752 44.6 / 41.9, 2331 x 2752 x
 // 4096 gated 62.9 / 57.0. Many rounds of long K gain nothing (700 x 16384 x 4096 101.6 / 104.2).
 static bool two_per_cu(int M, int N, int K) {
@@ -871,7 +871,7 @@ static bool two_per_cu(int M, int N, int K) {
 // epilogue. Worth it when the saved (1 - 1/s) of a round outweighs writing and re-reading the partial tiles,
 // i.e. for long K; plain and add epilogues only (the others have so many tiles that a thin round matters little).
 // A grid with fewer tiles than half the CUs is all tail: 128 x 1024 outputs are 16 tiles of 128x64.
-// Same box, without / with: NT 2331 x 2048 x 8192 (304 tiles of 128x128) 98 / 83 us, 2000 x 2560 x 10240 (320) 125 / 102,
+// Same card, without / with: NT 2331 x 2048 x 8192 (304 tiles of 128x128) 98 / 83 us, 2000 x 2560 x 10240 (320) 125 / 102,
 // NN 2000 x 2560 x 7680 101 / 84; 128 x 1024 x 4096 16.3 / 10.8, K = 3072 12.9 / 10.7. Below those lengths the second
 // kernel costs what the ranges save (2331 x 2048 x 2048: 29 us either way).
 struct HybridPlan { TileKind tile; int tail_begin, tail_tiles, splits; size_t ws_bytes; };

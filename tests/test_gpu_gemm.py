@@ -178,7 +178,8 @@ def test_small_tiles_in_k_ranges(dtype, layout, M, N, K):
 
 
 # K that is no multiple of the 64-deep slab: fewer than one slab, one element piece over, one under, odd (token counts of
-# weight gradients), against 256x256 tiles, 128x128 tiles and 128x64 tiles (all with ragged edges) and the K-range forms.
+# weight gradients), against 256x256 tiles, 128x128 tiles and 128x64 tiles (all with ragged edges). The K-range forms are
+# above, split slabs and short K in layout TN below (test_gemm_partial_last_slab_tn).
 @pytest.mark.parametrize("layout,Ks", [(B.NT, (8, 72, 200, 1016)), (B.NN, (8, 72, 200, 1016)), (B.TN, (1, 63, 65, 203, 1013))])
 @pytest.mark.parametrize("M,N", [(3592, 3336), (1664, 2056), (520, 136)])
 def test_gemm_partial_last_slab(layout, Ks, M, N):
