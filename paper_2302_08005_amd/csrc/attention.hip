@@ -25,37 +25,49 @@ namespace slapo {
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
-// ---- LDS tile [rows][D] of bf16 with rows padded by 16 bytes --------------------------------------
-// The LDS serves 256 B per clock (64 banks of 4 B), 16 lanes at a time. The same tile is read two ways:
-// 16 consecutive rows x one 16-byte chunk (operand with the contraction along D), and 4 consecutive rows
-// x 32 B with the transposing 8-byte read (operand with the contraction along the rows). A row pitch of
-// 2*D + 16 bytes keeps both conflict-free, and every fragment address is a per-lane base plus a
-// compile-time offset, so the inner loops spend no vector instructions on addressing.
+// ---- LDS tile [64 rows][D] of bf16, unpadded, 16-byte chunks permuted inside each row ---------------
+// The LDS serves 256 B per clock (64 banks of 4 B): 16 lanes of a 16-byte read, 32 lanes of a transposing 8-byte read.
+// The same tile is read both ways: 16 consecutive rows x one chunk (operand with the contraction along D), and 4
+// consecutive rows x 4 chunks with the transposing read (operand with the contraction along the rows). Position p of
+// row r holds chunk p ^ f(r); f is a bijection of the rows that share a chunk position (16 rows at D = 128; 8 pairs of
+// rows at D = 64, whose rows are half as long as the banks), so the first kind of read meets every bank group once,
+// and the bits of f that choose a group of four chunks come from the lowest bits of r, so the four rows of the second
+// kind lie in different groups. (Rows padded by 16 bytes, the layout before, are conflict-free for the first kind
+// only: the four rows of a transposing read overlapped in 12 of 16 banks at D = 128, and the LDS spent 50-59 % of its
+// cycles on conflicts there.) A fragment address is a per-lane base with a compile-time XOR and a compile-time offset.
 template <int D>
 struct Tile {
-  static constexpr int P = D + 8;          // row pitch in elements
+  static constexpr int P = D;              // row pitch in elements
   static constexpr int ELEMS = 64 * P;     // one 64-row tile
+  static __device__ __forceinline__ int f(int row) {   // of rows that are equal modulo 16 the same
+    return D == 128 ? ((row & 3) << 2) | ((row >> 2) & 3) : (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
+  }
 };
 // per-lane bases, computed once per kernel
 template <int D>
-__device__ __forceinline__ int rows_base(int lane) { return (lane & 31) * Tile<D>::P + (lane >> 5) * 8; }
+__device__ __forceinline__ int rows_base(int lane) {
+  const int row = lane & 31;
+  return row * Tile<D>::P + ((Tile<D>::f(row) ^ (lane >> 5)) << 3);
+}
 template <int D>
 __device__ __forceinline__ int tr_base(int lane) {
-  const int j = lane & 15, g = lane >> 4;
-  return (4 * (g >> 1) + (j >> 2)) * Tile<D>::P + 16 * (g & 1) + 4 * (j & 3);
+  const int j = lane & 15, g = lane >> 4, row = 4 * (g >> 1) + (j >> 2);
+  return row * Tile<D>::P + ((Tile<D>::f(row) ^ (2 * (g & 1) + ((j >> 1) & 1))) << 3) + 4 * (j & 1);
 }
-// MFMA operand whose 32 rows are tile rows r0.. and whose contraction runs along D (step s of 16)
+// MFMA operand whose 32 rows are tile rows r0.. (a multiple of 16) and whose contraction runs along D (step s of 16)
 template <int D>
 __device__ __forceinline__ bf16x8_t frag_rows(const bf16_t* tile, int base, int r0, int s) {
-  return *reinterpret_cast<const bf16x8_t*>(tile + base + r0 * Tile<D>::P + 16 * s);
+  return *reinterpret_cast<const bf16x8_t*>(tile + (base ^ (16 * s)) + r0 * Tile<D>::P);
 }
 // MFMA operand whose 32 rows are tile COLUMNS t*32.. and whose contraction runs over tile rows
-// c0 + {4kc..4kc+3, 8+4kc..8+4kc+3} (kc = lane/32): the order in which a 32x32 accumulator holds them.
+// c0 + {4kc..4kc+3, 8+4kc..8+4kc+3} (kc = lane/32; c0 a multiple of 16): the order in which a 32x32 accumulator holds
+// them. Eight rows further f differs in bit 1.
 template <int D>
 __device__ __forceinline__ bf16x8_t frag_tr(const bf16_t* tile, int base, int c0, int t) {
-  const bf16_t* p0 = tile + base + c0 * Tile<D>::P + t * 32;
+  const bf16_t* p0 = tile + (base ^ (32 * t)) + c0 * Tile<D>::P;
+  const bf16_t* p1 = tile + (base ^ (32 * t + 16)) + (c0 + 8) * Tile<D>::P;
   s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)p0);
-  s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)(p0 + 8 * Tile<D>::P));
+  s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4_t __attribute__((address_space(3)))*)p1);
   typedef short s16x8_t __attribute__((ext_vector_type(8)));
   s16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   return __builtin_bit_cast(bf16x8_t, v);
@@ -81,17 +93,14 @@ __device__ __forceinline__ int acc_row(int r, int lane) { return (r >> 2) * 8 + 
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
 // A 64 x D tile is brought in by direct global -> LDS loads (no staging registers, no ds_write). One
-// wave-level load fills 1 KB of consecutive LDS, lane l at byte 16 l, so the 16-byte padding at the end of every
-// tile row is simply one more slot: the tile is 64 * (D/8 + 1) slots = D/8 + 1 wave-level loads, and the lane
-// that lands on a padding slot fetches the row's first piece again (nobody reads the padding). The loads of
-// a tile are dealt out to the four wavefronts round-robin. Rows past the end of the sequence are whatever
+// wave-level load fills 1 KB of consecutive LDS, lane l at byte 16 l: the lane fetches the chunk that the permutation
+// puts there. The D/8 loads of a tile are dealt out to the four wavefronts. Rows past the end of the sequence are whatever
 // follows in memory (the next sample's rows, zero past the end of the tensor: the buffer bounds): finite
 // values that only ever meet masked scores.
 template <int D>
 struct TileDirect {
-  static constexpr int SPR = D / 8 + 1;            // 16-byte slots per padded row = wave-level loads per tile
-  static constexpr int MINE = (SPR + 3) / 4;       // loads per tile of one wavefront (at most)
-  static constexpr int LEAST = SPR / 4;            // ... and at least
+  static constexpr int SPR = D / 8;                // 16-byte chunks per row = wave-level loads per tile
+  static constexpr int MINE = SPR / 4;             // loads per tile of one wavefront
   unsigned voff[MINE];
   int wave;                                        // wave-uniform
   __device__ __forceinline__ void init(int lane, int wave_uniform, unsigned row_stride_bytes) {
@@ -99,21 +108,20 @@ struct TileDirect {
 #pragma unroll
     for (int k = 0; k < MINE; ++k) {
       const int slot = (wave + 4 * k) * 64 + lane, row = slot / SPR, pos = slot % SPR;
-      voff[k] = (unsigned)row * row_stride_bytes + (unsigned)(pos == D / 8 ? 0 : pos) * 16u;
+      voff[k] = (unsigned)row * row_stride_bytes + (unsigned)(pos ^ Tile<D>::f(row)) * 16u;
     }
   }
   // tile rows row0.. of the operand that starts at `base` (`bytes` long from there) -> LDS tile
   __device__ __forceinline__ void issue(const bf16_t* base, unsigned bytes, bf16_t* tile, unsigned row0_bytes) const {
 #pragma unroll
     for (int k = 0; k < MINE; ++k) {
-      const int instr = wave + 4 * k;
-      if (instr < SPR) buffer_load_lds_16_untracked(base, bytes, tile + instr * 512, voff[k], row0_bytes);
+      buffer_load_lds_16_untracked(base, bytes, tile + (wave + 4 * k) * 512, voff[k], row0_bytes);
     }
   }
 };
 
 // The tile loop of the forward kernel: a ring of NSTG LDS stages, tiles t+1 .. t+NSTG-1 on their way while
-// tile t is computed, one barrier per tile. LPT = loads every wavefront issues per tile step at the least:
+// tile t is computed, one barrier per tile. LPT = loads every wavefront issues per tile step:
 // waiting until at most (NSTG-2)*LPT loads are outstanding leaves only younger tiles in flight (loads
 // complete in issue order). On the last steps nothing is issued any more and the wait is for everything.
 template <int NSTG, int LPT, typename Issue, typename Compute>
@@ -362,7 +370,7 @@ __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const 
           o[t] = mfma16<F16>(frag_tr<D>(vt, ft_base, i * 32 + 16 * h, t), pf, o[t]);
       }
   };
-  tile_ring<FWD_STAGES<D>, 2 * TileDirect<D>::LEAST>(n_tiles, issue_tile, compute);
+  tile_ring<FWD_STAGES<D>, 2 * TileDirect<D>::MINE>(n_tiles, issue_tile, compute);
 
   const float l_tot = l + __shfl_xor(l, 32, 64);
   const float inv = l_tot > 0.f ? (DROP ? sh.drop.scale : 1.f) / l_tot : 0.f;
@@ -722,9 +730,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_bf16_kernel(AttnShape sh, c
   // Ring of NSTG stages: tile it + NSTG - 1 is requested while tile it is computed; the statistics of tile
   // it + 1 travel through a register and are requested BEFORE that step's tile loads, so that waiting for
   // them (loads complete in issue order) leaves the younger tile loads in flight. LPT = tile loads per step
-  // that every wavefront issues at the least.
+  // that every wavefront issues.
   if (n_tiles > 0) {
-    constexpr int LPT = 2 * TileDirect<D>::LEAST;
+    constexpr int LPT = 2 * TileDirect<D>::MINE;
     const float stat0 = load_stats(q_first * 64);
 #pragma unroll
     for (int t = 0; t < NSTG - 1; ++t)
@@ -883,7 +891,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_bf16_kernel(AttnShape sh, con
       }
     }
   };
-  tile_ring<2, 2 * TileDirect<D>::LEAST>(n_tiles, issue_tile, compute);
+  tile_ring<2, 2 * TileDirect<D>::MINE>(n_tiles, issue_tile, compute);
 
   if (my_q < S) {
     bf16_t* qrow = dqkv + ((int64_t)b * S + my_q) * rs + a * D;
