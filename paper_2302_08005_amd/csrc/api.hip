@@ -186,6 +186,20 @@ bool backward_on_one_stream(const slapo_layer_desc* d) {
   return 110.0 + products + 0.03 * T + 7e-4 * (A / d->heads) * d->seq < 184.0;
 }
 
+// Whether backward puts each weight gradient into the launch of the data gradient beside it (GradPair): always on one
+// stream, whose calls are bound by the number of their launches; on two streams where the products are small enough that
+// the smaller tiles of those launches cost less than three of the four forks (only the gradient of the output projection
+// still goes to the helper stream, beside the attention kernels). Not for the gated layer there, whose rotary passes keep the
+// caller's stream busy while the helper stream works. Steps in us, every weight gradient forked / paired:
+//   classic  hidden 512, 2048 tokens 186 / 170; 768, 2286 261 / 246; 1024, 600 201 / 176, 2000 296 / 282, 4096 470 / 495;
+//            1536, 640 269 / 255, 3000 648 / 676; 2048, 384 280 / 272, 1500 477 / 493; 256, 4096 364 / 351, 8192 253 / 264
+//   gated    hidden 512, 2048 tokens 208 / 211; 1024, 600 216 / 216, 2000 327 / 338; 2048, 384 299 / 322
+bool gradients_paired(const slapo_layer_desc* d) {
+  if (backward_on_one_stream(d)) return true;
+  const double T = (double)d->batch * d->seq, H = d->hidden, F = d->ffn, A = attn_width(d);
+  return !is_llama(d) && T <= 4096.0 && (4.0 * H * A + 2.0 * H * F) * T <= 3.2e10;
+}
+
 // byte offsets of the regions of `saved`
 struct SavedLayout {
   size_t qkv, attn, lse, z1, n1, y1, u, g, z2, mu1, rstd1, mu2, rstd2, total;
@@ -437,11 +451,14 @@ struct BackwardLink {
   void* dr2_below = nullptr;      // where the dR2 of the layer below goes ...
   DropoutParams dp_below;         // ... its mask stream (site 1 of that layer)
   void* db2_below = nullptr;      // ... and its b2 gradient (NULL: the family has no biases)
+  // (paired launches) where the sums over the partial rows go that the layer above left, which ride on my first launch;
+  // behind the call: those that I leave to the layer below
+  void* sums[3] = {nullptr, nullptr, nullptr};
 };
 
 static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, const void* x, const int32_t* seqlens,
                         const void* dy, const void* saved, void* dx, const slapo_layer_grads* gr, void* scratch,
-                        hipStream_t st, const BackwardLink* link = nullptr) {
+                        hipStream_t st, BackwardLink* link = nullptr) {
   const int dt = d->dtype, acc = d->accumulate_grads ? 1 : 0;
   const int T = d->batch * d->seq, H = d->hidden, F = d->ffn, A = attn_width(d);
   const SavedLayout L = saved_layout(d);
@@ -495,6 +512,73 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   // the LLaMA-style layer has no bias or offset gradients: those outputs are simply not produced
   void *g_b2 = llama ? nullptr : gr->b2, *g_bo = llama ? nullptr : gr->bo;
   void *g_ln1_b = llama ? nullptr : gr->ln1_b, *g_ln2_b = llama ? nullptr : gr->ln2_b;
+
+  if (gradients_paired(d) && (d->pre_ln || dx != x)) {   // (a dx on top of x would be written while the weight gradient beside it still reads x)
+    // The weight gradients share the launches of the data gradients (GradPair), and the sums behind the row kernels and
+    // the biases ride on them.
+    GradPair pr = {};
+    auto take_sums = [&](void* a, void* b, void* c) { pr.partials = prow; pr.nblk = nrow; pr.H = H; pr.sums[0] = a; pr.sums[1] = b; pr.sums[2] = c; };
+    auto data = [&](int epi, int M, int N, int K, const void* A_, const void* B_, void* C_, const void* aux) {
+      pr.epi = epi; pr.act = d->act; pr.M = M; pr.N = N; pr.K = K; pr.A = A_; pr.B = B_; pr.C = C_; pr.aux = aux;
+    };
+    auto weight = [&](int wM, int wN, const void* wA, const void* wB, void* dW, void* colsum_out) {
+      pr.wM = wM; pr.wN = wN; pr.wK = T; pr.wA = wA; pr.wB = wB; pr.dW = dW; pr.colsum = colsum_out; pr.accumulate = acc;
+    };
+    auto launch = [&] { launch_grad_pair(dt, pr, st); pr = GradPair{}; };
+    const int F1 = llama ? 2 * F : F;
+    // ---- FFN block ----
+    const void* dr2 = t1;
+    if (d->pre_ln && link && link->dr2_in) {
+      dr2 = link->dr2_in;
+      take_sums(link->sums[0], link->sums[1], link->sums[2]);
+    } else if (d->pre_ln) {
+      launch_bdrln_bwd(dt, T, H, dy, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, t1, prow, dp1, rms, st);
+      if (!llama) take_sums(nullptr, nullptr, g_b2);
+    } else {
+      launch_bdrln_bwd(dt, T, H, dy, sv + L.z2, mu2, rstd2, p->ln2_g, nullptr, t0, t1, prow, dp1, rms, st);
+      take_sums(gr->ln2_g, g_ln2_b, g_b2);
+    }
+    data(llama ? EPI_DGATE : EPI_DACT, T, F, H, dr2, p->w2, du, u);
+    weight(H, F, dr2, g, gr->w2, nullptr);
+    launch();
+    data(EPI_ADD, T, H, F1, du, p->w1, t0, d->pre_ln ? nullptr : t0);
+    weight(F1, H, du, y1, gr->w1, llama ? nullptr : gr->b1);
+    launch();
+    // ---- attention block ----
+    if (d->pre_ln) {
+      launch_bdrln_bwd(dt, T, H, t0, z1, mu2, rstd2, p->ln2_g, dy, t2, t3, prow, dp0, rms, st);
+      take_sums(gr->ln2_g, g_ln2_b, g_bo);
+    } else {
+      launch_bdrln_bwd(dt, T, H, t0, z1, mu1, rstd1, p->ln1_g, nullptr, t2, t3, prow, dp0, rms, st);
+      take_sums(gr->ln1_g, g_ln1_b, g_bo);
+    }
+    data(EPI_ADD, T, A, H, t3, p->wo, t0, nullptr);
+    if (side) pr.accumulate = acc;
+    else weight(H, A, t3, attn, gr->wo, nullptr);
+    launch();
+    if (side) {   // beside the attention kernels, which leave most of the chip free
+      fork(2);
+      dweight(H, A, t3, attn, gr->wo);
+    }
+    launch_attn_bwd(dt, as, qkv, seqlens, attn, t0, lse, delta, dqkv, st);
+    if (llama) {
+      float* table = (float*)(sc + W.rope);
+      if (!d->checkpoint) launch_rope_table(d->seq, A / d->heads, d->rope_base, table, st);
+      launch_rope(dt, T, d->seq, A, A / d->heads, table, dqkv, 1, st);
+    }
+    if (side) side->order(side->join, ws, st);   // the gradient of the output projection has long been there
+    data(EPI_ADD, T, H, 3 * A, dqkv, p->wqkv, d->pre_ln ? t0 : dx, d->pre_ln ? nullptr : t2);
+    weight(3 * A, H, dqkv, d->pre_ln ? sv + L.n1 : x, gr->wqkv, llama ? nullptr : gr->bqkv);
+    launch();
+    if (d->pre_ln && link && link->dr2_below) {
+      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, link->dr2_below, prow, link->dp_below, rms, st, 1);
+      link->sums[0] = gr->ln1_g; link->sums[1] = g_ln1_b; link->sums[2] = link->db2_below;
+    } else if (d->pre_ln) {
+      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, prow, dp0, rms, st);
+      reduce_rows(gr->ln1_g, g_ln1_b, nullptr);
+    }
+    return finish();
+  }
 
   // ---- FFN block ----
   const void* dr2 = t1;
@@ -642,11 +726,13 @@ int slapo_stack_bwd(const slapo_layer_desc* desc, int32_t n_layers, const slapo_
   }
   entry_error();
   const void* gin = dy;
+  BackwardLink link;
   for (int l = n_layers - 1; l >= 0; --l) {
     d.layer_id = desc->layer_id + l;
     const void* in = l == 0 ? x : (const char*)acts + (size_t)(l - 1) * ab;
     void* gout = l == 0 ? dx : pong + (size_t)(l & 1) * align256(ab);
-    BackwardLink link;
+    link.dr2_in = nullptr;
+    link.dr2_below = nullptr;
     if (d.pre_ln) {
       // Layer l reads buffer l&1 (on both streams) and writes the other one; that one was last read by the
       // weight gradient of layer l+1, which the join at the end of that layer's backward has waited for.

@@ -40,6 +40,26 @@ size_t weight_grad_ws_least_bytes(int dtype, int M, int N, int K);
 void launch_weight_grad(int dtype, int accumulate, int M, int N, int K, const void* A, const void* B, void* C,
                         float* ws, hipStream_t st, bool solo = false);
 
+// What backward computes from one gradient array, in one launch: the gradient that goes on (layout NN, C [M,N] = A [M,K]
+// B [K,N], epilogue EPI_DACT, EPI_DGATE or EPI_ADD; the latter adds nothing if aux is NULL), the weight gradient
+// dW [wM,wN] (+)= wA [wK,wM]^T wB [wK,wN] (NULL: none), the column sums of wA (a bias gradient; NULL: none) and the sums over the partial
+// rows [nblk][3][H] that an earlier row kernel left (outputs as in launch_colreduce3; partials NULL: none).
+struct GradPair {
+  int epi, act, M, N, K;
+  const void *A, *B;
+  void* C;
+  const void* aux;
+  int wM, wN, wK;
+  const void *wA, *wB;
+  void* dW;
+  void* colsum;
+  const float* partials;
+  int nblk, H;
+  void* sums[3];
+  int accumulate;
+};
+void launch_grad_pair(int dtype, const GradPair& p, hipStream_t st);
+
 struct AttnShape {
   int batch, seq, hidden, heads, causal;
   int lpt_heads = 0;   // causal block order: heads per longest-first group (set by the launchers; 0 = head by head)
