@@ -53,16 +53,16 @@ constexpr bool epi_used(int layout, int epi) {
                            : (epi == EPI_NONE || epi == EPI_ADD);
 }
 
-template <int LAYOUT, int BM, int BN, int WGM, int WGN, int KS, int NS, int PW, bool F16, bool ALL_EPI = false>
+template <int LAYOUT, int BM, int BN, int WGM, int WGN, int KS, int NS, int PW, bool F16, bool ALL_EPI = false, int BK = 64>
 static void launch_bf16_tile(int epi, int act, int M, int N, int K, const void* A, const void* B, void* C,
                              const void* bias, const void* aux_in, void* aux_out, hipStream_t st) {
   const int tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-  const size_t lds = gemm_lds_bytes<BM, BN, 64, WGM, WGN, KS, NS>();
+  const size_t lds = gemm_lds_bytes<BM, BN, BK, WGM, WGN, KS, NS>();
 #define SLAPO_GEMM(E)                                                                                       \
   do {                                                                                                      \
     if constexpr (ALL_EPI || epi_used(LAYOUT, E)) {                                                         \
-      auto kern = LAYOUT == GEMM_TN || K % 64 == 0 ? gemm_bf16_kernel<LAYOUT, BM, BN, 64, WGM, WGN, KS, NS, PW, false, E, F16> \
-                                                   : gemm_bf16_kernel<LAYOUT, BM, BN, 64, WGM, WGN, KS, NS, PW, LAYOUT != GEMM_TN, E, F16>; \
+      auto kern = LAYOUT == GEMM_TN || K % BK == 0 ? gemm_bf16_kernel<LAYOUT, BM, BN, BK, WGM, WGN, KS, NS, PW, false, E, F16> \
+                                                   : gemm_bf16_kernel<LAYOUT, BM, BN, BK, WGM, WGN, KS, NS, PW, LAYOUT != GEMM_TN, E, F16>; \
       (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);  \
       hipLaunchKernelGGL(kern, dim3(tiles), dim3((WGM * WGN * KS + PW) * 64), lds, st, M, N, K, (const bf16_t*)A,       \
                          (const bf16_t*)B, (bf16_t*)C, (const bf16_t*)bias, (const bf16_t*)aux_in,          \
@@ -85,9 +85,14 @@ static void launch_bf16_tile(int epi, int act, int M, int N, int K, const void* 
 // loads into two stages) when they still cover at least three quarters
 // of the 256 CUs. Otherwise 128x128 tiles (8 wavefronts, 64x32 each; TN: two sets of four, 64x64 each): a ring of four
 // stages filled by four loader wavefronts. 128x64 tiles of the same form (four computing wavefronts) where all of them
-// fit one round. K needs no particular multiple: TN products with K = 2286 tokens and 768 x 3072 outputs take 18.7 us
+// fit one round, and 64x64 tiles with 128-deep slabs (layouts NT and NN, K of two such slabs or more) where the latter would
+// leave half of the CUs idle:
+// such a product is a chain of slabs whose bytes each CU has to fetch by itself, so more CUs and fewer bytes per CU shorten
+// it. Forward of an encoder layer, 128x64 / 64x64, 64-deep slabs / 64x64, 128-deep: hidden 256, 1024 tokens 41.8 / 37.4 / 36.9
+// us; 512, 512 48.9 / 43.2 / 42.4; 1024, 128 47.7 / 43.5 / 42.7; 2048, 128 68.7 / 62.0 / 60.9 (deeper rings, or eight
+// computing wavefronts instead of four: nothing or 1-3 % more). K needs no particular multiple: TN products with K = 2286 tokens and 768 x 3072 outputs take 18.7 us
 // (41.7 with the register-staged kernel that such K used to go to), K = 2000 and 10240 x 2560 take 107 us (170 before).
-enum TileKind { TILE_256, TILE_128_SPLITSLAB, TILE_128_LOADERS, TILE_128x64_LOADERS };
+enum TileKind { TILE_256, TILE_128_SPLITSLAB, TILE_128_LOADERS, TILE_128x64_LOADERS, TILE_64_LOADERS };
 static TileKind select_tile(int layout, int M, int N, int K, bool solo) {
   const int64_t t256 = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
   const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
@@ -111,7 +116,8 @@ static TileKind select_tile(int layout, int M, int N, int K, bool solo) {
   // at K = 128 6.8 / 6.0 us (split-slab / plain), 512 9.0 / 8.1, 1024 12.5 / 11.6, 2048 18.3 / 18.8.
   // Two rounds of 128x64 tiles are slower than one of 128x128 (768 x 3072 outputs, K = 2286: 26.8 against 18.7 us), one
   // round is faster (2304 x 768: 14.9 against 17.4).
-  if ((int64_t)((M + 127) / 128) * ((N + 63) / 64) <= 256) return TILE_128x64_LOADERS;
+  const int64_t t128x64 = (int64_t)((M + 127) / 128) * ((N + 63) / 64);
+  if (t128x64 <= 256) return t128x64 <= 128 && layout != GEMM_TN && K >= 256 ? TILE_64_LOADERS : TILE_128x64_LOADERS;
   return layout == GEMM_TN && K > 1024 ? TILE_128_SPLITSLAB : TILE_128_LOADERS;
 }
 
@@ -140,6 +146,7 @@ static HybridPlan hybrid_plan(int layout, int epi, int M, int N, int K) {
   static const bool disabled = debug_flag("no-hybrid");
   if (disabled || (epi != EPI_NONE && epi != EPI_ADD)) return none;
   p.tile = select_tile(layout, M, N, K, false);
+  if (p.tile == TILE_64_LOADERS) p.tile = TILE_128x64_LOADERS;   // (K ranges bring the workgroups that the smaller tiles would)
   if (layout == GEMM_TN && p.tile != TILE_256) return none;   // (K ranges of their own: weight_grad_splits)
   const int bm = p.tile == TILE_256 ? 256 : 128, bn = p.tile == TILE_256 ? 256 : p.tile == TILE_128x64_LOADERS ? 64 : 128;
   const int tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
@@ -152,7 +159,7 @@ static HybridPlan hybrid_plan(int layout, int epi, int M, int N, int K) {
   // Time of a 64-deep slab of a round (256x256: a lower bound, the matrix cores' own time at 1.95 PFLOP/s; the kernel takes
   // 1.35 us), and the partial tiles written and read once at ~4 TB/s; the small tiles' rounds are short enough for the
   // second kernel's own 4 us to count.
-  const double slab_us = p.tile == TILE_256 ? 1.1 : p.tile == TILE_128_LOADERS ? 0.37 : 0.25;
+  const double slab_us = p.tile == TILE_256 ? 1.1 : p.tile == TILE_128_LOADERS ? 0.37 : 0.2;
   const double saved_us = (1.0 - 1.0 / s) * nk * slab_us;
   const double cost_us = 2.0 * rem * s * bm * bn * 4.0 / 4.0e6;
   if (saved_us < 1.5 * cost_us + (p.tile == TILE_256 ? 0.0 : 4.0)) return none;
@@ -267,6 +274,9 @@ static void launch_bf16(int epi, int act, int M, int N, int K, const void* A, co
       launch_bf16_tile<LAYOUT, 128, 128, 2, 4, 1, 4, 4, F16, true>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st); break;
     case TILE_128x64_LOADERS:
       launch_bf16_tile<LAYOUT, 128, 64, 2, 2, 1, 4, 4, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st); break;
+    case TILE_64_LOADERS:
+      if constexpr (LAYOUT != GEMM_TN) launch_bf16_tile<LAYOUT, 64, 64, 2, 2, 1, 3, 4, F16, false, 128>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
+      break;
   }
 }
 
@@ -370,7 +380,7 @@ void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool sol
   const char* b = f16 ? "true" : "false";
   const char* kt = layout != GEMM_TN && K % 64 != 0 ? "true" : "false";
   static const char* const shape[] = {"256, 256, 64, 2, 4, 1, 2, 0", "128, 128, 64, 2, 2, 2, 4, 4", "128, 128, 64, 2, 4, 1, 4, 4",
-                                      "128, 64, 64, 2, 2, 1, 4, 4"};
+                                      "128, 64, 64, 2, 2, 1, 4, 4", "64, 64, 128, 2, 2, 1, 3, 4"};
   if (with_ws && !(weight_grad && weight_grad_splits(M, N, K) > 1)) {
     const HybridPlan hp = hybrid_plan(layout, weight_grad ? EPI_NONE : epi, M, N, K);
     if (hp.ws_bytes) {
@@ -391,6 +401,7 @@ void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool sol
     snprintf(buf, len, "gemm_bf16_kernel<%d, 128, 128, 64, 2, 4, 1, 2, 4, %s, %d, %s, false>", layout, kt, epi, b);
     return;
   }
+  if (k == TILE_64_LOADERS) kt = K % 128 != 0 ? "true" : "false";
   snprintf(buf, len, "gemm_bf16_kernel<%d, %s, %s, %d, %s, false>", layout, shape[(int)k], kt, epi, b);
 }
 

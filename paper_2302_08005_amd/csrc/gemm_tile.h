@@ -85,7 +85,7 @@ __device__ __forceinline__ GateTerms gate_terms(float u, float w) {
 // addresses and 8 or 16 wavefronts: 16-byte reads 257 B per clock, plain 8-byte reads 164, transposing
 // 8-byte reads 120 (about the same instruction rate as the 16-byte read, half the bytes).
 //  - K-contiguous tile [rows][BK]: position p of row r holds chunk p ^ swzK(r), swzK(r) = (r / RP) % (BK/8),
-//    RP = rows per 256 B. A fragment read (one chunk of 16 consecutive rows) then lands in 16 different
+//    RP = rows per 256 B (2 at a depth of 64, 1 at 128). A fragment read (one chunk of 16 consecutive rows) then lands in 16 different
 //    16-byte bank groups. swzK depends on the lane only (wave tiles start at multiples of 32 rows), so a
 //    fragment address is a per-lane base plus (2*ks ^ per-lane constant).
 //  - M-contiguous tile [BK][W]: position p of k-row r holds chunk p ^ (swzM(r) << 1), i.e. 32-byte granules
@@ -159,13 +159,13 @@ __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, c
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
   constexpr int A_LOADS = BM * BK / 8 / NTHR, B_LOADS = BN * BK / 8 / NTHR;
   static_assert(A_LOADS >= 1 && B_LOADS >= 1, "tile too small for the thread count");
-  static_assert(BK == 64, "swizzles and fragment addresses written for 128-byte tile rows");
+  static_assert(BK == 64 || BK == 128, "swizzles and fragment addresses written for 128- and 256-byte tile rows");
   static_assert(TM % 2 == 0, "tile rows are multiplied in pairs");
   static_assert(NS >= 2 && NS <= 10, "stage count");
   constexpr int PA = A_KC ? BK : BM;        // row pitch of the A tile in elements (unpadded)
   constexpr int PB = B_KC ? BK : BN;
   constexpr int SA = BM * BK, SB = BN * BK;  // elements per stage
-  auto swzK = [](int row) { return (row / 2) % 8; };
+  auto swzK = [](int row) { return BK == 64 ? (row / 2) % 8 : row % 16; };
   auto swzM = [](int krow, auto width) {
     constexpr int W = decltype(width)::value;
     static_assert(W >= 64, "at least four 32-byte granules per tile row");
@@ -298,7 +298,7 @@ __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, c
   // row l % 16.
   // K-contiguous: chunk 4*ks + lane/16 of the row, stored at position (4*ks + lane/16) ^ swzK = (4*ks ^ fsw) with the two
   // low bits folded into the base.
-  const int fsw = swzK(lane & 15) & 4;
+  const int fsw = swzK(lane & 15) & (BK / 8 - 4);
   const int kc_low = (((lane >> 4) ^ swzK(lane & 15)) & 3) << 3;
   const int fa_base = (wm0 + (lane & 15)) * PA + kc_low;
   const int fb_base = (wn0 + (lane & 15)) * PB + kc_low;

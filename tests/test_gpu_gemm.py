@@ -344,3 +344,44 @@ def test_gemm_partial_last_slab_tn(M, N, Ks, name):
     for K in Ks:
         assert name in B.slapo_gemm_kernel_name(W.BF16, B.TN, B.EPI_NONE, M, N, K)
     test_gemm_partial_last_slab(B.TN, Ks, M, N)
+
+
+# 64x64 tiles with 128-deep slabs: K of whole slabs, one piece more, one less, odd slab counts; ragged edges
+@pytest.mark.parametrize("layout", [B.NT, B.NN])
+@pytest.mark.parametrize("M,N", [(64, 64), (65, 8), (129, 200), (9, 2048)])
+def test_gemm_64x64_tiles(layout, M, N):
+    Ks = (256, 264, 376, 640, 1016)
+    for K in Ks:
+        assert "64, 64, 128, 2, 2, 1, 3, 4, " + ("false" if K % 128 == 0 else "true") in B.slapo_gemm_kernel_name(W.BF16, layout, B.EPI_NONE, M, N, K)
+    test_gemm_partial_last_slab(layout, Ks, M, N)
+
+
+@pytest.mark.parametrize("dtype", [W.BF16, W.FP16])
+@pytest.mark.parametrize("layout", [B.NT, B.NN])
+def test_epilogues_of_64x64_tiles(layout, dtype):
+    """The bound of test_epilogues_of_every_tile_form, at the K that these tiles start from."""
+    M, N, name = 264, 144, "64, 64, 128, 2, 2, 1, 3, 4"
+    for K in (256, 328):
+        rng = np.random.default_rng(K + layout)
+        a, b = store(rng.standard_normal((M, K)), dtype), store(rng.standard_normal((K, N)) * K ** -0.5, dtype)
+        bias, aux = store(rng.standard_normal(N), dtype), store(rng.standard_normal((M, 2 * N)), dtype)
+        acc = a.astype(np.float64) @ b.astype(np.float64)
+        A, Bm = to_dev(a, dtype), to_dev(b.T.copy() if layout == B.NT else b, dtype)
+        keep = torch.empty(M, N, dtype=A.dtype, device=DEV)
+
+        def run(epi, act=W.GELU, width=N, aux_in=None, aux_out=None):
+            assert name in B.slapo_gemm_kernel_name(dtype, layout, epi, M, N, K)
+            out = torch.full((M, width), 7.0, dtype=A.dtype, device=DEV)
+            B.slapo_gemm(dtype, layout, epi, act, M, N, K, A, Bm, out, bias=to_dev(bias, dtype), aux_in=aux_in, aux_out=aux_out)
+            return out
+
+        if layout == B.NT:
+            gate, up = acc[:, ::2], acc[:, 1::2]
+            errs = {"bias": err(run(B.EPI_BIAS), acc + bias), "gelu": err(run(B.EPI_BIAS_ACT, aux_out=keep), _act(acc + bias, W.GELU))}
+            errs["gelu'"] = err(keep, _dact(acc + bias, W.GELU))
+            errs["gate"] = err(run(B.EPI_GATE, width=N // 2, aux_out=keep), gate / (1 + np.exp(-gate)) * up)
+        else:
+            aux1 = to_dev(aux[:, :N].copy(), dtype)
+            errs = {"add": err(run(B.EPI_ADD, aux_in=aux1), acc + aux[:, :N]), "dgelu": err(run(B.EPI_DACT, aux_in=aux1), acc * aux[:, :N]),
+                    "dgate": err(run(B.EPI_DGATE, width=2 * N, aux_in=to_dev(aux, dtype)), np.repeat(acc, 2, 1) * aux)}
+        assert all(v <= {W.BF16: 4e-3, W.FP16: 5e-4}[dtype] for v in errs.values()), (K, errs)
