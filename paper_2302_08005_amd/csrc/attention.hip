@@ -134,17 +134,28 @@ __device__ __forceinline__ void tile_ring(int n_tiles, Issue&& issue_tile, Compu
   if (n_tiles >= NSTG - 1) wait_loads_and_lds<(NSTG - 2) * LPT>();
   else wait_loads_and_lds<0>();
   block_barrier();
-  int stage = 0, fill = NSTG - 1;   // stage of tile `it`, stage that tile it + NSTG - 1 goes to
-  for (int it = 0; it < n_tiles; ++it) {
-    const bool more = it + NSTG - 1 < n_tiles;
-    if (more) issue_tile(fill, it + NSTG - 1);   // that stage was last read before the barrier that ended step it - 1
-    compute(stage, it);
-    if (more) wait_loads_and_lds<(NSTG - 2) * LPT>();
-    else wait_loads_and_lds<0>();
-    block_barrier();
-    stage = stage + 1 == NSTG ? 0 : stage + 1;
-    fill = fill + 1 == NSTG ? 0 : fill + 1;
+  for (int it0 = 0; it0 < n_tiles; it0 += NSTG) {
+#pragma unroll
+    for (int s = 0; s < NSTG; ++s) {   // (stages at compile time: a fragment address is a per-lane base plus an offset in the instruction)
+      const int it = it0 + s;
+      if (it >= n_tiles) break;        // uniform
+      const bool more = it + NSTG - 1 < n_tiles;
+      if (more) issue_tile((s + NSTG - 1) % NSTG, it + NSTG - 1);   // that stage was last read before the barrier that ended step it - 1
+      compute(s, it);
+      if (more) wait_loads_and_lds<(NSTG - 2) * LPT>();
+      else wait_loads_and_lds<0>();
+      block_barrier();
+    }
   }
+}
+
+// Small grids (few heads, few rows) leave most of the chip idle while each block walks its tiles one after the other. Their
+// blocks own 128 / G rows instead of 128 and their wavefronts form G groups that take every G-th tile of the walk (a step
+// brings in G tiles); the groups' results meet in LDS. G = 2: twice the blocks, half the steps.
+// Per-lane values of groups 1.. -> LDS, and back in group 0: slot [group - 1][row wavefront][register][lane].
+template <int G, int REGS>
+__device__ __forceinline__ float* group_slot(void* smem, int grp, int row_wave, int lane) {
+  return reinterpret_cast<float*>(smem) + ((grp - 1) * (4 / G) + row_wave) * (REGS * 64) + lane;
 }
 
 __device__ __forceinline__ int visible_keys(const AttnShape& sh, const int32_t* seqlens, int b) {
@@ -166,9 +177,9 @@ struct BlockId { int x, a, b; };
 // head: with head-by-head order a slot that has just finished a short block picks up the next head's longest one
 // late, and the grid ends on a ragged tail of long blocks (a list-scheduling estimate puts the head-by-head order
 // at 1.15-1.5x the balanced makespan for the causal benchmark shapes, the grouped order at 1.0-1.14x).
-__device__ __forceinline__ BlockId xcd_local_block(bool descending = false, int lpt_heads = 0) {
-  const int nx = gridDim.x, ny = gridDim.y, total = nx * ny * gridDim.z;
-  int w = blockIdx.x + nx * (blockIdx.y + ny * blockIdx.z);
+// `w`: position in a grid of nx x ny x nz blocks (the launch's own grid unless it holds several).
+__device__ __forceinline__ BlockId xcd_local_block(int w, int nx, int ny, int nz, bool descending = false, int lpt_heads = 0) {
+  const int total = nx * ny * nz;
   if (total % 8 == 0) w = (w & 7) * (total >> 3) + (w >> 3);
   int xi = w % nx, head = w / nx;
   if (lpt_heads > 1 && total % 8 == 0 && (total >> 3) % nx == 0) {
@@ -249,33 +260,39 @@ __device__ __forceinline__ uint32_t keep16_key_lane(const DropoutParams& dp, uin
   return bits;
 }
 
+__device__ __forceinline__ BlockId xcd_local_block(bool descending, int lpt_heads) {
+  return xcd_local_block(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), gridDim.x, gridDim.y, gridDim.z, descending, lpt_heads);
+}
+
 // =================================== forward =====================================================
 // LDS stages of the forward kernel's K/V ring. Two: with three or four the forward pass is 10-40 % slower on
 // every shape with more than two workgroups per CU (the LDS footprint costs resident workgroups, and those,
 // not the depth of the prefetch, are what hides the latencies here) and unchanged on the others.
 template <int D> constexpr int FWD_STAGES = 2;
 
-template <int D, bool DROP, bool F16>
+template <int D, bool DROP, bool F16, int G>
 __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const bf16_t* __restrict__ qkv,
                                                             const int32_t* __restrict__ seqlens,
                                                             bf16_t* __restrict__ out, float* __restrict__ lse) {
   constexpr int NS = D / 16, NT = D / 32;
   constexpr int TE = Tile<D>::ELEMS;
-  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];  // [2][K tile | V tile]
+  constexpr int RB = 128 / G;   // rows of the block
+  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];  // [2][G][K tile | V tile]
   const int S = sh.seq, H = sh.hidden;
   const BlockId blk = xcd_local_block(sh.causal != 0, sh.lpt_heads);
-  const int b = blk.b, a = blk.a, q_base = blk.x * 128;
+  const int b = blk.b, a = blk.a, q_base = blk.x * RB;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kc = lane >> 5;
+  const int row_wave = wave % (4 / G), grp = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave / (4 / G));
   const int fr_base = rows_base<D>(lane), ft_base = tr_base<D>(lane);
   const int64_t rs = 3 * (int64_t)H;
   const bf16_t* base = qkv + (int64_t)b * S * rs + a * D;
   const int kv_len = visible_keys(sh, seqlens, b);
   int kv_end = kv_len;
-  if (sh.causal && q_base + 128 < kv_end) kv_end = q_base + 128;
+  if (sh.causal && q_base + RB < kv_end) kv_end = q_base + RB;
   const int n_tiles = (kv_end + 63) / 64;
-  const int my_q = q_base + 32 * wave + (lane & 31);
+  const int my_q = q_base + 32 * row_wave + (lane & 31);
   const int q_ld = my_q < S ? my_q : S - 1;
-  const int wave_q_min = q_base + 32 * wave, wave_q_max = wave_q_min + 31;
+  const int wave_q_min = q_base + 32 * row_wave, wave_q_max = wave_q_min + 31;
   const float scale = rsqrtf((float)D), sl2 = LOG2E * scale;
 
   bf16x8_t qf[NS];
@@ -297,15 +314,20 @@ __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const 
   const bf16_t* vbase = base + 2 * H;
   const int64_t total_elems = (int64_t)sh.batch * S * rs;
   const unsigned kbytes = (unsigned)((total_elems - (kbase - qkv)) * 2), vbytes = (unsigned)((total_elems - (vbase - qkv)) * 2);
-  auto issue_tile = [&](int stage, int t) {
-    const unsigned row0_bytes = (unsigned)t * 64u * (unsigned)(rs * 2);
-    td.issue(kbase, kbytes, smem + stage * 2 * TE, row0_bytes);
-    td.issue(vbase, vbytes, smem + stage * 2 * TE + TE, row0_bytes);
+  auto issue_step = [&](int stage, int step) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int t = step * G + g;
+      if (t >= n_tiles) break;   // uniform
+      const unsigned row0_bytes = (unsigned)t * 64u * (unsigned)(rs * 2);
+      td.issue(kbase, kbytes, smem + (stage * G + g) * 2 * TE, row0_bytes);
+      td.issue(vbase, vbytes, smem + (stage * G + g) * 2 * TE + TE, row0_bytes);
+    }
   };
-  auto compute = [&](int stage, int it) {
-    const int kv0 = it * 64;
-    if (sh.causal && kv0 > wave_q_max) return;   // every key of the tile lies in this wave's future
-    const bf16_t* kt = smem + stage * 2 * TE;
+  auto compute = [&](int stage, int step) {
+    const int t = step * G + grp, kv0 = t * 64;
+    if ((G > 1 && t >= n_tiles) || (sh.causal && kv0 > wave_q_max)) return;   // every key of the tile lies in this wave's future
+    const bf16_t* kt = smem + (stage * G + grp) * 2 * TE;
     const bf16_t* vt = kt + TE;
     f32x16_t sc[2];
 #pragma unroll
@@ -370,7 +392,34 @@ __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const 
           o[t] = mfma16<F16>(frag_tr<D>(vt, ft_base, i * 32 + 16 * h, t), pf, o[t]);
       }
   };
-  tile_ring<FWD_STAGES<D>, 2 * TileDirect<D>::MINE>(n_tiles, issue_tile, compute);
+  tile_ring<FWD_STAGES<D>, G * 2 * TileDirect<D>::MINE>((n_tiles + G - 1) / G, issue_step, compute);
+  if constexpr (G > 1) {   // (the ring ends behind a barrier: the stages are free)
+    static_assert(FWD_STAGES<D> == 2, "partly filled steps are waited for as a whole");
+    constexpr int REGS = NT * 16 + 2;
+    if (grp > 0) {
+      float* p = group_slot<G, REGS>(smem, grp, row_wave, lane);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) p[(t * 16 + r) * 64] = o[t][r];
+      p[NT * 16 * 64] = m;
+      p[(NT * 16 + 1) * 64] = l;
+    }
+    __syncthreads();
+    if (grp > 0) return;
+    for (int g = 1; g < G; ++g) {
+      const float* p = group_slot<G, REGS>(smem, g, row_wave, lane);
+      const float m2 = p[NT * 16 * 64], m_new = fmaxf(m, m2);
+      const float mine = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_new) * sl2);
+      const float theirs = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m2 - m_new) * sl2);
+      l = l * mine + p[(NT * 16 + 1) * 64] * theirs;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[t][r] = o[t][r] * mine + p[(t * 16 + r) * 64] * theirs;
+      m = m_new;
+    }
+  }
 
   const float l_tot = l + __shfl_xor(l, 32, 64);
   const float inv = l_tot > 0.f ? (DROP ? sh.drop.scale : 1.f) / l_tot : 0.f;
@@ -430,16 +479,16 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(AttnShape sh, const T* 
 // for each other at the barrier, not for the next tile).
 template <int D> constexpr int DKDV_STAGES = 2;
 
-template <int D, bool DROP, bool F16>
-__global__ __launch_bounds__(256) void attn_bwd_dkdv_bf16_kernel(AttnShape sh, const bf16_t* __restrict__ qkv,
-                                                                 const int32_t* __restrict__ seqlens,
-                                                                 const bf16_t* __restrict__ dout,
-                                                                 const float* __restrict__ lse,
-                                                                 const float* __restrict__ delta,
-                                                                 bf16_t* __restrict__ dqkv) {
+// OWN_DELTA: delta = rowsum(dO * O) of each query tile is computed here (see attn_bwd_both_kernel) instead of read.
+template <int D, bool DROP, bool F16, bool OWN_DELTA, int G>
+__device__ __forceinline__ void attn_bwd_dkdv_block(const BlockId blk, const AttnShape& sh, const bf16_t* __restrict__ qkv,
+                                                    const int32_t* __restrict__ seqlens, const bf16_t* __restrict__ out,
+                                                    const bf16_t* __restrict__ dout, const float* __restrict__ lse,
+                                                    const float* __restrict__ delta, bf16_t* __restrict__ dqkv) {
   constexpr int NS = D / 16, NT = D / 32;
   constexpr int TE = Tile<D>::ELEMS;
-  constexpr int STAGE = 2 * TE + 256;   // bf16 units: Q tile, dO tile, 64 lse + 64 delta floats
+  constexpr int TILE = 2 * TE + 256;    // bf16 units: Q tile, dO tile, 64 lse + 64 delta floats
+  constexpr int STAGE = G * TILE, RB = 128 / G;
   constexpr int FB = 4;                 // k-steps of fragment prefetch (register budget: 8 FB registers)
   constexpr int NSTG = DKDV_STAGES<D>;
   constexpr bool ACC_A = (D == 128);    // dK/dV accumulators in AGPRs (see mfma16_agpr)
@@ -447,9 +496,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_bf16_kernel(AttnShape sh, c
   static_assert(!PIPE || (NS == 8 && NT == 4), "the pipelined rounds are written for D = 128");
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
   const int S = sh.seq, H = sh.hidden;
-  const BlockId blk = xcd_local_block(false, sh.lpt_heads);
-  const int b = blk.b, a = blk.a, kv_base = blk.x * 128;
+  const int b = blk.b, a = blk.a, kv_base = blk.x * RB;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kc = lane >> 5;
+  const int row_wave = wave % (4 / G), grp = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave / (4 / G));
   const int fr_base = rows_base<D>(lane), ft_base = tr_base<D>(lane);
   const int64_t rs = 3 * (int64_t)H;
   const bf16_t* base = qkv + (int64_t)b * S * rs + a * D;
@@ -457,9 +506,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_bf16_kernel(AttnShape sh, c
   const float* lse_row = lse + ((int64_t)b * sh.heads + a) * S;
   const float* delta_row = delta + ((int64_t)b * sh.heads + a) * S;
   const int kv_len = visible_keys(sh, seqlens, b);
-  const int my_kv = kv_base + 32 * wave + (lane & 31);
+  const int my_kv = kv_base + 32 * row_wave + (lane & 31);
   const int kv_ld = my_kv < S ? my_kv : S - 1;
-  const int wave_kv_min = kv_base + 32 * wave;
+  const int wave_kv_min = kv_base + 32 * row_wave;
   const bool wave_kv_edge = wave_kv_min + 32 > kv_len;   // some of this wave's keys are hidden
   // DROP: block index of (query 0, key 0) of this head, and this wavefront's exchange area behind the stages
   const uint64_t head_blk = ((((uint64_t)b * sh.heads + a) * S) * (uint64_t)S) >> 3;
@@ -482,14 +531,43 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_bf16_kernel(AttnShape sh, c
   const int n_tiles = (kv_base < kv_len) ? (S + 63) / 64 - q_first : 0;  // nothing to do for fully hidden keys
   const int stat_row = tid & 63;
   // threads 0..63 carry lse, threads 64..127 delta, threads 128..255 duplicate them (same values to the same
-  // slots, so no thread is special). The value is only touched when it is stored to LDS after the step's
-  // compute, so the load stays in flight like the tile loads.
-  const float* stat_src = (tid & 127) < 64 ? lse_row : delta_row;
-  const float stat_mul = (tid & 127) < 64 ? LOG2E : 1.0f;
-  auto load_stats = [&](int q0) -> float {
-    int q = q0 + stat_row;
+  // slots, so no thread is special) or the second tile of a step; OWN_DELTA: every 64 threads lse, of the step's tiles in turn. The value is only
+  // touched when it is stored to LDS after the step's compute, so the load stays in flight like the tile loads.
+  const float* stat_src = OWN_DELTA || (tid & 127) < 64 ? lse_row : delta_row;
+  const float stat_mul = OWN_DELTA || (tid & 127) < 64 ? LOG2E : 1.0f;
+  const int stat_tile = OWN_DELTA ? (tid >> 6) % G : (tid >> 7) % G;
+  auto load_stats = [&](int step) -> float {
+    int q = (q_first + step * G + stat_tile) * 64 + stat_row;
     q = q < S ? q : S - 1;
     return stat_src[q];
+  };
+  // OWN_DELTA: four threads per query row, D / 4 elements of O and dO each, requested a tile ahead like the rest
+  struct DeltaRows { bf16x8_t o[D / 32], d[D / 32]; };
+  const bf16_t* obase = out + (int64_t)b * S * H + a * D;
+  auto load_delta_rows = [&](int t, DeltaRows& r) {
+    int q = (q_first + t) * 64 + (tid >> 2);
+    q = q < S ? q : S - 1;
+    const int64_t at = (int64_t)q * H + (tid & 3) * (D / 4);
+#pragma unroll
+    for (int k = 0; k < D / 32; ++k) {
+      r.o[k] = *reinterpret_cast<const bf16x8_t*>(obase + at + 8 * k);
+      r.d[k] = *reinterpret_cast<const bf16x8_t*>(dobase + at + 8 * k);
+    }
+  };
+  auto store_delta = [&](int stage, int g, const DeltaRows& r) {
+    float v = 0.f;
+#pragma unroll
+    for (int k = 0; k < D / 32; ++k) {
+      const u32x4_t ow = __builtin_bit_cast(u32x4_t, r.o[k]), dw = __builtin_bit_cast(u32x4_t, r.d[k]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v = fmaf(unpack_lo<F16>(ow[e]), unpack_lo<F16>(dw[e]), v);
+        v = fmaf(unpack_hi<F16>(ow[e]), unpack_hi<F16>(dw[e]), v);
+      }
+    }
+    v += __shfl_xor(v, 1, 64);
+    v += __shfl_xor(v, 2, 64);
+    if ((tid & 3) == 0) reinterpret_cast<float*>(smem + stage * STAGE + g * TILE + 2 * TE)[64 + (tid >> 2)] = v;
   };
   // Q and dO tiles of 64 queries: direct loads into two LDS stages, tile t+1 on its way while tile t is computed
   TileDirect<D> tq, tdo;
@@ -497,15 +575,21 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_bf16_kernel(AttnShape sh, c
   tdo.init(lane, __builtin_amdgcn_readfirstlane(wave), (unsigned)(H * 2));
   const unsigned qbytes = (unsigned)(((int64_t)sh.batch * S * rs - (base - qkv)) * 2);
   const unsigned dbytes = (unsigned)(((int64_t)sh.batch * S * H - (dobase - dout)) * 2);
-  auto issue_tile = [&](int stage, int t) {
-    const unsigned q0 = (unsigned)(q_first + t) * 64u;
-    tq.issue(base, qbytes, smem + stage * STAGE, q0 * (unsigned)(rs * 2));
-    tdo.issue(dobase, dbytes, smem + stage * STAGE + TE, q0 * (unsigned)(H * 2));
+  auto issue_step = [&](int stage, int step) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int t = step * G + g;
+      if (t >= n_tiles) break;   // uniform
+      const unsigned q0 = (unsigned)(q_first + t) * 64u;
+      tq.issue(base, qbytes, smem + stage * STAGE + g * TILE, q0 * (unsigned)(rs * 2));
+      tdo.issue(dobase, dbytes, smem + stage * STAGE + g * TILE + TE, q0 * (unsigned)(H * 2));
+    }
   };
-  auto store_stats = [&](int stage, float v) { reinterpret_cast<float*>(smem + stage * STAGE + 2 * TE)[tid & 127] = v * stat_mul; };
-  auto compute = [&](int stage, int it) {
-    const int q0 = (q_first + it) * 64;
-    const bf16_t* qtile = smem + stage * STAGE;
+  auto store_stats = [&](int stage, float v) { reinterpret_cast<float*>(smem + stage * STAGE + stat_tile * TILE + 2 * TE)[OWN_DELTA ? tid & 63 : tid & 127] = v * stat_mul; };
+  auto compute = [&](int stage, int step) {
+    if (G > 1 && step * G + grp >= n_tiles) return;
+    const int q0 = (q_first + step * G + grp) * 64;
+    const bf16_t* qtile = smem + stage * STAGE + grp * TILE;
     const bf16_t* dtile = qtile + TE;
     const float* stats = reinterpret_cast<const float*>(qtile + 2 * TE);
     if constexpr (PIPE) {
@@ -727,38 +811,81 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_bf16_kernel(AttnShape sh, c
       }
     }
   };
-  // Ring of NSTG stages: tile it + NSTG - 1 is requested while tile it is computed; the statistics of tile
-  // it + 1 travel through a register and are requested BEFORE that step's tile loads, so that waiting for
+  // Ring of NSTG stages: step it + NSTG - 1 is requested while step it is computed; the statistics of step
+  // it + 1 travel through registers and are requested BEFORE that step's tile loads, so that waiting for
   // them (loads complete in issue order) leaves the younger tile loads in flight. LPT = tile loads per step
   // that every wavefront issues.
-  if (n_tiles > 0) {
-    constexpr int LPT = 2 * TileDirect<D>::MINE;
-    const float stat0 = load_stats(q_first * 64);
+  const int n_steps = (n_tiles + G - 1) / G;
+  if (n_steps > 0) {
+    constexpr int LPT = G * 2 * TileDirect<D>::MINE;
+    static_assert(G == 1 || NSTG == 2, "partly filled steps are waited for as a whole");
+    DeltaRows rows[G];
+    const float stat0 = load_stats(0);
+    if constexpr (OWN_DELTA) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) load_delta_rows(g, rows[g]);
+    }
 #pragma unroll
     for (int t = 0; t < NSTG - 1; ++t)
-      if (t < n_tiles) issue_tile(t, t);
+      if (t < n_steps) issue_step(t, t);
     store_stats(0, stat0);
-    if (n_tiles >= NSTG - 1) wait_loads_and_lds<(NSTG - 2) * LPT>();
+    if constexpr (OWN_DELTA) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) store_delta(0, g, rows[g]);
+    }
+    if (n_steps >= NSTG - 1) wait_loads_and_lds<(NSTG - 2) * LPT>();
     else wait_loads_and_lds<0>();
     block_barrier();
-    int stage = 0, fill = NSTG - 1;
-    for (int it = 0; it < n_tiles; ++it) {
-      const bool more = it + 1 < n_tiles, far = it + NSTG - 1 < n_tiles;
-      const int next = stage + 1 == NSTG ? 0 : stage + 1;
-      float next_stat = 0.f;
-      if (more) next_stat = load_stats((q_first + it + 1) * 64);
-      if (far) issue_tile(fill, it + NSTG - 1);   // that stage was last read before the barrier that ended step it - 1
-      compute(stage, it);
-      if (more) store_stats(next, next_stat);
-      if (far) wait_loads_and_lds<(NSTG - 2) * LPT>();
-      else wait_loads_and_lds<0>();
-      block_barrier();
-      stage = next;
-      fill = fill + 1 == NSTG ? 0 : fill + 1;
+    for (int it0 = 0; it0 < n_steps; it0 += NSTG) {
+#pragma unroll
+      for (int st = 0; st < NSTG; ++st) {   // (stages at compile time, as in tile_ring)
+        const int it = it0 + st, next = (st + 1) % NSTG;
+        if (it >= n_steps) break;           // uniform
+        const bool more = it + 1 < n_steps, far = it + NSTG - 1 < n_steps;
+        float next_stat = 0.f;
+        if (more) {
+          next_stat = load_stats(it + 1);
+          if constexpr (OWN_DELTA) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) load_delta_rows((it + 1) * G + g, rows[g]);
+          }
+        }
+        if (far) issue_step((st + NSTG - 1) % NSTG, it + NSTG - 1);   // that stage was last read before the barrier that ended step it - 1
+        compute(st, it);
+        if (more) {
+          store_stats(next, next_stat);
+          if constexpr (OWN_DELTA) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) store_delta(next, g, rows[g]);
+          }
+        }
+        if (far) wait_loads_and_lds<(NSTG - 2) * LPT>();
+        else wait_loads_and_lds<0>();
+        block_barrier();
+      }
     }
   }
 
   if (ACC_A) agpr_results_ready();
+  if constexpr (G > 1) {   // (behind the last barrier: the stages are free)
+    constexpr int REGS = 2 * NT * 16;
+    if (grp > 0) {
+      float* p = group_slot<G, REGS>(smem, grp, row_wave, lane);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { p[(t * 16 + r) * 64] = dk[t][r]; p[((NT + t) * 16 + r) * 64] = dv[t][r]; }
+    }
+    __syncthreads();
+    if (grp > 0) return;
+    for (int g = 1; g < G; ++g) {
+      const float* p = group_slot<G, REGS>(smem, g, row_wave, lane);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { dk[t][r] += p[(t * 16 + r) * 64]; dv[t][r] += p[((NT + t) * 16 + r) * 64]; }
+    }
+  }
   if (my_kv < S) {
     bf16_t* krow = dqkv + ((int64_t)b * S + my_kv) * rs + H + a * D;
     bf16_t* vrow = krow + H;
@@ -778,31 +905,29 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_bf16_kernel(AttnShape sh, c
 }
 
 // ============================ backward: dQ per query tile ========================================
-template <int D, bool DROP, bool F16>
-__global__ __launch_bounds__(256) void attn_bwd_dq_bf16_kernel(AttnShape sh, const bf16_t* __restrict__ qkv,
-                                                               const int32_t* __restrict__ seqlens,
-                                                               const bf16_t* __restrict__ out,
-                                                               const bf16_t* __restrict__ dout,
-                                                               const float* __restrict__ lse,
-                                                               float* __restrict__ delta,
-                                                               bf16_t* __restrict__ dqkv) {
+template <int D, bool DROP, bool F16, int G>
+__device__ __forceinline__ void attn_bwd_dq_block(const BlockId blk, const AttnShape& sh, const bf16_t* __restrict__ qkv,
+                                                  const int32_t* __restrict__ seqlens, const bf16_t* __restrict__ out,
+                                                  const bf16_t* __restrict__ dout, const float* __restrict__ lse,
+                                                  float* __restrict__ delta, bf16_t* __restrict__ dqkv) {
   constexpr int NS = D / 16, NT = D / 32;
   constexpr int TE = Tile<D>::ELEMS;
-  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];  // [2][K tile | V tile]
+  constexpr int RB = 128 / G;
+  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];  // [2][G][K tile | V tile]
   const int S = sh.seq, H = sh.hidden;
-  const BlockId blk = xcd_local_block(sh.causal != 0, sh.lpt_heads);
-  const int b = blk.b, a = blk.a, q_base = blk.x * 128;
+  const int b = blk.b, a = blk.a, q_base = blk.x * RB;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kc = lane >> 5;
+  const int row_wave = wave % (4 / G), grp = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave / (4 / G));
   const int fr_base = rows_base<D>(lane), ft_base = tr_base<D>(lane);
   const int64_t rs = 3 * (int64_t)H;
   const bf16_t* base = qkv + (int64_t)b * S * rs + a * D;
   const int kv_len = visible_keys(sh, seqlens, b);
   int kv_end = kv_len;
-  if (sh.causal && q_base + 128 < kv_end) kv_end = q_base + 128;
+  if (sh.causal && q_base + RB < kv_end) kv_end = q_base + RB;
   const int n_tiles = (kv_end + 63) / 64;
-  const int my_q = q_base + 32 * wave + (lane & 31);
+  const int my_q = q_base + 32 * row_wave + (lane & 31);
   const int q_ld = my_q < S ? my_q : S - 1;
-  const int wave_q_min = q_base + 32 * wave, wave_q_max = wave_q_min + 31;
+  const int wave_q_min = q_base + 32 * row_wave, wave_q_max = wave_q_min + 31;
   const float scale = rsqrtf((float)D), sl2 = LOG2E * scale;
 
   bf16x8_t qf[NS], df[NS];
@@ -829,7 +954,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_bf16_kernel(AttnShape sh, con
     }
   }
   my_delta += __shfl_xor(my_delta, 32, 64);
-  if (kc == 0 && my_q < S) delta[((int64_t)b * sh.heads + a) * S + my_q] = my_delta;
+  if (delta != nullptr && kc == 0 && grp == 0 && my_q < S) delta[((int64_t)b * sh.heads + a) * S + my_q] = my_delta;
   f32x16_t dq[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -843,15 +968,20 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_bf16_kernel(AttnShape sh, con
   const bf16_t* vbase = base + 2 * H;
   const int64_t total_elems = (int64_t)sh.batch * S * rs;
   const unsigned kbytes = (unsigned)((total_elems - (kbase - qkv)) * 2), vbytes = (unsigned)((total_elems - (vbase - qkv)) * 2);
-  auto issue_tile = [&](int stage, int t) {
-    const unsigned row0_bytes = (unsigned)t * 64u * (unsigned)(rs * 2);
-    td.issue(kbase, kbytes, smem + stage * 2 * TE, row0_bytes);
-    td.issue(vbase, vbytes, smem + stage * 2 * TE + TE, row0_bytes);
+  auto issue_step = [&](int stage, int step) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int t = step * G + g;
+      if (t >= n_tiles) break;   // uniform
+      const unsigned row0_bytes = (unsigned)t * 64u * (unsigned)(rs * 2);
+      td.issue(kbase, kbytes, smem + (stage * G + g) * 2 * TE, row0_bytes);
+      td.issue(vbase, vbytes, smem + (stage * G + g) * 2 * TE + TE, row0_bytes);
+    }
   };
-  auto compute = [&](int stage, int it) {
-    const int kv0 = it * 64;
-    if (sh.causal && kv0 > wave_q_max) return;
-    const bf16_t* kt = smem + stage * 2 * TE;
+  auto compute = [&](int stage, int step) {
+    const int tile = step * G + grp, kv0 = tile * 64;
+    if ((G > 1 && tile >= n_tiles) || (sh.causal && kv0 > wave_q_max)) return;
+    const bf16_t* kt = smem + (stage * G + grp) * 2 * TE;
     const bf16_t* vt = kt + TE;
     const bool edge = (kv0 + 64 > kv_len) || (sh.causal && kv0 + 63 > wave_q_min);
 #pragma unroll
@@ -891,7 +1021,26 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_bf16_kernel(AttnShape sh, con
       }
     }
   };
-  tile_ring<2, 2 * TileDirect<D>::MINE>(n_tiles, issue_tile, compute);
+  tile_ring<2, G * 2 * TileDirect<D>::MINE>((n_tiles + G - 1) / G, issue_step, compute);
+  if constexpr (G > 1) {
+    constexpr int REGS = NT * 16;
+    if (grp > 0) {
+      float* p = group_slot<G, REGS>(smem, grp, row_wave, lane);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) p[(t * 16 + r) * 64] = dq[t][r];
+    }
+    __syncthreads();
+    if (grp > 0) return;
+    for (int g = 1; g < G; ++g) {
+      const float* p = group_slot<G, REGS>(smem, g, row_wave, lane);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dq[t][r] += p[(t * 16 + r) * 64];
+    }
+  }
 
   if (my_q < S) {
     bf16_t* qrow = dqkv + ((int64_t)b * S + my_q) * rs + a * D;
@@ -905,6 +1054,40 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_bf16_kernel(AttnShape sh, con
         *reinterpret_cast<uint2*>(qrow + t * 32 + g * 8 + 4 * kc) = w;
       }
   }
+}
+
+// ============================ backward: the launches =============================================
+template <int D, bool DROP, bool F16>
+__global__ __launch_bounds__(256) void attn_bwd_dq_bf16_kernel(AttnShape sh, const bf16_t* __restrict__ qkv,
+                                                               const int32_t* __restrict__ seqlens, const bf16_t* __restrict__ out,
+                                                               const bf16_t* __restrict__ dout, const float* __restrict__ lse,
+                                                               float* __restrict__ delta, bf16_t* __restrict__ dqkv) {
+  attn_bwd_dq_block<D, DROP, F16, 1>(xcd_local_block(sh.causal != 0, sh.lpt_heads), sh, qkv, seqlens, out, dout, lse, delta, dqkv);
+}
+template <int D, bool DROP, bool F16>
+__global__ __launch_bounds__(256) void attn_bwd_dkdv_bf16_kernel(AttnShape sh, const bf16_t* __restrict__ qkv,
+                                                                 const int32_t* __restrict__ seqlens, const bf16_t* __restrict__ dout,
+                                                                 const float* __restrict__ lse, const float* __restrict__ delta,
+                                                                 bf16_t* __restrict__ dqkv) {
+  attn_bwd_dkdv_block<D, DROP, F16, false, 1>(xcd_local_block(false, sh.lpt_heads), sh, qkv, seqlens, nullptr, dout, lse, delta, dqkv);
+}
+// Both in one launch, for grids so small that the blocks of the two find room side by side: the dK/dV blocks first (they
+// take longer), each with its own delta of every query tile (O is read once more, which a chip that is mostly idle does
+// not notice), so that neither kind waits for the other. Two groups at 128-wide heads have no registers left for that:
+// delta comes from a kernel in front.
+template <int D, int G> constexpr bool OWN_DELTAS = D == 64 || G == 1;
+template <int D, bool DROP, bool F16, int G>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_both_kernel(AttnShape sh, int blocks_x, const bf16_t* __restrict__ qkv,
+                                                            const int32_t* __restrict__ seqlens, const bf16_t* __restrict__ out,
+                                                            const bf16_t* __restrict__ dout, const float* __restrict__ lse,
+                                                            float* delta, bf16_t* __restrict__ dqkv) {
+  const int blocks = blocks_x * sh.heads * sh.batch, w = blockIdx.x;
+  if (w < blocks)
+    attn_bwd_dkdv_block<D, DROP, F16, OWN_DELTAS<D, G>, G>(xcd_local_block(w, blocks_x, sh.heads, sh.batch, false, sh.lpt_heads), sh, qkv,
+                                                           seqlens, out, dout, lse, delta, dqkv);
+  else
+    attn_bwd_dq_block<D, DROP, F16, G>(xcd_local_block(w - blocks, blocks_x, sh.heads, sh.batch, sh.causal != 0, sh.lpt_heads), sh, qkv,
+                                       seqlens, out, dout, lse, OWN_DELTAS<D, G> ? delta : nullptr, dqkv);
 }
 
 // =================================== fp32 / generic simple kernels ===============================
@@ -1062,13 +1245,29 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_simple_kernel(AttnShape sh,
 }
 
 // =================================== launchers ===================================================
+// Blocks of 128 rows that the chip runs at a time where they fit a CU twice (64-wide heads) or once.
+template <int D> constexpr int64_t ONE_ROUND = D == 64 ? 512 : 256;
+static int64_t attn_blocks(const AttnShape& s) { return (int64_t)((s.seq + 127) / 128) * s.heads * s.batch; }
+
+template <int D, bool F16, int G>
+static void fwd_bf16_groups(const AttnShape& s, const void* qkv, const int32_t* seqlens, void* out, float* lse, hipStream_t st) {
+  constexpr size_t tiles = (size_t)FWD_STAGES<D> * G * 2 * Tile<D>::ELEMS * sizeof(bf16_t);
+  constexpr size_t meet = (size_t)(G - 1) * (4 / G) * (D / 2 + 2) * 64 * sizeof(float), lds = tiles > meet ? tiles : meet;
+  auto kern = s.drop.thr ? attn_fwd_bf16_kernel<D, true, F16, G> : attn_fwd_bf16_kernel<D, false, F16, G>;
+  (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  constexpr int rows = 128 / G;
+  hipLaunchKernelGGL(kern, dim3((s.seq + rows - 1) / rows, s.heads, s.batch), dim3(256), lds, st, s, (const bf16_t*)qkv,
+                     seqlens, (bf16_t*)out, lse);
+}
 template <int D, bool F16>
 static void fwd_bf16(const AttnShape& s, const void* qkv, const int32_t* seqlens, void* out, float* lse, hipStream_t st) {
-  const size_t lds = (size_t)FWD_STAGES<D> * 2 * Tile<D>::ELEMS * sizeof(bf16_t);
-  auto kern = s.drop.thr ? attn_fwd_bf16_kernel<D, true, F16> : attn_fwd_bf16_kernel<D, false, F16>;
-  (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL(kern, dim3((s.seq + 127) / 128, s.heads, s.batch), dim3(256), lds, st, s, (const bf16_t*)qkv,
-                     seqlens, (bf16_t*)out, lse);
+  // Two groups per block while the doubled blocks still run in one round (causal blocks are half as long) and there is more
+  // than one tile to share. Blocks of 128 rows, one / two groups, us: 64-wide 16 (one sample of 128) 5.8 / 5.1, 128 (1024
+  // tokens, causal) 20.0 / 13.0, 256 (4 x 512) 12.1 / 10.3, 320 15.3 / 16.2; 128-wide 64 (2 x 1024, causal) 27.1 / 18.9, 128
+  // (8192, causal) 165 / 113, 256 (4 x 1024, causal) 27.9 / 25.4, 320 42.9 / 43.9.
+  const int64_t room = s.causal ? ONE_ROUND<D> : ONE_ROUND<D> / 2;
+  if (attn_blocks(s) <= (room < 256 ? room : 256) && s.seq > 64) fwd_bf16_groups<D, F16, 2>(s, qkv, seqlens, out, lse, st);
+  else fwd_bf16_groups<D, F16, 1>(s, qkv, seqlens, out, lse, st);
 }
 template <int D>
 static void fwd_f32(const AttnShape& s, const void* qkv, const int32_t* seqlens, void* out, float* lse, hipStream_t st) {
@@ -1096,20 +1295,48 @@ void launch_attn_fwd(int dtype, const AttnShape& s0, const void* qkv, const int3
   else { if (D == 64) fwd_bf16<64, false>(s, qkv, seqlens, out, lse, st); else fwd_bf16<128, false>(s, qkv, seqlens, out, lse, st); }
 }
 
+template <int D, bool F16, int G>
+static void bwd_both(const AttnShape& s, const void* qkv, const int32_t* seqlens, const void* out, const void* dout,
+                     const float* lse, float* delta, void* dqkv, hipStream_t st) {
+  constexpr size_t tiles = (size_t)DKDV_STAGES<D> * G * (2 * Tile<D>::ELEMS + 256) * sizeof(bf16_t);
+  constexpr size_t meet = (size_t)(G - 1) * (4 / G) * D * 64 * sizeof(float);
+  const size_t main = tiles + (s.drop.thr ? 4 * 2048 : 0), lds = main > meet ? main : meet;
+  auto kern = s.drop.thr ? attn_bwd_both_kernel<D, true, F16, G> : attn_bwd_both_kernel<D, false, F16, G>;
+  (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (!OWN_DELTAS<D, G>) {
+    using T = std::conditional_t<F16, f16_t, bf16_t>;
+    const int64_t items = (int64_t)s.batch * s.seq * s.heads * 8;
+    hipLaunchKernelGGL((attn_delta_kernel<T, D>), dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, s, (const T*)out, (const T*)dout, delta);
+  }
+  constexpr int rows = 128 / G;
+  const int blocks_x = (s.seq + rows - 1) / rows;
+  hipLaunchKernelGGL(kern, dim3(2 * blocks_x * s.heads * s.batch), dim3(256), lds, st, s, blocks_x, (const bf16_t*)qkv, seqlens,
+                     (const bf16_t*)out, (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv);
+}
 template <int D, bool F16>
 static void bwd_bf16(const AttnShape& s, const void* qkv, const int32_t* seqlens, const void* out, const void* dout,
                      const float* lse, float* delta, void* dqkv, hipStream_t st) {
   dim3 grid((s.seq + 127) / 128, s.heads, s.batch);
+  const size_t lds_dq = (size_t)4 * Tile<D>::ELEMS * sizeof(bf16_t);
+  // with dropout: 2 KB per wavefront behind the stages for the exchange of mask draws
+  const size_t lds_dkdv = (size_t)DKDV_STAGES<D> * (2 * Tile<D>::ELEMS + 256) * sizeof(bf16_t) + (s.drop.thr ? 4 * 2048 : 0);
+  // One launch while either kind's blocks alone fit one round; two groups per block while the four times as many blocks do.
+  // Two launches / one / one with two groups, us: 64-wide 16 blocks (one sample of 128) 14.6 / 8.7 / 7.0, 128 (1024 tokens,
+  // causal) 48.7 / 32.8 / 24.1, 192 (4 x 512, 12 heads) 31 / 22.5 / 26.2, 256 (2048, causal) 90 / 62 / 47, 512 (8 x 512, padded)
+  // 48.5 / 45.3 / 54, 1536 (6 x 1024, causal) 132 / 141; 128-wide 64 (2 x 1024, causal) 68 / 44.5 / 29, 128 (2 x 512) 44 / 29 / 34.5,
+  // 192 (3 x 1024, causal) 73 / 46 / 57, 256 (4 x 1024, causal) 74 / 56 / 68, 384 80 / 85.
+  const int64_t blocks = attn_blocks(s);
+  if (blocks <= ONE_ROUND<D> / (s.causal ? 2 : 4) && s.seq > 64) return bwd_both<D, F16, 2>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
+  if (blocks <= ONE_ROUND<D>) return bwd_both<D, F16, 1>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
   {  // dQ first: it also produces delta = rowsum(dO * O), which the dK/dV kernel reads
-    const size_t lds = (size_t)4 * Tile<D>::ELEMS * sizeof(bf16_t);
+    const size_t lds = lds_dq;
     auto kern = s.drop.thr ? attn_bwd_dq_bf16_kernel<D, true, F16> : attn_bwd_dq_bf16_kernel<D, false, F16>;
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, s, (const bf16_t*)qkv, seqlens, (const bf16_t*)out,
                        (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv);
   }
   {
-    // with dropout: 2 KB per wavefront behind the stages for the exchange of mask draws
-    const size_t lds = (size_t)DKDV_STAGES<D> * (2 * Tile<D>::ELEMS + 256) * sizeof(bf16_t) + (s.drop.thr ? 4 * 2048 : 0);
+    const size_t lds = lds_dkdv;
     auto kern = s.drop.thr ? attn_bwd_dkdv_bf16_kernel<D, true, F16> : attn_bwd_dkdv_bf16_kernel<D, false, F16>;
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, s, (const bf16_t*)qkv, seqlens, (const bf16_t*)dout, lse,

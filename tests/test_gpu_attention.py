@@ -96,3 +96,16 @@ def test_sample_without_visible_keys_yields_zeros_not_nans(dtype, causal):
     assert torch.isfinite(dqkv).all() and (dqkv[S:2 * S] == 0).all()
     dqkv_ref = L.attention_bwd(cfg, qkv.astype(np.float64), P, dout.astype(np.float64))
     assert err(dqkv[keep], dqkv_ref[keep]) <= TOL[dtype]
+
+
+# either side of the lines between the forms of the kernels: two groups of wavefronts per block (small grids), one; dQ and
+# dK/dV in one launch, in two. Sequences of one to five tiles, ragged, masked, with dropout.
+@pytest.mark.parametrize("dtype", [W.BF16, W.FP16])
+@pytest.mark.parametrize("case", [
+    (3, 64, 2, 64, 0, [64, 1, 33], 1.0), (1, 8, 1, 128, 1, None, 1.0), (2, 65, 2, 64, 1, None, 4.0), (2, 72, 2, 128, 0, [72, 64], 1.0, 0.2),
+    (5, 130, 13, 64, 0, [130, 64, 65, 1, 128], 1.0), (5, 200, 13, 64, 1, None, 4.0), (9, 200, 15, 64, 0, None, 1.0), (9, 200, 15, 64, 1, None, 1.0, 0.1),
+    (9, 200, 30, 64, 1, [200, 3, 64, 65, 128, 129, 192, 193, 199], 1.0), (3, 200, 11, 128, 0, [200, 65, 128], 1.0), (3, 264, 11, 128, 1, None, 4.0),
+    (5, 136, 14, 128, 0, None, 1.0, 0.1), (5, 264, 14, 128, 1, [264, 1, 64, 200, 257], 1.0), (7, 200, 19, 128, 1, None, 1.0),
+], ids=str)
+def test_attention_forms_by_grid_size(dtype, case):
+    test_attention_fwd_bwd(dtype, case)
