@@ -32,7 +32,7 @@ __global__ __launch_bounds__(WAVES * 64) void bdrln_fwd_kernel(
           float a[8], b[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
           load8(r + base + c * 8, a);
           if (bias) load8(bias + c * 8, b);
-          const uint32_t keep = dropout_keep8(dp, (uint64_t)(base >> 3) + (uint64_t)c);
+          const uint32_t keep = dp.thr ? dropout_keep8(dp, (uint64_t)(base >> 3) + (uint64_t)c) : 0xffu;   // (uniform)
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             const float t = (a[j] + b[j]) * dp.scale;
@@ -93,11 +93,13 @@ __device__ __forceinline__ void round_as(float (&v)[8]) {
 // Backward of out = LN(z), z = res + keep*(r+bias)*scale.  See slapo_bdrln_bwd for the contract.
 // dr_from_stored: the branch gradient dr is derived from dz as stored (rounded to T) rather than from the
 // fp32 value, i.e. dz_out and dr_out are those of two kernels in a row (dz first, then dr from the stored dz).
+// dr_out == dz_out: nothing is dropped, the two are one array; it is stored once and summed as dr.
 template <typename T, int NCH, bool LN, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void bdrln_bwd_kernel(
     int64_t rows, int H, const T* __restrict__ dout, const T* __restrict__ z, const float* __restrict__ mu,
     const float* __restrict__ rstd, const T* __restrict__ gamma, const T* __restrict__ dres_in,
-    T* __restrict__ dz_out, T* __restrict__ dr_out, float* __restrict__ partials, DropoutParams dp, int dr_from_stored) {
+    T* dz_out, T* dr_out, float* __restrict__ partials, DropoutParams dp, int dr_from_stored) {
+  const bool one_array = dr_out == dz_out;
   extern __shared__ float red[];  // [WAVES/2][3][H]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nchunk = H >> 3;
@@ -172,10 +174,10 @@ __global__ __launch_bounds__(WAVES * 64) void bdrln_bwd_kernel(
 #pragma unroll
           for (int j = 0; j < 8; ++j) dz[j] += res[i][j];
         }
-        if (dz_out) store8(dz_out + base + c * 8, dz);
+        if (dz_out && !one_array) store8(dz_out + base + c * 8, dz);
         if (dr_out) {
           if (dr_from_stored) round_as<T>(dz);
-          const uint32_t keep = dropout_keep8(dp, (uint64_t)(base >> 3) + (uint64_t)c);
+          const uint32_t keep = dp.thr ? dropout_keep8(dp, (uint64_t)(base >> 3) + (uint64_t)c) : 0xffu;   // (uniform)
           float dr[8];
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
@@ -247,8 +249,9 @@ template <typename T, bool LN, int R, int MAXT, bool ONE = false>
 __global__ __launch_bounds__(MAXT) void bdrln_bwd_wide_kernel(
     int64_t rows, int H, const T* __restrict__ dout, const T* __restrict__ z, const float* __restrict__ mu,
     const float* __restrict__ rstd, const T* __restrict__ gamma, const T* __restrict__ dres_in,
-    T* __restrict__ dz_out, T* __restrict__ dr_out, float* __restrict__ partials, DropoutParams dp, int dr_from_stored,
+    T* dz_out, T* dr_out, float* __restrict__ partials, DropoutParams dp, int dr_from_stored,
     int NW, int G) {
+  const bool one_array = dr_out == dz_out;
   extern __shared__ __attribute__((aligned(16))) float wsm[];   // per-row sums [2][G][R][NW][2]; at the end column sums [G-1][3][H]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int group = wave / NW, gw = wave - group * NW;
@@ -340,10 +343,10 @@ __global__ __launch_bounds__(MAXT) void bdrln_bwd_wide_kernel(
 #pragma unroll
           for (int e = 0; e < 8; ++e) dz[e] += res[e];
         }
-        if (dz_out) store8(dz_out + base + c * 8, dz);
+        if (dz_out && !one_array) store8(dz_out + base + c * 8, dz);
         if (dr_out) {
           if (dr_from_stored) round_as<T>(dz);
-          const uint32_t keep = dropout_keep8(dp, (uint64_t)(base >> 3) + (uint64_t)c);
+          const uint32_t keep = dp.thr ? dropout_keep8(dp, (uint64_t)(base >> 3) + (uint64_t)c) : 0xffu;   // (uniform)
           float dr[8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
