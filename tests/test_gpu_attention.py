@@ -109,3 +109,11 @@ def test_sample_without_visible_keys_yields_zeros_not_nans(dtype, causal):
 ], ids=str)
 def test_attention_forms_by_grid_size(dtype, case):
     test_attention_fwd_bwd(dtype, case)
+
+
+# fp32: sequences whose scores fit the LDS and the first that do not; one row more and less than whole 16-row blocks
+@pytest.mark.parametrize("case", [
+    (1, 1024, 1, 64, 1, [1000], 1.0), (1, 1024, 1, 128, 0, None, 1.0), (1, 1032, 1, 64, 0, [1031], 1.0), (2, 1, 1, 64, 0, None, 1.0),
+    (3, 15, 2, 128, 1, None, 4.0), (2, 17, 3, 64, 0, [17, 16], 1.0), (2, 40, 2, 64, 1, [40, 33], 1.0, 0.3), (1, 136, 2, 128, 0, [129], 1.0, 0.2)], ids=str)
+def test_attention_fp32_forms(case):
+    test_attention_fwd_bwd(W.FP32, case)
