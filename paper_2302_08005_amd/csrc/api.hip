@@ -347,6 +347,7 @@ struct ForwardLink {
   bool ln1_done = false;                       // the layer below has filled n1, mu1, rstd1 of `saved`
   const slapo_layer_params* above = nullptr;   // the layer above: its first LayerNorm rides on my last kernel
   void* above_saved = nullptr;                 // ... and lands in the n1, mu1, rstd1 regions of its `saved`
+  bool rope_done = false;                      // the rotary table stands in `scratch` already
 };
 
 // The forward launch sequence; `saved` receives the activations. Also the first half of a checkpointed
@@ -378,11 +379,10 @@ static void run_forward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     attn_in = n1;
   }
   if (llama) {
-    // no biases; queries and keys are rotated in place by their position before the attention reads them
+    // no biases; queries and keys are rotated by their position in the projection's epilogue
     float* table = (float*)(sc + W.rope);
-    launch_rope_table(d->seq, A / d->heads, d->rope_base, table, st);
-    launch_gemm(dt, GEMM_NT, EPI_NONE, d->act, T, 3 * A, H, attn_in, p->wqkv, qkv, nullptr, nullptr, nullptr, st, true);
-    launch_rope(dt, T, d->seq, A, A / d->heads, table, qkv, 0, st);
+    if (!(link && link->rope_done)) launch_rope_table(d->seq, A / d->heads, d->rope_base, table, st);
+    launch_gemm(dt, GEMM_NT, EPI_ROPE, rope_act(d->seq, A / d->heads), T, 3 * A, H, attn_in, p->wqkv, qkv, table, nullptr, nullptr, st, true);
   } else {
     launch_gemm(dt, GEMM_NT, EPI_BIAS, d->act, T, 3 * A, H, attn_in, p->wqkv, qkv, p->bqkv, nullptr, nullptr, st, true);
   }
@@ -452,6 +452,7 @@ static int check_backward_args(const slapo_layer_desc* d, const slapo_layer_para
 // and the lower layer starts at its first GEMM.
 struct BackwardLink {
   bool above = false, below = false;   // there is a layer above / below
+  bool rope_done = false;              // the rotary table stands in `scratch` already
   const void* dr2_in = nullptr;   // my dR2, already produced (with my b2 gradient) by the layer above
   void* dr2_below = nullptr;      // where the dR2 of the layer below goes ...
   DropoutParams dp_below;         // ... its mask stream (site 1 of that layer)
@@ -474,7 +475,9 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     // site, element), so the recomputed activations are bit for bit those of the original forward. The layer
     // output lands in a gradient buffer that backward overwrites later.
     char* acts = (char*)scratch + W.acts;
-    run_forward(d, p, x, seqlens, (char*)scratch + W.t1, acts, scratch, st, true);
+    ForwardLink again;
+    again.rope_done = link && link->rope_done;
+    run_forward(d, p, x, seqlens, (char*)scratch + W.t1, acts, scratch, st, true, &again);
     saved = acts;
   }
   const char* sv = (const char*)saved;
@@ -485,7 +488,7 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   const float *mu2 = (const float*)(sv + L.mu2), *rstd2 = (const float*)(sv + L.rstd2);
   void *t0 = sc + W.t0, *t1 = sc + W.t1, *t2 = sc + W.t2, *t3 = sc + W.t3, *du = sc + W.du, *dqkv = sc + W.dqkv;
   float *delta = (float*)(sc + W.delta), *prow = (float*)(sc + W.part_row), *pcol = (float*)(sc + W.part_col), *pcol2 = (float*)(sc + W.part_col2);
-  const AttnShape as = make_attn_shape(d);
+  AttnShape as = make_attn_shape(d);
   const DropoutParams dp0 = make_dropout(d, 0), dp1 = make_dropout(d, 1);
   const int nrow = bdrln_bwd_blocks(T), ncol = colsum_blocks(T);
   // Nothing dropped: a branch's gradient is the residual's, so no copy of it is made (the array in front of the feed-forward
@@ -519,6 +522,11 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
 
   const bool llama = is_llama(d);
   const int rms = llama ? 1 : 0;
+  if (llama) {
+    // the gradients of the rotated queries and keys are turned back (the rotation's transpose) as attention stores them
+    as.rope = (const float*)(sc + W.rope);
+    if (!d->checkpoint && !(link && link->rope_done)) launch_rope_table(d->seq, A / d->heads, d->rope_base, (float*)(sc + W.rope), st);   // else it stands there
+  }
   // the LLaMA-style layer has no bias or offset gradients: those outputs are simply not produced
   void *g_b2 = llama ? nullptr : gr->b2, *g_bo = llama ? nullptr : gr->bo;
   void *g_ln1_b = llama ? nullptr : gr->ln1_b, *g_ln2_b = llama ? nullptr : gr->ln2_b;
@@ -577,11 +585,6 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
       dweight(H, A, dr1, attn, gr->wo);
     }
     launch_attn_bwd(dt, as, qkv, seqlens, attn, t0, lse, delta, dqkv, st);
-    if (llama) {
-      float* table = (float*)(sc + W.rope);
-      if (!d->checkpoint) launch_rope_table(d->seq, A / d->heads, d->rope_base, table, st);
-      launch_rope(dt, T, d->seq, A, A / d->heads, table, dqkv, 1, st);
-    }
     if (side) side->order(side->join, ws, st);   // the gradient of the output projection has long been there
     data(EPI_ADD, T, H, 3 * A, dqkv, p->wqkv, d->pre_ln ? t0 : dx, d->pre_ln ? nullptr : t2);
     weight(3 * A, H, dqkv, d->pre_ln ? sv + L.n1 : x, gr->wqkv, llama ? nullptr : gr->bqkv);
@@ -641,12 +644,6 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   dweight(H, A, dr1, attn, gr->wo);
   launch_gemm(dt, GEMM_NN, EPI_NONE, d->act, T, A, H, dr1, p->wo, t0, nullptr, nullptr, nullptr, st, solo, gws, gwb);
   launch_attn_bwd(dt, as, qkv, seqlens, attn, t0, lse, delta, dqkv, st);
-  if (llama) {
-    // the attention gradients are w.r.t. the rotated queries and keys: turn them back (the rotation's transpose)
-    float* table = (float*)(sc + W.rope);
-    if (!d->checkpoint) launch_rope_table(d->seq, A / d->heads, d->rope_base, table, st);   // else the recomputed forward just wrote it
-    launch_rope(dt, T, d->seq, A, A / d->heads, table, dqkv, 1, st);
-  }
   fork(3);
   if (d->pre_ln) {
     dweight(3 * A, H, dqkv, sv + L.n1, gr->wqkv);
@@ -725,6 +722,7 @@ int slapo_stack_fwd(const slapo_layer_desc* desc, int32_t n_layers, const slapo_
       link.ln1_done = l > 0;
       if (l + 1 < n_layers) { link.above = params + l + 1; link.above_saved = saved_of(l + 1); }
     }
+    link.rope_done = l > 0;
     run_forward(&d, params + l, in, seqlens, out, saved_of(l), scratch, (hipStream_t)stream, false, &link);
   }
   return finish();
@@ -757,6 +755,7 @@ int slapo_stack_bwd(const slapo_layer_desc* desc, int32_t n_layers, const slapo_
     link.dr2_below = nullptr;
     link.above = l + 1 < n_layers;
     link.below = l > 0;
+    link.rope_done = link.above;
     if (d.pre_ln && !dropout_keeps_all(make_dropout(&d, 1))) {   // (nothing dropped: the gradient that flows down is the branch's too)
       // Layer l reads buffer l&1 (on both streams) and writes the other one; that one was last read by the
       // weight gradient of layer l+1, which the join at the end of that layer's backward has waited for.

@@ -87,6 +87,14 @@ __device__ __forceinline__ bf16x8_t pack8(const f32x16_t& v, int h) {
 // The value exists in ordinary registers at this point of the program: an ordering anchor for operations that
 // have no side effects of their own (nothing is emitted).
 __device__ __forceinline__ void pin_here(f32x16_t& v) { asm volatile("" : "+v"(v)); }
+// Backward of the rotary embedding on four consecutive columns (two pairs) of a head of width d: turned by the negative
+// angles of the row's position. (16-bit gradients are rounded first, like the array that a pass of its own would read.)
+__device__ __forceinline__ void rope_back(float (&v)[4], const float* __restrict__ table, int pos, int d, int col) {
+  const float4 w = *reinterpret_cast<const float4*>(table + (int64_t)pos * d + col);
+  const float a0 = v[0], b0 = v[1], a1 = v[2], b1 = v[3];
+  v[0] = a0 * w.x + b0 * w.y; v[1] = b0 * w.x - a0 * w.y;
+  v[2] = a1 * w.z + b1 * w.w; v[3] = b1 * w.z - a1 * w.w;
+}
 // row index inside a 32x32 accumulator tile of register r
 __device__ __forceinline__ int acc_row(int r, int lane) { return (r >> 2) * 8 + 4 * (lane >> 5) + (r & 3); }
 
@@ -305,6 +313,10 @@ __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const 
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[t][r] = 0.f;
   float m = -INFINITY, l = 0.f;   // running maximum (raw score units) and sum of this lane's half row
+  // G > 1: the groups tell each other the maxima of a step's tiles, so that every tile's probabilities are taken (and
+  // rounded) against the maximum of all keys up to it, as if one group walked the tiles in order. `seen`: of all steps so far.
+  float seen = -INFINITY;
+  float* maxima = reinterpret_cast<float*>(smem + FWD_STAGES<D> * G * 2 * TE) + row_wave * 32 + (lane & 31);   // [G][RB]
   const uint64_t row_blk = ((((uint64_t)b * sh.heads + a) * S + (uint64_t)q_ld) * (uint64_t)S) >> 3;   // DROP: block of key 0
 
   // K and V tiles of 64 keys: direct loads into two LDS stages, tile t+1 on its way while tile t is computed
@@ -326,35 +338,52 @@ __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const 
   };
   auto compute = [&](int stage, int step) {
     const int t = step * G + grp, kv0 = t * 64;
-    if ((G > 1 && t >= n_tiles) || (sh.causal && kv0 > wave_q_max)) return;   // every key of the tile lies in this wave's future
+    const bool mine = !((G > 1 && t >= n_tiles) || (sh.causal && kv0 > wave_q_max));   // else every key of the tile lies in this wave's future
+    if (G == 1 && !mine) return;
     const bf16_t* kt = smem + (stage * G + grp) * 2 * TE;
     const bf16_t* vt = kt + TE;
     f32x16_t sc[2];
+    float mx = -INFINITY;
+    if (mine) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < 2; ++i) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) sc[i][r] = 0.f;
+        for (int r = 0; r < 16; ++r) sc[i][r] = 0.f;
 #pragma unroll
-      for (int s = 0; s < NS; ++s)
-        sc[i] = mfma16<F16>(frag_rows<D>(kt, fr_base, i * 32, s), qf[s], sc[i]);
-    }
-    if ((kv0 + 64 > kv_len) || (sh.causal && kv0 + 63 > wave_q_min)) {   // tile crosses a mask boundary
+        for (int s = 0; s < NS; ++s)
+          sc[i] = mfma16<F16>(frag_rows<D>(kt, fr_base, i * 32, s), qf[s], sc[i]);
+      }
+      if ((kv0 + 64 > kv_len) || (sh.causal && kv0 + 63 > wave_q_min)) {   // tile crosses a mask boundary
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int kv = kv0 + i * 32 + acc_row(r, lane);
+            const bool hide = (kv >= kv_len) | ((sh.causal != 0) & (kv > my_q));
+            sc[i][r] = hide ? -INFINITY : sc[i][r];
+          }
+      }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int kv = kv0 + i * 32 + acc_row(r, lane);
-          const bool hide = (kv >= kv_len) | ((sh.causal != 0) & (kv > my_q));
-          sc[i][r] = hide ? -INFINITY : sc[i][r];
-        }
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[i][r]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
     }
-    float mx = -INFINITY;
+    float before = m;   // maximum of all keys in front of this tile
+    if constexpr (G > 1) {
+      if (kc == 0) maxima[grp * RB] = mx;
+      wait_loads_and_lds<63>();
+      block_barrier();
+      before = seen;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[i][r]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m, mx);
+      for (int g = 0; g < G; ++g) {
+        const float v = maxima[g * RB];
+        before = g < grp ? fmaxf(before, v) : before;
+        seen = fmaxf(seen, v);
+      }
+      if (!mine) return;
+    }
+    const float m_new = fmaxf(before, mx);
     if (__any(m_new > m)) {   // some row's maximum grew: rescale what has been accumulated
       const float alpha = __builtin_amdgcn_exp2f((m - m_new) * sl2);   // m = -inf gives 0; m = m_new gives 1
       const float al = (m_new == -INFINITY) ? 0.f : alpha;             // avoids inf - inf for rows still empty
@@ -894,8 +923,10 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(const BlockId blk, const Att
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         uint2 w;
-        w.x = pack2<F16>(dk[t][4 * g] * scale, dk[t][4 * g + 1] * scale);
-        w.y = pack2<F16>(dk[t][4 * g + 2] * scale, dk[t][4 * g + 3] * scale);
+        float v[4] = {dk[t][4 * g] * scale, dk[t][4 * g + 1] * scale, dk[t][4 * g + 2] * scale, dk[t][4 * g + 3] * scale};
+        if (sh.rope) { round_pairs<F16>(v); rope_back(v, sh.rope, my_kv, D, t * 32 + g * 8 + 4 * kc); }   // (uniform)
+        w.x = pack2<F16>(v[0], v[1]);
+        w.y = pack2<F16>(v[2], v[3]);
         *reinterpret_cast<uint2*>(krow + t * 32 + g * 8 + 4 * kc) = w;
         w.x = pack2<F16>(dv[t][4 * g], dv[t][4 * g + 1]);
         w.y = pack2<F16>(dv[t][4 * g + 2], dv[t][4 * g + 3]);
@@ -1049,8 +1080,10 @@ __device__ __forceinline__ void attn_bwd_dq_block(const BlockId blk, const AttnS
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         uint2 w;
-        w.x = pack2<F16>(dq[t][4 * g] * scale, dq[t][4 * g + 1] * scale);
-        w.y = pack2<F16>(dq[t][4 * g + 2] * scale, dq[t][4 * g + 3] * scale);
+        float v[4] = {dq[t][4 * g] * scale, dq[t][4 * g + 1] * scale, dq[t][4 * g + 2] * scale, dq[t][4 * g + 3] * scale};
+        if (sh.rope) { round_pairs<F16>(v); rope_back(v, sh.rope, my_q, D, t * 32 + g * 8 + 4 * kc); }   // (uniform)
+        w.x = pack2<F16>(v[0], v[1]);
+        w.y = pack2<F16>(v[2], v[3]);
         *reinterpret_cast<uint2*>(qrow + t * 32 + g * 8 + 4 * kc) = w;
       }
   }
@@ -1278,7 +1311,9 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(AttnShape sh, int blo
       const f32x4_t dv = weighted_rows(p_rows, dobase + ct * 16, H, first, end, S, lane);
       if (row < S) {
         float* o = dbase + row * rs + H + ct * 16 + 4 * g;
-        *reinterpret_cast<float4*>(o) = make_float4(dk[0] * scale, dk[1] * scale, dk[2] * scale, dk[3] * scale);
+        float v[4] = {dk[0] * scale, dk[1] * scale, dk[2] * scale, dk[3] * scale};
+        if (sh.rope) rope_back(v, sh.rope, row, D, ct * 16 + 4 * g);
+        *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
         *reinterpret_cast<float4*>(o + H) = make_float4(dv[0], dv[1], dv[2], dv[3]);
       }
     }
@@ -1311,7 +1346,11 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(AttnShape sh, int blo
     __syncthreads();
     for (int ct = wave; ct < D / 16; ct += 4) {
       const f32x4_t dq = weighted_rows(ds_rows, base + H + ct * 16, rs, 0, tiles, kv_end, lane);
-      if (row < S) *reinterpret_cast<float4*>(dbase + row * rs + ct * 16 + 4 * g) = make_float4(dq[0] * scale, dq[1] * scale, dq[2] * scale, dq[3] * scale);
+      if (row < S) {
+        float v[4] = {dq[0] * scale, dq[1] * scale, dq[2] * scale, dq[3] * scale};
+        if (sh.rope) rope_back(v, sh.rope, row, D, ct * 16 + 4 * g);
+        *reinterpret_cast<float4*>(dbase + row * rs + ct * 16 + 4 * g) = make_float4(v[0], v[1], v[2], v[3]);
+      }
     }
   }
 }
@@ -1343,6 +1382,11 @@ __device__ __forceinline__ float rows_sum(const float* w, const float* __restric
   }
   for (; j < end; ++j) acc = fmaf(w[j], x[j * stride], acc);
   return acc;
+}
+// rope_back for a lane that holds one column, the other one of its pair in the neighbouring lane
+__device__ __forceinline__ float rope_back1(float v, const float* __restrict__ table, int pos, int d, int col) {
+  const float other = __shfl_xor(v, 1, 64), cs = table[(int64_t)pos * d + (col & ~1)], sn = table[(int64_t)pos * d + (col | 1)];
+  return col & 1 ? v * cs - other * sn : v * cs + other * sn;
 }
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_fwd_simple_kernel(AttnShape sh, const T* __restrict__ qkv,
@@ -1421,8 +1465,9 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_simple_kernel(AttnShape sh, c
   }
   __builtin_amdgcn_wave_barrier();
   for (int dd = lane; dd < D; dd += 64) {
-    const float acc = rows_sum(ds, base + H + dd, rs, 0, kv_end, 0.f);
-    from_f32(dqkv[((int64_t)b * S + i) * rs + a * D + dd], acc * scale);
+    float v = rows_sum(ds, base + H + dd, rs, 0, kv_end, 0.f) * scale;
+    if (sh.rope) v = rope_back1(v, sh.rope, i, D, dd);
+    from_f32(dqkv[((int64_t)b * S + i) * rs + a * D + dd], v);
   }
 }
 
@@ -1463,9 +1508,10 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_simple_kernel(AttnShape sh,
   }
   __builtin_amdgcn_wave_barrier();
   for (int dd = lane; dd < D; dd += 64) {
-    const float dk = rows_sum(ds, base + dd, rs, i_first, S, 0.f);
+    float dk = rows_sum(ds, base + dd, rs, i_first, S, 0.f) * scale;
+    if (sh.rope) dk = rope_back1(dk, sh.rope, j, D, dd);
     const float dv = rows_sum(ps, dout + (int64_t)b * S * H + a * D + dd, H, i_first, S, 0.f);
-    from_f32(dqkv[((int64_t)b * S + j) * rs + H + a * D + dd], dk * scale);
+    from_f32(dqkv[((int64_t)b * S + j) * rs + H + a * D + dd], dk);
     from_f32(dqkv[((int64_t)b * S + j) * rs + 2 * H + a * D + dd], dv);
   }
 }
@@ -1477,7 +1523,7 @@ static int64_t attn_blocks(const AttnShape& s) { return (int64_t)((s.seq + 127) 
 
 template <int D, bool F16, int G>
 static void fwd_bf16_groups(const AttnShape& s, const void* qkv, const int32_t* seqlens, void* out, float* lse, hipStream_t st) {
-  constexpr size_t tiles = (size_t)FWD_STAGES<D> * G * 2 * Tile<D>::ELEMS * sizeof(bf16_t);
+  constexpr size_t tiles = (size_t)FWD_STAGES<D> * G * 2 * Tile<D>::ELEMS * sizeof(bf16_t) + (G > 1 ? 128 * sizeof(float) : 0);
   constexpr size_t meet = (size_t)(G - 1) * (4 / G) * (D / 2 + 2) * 64 * sizeof(float), lds = tiles > meet ? tiles : meet;
   auto kern = s.drop.thr ? attn_fwd_bf16_kernel<D, true, F16, G> : attn_fwd_bf16_kernel<D, false, F16, G>;
   (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1488,9 +1534,11 @@ static void fwd_bf16_groups(const AttnShape& s, const void* qkv, const int32_t* 
 template <int D, bool F16>
 static void fwd_bf16(const AttnShape& s, const void* qkv, const int32_t* seqlens, void* out, float* lse, hipStream_t st) {
   // Two groups per block while the doubled blocks still run in one round (causal blocks are half as long) and there is more
-  // than one tile to share. Blocks of 128 rows, one / two groups, us: 64-wide 16 (one sample of 128) 5.8 / 5.1, 128 (1024
-  // tokens, causal) 20.0 / 13.0, 256 (4 x 512) 12.1 / 10.3, 320 15.3 / 16.2; 128-wide 64 (2 x 1024, causal) 27.1 / 18.9, 128
-  // (8192, causal) 165 / 113, 256 (4 x 1024, causal) 27.9 / 25.4, 320 42.9 / 43.9.
+  // than one tile to share. Blocks of 128 rows, one / two groups, us: 64-wide 16 (one sample of 128) 5.8 / 5.2, 128 (1024
+  // tokens, causal) 20.0 / 14.1, 256 (4 x 512) 12.1 / 11.3, 320 15.3 / 16.2; 128-wide 64 (2 x 1024, causal) 27.1 / 18.9, 128
+  // (8192, causal) 165 / 112, 256 (4 x 1024, causal) 27.9 / 25.4, 320 42.9 / 43.9. (Telling each other the maxima costs up to
+  // 1 us of these; without it the probabilities are rounded against other maxima and the output differs by 1-2e-3 in bf16
+  // from that of one group, with it by 2-4e-5, like any other order of sums.)
   const int64_t room = s.causal ? ONE_ROUND<D> : ONE_ROUND<D> / 2;
   if (attn_blocks(s) <= (room < 256 ? room : 256) && s.seq > 64) fwd_bf16_groups<D, F16, 2>(s, qkv, seqlens, out, lse, st);
   else fwd_bf16_groups<D, F16, 1>(s, qkv, seqlens, out, lse, st);

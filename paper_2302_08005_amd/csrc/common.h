@@ -114,6 +114,17 @@ __device__ __forceinline__ void store8(float* p, const float (&v)[8]) {
   *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
   *reinterpret_cast<float4*>(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
 }
+// Replaces fp32 values by what they read back as after a store in the 16-bit format: a kernel that goes on from them
+// computes, bit for bit, what a kernel of its own that reads the stored array would.
+template <bool F16, int N>
+__device__ __forceinline__ void round_pairs(float (&v)[N]) {
+#pragma unroll
+  for (int e = 0; e < N; e += 2) {
+    const uint32_t w = pack2<F16>(v[e], v[e + 1]);
+    v[e] = unpack_lo<F16>(w);
+    v[e + 1] = unpack_hi<F16>(w);
+  }
+}
 // Eight elements kept in their storage form (so that a prefetched row costs few registers) until used.
 template <typename T> struct Raw8;
 template <> struct Raw8<bf16_t> {

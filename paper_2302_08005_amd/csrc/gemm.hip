@@ -48,7 +48,7 @@ static bool f32_wide(int M, int N) { return (int64_t)((M + 31) / 32) * ((N + 31)
 
 // epilogue / layout pairs the layer itself uses; the others exist as 128x128 tiles only
 constexpr bool epi_used(int layout, int epi) {
-  return layout == GEMM_NT ? (epi == EPI_NONE || epi == EPI_BIAS || epi == EPI_BIAS_ACT || epi == EPI_GATE)
+  return layout == GEMM_NT ? (epi == EPI_NONE || epi == EPI_BIAS || epi == EPI_BIAS_ACT || epi == EPI_GATE || epi == EPI_ROPE)
        : layout == GEMM_NN ? (epi == EPI_NONE || epi == EPI_DACT || epi == EPI_ADD || epi == EPI_DGATE)
                            : (epi == EPI_NONE || epi == EPI_ADD);
 }
@@ -60,7 +60,7 @@ static void launch_bf16_tile(int epi, int act, int M, int N, int K, const void* 
   const size_t lds = gemm_lds_bytes<BM, BN, BK, WGM, WGN, KS, NS>();
 #define SLAPO_GEMM(E)                                                                                       \
   do {                                                                                                      \
-    if constexpr (ALL_EPI || epi_used(LAYOUT, E)) {                                                         \
+    if constexpr ((ALL_EPI && E != EPI_ROPE) || epi_used(LAYOUT, E)) {                                                         \
       auto kern = LAYOUT == GEMM_TN || K % BK == 0 ? gemm_bf16_kernel<LAYOUT, BM, BN, BK, WGM, WGN, KS, NS, PW, false, E, F16> \
                                                    : gemm_bf16_kernel<LAYOUT, BM, BN, BK, WGM, WGN, KS, NS, PW, LAYOUT != GEMM_TN, E, F16>; \
       (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);  \
@@ -76,6 +76,7 @@ static void launch_bf16_tile(int epi, int act, int M, int N, int K, const void* 
     case EPI_DACT: SLAPO_GEMM(EPI_DACT); break;
     case EPI_GATE: SLAPO_GEMM(EPI_GATE); break;
     case EPI_DGATE: SLAPO_GEMM(EPI_DGATE); break;
+    case EPI_ROPE: SLAPO_GEMM(EPI_ROPE); break;
     default: SLAPO_GEMM(EPI_ADD); break;
   }
 #undef SLAPO_GEMM

@@ -62,6 +62,21 @@ __device__ __forceinline__ void epilogue_store(int epi, int act, float acc, int6
   from_f32(C[idx], v);
 }
 
+// Turns PAIRS adjacent pairs of row m, from column n of the packed queries and keys on, by the angles of the row's position
+// (act = rope_act: sequence length and head width 64 or 128).
+template <int PAIRS, int N>
+__device__ __forceinline__ void rope_turn(float (&v)[N], const float* __restrict__ table, int act, int m, int n) {
+  const int seq = act >> 1, half = act & 1 ? 64 : 32;
+  const float* t = table + ((int64_t)(m % seq) * half + ((n & (2 * half - 1)) >> 1)) * 2;
+#pragma unroll
+  for (int e = 0; e < PAIRS; e += 2) {
+    const float4 w = *reinterpret_cast<const float4*>(t + 2 * e);   // cos, sin of two pairs
+    const float a0 = v[2 * e], b0 = v[2 * e + 1], a1 = v[2 * e + 2], b1 = v[2 * e + 3];
+    v[2 * e] = a0 * w.x - b0 * w.y; v[2 * e + 1] = a0 * w.y + b0 * w.x;
+    v[2 * e + 2] = a1 * w.z - b1 * w.w; v[2 * e + 3] = a1 * w.w + b1 * w.z;
+  }
+}
+
 // silu(u) = u * sigmoid(u) and the two factors the gated feed-forward block keeps for backward
 struct GateTerms { float out, dgate, dup; };   // silu(u) * w, w * silu'(u), silu(u)
 template <bool FAST>
@@ -595,6 +610,11 @@ __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, c
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] += u[e];
           }
+        } else if constexpr (EPI == EPI_ROPE) {
+          if (n < 2 * (N / 3)) {
+            round_pairs<F16>(v);   // what a kernel that turns the stored product would read
+            rope_turn<4>(v, reinterpret_cast<const float*>(bias), act, m, n);
+          }
         } else if (EPI == EPI_GATE) {
           // columns come as (gate, up) pairs: four gated values go to C [M,N/2], the backward factors stay [M,N]
           float f[8], o[4];
@@ -756,6 +776,10 @@ __device__ __forceinline__ void gemm_f32_tile(int block, float* lds, int M, int 
       aux_out[(int64_t)m * N + n + j] = t.dgate;
       aux_out[(int64_t)m * N + n + j + 1] = t.dup;
     }
+  } else if (epi == EPI_ROPE) {
+    if (n < 2 * (N / 3)) rope_turn<2>(v, bias, act, m, n);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) C[(int64_t)m * N + n + j] = v[j];
   } else if (epi == EPI_DGATE) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {

@@ -15,7 +15,10 @@ enum { GEMM_NT = 0, GEMM_NN = 1, GEMM_TN = 2 };
 // EPI_DGATE: the product is that gradient [M,N]; C [M,2N] = (acc * aux_in[m,2n], acc * aux_in[m,2n+1]).
 // EPI_SPLITK (internal to the weight-gradient path): the workgroup covers one of `act` K ranges of its tile and
 //   writes the fp32 accumulators to aux_out (a float workspace [splits][M][N]); splitk_reduce sums them.
-enum { EPI_NONE = 0, EPI_BIAS = 1, EPI_BIAS_ACT = 2, EPI_DACT = 3, EPI_ADD = 4, EPI_GATE = 5, EPI_DGATE = 6, EPI_SPLITK = 7 };
+// EPI_ROPE (internal to the gated layer's QKV projection): the first two thirds of the columns are heads whose adjacent
+//   pairs are turned by the angles of the row's position; bias = the (cos, sin) table (launch_rope_table), act = rope_act(...).
+enum { EPI_NONE = 0, EPI_BIAS = 1, EPI_BIAS_ACT = 2, EPI_DACT = 3, EPI_ADD = 4, EPI_GATE = 5, EPI_DGATE = 6, EPI_SPLITK = 7, EPI_ROPE = 8 };
+inline int rope_act(int seq, int head_dim) { return 2 * seq + (head_dim == 128 ? 1 : 0); }
 
 // solo: nothing else runs beside this GEMM (it may then pick tiles by round count, see launch_bf16)
 // ws / ws_bytes: optional fp32 workspace (gemm_ws_bytes says how much a shape can use; 0: none). With it, a grid
@@ -65,6 +68,8 @@ struct AttnShape {
   int lpt_heads = 0;   // causal block order: heads per longest-first group (set by the launchers; 0 = head by head)
   // dropout on the attention probabilities (site 2; element ((b*heads + a)*seq + i)*seq + j); thr == 0: none
   DropoutParams drop = {0u, 0u, 2u, 0u, 0u, 1.0f};
+  // backward: (cos, sin) table of the rotation that queries and keys went through (NULL: none); dQ and dK are turned back
+  const float* rope = nullptr;
 };
 void launch_attn_fwd(int dtype, const AttnShape& s, const void* qkv, const int32_t* seqlens, void* out,
                      float* lse, hipStream_t st);
