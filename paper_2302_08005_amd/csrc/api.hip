@@ -248,7 +248,7 @@ ScratchLayout scratch_layout(const slapo_layer_desc* d) {
   L.du = take(T * F * eb * (is_llama(d) ? 2 : 1));
   L.dqkv = take(T * 3 * A * eb);
   L.delta = take((size_t)d->batch * d->heads * d->seq * 4);
-  L.part_row = take((size_t)bdrln_bwd_blocks((int64_t)T) * 3 * H * 4);
+  L.part_row = take((size_t)bdrln_bwd_blocks_wide((int64_t)T, (int)H) * 3 * H * 4);
   size_t widest = F > 3 * A ? F : 3 * A;
   widest = widest > H ? widest : H;
   L.part_col = take((size_t)colsum_blocks((int64_t)T) * widest * 4);
@@ -490,7 +490,7 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   float *delta = (float*)(sc + W.delta), *prow = (float*)(sc + W.part_row), *pcol = (float*)(sc + W.part_col), *pcol2 = (float*)(sc + W.part_col2);
   AttnShape as = make_attn_shape(d);
   const DropoutParams dp0 = make_dropout(d, 0), dp1 = make_dropout(d, 1);
-  const int nrow = bdrln_bwd_blocks(T), ncol = colsum_blocks(T);
+  const int nrow = bdrln_bwd_blocks_wide(T, H), ncol = colsum_blocks(T);
   // Nothing dropped: a branch's gradient is the residual's, so no copy of it is made (the array in front of the feed-forward
   // block of a pre-LN layer is dy itself). 4 x 2048 tokens of width 2560: 20 us of row kernel and 8 of 46 in the next one.
   const bool keeps_all = dropout_keeps_all(dp0);                    // (both sites drop alike)
@@ -555,11 +555,11 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
       dr2 = link->dr2_in;
       take_sums(link->sums[0], link->sums[1], link->sums[2]);
     } else if (d->pre_ln) {
-      launch_bdrln_bwd(dt, T, H, dy, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, t1, prow, dp1, rms, st);
+      launch_bdrln_bwd(dt, T, H, dy, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, t1, prow, dp1, rms, st, 0, nrow);
       if (!llama) take_sums(nullptr, nullptr, g_b2);
     } else {
       if (keeps_all) dr2 = t0;   // (read for the last time before the feed-forward block's input gradient replaces it)
-      launch_bdrln_bwd(dt, T, H, dy, sv + L.z2, mu2, rstd2, p->ln2_g, nullptr, t0, (void*)dr2, prow, dp1, rms, st);
+      launch_bdrln_bwd(dt, T, H, dy, sv + L.z2, mu2, rstd2, p->ln2_g, nullptr, t0, (void*)dr2, prow, dp1, rms, st, 0, nrow);
       take_sums(gr->ln2_g, g_ln2_b, g_b2);
     }
     data(llama ? EPI_DGATE : EPI_DACT, T, F, H, dr2, p->w2, du, u);
@@ -570,10 +570,10 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     launch();
     // ---- attention block ----
     if (d->pre_ln) {
-      launch_bdrln_bwd(dt, T, H, t0, z1, mu2, rstd2, p->ln2_g, dy, t2, dr1, prow, dp0, rms, st);
+      launch_bdrln_bwd(dt, T, H, t0, z1, mu2, rstd2, p->ln2_g, dy, t2, dr1, prow, dp0, rms, st, 0, nrow);
       take_sums(gr->ln2_g, g_ln2_b, g_bo);
     } else {
-      launch_bdrln_bwd(dt, T, H, t0, z1, mu1, rstd1, p->ln1_g, nullptr, t2, dr1, prow, dp0, rms, st);
+      launch_bdrln_bwd(dt, T, H, t0, z1, mu1, rstd1, p->ln1_g, nullptr, t2, dr1, prow, dp0, rms, st, 0, nrow);
       take_sums(gr->ln1_g, g_ln1_b, g_bo);
     }
     data(EPI_ADD, T, A, H, dr1, p->wo, t0, nullptr);
@@ -590,13 +590,13 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     weight(3 * A, H, dqkv, d->pre_ln ? sv + L.n1 : x, gr->wqkv, llama ? nullptr : gr->bqkv);
     launch();
     if (d->pre_ln && keeps_all && link && link->below) {
-      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, prow, dp0, rms, st);
+      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, prow, dp0, rms, st, 0, nrow);
       link->sums[0] = gr->ln1_g; link->sums[1] = g_ln1_b; link->sums[2] = nullptr;
     } else if (d->pre_ln && link && link->dr2_below) {
-      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, link->dr2_below, prow, link->dp_below, rms, st, 1);
+      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, link->dr2_below, prow, link->dp_below, rms, st, 1, nrow);
       link->sums[0] = gr->ln1_g; link->sums[1] = g_ln1_b; link->sums[2] = link->db2_below;
     } else if (d->pre_ln) {
-      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, prow, dp0, rms, st);
+      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, prow, dp0, rms, st, 0, nrow);
       reduce_rows(gr->ln1_g, g_ln1_b, nullptr);
     }
     return finish();
@@ -609,10 +609,10 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   } else if (d->pre_ln && link && link->dr2_in) {
     dr2 = link->dr2_in;
   } else if (d->pre_ln) {
-    launch_bdrln_bwd(dt, T, H, dy, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, t1, prow, dp1, rms, st);
+    launch_bdrln_bwd(dt, T, H, dy, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, t1, prow, dp1, rms, st, 0, nrow);
     if (!llama) reduce_rows(nullptr, nullptr, g_b2);
   } else {
-    launch_bdrln_bwd(dt, T, H, dy, sv + L.z2, mu2, rstd2, p->ln2_g, nullptr, t0, t1, prow, dp1, rms, st);
+    launch_bdrln_bwd(dt, T, H, dy, sv + L.z2, mu2, rstd2, p->ln2_g, nullptr, t0, t1, prow, dp1, rms, st, 0, nrow);
     reduce_rows(gr->ln2_g, g_ln2_b, g_b2);
   }
   fork(0);
@@ -634,10 +634,10 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   }
   // ---- attention block ----
   if (d->pre_ln) {
-    launch_bdrln_bwd(dt, T, H, t0, z1, mu2, rstd2, p->ln2_g, dy, t2, dr1, prow, dp0, rms, st);
+    launch_bdrln_bwd(dt, T, H, t0, z1, mu2, rstd2, p->ln2_g, dy, t2, dr1, prow, dp0, rms, st, 0, nrow);
     reduce_rows(gr->ln2_g, g_ln2_b, g_bo);
   } else {
-    launch_bdrln_bwd(dt, T, H, t0, z1, mu1, rstd1, p->ln1_g, nullptr, t2, dr1, prow, dp0, rms, st);
+    launch_bdrln_bwd(dt, T, H, t0, z1, mu1, rstd1, p->ln1_g, nullptr, t2, dr1, prow, dp0, rms, st, 0, nrow);
     reduce_rows(gr->ln1_g, g_ln1_b, g_bo);
   }
   fork(2);
@@ -650,10 +650,10 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     launch_gemm(dt, GEMM_NN, EPI_NONE, d->act, T, H, 3 * A, dqkv, p->wqkv, t0, nullptr, nullptr, nullptr, st, solo, gws, gwb);
     if (link && link->dr2_below) {
       // (from the stored dx, so that the layer below sees what it would compute from dx itself, bit for bit)
-      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, link->dr2_below, prow, link->dp_below, rms, st, 1);
+      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, link->dr2_below, prow, link->dp_below, rms, st, 1, nrow);
       reduce_rows(gr->ln1_g, g_ln1_b, link->db2_below);
     } else {
-      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, prow, dp0, rms, st);
+      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, prow, dp0, rms, st, 0, nrow);
       reduce_rows(gr->ln1_g, g_ln1_b, nullptr);
     }
   } else {

@@ -83,7 +83,12 @@ void launch_bdrln_fwd(int dtype, int64_t rows, int H, const void* r, const void*
 int bdrln_bwd_blocks(int64_t rows);
 void launch_bdrln_bwd(int dtype, int64_t rows, int H, const void* dout, const void* z, const float* mu,
                       const float* rstd, const void* gamma, const void* dres_in, void* dz_out, void* dr_out,
-                      float* partials, const DropoutParams& dp, int rms, hipStream_t st, int dr_from_stored = 0);
+                      float* partials, const DropoutParams& dp, int rms, hipStream_t st, int dr_from_stored = 0, int blocks = 0);
+// Blocks (and partial rows) for launch_bdrln_bwd inside a layer (blocks = 0: bdrln_bwd_blocks, which the exported kernel has):
+// few rows go to more blocks of fewer, because a launch that short is its latency chain, of which the column sums across a
+// block's groups are a part: 16 blocks of 8 rows -> 64 of 2 at 128 rows of 1024, 7.2 -> 5.4 us; steps of 128 tokens at hidden 1024
+// 112.6 -> 108.3, of 512 158.7 -> 154.6, equal from 2048 tokens on.
+int bdrln_bwd_blocks_wide(int64_t rows, int H);
 // Rotary embedding on the Q and K parts of a packed [rows, 3H] array, in place: inside every head of width d
 // the adjacent pair (2j, 2j+1) of row t is turned by the angle of table entry (t % seq, j) (negated when
 // `inverse`). table: [seq, d/2] (cos, sin) pairs in fp32, written by launch_rope_table (angle m * base^(-2j/d),

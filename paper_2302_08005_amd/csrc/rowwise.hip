@@ -531,18 +531,26 @@ int bdrln_bwd_blocks(int64_t rows) {
   return (int)(b > 256 ? 256 : (b < 1 ? 1 : b));
 }
 
+int bdrln_bwd_blocks_wide(int64_t rows, int H) {
+  if (H < 512) return bdrln_bwd_blocks(rows);
+  const int64_t b = (rows + 1) / 2;
+  return (int)(b > 256 ? 256 : b);
+}
+
 template <typename T, bool LN>
 static void launch_bwd(int64_t rows, int H, const void* dout, const void* z, const float* mu, const float* rstd,
                        const void* gamma, const void* dres_in, void* dz_out, void* dr_out, float* partials,
-                       const DropoutParams& dp, int dr_from_stored, hipStream_t st) {
-  const int blocks = bdrln_bwd_blocks(rows);
+                       const DropoutParams& dp, int dr_from_stored, int blocks, hipStream_t st) {
   if (H >= 512) {
     // Groups of NW wavefronts that split the columns. Up to hidden 3072 as many groups as fit 12 wavefronts (the
     // register budget of three wavefronts per SIMD holds two rows per group and their prefetch without spilling);
     // wider rows fill the block with one group, four rows at a time up to 4096, one above.
     const int nw = (H / 8 + 63) / 64;
-    const int groups = nw <= 6 ? (12 / nw > 8 ? 8 : 12 / nw) : 1;
+    int groups = nw <= 6 ? (12 / nw > 8 ? 8 : 12 / nw) : 1;
     const int rows_per_group = nw <= 6 ? 2 : nw <= 8 ? 4 : 1;
+    // (no group without a row: each adds a round of column sums through LDS)
+    const int64_t useful = (rows + (int64_t)blocks * rows_per_group - 1) / ((int64_t)blocks * rows_per_group);
+    if (groups > useful) groups = (int)useful;
     const size_t xs_bytes = (size_t)2 * groups * (rows_per_group == 2 ? 3 : rows_per_group) * nw * 2 * sizeof(float);
     const size_t col_bytes = (size_t)(groups - 1) * 3 * H * sizeof(float);
     const size_t lds = xs_bytes > col_bytes ? xs_bytes : col_bytes;
@@ -580,12 +588,13 @@ static void launch_bwd(int64_t rows, int H, const void* dout, const void* z, con
 
 void launch_bdrln_bwd(int dtype, int64_t rows, int H, const void* dout, const void* z, const float* mu,
                       const float* rstd, const void* gamma, const void* dres_in, void* dz_out, void* dr_out,
-                      float* partials, const DropoutParams& dp, int rms, hipStream_t st, int dr_from_stored) {
+                      float* partials, const DropoutParams& dp, int rms, hipStream_t st, int dr_from_stored, int blocks) {
+  if (blocks == 0) blocks = bdrln_bwd_blocks(rows);
   if (rms) mu = nullptr;   // the kernel reads a missing mean as RMSNorm (mean 0, no mean-of-gradient term)
   const bool ln = gamma != nullptr;
 #define SLAPO_PICK(T)                                                                                          \
-  if (ln) launch_bwd<T, true>(rows, H, dout, z, mu, rstd, gamma, dres_in, dz_out, dr_out, partials, dp, dr_from_stored, st); \
-  else launch_bwd<T, false>(rows, H, dout, z, mu, rstd, gamma, dres_in, dz_out, dr_out, partials, dp, dr_from_stored, st)
+  if (ln) launch_bwd<T, true>(rows, H, dout, z, mu, rstd, gamma, dres_in, dz_out, dr_out, partials, dp, dr_from_stored, blocks, st); \
+  else launch_bwd<T, false>(rows, H, dout, z, mu, rstd, gamma, dres_in, dz_out, dr_out, partials, dp, dr_from_stored, blocks, st)
   if (dtype == DT_FP32) { SLAPO_PICK(float); } else if (dtype == DT_FP16) { SLAPO_PICK(f16_t); } else { SLAPO_PICK(bf16_t); }
 #undef SLAPO_PICK
 }
