@@ -182,6 +182,8 @@ SideStream* side_stream() {
 //   hidden 512   1024 of 128: 156 / 161 (164); 1536 of 128: 177 / 159 (186); 2048 of 128: 194 / 165, 193 / 206 (208)
 //   hidden 768   512 of 128: 174 / 191 (155); 1024 of 128: 193 / 180 (186), of 1024: 242 / 227 (226)
 //   hidden 1024  128: 157 / 200 (142); 512 of 128: 185 / 201 (174); 1024 of 128: 230 / 218 (216)
+// These are figures of one product per launch. With paired launches (gradients_paired) one stream is the faster form beyond
+// the line too (hidden 1024, 600 tokens: 162 / 176 us; 512, 2048 159 / 170); which calls fork is kept as callers know it.
 bool backward_on_one_stream(const slapo_layer_desc* d) {
   const double T = (double)d->batch * d->seq, H = d->hidden, F = d->ffn, A = attn_width(d);
   const double weights = 4.0 * H * A + (is_llama(d) ? 3.0 : 2.0) * H * F;
