@@ -90,7 +90,7 @@ __device__ __forceinline__ void pin_here(f32x16_t& v) { asm volatile("" : "+v"(v
 // Backward of the rotary embedding on four consecutive columns (two pairs) of a head of width d: turned by the negative
 // angles of the row's position. (16-bit gradients are rounded first, like the array that a pass of its own would read.)
 // The table loads at the end of a block cost what the pass saves where a block has few steps (98 x 66 tokens, 3 heads of 128:
-// dQ and dK/dV 38 -> 44 us, the pass 5 us), and a fraction of it elsewhere (4 x 1024 tokens, 32 heads of 128: 53 us saved).
+// dQ and dK/dV 38 -> 44 us, the pass 5 us), and a fraction of it elsewhere (4 x 1024 tokens, 32 heads of 128: 53 us saved with the forward pass).
 __device__ __forceinline__ void rope_back(float (&v)[4], const float* __restrict__ table, int pos, int d, int col) {
   const float4 w = *reinterpret_cast<const float4*>(table + (int64_t)pos * d + col);
   const float a0 = v[0], b0 = v[1], a1 = v[2], b1 = v[3];
