@@ -93,9 +93,8 @@ __device__ __forceinline__ void pin_here(f32x16_t& v) { asm volatile("" : "+v"(v
 // dQ and dK/dV 38 -> 44 us, the pass 5 us), and a fraction of it elsewhere (4 x 1024 tokens, 32 heads of 128: 53 us saved with the forward pass).
 __device__ __forceinline__ void rope_back(float (&v)[4], const float* __restrict__ table, int pos, int d, int col) {
   const float4 w = *reinterpret_cast<const float4*>(table + (int64_t)pos * d + col);
-  const float a0 = v[0], b0 = v[1], a1 = v[2], b1 = v[3];
-  v[0] = a0 * w.x + b0 * w.y; v[1] = b0 * w.x - a0 * w.y;
-  v[2] = a1 * w.z + b1 * w.w; v[3] = b1 * w.z - a1 * w.w;
+  turn_pair(v[0], v[1], w.x, -w.y);
+  turn_pair(v[2], v[3], w.z, -w.w);
 }
 // row index inside a 32x32 accumulator tile of register r
 __device__ __forceinline__ int acc_row(int r, int lane) { return (r >> 2) * 8 + 4 * (lane >> 5) + (r & 3); }
@@ -1388,7 +1387,9 @@ __device__ __forceinline__ float rows_sum(const float* w, const float* __restric
 // rope_back for a lane that holds one column, the other one of its pair in the neighbouring lane
 __device__ __forceinline__ float rope_back1(float v, const float* __restrict__ table, int pos, int d, int col) {
   const float other = __shfl_xor(v, 1, 64), cs = table[(int64_t)pos * d + (col & ~1)], sn = table[(int64_t)pos * d + (col | 1)];
-  return col & 1 ? v * cs - other * sn : v * cs + other * sn;
+  float a = col & 1 ? other : v, b = col & 1 ? v : other;
+  turn_pair(a, b, cs, -sn);
+  return col & 1 ? b : a;
 }
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_fwd_simple_kernel(AttnShape sh, const T* __restrict__ qkv,

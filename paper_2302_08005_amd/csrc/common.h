@@ -125,6 +125,14 @@ __device__ __forceinline__ void round_pairs(float (&v)[N]) {
     v[e + 1] = unpack_hi<F16>(w);
   }
 }
+// Rotary turn of an adjacent pair; the other way round with -sn. Which of the two products of a sum is the rounded one is
+// spelled out, so that every kernel that turns pairs gives the same bits (left to the compiler it differs by kernel, and one
+// flipped rounding of a query or key moves whole rows behind it: 0.4 % in the outputs of a LLaMA-7B-shaped layer).
+__device__ __forceinline__ void turn_pair(float& a, float& b, float cs, float sn) {
+  const float x = fmaf(a, cs, -(b * sn));
+  b = fmaf(a, sn, b * cs);
+  a = x;
+}
 // Eight elements kept in their storage form (so that a prefetched row costs few registers) until used.
 template <typename T> struct Raw8;
 template <> struct Raw8<bf16_t> {

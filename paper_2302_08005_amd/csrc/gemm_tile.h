@@ -71,9 +71,8 @@ __device__ __forceinline__ void rope_turn(float (&v)[N], const float* __restrict
 #pragma unroll
   for (int e = 0; e < PAIRS; e += 2) {
     const float4 w = *reinterpret_cast<const float4*>(t + 2 * e);   // cos, sin of two pairs
-    const float a0 = v[2 * e], b0 = v[2 * e + 1], a1 = v[2 * e + 2], b1 = v[2 * e + 3];
-    v[2 * e] = a0 * w.x - b0 * w.y; v[2 * e + 1] = a0 * w.y + b0 * w.x;
-    v[2 * e + 2] = a1 * w.z - b1 * w.w; v[2 * e + 3] = a1 * w.w + b1 * w.z;
+    turn_pair(v[2 * e], v[2 * e + 1], w.x, w.y);
+    turn_pair(v[2 * e + 2], v[2 * e + 3], w.z, w.w);
   }
 }
 

@@ -701,9 +701,7 @@ __global__ __launch_bounds__(256) void rope_kernel(int64_t rows, int seq, int H,
   load8(p, v);
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const float s = inverse ? -sn[e] : sn[e], a = v[2 * e], b = v[2 * e + 1];
-    v[2 * e] = a * cs[e] - b * s;
-    v[2 * e + 1] = a * s + b * cs[e];
+    turn_pair(v[2 * e], v[2 * e + 1], cs[e], inverse ? -sn[e] : sn[e]);
   }
   store8(p, v);
 }

@@ -198,3 +198,43 @@ def test_llama_layer_parity_degenerate_sizes(cfg):
     errs, _, _ = run_case(cfg, check_saved=cfg.hidden <= 4096)   # (intermediates: see the classic layer's test)
     bad = {k: v for k, v in errs.items() if not v <= TOL[cfg.dtype]}
     assert not bad, (bad, errs)
+
+
+# The layer turns queries and keys inside the projection's epilogue and their gradients as attention stores them: the bits
+# are those of the products with the rotary kernel behind them. Several tile sizes, either head width, padded rows of tiles,
+# fp32 on either side of the sequence length at which its attention kernels change.
+@pytest.mark.parametrize("dtype,batch,seq,hidden,heads", [
+    (W.BF16, 2, 264, 512, 4), (W.FP16, 3, 200, 384, 6), (W.BF16, 4, 512, 512, 8), (W.BF16, 4, 1024, 2048, 16), (W.BF16, 1, 3, 128, 1),
+    (W.FP32, 2, 100, 256, 2), (W.FP32, 1, 1032, 128, 2), (W.FP32, 1, 1030, 128, 1)])
+def test_rotary_turn_inside_the_layer_has_the_bits_of_the_kernel(dtype, batch, seq, hidden, heads):
+    F = 2 * hidden
+    cfg = W.LayerConfig("turn", batch, seq, hidden, heads, F, causal=1, dropout_p=0.0, dtype=dtype, pre_ln=1, ln_eps=1e-6, arch=W.LLAMA,
+                        config_id=51)
+    layer = B.Layer(cfg, W.make_params(cfg))
+    p, T, H = layer.params, batch * seq, hidden
+    gen = torch.Generator(device=DEV).manual_seed(7)
+    x, dy = (torch.randn(T, H, device=DEV, generator=gen).to(layer.dt) for _ in range(2))
+    layer.forward(x)
+    layer.backward(x, None, dy)
+    new = lambda rows, cols: torch.empty(rows, cols, dtype=layer.dt, device=DEV)
+    stat = lambda *s: torch.empty(*s, dtype=torch.float32, device=DEV)
+    table = stat(seq, hidden // heads // 2, 2)
+
+    n1, qkv = layer.saved_tensor("n1"), new(T, 3 * H)
+    B.slapo_gemm(dtype, B.NT, B.EPI_NONE, 0, T, 3 * H, H, n1, p["wqkv"], qkv)
+    B.slapo_rope(layer.desc, qkv, table, 0)
+    assert torch.equal(qkv.view(-1), layer.saved_tensor("qkv"))
+
+    du, dn2, dz1, da, dqkv = new(T, 2 * F), new(T, H), new(T, H), new(T, H), new(T, 3 * H)
+    B.slapo_gemm(dtype, B.NN, B.EPI_DGATE, 0, T, F, H, dy, p["w2"], du, aux_in=layer.saved_tensor("dgate"))
+    B.slapo_gemm(dtype, B.NN, B.EPI_NONE, 0, T, H, 2 * F, du, p["w1"], dn2)
+    B.slapo_bdrln_bwd(layer.desc, 0, T, dn2, layer.saved_tensor("z1"), None, layer.saved_tensor("rstd2"), p["ln2_g"], dy, dz1, None,
+                      stat(B.slapo_bdrln_bwd_blocks(T) * 3 * H))
+    B.slapo_gemm(dtype, B.NN, B.EPI_NONE, 0, T, H, H, dz1, p["wo"], da)
+    B.slapo_attn_bwd(layer.desc, qkv, None, layer.saved_tensor("attn"), da, layer.saved_tensor("lse"), stat(batch, heads, seq), dqkv)
+    B.slapo_rope(layer.desc, dqkv, table, 1)
+    dw = torch.empty_like(p["wqkv"])
+    ws = torch.empty(max(16, B.slapo_weight_grad_workspace(dtype, 3 * H, H, T)), dtype=torch.uint8, device=DEV)
+    B.slapo_weight_grad(dtype, 0, 3 * H, H, T, dqkv, n1, dw, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(dw, layer.grads["wqkv"])
