@@ -1159,10 +1159,14 @@ __device__ __forceinline__ f32x4_t rows_times_rows(const RowFrags<D>& a, const R
   return acc;
 }
 // sum over rows 16 t0 .. 16 t1 - 1 of w[lane % 16][row] * x[row][column of the lane]; element r: column 4 (lane / 16) + r of the
-// 16 columns that start at x, for row lane % 16 of w (rows at or beyond `rows`, whose weights are 0, are read as the one in
-// front: hidden keys' values are not touched)
+// 16 columns that start at x, for row lane % 16 of w. That row of w sees the rows first <= row < end of x (end <= rows); its
+// weights elsewhere are 0. Rows at or beyond `rows` are read as the one in front.
+// A chunk's rows are common to all 16 rows of w, and 0 times an infinity or a NaN is no zero. So a result that is not finite
+// is taken again with such values left out of the products and added only to the rows of w that see them: nothing hidden
+// reaches a result, and columns without such values keep their bits. (Tests per chunk instead of one at the end: 512 tokens,
+// 6 heads of 64, causal forward 16.2 -> 17.7 us, backward 25.3 -> 27.3.)
 __device__ __forceinline__ f32x4_t weighted_rows(const float* w, const float* __restrict__ x, int64_t stride, int t0, int t1, int rows,
-                                                 int lane) {
+                                                 int first, int end, int lane) {
   const int i = lane & 15, g = lane >> 4;
   f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
   struct Chunk { float4 w; float x[4]; };
@@ -1176,6 +1180,12 @@ __device__ __forceinline__ f32x4_t weighted_rows(const float* w, const float* __
     }
     return c;
   };
+  auto add = [&](const Chunk& c) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c.x[0], c.w.x, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c.x[1], c.w.y, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c.x[2], c.w.z, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c.x[3], c.w.w, acc, 0, 0, 0);
+  };
   constexpr int U = 4;   // chunks in flight
   for (int t = t0; t < t1; t += U) {
     Chunk c[U];
@@ -1184,12 +1194,28 @@ __device__ __forceinline__ f32x4_t weighted_rows(const float* w, const float* __
       if (t + u < t1) c[u] = fetch(t + u);   // (uniform)
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (t + u < t1) {
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c[u].x[0], c[u].w.x, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c[u].x[1], c[u].w.y, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c[u].x[2], c[u].w.z, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c[u].x[3], c[u].w.w, acc, 0, 0, 0);
-      }
+      if (t + u < t1) add(c[u]);
+  }
+  auto finite = [](float v) { return fabsf(v) < INFINITY; };
+  if (__any(!(finite(acc[0]) && finite(acc[1]) && finite(acc[2]) && finite(acc[3])))) {
+    acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int t = t0; t < t1; ++t) {
+      Chunk c = fetch(t);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) c.x[s] = finite(c.x[s]) ? c.x[s] : 0.f;
+      add(c);
+    }
+    const int from = first > 16 * t0 ? first : 16 * t0, to = end < 16 * t1 ? end : 16 * t1;
+#pragma unroll 1
+    for (int row = from; row < to; ++row) {
+      const float4 v = *reinterpret_cast<const float4*>(x + (int64_t)row * stride + 4 * g);
+      const float wr = w[row];
+      if (!finite(v.x)) acc[0] = fmaf(v.x, wr, acc[0]);
+      if (!finite(v.y)) acc[1] = fmaf(v.y, wr, acc[1]);
+      if (!finite(v.z)) acc[2] = fmaf(v.z, wr, acc[2]);
+      if (!finite(v.w)) acc[3] = fmaf(v.w, wr, acc[3]);
+    }
   }
   return acc;
 }
@@ -1235,11 +1261,10 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnShape sh, const f
     float mx = -INFINITY;
     for (int j = c; j < n; j += 16) mx = fmaxf(mx, p[j]);
     mx = over16(mx, [](float x, float y) { return fmaxf(x, y); });
-    const float top = mx == -INFINITY ? 0.f : mx;
     const uint64_t e_row = (((uint64_t)b * sh.heads + a) * S + clamp_row(q0 + row, S)) * S;   // element index of probability (row, 0)
     float sum = 0.f;
     for (int j = c; j < n; j += 16) {
-      const float e = __expf(p[j] - top);
+      const float e = __expf(p[j] - mx);
       sum += e;                                                        // the softmax is normalised before dropout
       p[j] = (sh.drop.thr != 0 && !dropout_keep1(sh.drop, e_row + j)) ? 0.f : e;
     }
@@ -1251,8 +1276,9 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnShape sh, const f
   }
   __syncthreads();
   const float inv = inv_sum[i];
+  const int seen = sh.causal && q + 1 < kv_end ? q + 1 : kv_end;   // keys in front of this one are visible to query q
   for (int ct = wave; ct < D / 16; ct += 4) {
-    const f32x4_t o = weighted_rows(f32sm + i * pitch, base + 2 * H + ct * 16, rs, 0, tiles, kv_end, lane);
+    const f32x4_t o = weighted_rows(f32sm + i * pitch, base + 2 * H + ct * 16, rs, 0, tiles, kv_end, 0, seen, lane);
     if (q < S) *reinterpret_cast<float4*>(out + ((int64_t)b * S + q) * H + a * D + ct * 16 + 4 * g) = make_float4(o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
   }
 }
@@ -1276,7 +1302,7 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(AttnShape sh, int blo
   const float* lse_row = lse + (int64_t)head * S;       // (head counts the heads of all samples)
   const float* delta_row = delta + (int64_t)head * S;
   const int kv_len = visible_keys(sh, seqlens, b);
-  const float scale = rsqrtf((float)D);
+  const float scale = rsqrtf((float)D), keep_scale = sh.drop.thr != 0 ? sh.drop.scale : 1.f;
   const uint64_t e_head = (uint64_t)head * S * S;       // element index of probability (0, 0)
   float *ds_rows = f32sm + i * pitch, *p_rows = f32sm + (16 + i) * pitch;
   if (keys) {
@@ -1298,18 +1324,19 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(AttnShape sh, int blo
         const int q = 16 * t + 4 * g + r;
         const bool hide = (row >= kv_len) | (q >= S) | ((sh.causal != 0) & (row > q));
         const float p = hide ? 0.f : __expf(sc[r] * scale - ls[r]);
-        float kept = 1.f;
-        if (sh.drop.thr != 0) kept = dropout_keep1(sh.drop, e_head + (uint64_t)clamp_row(q, S) * S + clamp_row(row, S)) ? sh.drop.scale : 0.f;
-        pv[r] = p * kept;                               // what multiplied V in the forward pass
-        ds[r] = hide ? 0.f : p * (dp[r] * kept - de[r]);
+        bool keep = true;
+        if (sh.drop.thr != 0) keep = dropout_keep1(sh.drop, e_head + (uint64_t)clamp_row(q, S) * S + clamp_row(row, S));
+        pv[r] = keep ? p * keep_scale : 0.f;            // what multiplied V in the forward pass
+        ds[r] = hide ? 0.f : p * ((keep ? dp[r] * keep_scale : 0.f) - de[r]);
       }
       *reinterpret_cast<f32x4_t*>(p_rows + 16 * t + 4 * g) = pv;
       *reinterpret_cast<f32x4_t*>(ds_rows + 16 * t + 4 * g) = ds;
     }
     __syncthreads();
+    const int seen_from = sh.causal ? row : 0, seen_to = row < kv_len ? S : 0;   // queries that see key `row`
     for (int ct = wave; ct < D / 16; ct += 4) {
-      const f32x4_t dk = weighted_rows(ds_rows, base + ct * 16, rs, first, end, S, lane);
-      const f32x4_t dv = weighted_rows(p_rows, dobase + ct * 16, H, first, end, S, lane);
+      const f32x4_t dk = weighted_rows(ds_rows, base + ct * 16, rs, first, end, S, seen_from, seen_to, lane);
+      const f32x4_t dv = weighted_rows(p_rows, dobase + ct * 16, H, first, end, S, seen_from, seen_to, lane);
       if (row < S) {
         float* o = dbase + row * rs + H + ct * 16 + 4 * g;
         float v[4] = {dk[0] * scale, dk[1] * scale, dk[2] * scale, dk[3] * scale};
@@ -1339,14 +1366,14 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(AttnShape sh, int blo
       for (int r = 0; r < 4; ++r) {
         const int key = 16 * t + 4 * g + r;
         const bool hide = (key >= kv_end) | ((sh.causal != 0) & (key > q));
-        const float kept = sh.drop.thr == 0 ? 1.f : (keep >> r) & 1u ? sh.drop.scale : 0.f;
-        ds[r] = hide ? 0.f : __expf(sc[r] * scale - my_lse) * (dp[r] * kept - my_delta);
+        ds[r] = hide ? 0.f : __expf(sc[r] * scale - my_lse) * (((keep >> r) & 1u ? dp[r] * keep_scale : 0.f) - my_delta);
       }
       *reinterpret_cast<f32x4_t*>(ds_rows + 16 * t + 4 * g) = ds;
     }
     __syncthreads();
+    const int seen = sh.causal && row + 1 < kv_end ? row + 1 : kv_end;
     for (int ct = wave; ct < D / 16; ct += 4) {
-      const f32x4_t dq = weighted_rows(ds_rows, base + H + ct * 16, rs, 0, tiles, kv_end, lane);
+      const f32x4_t dq = weighted_rows(ds_rows, base + H + ct * 16, rs, 0, tiles, kv_end, 0, seen, lane);
       if (row < S) {
         float v[4] = {dq[0] * scale, dq[1] * scale, dq[2] * scale, dq[3] * scale};
         if (sh.rope) rope_back(v, sh.rope, row, D, ct * 16 + 4 * g);

@@ -117,3 +117,67 @@ def test_attention_forms_by_grid_size(dtype, case):
     (3, 15, 2, 128, 1, None, 4.0), (2, 17, 3, 64, 0, [17, 16], 1.0), (2, 40, 2, 64, 1, [40, 33], 1.0, 0.3), (1, 136, 2, 128, 0, [129], 1.0, 0.2)], ids=str)
 def test_attention_fp32_forms(case):
     test_attention_fwd_bwd(W.FP32, case)
+
+
+# fp32: an infinity or a NaN reaches the rows that see it and no other: not the earlier tokens of its 16-row block (causal),
+# not through padded keys, not through dropped probabilities. Short sequences (scores in LDS) and the plain kernels.
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("S,d,causal,length,pd", [(40, 64, 1, 40, 0.0), (37, 128, 1, 21, 0.0), (50, 64, 0, 21, 0.0), (90, 64, 1, 90, 0.0),
+                                                  (40, 64, 1, 40, 0.3), (48, 128, 0, 41, 0.3), (1032, 64, 1, 1020, 0.0)])
+def test_fp32_attention_keeps_values_that_are_not_finite_apart(S, d, causal, length, pd, bad):
+    h, H = 2, 2 * d
+    cfg = W.LayerConfig("t", 1, S, H, h, 64, causal=causal, dtype=W.FP32, attn_dropout_p=pd)
+    desc, gen = B.make_desc(cfg), torch.Generator(device=DEV).manual_seed(S)
+    qkv, dout = (torch.randn(S, w, device=DEV, generator=gen) for w in (3 * H, H))
+    lens = torch.tensor([length], dtype=torch.int32, device=DEV)
+    new = lambda *s: torch.full(s, 7.0, device=DEV)
+
+    def forward(qkv):
+        out, lse = new(S, H), new(1, h, S)
+        B.slapo_attn_fwd(desc, qkv, lens, out, lse)
+        return out, lse
+
+    def backward(qkv, dout):
+        dqkv = new(S, 3 * H)
+        B.slapo_attn_bwd(desc, qkv, lens, out0, dout, lse0, new(1, h, S), dqkv)
+        return dqkv.view(S, 3, h, d)   # (query, key, value gradients of each head)
+
+    i = torch.arange(S, device=DEV)
+    visible = (i[None, :] < length) & ((i[None, :] <= i[:, None]) | (causal == 0))   # [query, key]
+    kept = torch.from_numpy(np.asarray(L.attention_keep(cfg)[0, 0], dtype=bool)).to(DEV) if pd else torch.ones_like(visible)
+    out0, lse0 = forward(qkv)
+    g0 = backward(qkv, dout)
+    assert torch.isfinite(out0).all() and torch.isfinite(g0).all()
+    for t in sorted({0, 5, 17, 31, length - 1, S - 1}):
+        planted = [qkv.clone() for _ in range(3)]
+        for part in range(3):
+            planted[part][t, part * H + 3] = bad
+        # forward, a value: column 3 of the queries that see it (dropped ones count: 0 times the value, as it always was)
+        out, _ = forward(planted[2])
+        hit = torch.zeros_like(out, dtype=torch.bool)
+        hit[:, 3] = visible[:, t]
+        assert torch.equal(out[~hit], out0[~hit]) and not torch.isfinite(out[hit]).any()
+        if bad == float("inf") and not pd:
+            assert torch.isposinf(out[hit]).all()
+        # forward, a key: whole rows
+        out, _ = forward(planted[1])
+        assert torch.equal(out[~visible[:, t]], out0[~visible[:, t]])
+        # backward, a value: the query gradients of the queries that see it undropped, and its own key's gradient
+        g = backward(planted[2], dout)
+        rows = visible[:, t] & kept[:, t]
+        assert torch.equal(g[~rows, 0], g0[~rows, 0]) and not torch.isfinite(g[rows, 0, 0]).any()
+        assert torch.equal(g[i != t, 1], g0[i != t, 1]) and torch.equal(g[:, 2], g0[:, 2])
+        # a key
+        g = backward(planted[1], dout)
+        assert torch.equal(g[~visible[:, t], 0], g0[~visible[:, t], 0]) and torch.equal(g[i != t, 1:], g0[i != t, 1:])
+        # a query, and a gradient of the output: keys that the query does not see
+        for g in (backward(planted[0], dout), backward(qkv, torch.where((i == t)[:, None] & (torch.arange(H, device=DEV) == 3), bad, dout))):
+            assert torch.equal(g[i != t, 0], g0[i != t, 0]) and torch.equal(g[~visible[t], 1:], g0[~visible[t], 1:])
+            assert torch.equal(g[:, :, 1], g0[:, :, 1])
+        assert not torch.isfinite(g[visible[t], 2, 0, 3]).any()   # (the latter: column 3 of the values' gradients)
+    # a row whose visible scores are all -inf has no softmax
+    planted = qkv.clone()
+    planted[0, 3], planted[0, H + 3] = 1.0, -float("inf")
+    if causal:
+        out, lse = forward(planted)
+        assert torch.isnan(out[0, :d]).all() and torch.isneginf(lse[0, 0, 0]) and torch.equal(out[1:, d:], out0[1:, d:])
