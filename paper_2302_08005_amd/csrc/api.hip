@@ -13,6 +13,10 @@ using namespace slapo;
 namespace {
 
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
+inline bool overlap(const void* a, const void* b, size_t bytes) {   // arrays of `bytes` each
+  const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+  return p < q + bytes && q < p + bytes;
+}
 inline bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
 
 // width of each of Q, K, V (heads * head dim): the hidden size unless the descriptor says otherwise
@@ -497,6 +501,7 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   // block of a pre-LN layer is dy itself). 4 x 2048 tokens of width 2560: 20 us of row kernel and 8 of 46 in the next one.
   const bool keeps_all = dropout_keeps_all(dp0);                    // (both sites drop alike)
   const bool dy_is_dr2 = d->pre_ln && keeps_all && dx != dy;        // (a dx on top of dy is written while the helper stream reads dr2)
+  const bool dx_on_x = !d->pre_ln && overlap(dx, x, (size_t)T * H * (dt == SLAPO_FP32 ? 4 : 2));   // (a pre-LN layer's dx is written row by row behind the read, and no weight gradient reads x)
   // `st` carries the data-gradient chain; `ws` the weight / bias gradients that hang off it
   SideStream* side = backward_on_one_stream(d) ? nullptr : side_stream();
   const bool solo = side == nullptr;   // one stream: every GEMM has the chip to itself
@@ -533,7 +538,7 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   void *g_b2 = llama ? nullptr : gr->b2, *g_bo = llama ? nullptr : gr->bo;
   void *g_ln1_b = llama ? nullptr : gr->ln1_b, *g_ln2_b = llama ? nullptr : gr->ln2_b;
 
-  if (gradients_paired(d) && (d->pre_ln || dx != x)) {   // (a dx on top of x would be written while the weight gradient beside it still reads x)
+  if (gradients_paired(d) && !dx_on_x) {   // (it would be written while the weight gradient beside it still reads x)
     // The weight gradients share the launches of the data gradients (GradPair), and the sums behind the row kernels and
     // the biases ride on them.
     GradPair pr = {};
@@ -660,6 +665,7 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     }
   } else {
     dweight(3 * A, H, dqkv, x, gr->wqkv);
+    if (side && dx_on_x) side->order(side->join, ws, st);   // the helper stream has read x before dx is written there
     launch_gemm(dt, GEMM_NN, EPI_ADD, d->act, T, H, 3 * A, dqkv, p->wqkv, dx, nullptr, t2, nullptr, st, solo, gws, gwb);
   }
   // the last bias gradient goes behind the data gradient on the caller's stream: the helper stream's last

@@ -39,10 +39,8 @@ def err(got, ref):
 TOL = {W.FP32: 1e-4, W.BF16: 2e-2, W.FP16: 2.5e-3}
 
 
-def forks(step):
-    """True if the work that `step` enqueues branches off the caller's stream: captured, it is then no mere chain."""
-    step()                                          # (first-call set-up stays outside the capture)
-    torch.cuda.synchronize()
+def captured(step):
+    """(nodes, edges) of the graph that `step` is captured as; nothing of it is run."""
     graph = torch.cuda.CUDAGraph(keep_graph=True)
     with torch.cuda.graph(graph):
         step()
@@ -51,4 +49,12 @@ def forks(step):
     raw, nodes, edges = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0), ctypes.c_size_t(0)
     assert hip.hipGraphGetNodes(raw, None, ctypes.byref(nodes)) == 0 and nodes.value > 1
     assert hip.hipGraphGetEdges(raw, None, None, ctypes.byref(edges)) == 0
-    return edges.value != nodes.value - 1
+    return nodes.value, edges.value
+
+
+def forks(step):
+    """True if the work that `step` enqueues branches off the caller's stream: captured, it is then no mere chain."""
+    step()                                          # (first-call set-up stays outside the capture)
+    torch.cuda.synchronize()
+    nodes, edges = captured(step)
+    return edges != nodes - 1

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import workloads as W
-from gpu_util import TOL, err, to_np
+from gpu_util import DEV, TOL, captured, err, to_np
 from paper_2302_08005_amd import binding as B
 from test_gpu_layer import run_case
 
@@ -53,3 +53,29 @@ def test_input_gradient_on_top_of_the_input():
     assert err(x2, to_np(dx)) <= TOL[c.dtype]
     for k in W.PARAM_NAMES:
         assert err(layer.grads[k], to_np(want[k])) <= TOL[c.dtype], k
+
+
+@pytest.mark.parametrize("c", [
+    cfg("paired-two-streams", 4, 523, 512, 8, 2048), cfg("paired-two-streams-no-dropout", 4, 523, 512, 8, 2048, dropout_p=0.0),
+    cfg("forked", 5, 1000, 512, 8, 1024), cfg("forked-half-checkpoint", 5, 1000, 512, 8, 1024, W.FP16)], ids=lambda c: c.name)
+def test_input_gradient_on_top_of_the_input_on_two_streams(c):
+    """The weight gradient of the QKV projection, on the helper stream, has read x before dx is written there."""
+    layer = B.Layer(c, W.make_params(c), checkpoint=int("checkpoint" in c.name))
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    x, dy = (torch.randn(c.batch, c.seq, c.hidden, device=DEV, generator=gen).to(layer.dt) for _ in range(2))
+    layer.forward(x)
+    dx = layer.backward(x, None, dy)
+    want = {k: v.clone() for k, v in layer.grads.items()}
+    if "forked" in c.name:   # captured, the same launches have one dependence more
+        step = lambda out: B.slapo_layer_bwd(layer.desc, layer.params, x, None, dy, layer.saved, out, layer.grads, layer.scratch)
+        (nodes, edges), (nodes2, edges2) = captured(lambda: step(dx)), captured(lambda: step(x))
+        assert nodes2 == nodes and edges2 == edges + 1
+    for _ in range(3):
+        x2 = x.clone()
+        B.slapo_layer_bwd(layer.desc, layer.params, x2, None, dy, layer.saved, x2, layer.grads, layer.scratch)
+        torch.cuda.synchronize()
+        if "forked" in c.name:   # the same launches, ordered
+            assert torch.equal(x2, dx) and all(torch.equal(layer.grads[k], want[k]) for k in W.PARAM_NAMES)
+        assert err(x2, to_np(dx)) <= TOL[c.dtype]
+        for k in W.PARAM_NAMES:
+            assert err(layer.grads[k], to_np(want[k])) <= TOL[c.dtype], k
