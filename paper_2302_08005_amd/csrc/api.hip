@@ -500,8 +500,9 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   // Nothing dropped: a branch's gradient is the residual's, so no copy of it is made (the array in front of the feed-forward
   // block of a pre-LN layer is dy itself). 4 x 2048 tokens of width 2560: 20 us of row kernel and 8 of 46 in the next one.
   const bool keeps_all = dropout_keeps_all(dp0);                    // (both sites drop alike)
-  const bool dy_is_dr2 = d->pre_ln && keeps_all && dx != dy;        // (a dx on top of dy is written while the helper stream reads dr2)
-  const bool dx_on_x = !d->pre_ln && overlap(dx, x, (size_t)T * H * (dt == SLAPO_FP32 ? 4 : 2));   // (a pre-LN layer's dx is written row by row behind the read, and no weight gradient reads x)
+  const size_t array = (size_t)T * H * (dt == SLAPO_FP32 ? 4 : 2);
+  const bool dy_is_dr2 = d->pre_ln && keeps_all && !overlap(dx, dy, array);   // (a dx on top of dy is written while the helper stream reads dr2)
+  const bool dx_on_x = !d->pre_ln && overlap(dx, x, array);   // (a pre-LN layer's dx is written row by row behind the read, and no weight gradient reads x)
   // `st` carries the data-gradient chain; `ws` the weight / bias gradients that hang off it
   SideStream* side = backward_on_one_stream(d) ? nullptr : side_stream();
   const bool solo = side == nullptr;   // one stream: every GEMM has the chip to itself

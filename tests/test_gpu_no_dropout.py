@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import workloads as W
-from gpu_util import TOL, err, to_np
+from gpu_util import DEV, TOL, captured, err, to_np
 from paper_2302_08005_amd import binding as B
 from test_gpu_layer import run_case
 from test_gpu_stack import test_stack_matches_oracle_chain_and_single_layer_calls as stack_matches
@@ -43,3 +43,23 @@ def test_layers_without_dropout(c):
     cfg("stack-llama", 2, 72, 256, 4, 344, ln_eps=1e-6, arch=W.LLAMA, config_id=95)], ids=lambda c: c.name)
 def test_stacks_without_dropout(c):
     stack_matches(c)
+
+
+@pytest.mark.parametrize("c", [cfg("one-stream", 2, 67, 256, 4, 1000), cfg("forked", 5, 1000, 512, 8, 1024)], ids=lambda c: c.name)
+def test_input_gradient_partly_on_top_of_dy(c):
+    """dx from 40 rows into dy on: as with dx on dy, no launch beside the one that writes dx reads dy."""
+    layer, T = B.Layer(c, W.make_params(c)), c.batch * c.seq
+    gen = torch.Generator(device=DEV).manual_seed(6)
+    x, both = (torch.randn(rows, c.hidden, device=DEV, generator=gen).to(layer.dt) for rows in (T, T + 40))
+    dy, dx = both[:T], both[40:]
+    layer.forward(x)
+    whole = dy.clone()
+    step = lambda g, out: B.slapo_layer_bwd(layer.desc, layer.params, x, None, g, layer.saved, out, layer.grads, layer.scratch)
+    step(whole, whole)                                   # dx on dy
+    want, grads = whole.clone(), {k: v.clone() for k, v in layer.grads.items()}
+    assert captured(lambda: step(dy, dx)) == captured(lambda: step(whole, whole))
+    step(dy, dx)
+    torch.cuda.synchronize()
+    assert torch.equal(dx, want)
+    for k in W.PARAM_NAMES:
+        assert torch.equal(layer.grads[k], grads[k]), k
