@@ -1284,6 +1284,8 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnShape sh, const f
 }
 
 // dQ and dK/dV blocks in one launch, dK/dV (which take longer) first; delta = rowsum(dO * O) comes from a kernel in front.
+// Grid: (blocks of 16 rows of all heads, samples, kind); in one dimension, the work items of a batch of many short samples
+// would not fit 32 bits.
 template <int D>
 __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(AttnShape sh, int blocks_x, const float* __restrict__ qkv,
                                                            const int32_t* __restrict__ seqlens, const float* __restrict__ dout,
@@ -1291,10 +1293,8 @@ __global__ __launch_bounds__(256) void attn_bwd_f32_kernel(AttnShape sh, int blo
                                                            float* __restrict__ dqkv) {
   extern __shared__ __attribute__((aligned(16))) float f32sm[];   // dS [16][pitch]; dK/dV: P behind it
   const int S = sh.seq, H = sh.hidden, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15, g = lane >> 4, pitch = f32_pitch(S);
-  const int blocks = blocks_x * sh.heads * sh.batch;
-  const bool keys = (int)blockIdx.x < blocks;
-  const int w = keys ? blockIdx.x : blockIdx.x - blocks;
-  const int row0 = (w % blocks_x) * 16, head = w / blocks_x, a = head % sh.heads, b = head / sh.heads, row = row0 + i;
+  const bool keys = blockIdx.z == 0;
+  const int row0 = ((int)blockIdx.x % blocks_x) * 16, a = (int)blockIdx.x / blocks_x, b = blockIdx.y, head = b * sh.heads + a, row = row0 + i;
   const int64_t rs = 3 * (int64_t)H;
   const float* base = qkv + (int64_t)b * S * rs + a * D;
   const float* dobase = dout + (int64_t)b * S * H + a * D;
@@ -1665,7 +1665,7 @@ static void bwd_f32(const AttnShape& s, const void* qkv, const int32_t* seqlens,
     auto kern = attn_bwd_f32_kernel<D>;
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     const int blocks_x = (s.seq + 15) / 16;
-    hipLaunchKernelGGL(kern, dim3(2 * blocks_x * s.heads * s.batch), dim3(256), lds, st, s, blocks_x, (const float*)qkv, seqlens,
+    hipLaunchKernelGGL(kern, dim3(blocks_x * s.heads, s.batch, 2), dim3(256), lds, st, s, blocks_x, (const float*)qkv, seqlens,
                        (const float*)dout, lse, (const float*)delta, (float*)dqkv);
     return;
   }

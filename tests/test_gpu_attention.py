@@ -181,3 +181,22 @@ def test_fp32_attention_keeps_values_that_are_not_finite_apart(S, d, causal, len
     if causal:
         out, lse = forward(planted)
         assert torch.isnan(out[0, :d]).all() and torch.isneginf(lse[0, 0, 0]) and torch.equal(out[1:, d:], out0[1:, d:])
+
+
+def test_fp32_backward_of_very_many_short_samples():
+    """One token per sample, as many heads and samples as the descriptor takes: every softmax is 1, dV = dO, dQ = dK = 0."""
+    n, h, d = 65535, 170, 64
+    cfg = W.LayerConfig("t", n, 1, 64, h, 64, causal=0, dtype=W.FP32, attn_dim=h * d)
+    desc = B.make_desc(cfg)
+    qkv = torch.randn(n, 3 * h * d, device=DEV)
+    v = qkv[:, 2 * h * d:]
+    out, lse = torch.empty(n, h * d, device=DEV), torch.empty(n, h, 1, device=DEV)
+    B.slapo_attn_fwd(desc, qkv, None, out, lse)
+    assert torch.equal(out, v)
+    dqkv = torch.full_like(qkv, 7.0)
+    B.slapo_attn_bwd(desc, qkv, None, out, out, lse, torch.empty_like(lse), dqkv)
+    torch.cuda.synchronize()
+    # scores stay below 8 (8 sigma), so exp(score - lse) is 1 up to 8 * 2^-24; dP and delta are sums of 64 products that differ
+    # in their order only: 64 * 2^-24 * |v|^2 (below 200), times a key or query element (below 7) / 8
+    assert float((dqkv[:, 2 * h * d:] - out).abs().max()) <= 1e-5
+    assert float(dqkv[:, :2 * h * d].abs().max()) <= 1e-3
