@@ -1561,16 +1561,34 @@ static void fwd_bf16_groups(const AttnShape& s, const void* qkv, const int32_t* 
   hipLaunchKernelGGL(kern, dim3((s.seq + rows - 1) / rows, s.heads, s.batch), dim3(256), lds, st, s, (const bf16_t*)qkv,
                      seqlens, (bf16_t*)out, lse);
 }
+// Two groups per block, by the number of 64-row blocks that this makes and of those that run at a time (ONE_ROUND):
+// - at most one per CU, whatever the sequence: 1.0-1.6 times as fast as blocks of 128 rows from 65 tokens on.
+// - two per CU (64-wide heads): causal blocks, whose lengths differ, gain 0.97-1.4. Others gain 1.02-1.19 where the
+//   sequence has an even number of 64-row blocks or is long, and lose 3-10 % where a short one has an odd number (136 or 520
+//   tokens: half of a 128-row block's wavefronts have no rows and cost it nothing) or is one block of 128.
+// - up to two rounds of 128-wide causal blocks that start longest-first (lpt_heads_for: heads x samples in eights): the more
+//   the longer the sequence, and a few more where mask draws lengthen the blocks. In another order fewer (the second round
+//   starts late: 7 x 104 tokens, 20 heads 10.8 -> 14.9 us), the fewest with an odd number of 64-row blocks.
+// Blocks of 128 rows / two groups, us (heads of all samples x tokens). 64-wide: 16 x 128 5.8 / 5.2; 64 x 512 11.9 / 10.8; 72 x 384
+// 9.8 / 9.2; 96 x 136 7.1 / 7.6; causal 16 x 1024 20.0 / 14.1. 128-wide: 14 x 1032 28.4 / 22.4, 17 x 1032 28.5 / 39; causal 16 x
+// 1032 27.1 / 18.8, 48 x 384 14.7 / 13.4, 64 x 384 14.9 / 15.4, 48 x 512 17.4 / 16.7, 64 x 512 17.7 / 18.4, 32 x 1024 27.7 / 24.7, 8
+// x 4096 88 / 64; not in eights 30 x 640 20.0 / 22.7, 20 x 776 22.3 / 18.0, 22 x 776 22.4 / 23.8, 20 x 1024 27.3 / 26.0, 22 x 1024
+// 27.6 / 29.3, 12 x 2048 47.9 / 40.0, 9 x 2056 47.7 / 55.
+// (Telling each other the maxima costs up to 1 us of these; without it the probabilities are rounded against other maxima
+// and the output differs by 1-2e-3 in bf16 from that of one group, with it by 2-4e-5, like any other order of sums.)
+template <int D>
+static bool fwd_two_groups(const AttnShape& s) {
+  const int64_t per_head = (s.seq + 63) / 64, heads = (int64_t)s.heads * s.batch, blocks = per_head * heads;
+  if (s.seq <= 64) return false;
+  if (blocks <= 256) return true;
+  if (blocks <= ONE_ROUND<D>) return s.causal || (per_head % 2 == 0 && s.seq > 192) || s.seq >= 768;
+  if (D == 64 || !s.causal) return false;
+  if (heads % 8 != 0) return s.seq >= 640 && blocks <= (per_head % 2 ? 280 : s.seq < 1640 ? 220 + s.seq / 10 : 384);
+  return blocks <= 512 && blocks <= (s.drop.thr && s.seq >= 384 ? 192 : 128) + s.seq / 2;
+}
 template <int D, bool F16>
 static void fwd_bf16(const AttnShape& s, const void* qkv, const int32_t* seqlens, void* out, float* lse, hipStream_t st) {
-  // Two groups per block while the doubled blocks still run in one round (causal blocks are half as long) and there is more
-  // than one tile to share. Blocks of 128 rows, one / two groups, us: 64-wide 16 (one sample of 128) 5.8 / 5.2, 128 (1024
-  // tokens, causal) 20.0 / 14.1, 256 (4 x 512) 12.1 / 11.3, 320 15.3 / 16.2; 128-wide 64 (2 x 1024, causal) 27.1 / 18.9, 128
-  // (8192, causal) 165 / 112, 256 (4 x 1024, causal) 27.9 / 25.4, 320 42.9 / 43.9. (Telling each other the maxima costs up to
-  // 1 us of these; without it the probabilities are rounded against other maxima and the output differs by 1-2e-3 in bf16
-  // from that of one group, with it by 2-4e-5, like any other order of sums.)
-  const int64_t room = s.causal ? ONE_ROUND<D> : ONE_ROUND<D> / 2;
-  if (attn_blocks(s) <= (room < 256 ? room : 256) && s.seq > 64) fwd_bf16_groups<D, F16, 2>(s, qkv, seqlens, out, lse, st);
+  if (fwd_two_groups<D>(s)) fwd_bf16_groups<D, F16, 2>(s, qkv, seqlens, out, lse, st);
   else fwd_bf16_groups<D, F16, 1>(s, qkv, seqlens, out, lse, st);
 }
 template <int D>

@@ -39,17 +39,32 @@ def err(got, ref):
 TOL = {W.FP32: 1e-4, W.BF16: 2e-2, W.FP16: 2.5e-3}
 
 
-def captured(step):
-    """(nodes, edges) of the graph that `step` is captured as; nothing of it is run."""
+class _KernelNode(ctypes.Structure):   # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint32 * 3),
+                ("args", ctypes.c_void_p), ("shared", ctypes.c_uint32)]
+
+
+def captured(step, grids=False):
+    """(nodes, edges) of the graph that `step` is captured as, or the grids of its kernels; nothing of it is run."""
     graph = torch.cuda.CUDAGraph(keep_graph=True)
     with torch.cuda.graph(graph):
         step()
     with open("/proc/self/maps") as f:
         hip = ctypes.CDLL(next(l.split()[-1] for l in f if "libamdhip64" in l))
     raw, nodes, edges = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0), ctypes.c_size_t(0)
-    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(nodes)) == 0 and nodes.value > 1
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(nodes)) == 0 and nodes.value > 0
     assert hip.hipGraphGetEdges(raw, None, None, ctypes.byref(edges)) == 0
-    return nodes.value, edges.value
+    if not grids:
+        return nodes.value, edges.value
+    each, out = (ctypes.c_void_p * nodes.value)(), []
+    assert hip.hipGraphGetNodes(raw, each, ctypes.byref(nodes)) == 0
+    for n in each:
+        kind, k = ctypes.c_int(-1), _KernelNode()
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(n), ctypes.byref(kind)) == 0
+        if kind.value == 0:   # hipGraphNodeTypeKernel
+            assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(n), ctypes.byref(k)) == 0
+            out.append(tuple(k.grid))
+    return out
 
 
 def forks(step):
@@ -57,4 +72,5 @@ def forks(step):
     step()                                          # (first-call set-up stays outside the capture)
     torch.cuda.synchronize()
     nodes, edges = captured(step)
+    assert nodes > 1
     return edges != nodes - 1

@@ -6,7 +6,7 @@ import torch
 import workloads as W
 from oracle import layer as L
 from paper_2302_08005_amd import binding as B
-from gpu_util import DEV, TOL, err, store, to_dev
+from gpu_util import DEV, TOL, captured, err, store, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -200,3 +200,28 @@ def test_fp32_backward_of_very_many_short_samples():
     # in their order only: 64 * 2^-24 * |v|^2 (below 200), times a key or query element (below 7) / 8
     assert float((dqkv[:, 2 * h * d:] - out).abs().max()) <= 1e-5
     assert float(dqkv[:, :2 * h * d].abs().max()) <= 1e-3
+
+
+# on either side of the lines between blocks of 128 rows and two groups over 64: one block per CU, one round, and for causal
+# blocks that start longest-first more than one; sequences with an odd number of 64-row blocks
+@pytest.mark.parametrize("batch,seq,heads,d,causal,rows", [
+    (7, 104, 20, 128, 1, 128), (32, 104, 4, 128, 1, 64), (43, 136, 2, 128, 0, 128), (42, 136, 2, 128, 0, 64), (3, 64, 2, 64, 0, 128),
+    (24, 136, 4, 64, 0, 128), (24, 136, 4, 64, 1, 64), (18, 200, 4, 64, 0, 64), (9, 776, 4, 64, 0, 64), (44, 264, 4, 64, 1, 128),
+    (8, 512, 8, 64, 1, 64), (9, 512, 8, 64, 1, 128), (6, 384, 8, 128, 1, 64), (7, 384, 8, 128, 1, 128), (33, 512, 1, 128, 1, 128),
+    (1, 776, 20, 128, 1, 64), (1, 776, 22, 128, 1, 128), (1, 640, 30, 128, 1, 128),
+    (1, 1024, 20, 128, 1, 64), (1, 1032, 18, 128, 1, 128), (1, 1536, 14, 128, 1, 64)])
+def test_which_forward_grids_have_two_groups(batch, seq, heads, d, causal, rows):
+    H = heads * d
+    desc = B.make_desc(W.LayerConfig("t", batch, seq, H, heads, 64, causal=causal, dtype=W.BF16))
+    qkv, out = (torch.randn(batch * seq, w, device=DEV).to(torch.bfloat16) for w in (3 * H, H))
+    lse = torch.empty(batch, heads, seq, device=DEV)
+    call = lambda: B.slapo_attn_fwd(desc, qkv, None, out, lse)
+    call()
+    torch.cuda.synchronize()
+    assert captured(call, grids=True) == [((seq + rows - 1) // rows, heads, batch)]
+    q, k, v = (qkv[:, i * H:(i + 1) * H].view(batch, seq, heads, d).transpose(1, 2).float() for i in range(3))
+    scores = torch.matmul(q, k.transpose(-1, -2).contiguous()) / d ** 0.5
+    if causal:
+        scores = scores.masked_fill(torch.ones(seq, seq, device=DEV, dtype=torch.bool).triu(1), float("-inf"))
+    ref = torch.matmul(scores.softmax(-1), v.contiguous()).transpose(1, 2).reshape(batch * seq, H)
+    assert err(out, ref.cpu().numpy()) <= TOL[W.BF16]
