@@ -1649,14 +1649,19 @@ static void bwd_bf16(const AttnShape& s, const void* qkv, const int32_t* seqlens
   const size_t lds_dq = (size_t)4 * Tile<D>::ELEMS * sizeof(bf16_t);
   // with dropout: 2 KB per wavefront behind the stages for the exchange of mask draws
   const size_t lds_dkdv = (size_t)DKDV_STAGES<D> * (2 * Tile<D>::ELEMS + 256) * sizeof(bf16_t) + (s.drop.thr ? 4 * 2048 : 0);
-  // One launch while either kind's blocks alone fit one round; two groups per block while the four times as many blocks do.
+  // One launch while either kind's blocks alone fit one round (128-wide blocks that do not differ in length: while they
+  // leave an eighth of the chip free, with mask draws three eighths); two groups per block while the four times as many
+  // blocks do.
   // Two launches / one / one with two groups, us: 64-wide 16 blocks (one sample of 128) 14.6 / 8.7 / 7.0, 128 (1024 tokens,
   // causal) 48.7 / 32.8 / 24.1, 192 (4 x 512, 12 heads) 31 / 22.5 / 26.2, 256 (2048, causal) 90 / 62 / 47, 512 (8 x 512, padded)
   // 48.5 / 45.3 / 54, 1536 (6 x 1024, causal) 132 / 141; 128-wide 64 (2 x 1024, causal) 68 / 44.5 / 29, 128 (2 x 512) 44 / 29 / 34.5,
-  // 192 (3 x 1024, causal) 73 / 46 / 57, 256 (4 x 1024, causal) 74 / 56 / 68, 384 80 / 85.
-  const int64_t blocks = attn_blocks(s);
+  // 192 (3 x 1024, causal) 73 / 46 / 57, 256 (4 x 1024, causal) 74 / 56 / 68, 384 80 / 85; not causal 216 (24 x 1032) 84 / 77,
+  // 255 (15 x 2056) 159 / 166. With mask draws, 64-wide 16 blocks 18.7 / - / 9.2, 128 (1024, causal) 85 / - / 43, 256 (4 x 512) 48.5 /
+  // 34.8, 512 (8 x 512) 70.5 / 65.3; 128-wide causal 256 116 / 85, not causal 160 (32 x 520) 69 / 61, 189 (21 x 1032) 122 / 130, 256
+  // (4 x 512) 69.2 / 71.5.
+  const int64_t blocks = attn_blocks(s), room = D == 64 || s.causal ? ONE_ROUND<D> : s.drop.thr ? 160 : 224;
   if (blocks <= ONE_ROUND<D> / (s.causal ? 2 : 4) && s.seq > 64) return bwd_both<D, F16, 2>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
-  if (blocks <= ONE_ROUND<D>) return bwd_both<D, F16, 1>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
+  if (blocks <= room) return bwd_both<D, F16, 1>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
   {  // dQ first: it also produces delta = rowsum(dO * O), which the dK/dV kernel reads
     const size_t lds = lds_dq;
     auto kern = s.drop.thr ? attn_bwd_dq_bf16_kernel<D, true, F16> : attn_bwd_dq_bf16_kernel<D, false, F16>;

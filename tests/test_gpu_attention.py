@@ -225,3 +225,16 @@ def test_which_forward_grids_have_two_groups(batch, seq, heads, d, causal, rows)
         scores = scores.masked_fill(torch.ones(seq, seq, device=DEV, dtype=torch.bool).triu(1), float("-inf"))
     ref = torch.matmul(scores.softmax(-1), v.contiguous()).transpose(1, 2).reshape(batch * seq, H)
     assert err(out, ref.cpu().numpy()) <= TOL[W.BF16]
+
+
+# 128-wide heads without a causal mask: the most blocks whose dQ and dK/dV share a launch, with and without mask draws
+@pytest.mark.parametrize("batch,seq,pd,one", [(14, 200, 0.0, True), (15, 136, 0.0, False), (10, 136, 0.1, True), (11, 136, 0.1, False)])
+def test_which_backward_grids_are_one_launch(batch, seq, pd, one):
+    heads, d = 8, 128
+    test_attention_fwd_bwd(W.BF16, (batch, seq, heads, d, 0, None, 1.0) + ((pd,) if pd else ()))
+    desc = B.make_desc(W.LayerConfig("t", batch, seq, heads * d, heads, 64, causal=0, dtype=W.BF16, attn_dropout_p=pd))
+    qkv, out, dqkv = (torch.zeros(batch * seq, w * heads * d, device=DEV, dtype=torch.bfloat16) for w in (3, 1, 3))
+    lse, delta = (torch.zeros(batch, heads, seq, device=DEV) for _ in range(2))
+    grids = captured(lambda: B.slapo_attn_bwd(desc, qkv, None, out, out, lse, delta, dqkv), grids=True)
+    x = (seq + 127) // 128
+    assert grids == ([(2 * x * heads * batch, 1, 1)] if one else [(x, heads, batch)] * 2)
