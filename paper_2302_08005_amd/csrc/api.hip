@@ -198,15 +198,23 @@ bool backward_on_one_stream(const slapo_layer_desc* d) {
 // Whether backward puts each weight gradient into the launch of the data gradient beside it (GradPair): always on one
 // stream, whose calls are bound by the number of their launches; on two streams where the products are small enough that
 // the smaller tiles of those launches cost less than three of the four forks (only the gradient of the output projection
-// still goes to the helper stream, beside the attention kernels). Not for the gated layer there, whose rotary passes keep the
-// caller's stream busy while the helper stream works. Steps in us, every weight gradient forked / paired:
+// still goes to the helper stream, beside the attention kernels). Few tokens do not make the products small: with weights
+// beyond 64 million elements reading them and writing their gradients is most of the step, and plain launches on two
+// streams do that faster (fp32 products, which are bound by arithmetic, gain at every size). Not for the gated layer on
+// two streams: its wider products lose more to the smaller tiles than the forks cost, but for the narrowest layers.
+// Steps in us, every weight gradient forked / paired:
 //   classic  hidden 512, 2048 tokens 186 / 170; 768, 2286 261 / 246; 1024, 600 201 / 176, 2000 296 / 282, 4096 470 / 495;
 //            1536, 640 269 / 255, 3000 648 / 676; 2048, 384 280 / 272, 1500 477 / 493; 256, 4096 364 / 351, 8192 253 / 264
-//   gated    hidden 512, 2048 tokens 208 / 211; 1024, 600 216 / 216, 2000 327 / 338; 2048, 384 299 / 322
+//   few tokens, two machines: 2048 (50 M), 46 tokens 244 / 193, 189 / 193, 256 258 / 233, 240 / 238; 2304 (64 M), 128 227 / 233;
+//            2432 (71 M), 46 215 / 226; 2560 (79 M), 46 253 / 273, 128 260 / 305; 4096 (201 M), 128 486 / 568
+//   fp32     2560, 128 1271 / 1232; 4096, 16 1187 / 1125
+//   gated    hidden 512, 2048 tokens 194 / 180, 4000 257 / 272; 1024, 600 203 / 182, 1000 199 / 221, 2000 308 / 334; 2048, 384 268
+//            / 294, 600 354 / 361; 4096 (an eighth of the heads and columns), 2048 492 / 527
 bool gradients_paired(const slapo_layer_desc* d) {
   if (backward_on_one_stream(d)) return true;
   const double T = (double)d->batch * d->seq, H = d->hidden, F = d->ffn, A = attn_width(d);
-  return !is_llama(d) && T <= 4096.0 && (4.0 * H * A + 2.0 * H * F) * T <= 3.2e10;
+  const double weights = 4.0 * H * A + 2.0 * H * F;
+  return !is_llama(d) && T <= 4096.0 && weights * T <= 3.2e10 && (weights <= 6.4e7 || d->dtype == SLAPO_FP32);
 }
 
 // byte offsets of the regions of `saved`

@@ -79,3 +79,16 @@ def test_input_gradient_on_top_of_the_input_on_two_streams(c):
         assert err(x2, to_np(dx)) <= TOL[c.dtype]
         for k in W.PARAM_NAMES:
             assert err(layer.grads[k], to_np(want[k])) <= TOL[c.dtype], k
+
+
+# few tokens, many weights: beyond 64 million the gradients have a launch each (fp32: never)
+@pytest.mark.parametrize("hidden,tokens,dtype,paired", [(2048, 128, W.BF16, True), (2304, 16, W.FP16, True), (2560, 16, W.BF16, False),
+                                                        (2560, 16, W.FP32, True)])
+def test_which_calls_pair_their_gradients(hidden, tokens, dtype, paired):
+    c = cfg("few-tokens", 1, tokens, hidden, hidden // 128, 4 * hidden, dtype, pre_ln=1, causal=1)
+    errs, layer, (x, _, dy, _, dx) = run_case(c, check_saved=False)
+    assert all(v <= TOL[dtype] for v in errs.values()), errs
+    launches = captured(lambda: B.slapo_layer_bwd(layer.desc, layer.params, x, None, dy, layer.saved, dx, layer.grads, layer.scratch), grids=True)
+    # three row kernels, four products with the gradients beside them, the last sums, attention (one to three), the gradient
+    # of the output projection if it is forked; else eight products (and the second kernels of K ranges) and six sums
+    assert len(launches) <= 12 if paired else len(launches) >= 17
