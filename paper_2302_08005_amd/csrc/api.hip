@@ -659,6 +659,7 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   fork(2);
   dweight(H, A, dr1, attn, gr->wo);
   launch_gemm(dt, GEMM_NN, EPI_NONE, d->act, T, A, H, dr1, p->wo, t0, nullptr, nullptr, nullptr, st, solo, gws, gwb);
+  as.beside = side && splitk_ws;
   launch_attn_bwd(dt, as, qkv, seqlens, attn, t0, lse, delta, dqkv, st);
   fork(3);
   if (d->pre_ln) {

@@ -1659,9 +1659,14 @@ static void bwd_bf16(const AttnShape& s, const void* qkv, const int32_t* seqlens
   // 255 (15 x 2056) 159 / 166. With mask draws, 64-wide 16 blocks 18.7 / - / 9.2, 128 (1024, causal) 85 / - / 43, 256 (4 x 512) 48.5 /
   // 34.8, 512 (8 x 512) 70.5 / 65.3; 128-wide causal 256 116 / 85, not causal 160 (32 x 520) 69 / 61, 189 (21 x 1032) 122 / 130, 256
   // (4 x 512) 69.2 / 71.5.
+  // Beside weight gradients in K ranges (s.beside) two launches again from 129 to 256 blocks of 64-wide heads: one at a time
+  // they leave the half of every CU's LDS that a workgroup of those needs. Steps at hidden 256, two launches / one: 52 x 128 tokens
+  // 215 / 217 us, 10 x 670 234 / 246, 16 x 512 245 / 255, 7 x 1024 229 / 253, 8 x 1024 262 / 271; up to 6143 tokens, without K
+  // ranges, the other way round (7 x 670 218 / 206).
   const int64_t blocks = attn_blocks(s), room = D == 64 || s.causal ? ONE_ROUND<D> : s.drop.thr ? 160 : 224;
   if (blocks <= ONE_ROUND<D> / (s.causal ? 2 : 4) && s.seq > 64) return bwd_both<D, F16, 2>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
-  if (blocks <= room) return bwd_both<D, F16, 1>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
+  const bool make_way = D == 64 && s.beside && blocks > 128 && blocks <= 256;
+  if (blocks <= room && !make_way) return bwd_both<D, F16, 1>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
   {  // dQ first: it also produces delta = rowsum(dO * O), which the dK/dV kernel reads
     const size_t lds = lds_dq;
     auto kern = s.drop.thr ? attn_bwd_dq_bf16_kernel<D, true, F16> : attn_bwd_dq_bf16_kernel<D, false, F16>;

@@ -70,6 +70,7 @@ struct AttnShape {
   DropoutParams drop = {0u, 0u, 2u, 0u, 0u, 1.0f};
   // backward: (cos, sin) table of the rotation that queries and keys went through (NULL: none); dQ and dK are turned back
   const float* rope = nullptr;
+  bool beside = false;   // backward: another stream computes weight gradients in K ranges meanwhile
 };
 void launch_attn_fwd(int dtype, const AttnShape& s, const void* qkv, const int32_t* seqlens, void* out,
                      float* lse, hipStream_t st);

@@ -6,7 +6,7 @@ import torch
 import workloads as W
 from oracle import layer as L
 from paper_2302_08005_amd import binding as B
-from gpu_util import DEV, TOL, err, forks, to_np
+from gpu_util import DEV, TOL, captured, err, forks, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -291,3 +291,20 @@ def test_two_streams_accumulate_and_recompute(cfg, monkeypatch):
     monkeypatch.setitem(globals(), "SMALL", [cfg] * 5)
     test_layer_is_deterministic_and_accumulates()
     test_checkpoint_mode_recomputes_to_the_same_bits(0)
+
+
+# backward attention of a layer whose weight gradients run beside it in K ranges: two launches from 129 to 256 blocks
+@pytest.mark.parametrize("batch,seq,two", [(13, 512, True), (11, 512, False), (8, 1024, True), (17, 512, False)])
+def test_backward_attention_beside_weight_gradients_in_k_ranges(batch, seq, two):
+    cfg = W.LayerConfig("beside", batch, seq, 256, 4, 512, causal=0, dropout_p=0.1, dtype=W.BF16, config_id=75)
+    if two and batch > 8:
+        errs, layer, (x, _, dy, _, dx) = run_case(cfg, check_saved=False)
+        assert all(v <= TOL[cfg.dtype] for v in errs.values()), errs
+    else:
+        layer = B.Layer(cfg, W.make_params(cfg))
+        x = dy = torch.zeros(cfg.batch, seq, 256, dtype=layer.dt, device=DEV)
+    dx = torch.empty_like(x)
+    step = lambda: B.slapo_layer_bwd(layer.desc, layer.params, x, None, dy, layer.saved, dx, layer.grads, layer.scratch)
+    layer.forward(x)
+    assert forks(step)
+    assert captured(step, grids=True).count((seq // 128, 4, batch)) == (2 if two else 0)
