@@ -67,10 +67,16 @@ def captured(step, grids=False):
     return out
 
 
-def forks(step):
-    """True if the work that `step` enqueues branches off the caller's stream: captured, it is then no mere chain."""
+def branches(step):
+    """How often the work that `step` enqueues leaves the caller's stream and comes back: captured, the edges beyond a chain's.
+    Backward with every weight gradient on the helper stream: 3 (one per fork but the first); with the gradients in the
+    launches of the data gradients and only that of the output projection there: 1."""
     step()                                          # (first-call set-up stays outside the capture)
     torch.cuda.synchronize()
     nodes, edges = captured(step)
     assert nodes > 1
-    return edges != nodes - 1
+    return edges - (nodes - 1)
+
+
+def forks(step):
+    return branches(step) != 0

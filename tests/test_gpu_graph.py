@@ -54,11 +54,13 @@ def test_captured_step_replays_to_the_same_bits(cfg):
             assert torch.equal(g, w), (replay, i)
 
 
-# above the size from which backward forks onto the helper stream (CASES stay below it)
+# above the size from which backward forks onto the helper stream (CASES stay below it): once, and with every weight gradient
 @pytest.mark.parametrize("cfg", [
     W.LayerConfig("graph-two-streams-postln-bf16", 6, 381, 768, 12, 3072, causal=0, dropout_p=0.1, dtype=W.BF16, len_lo=50, len_hi=381, config_id=53),
     W.LayerConfig("graph-two-streams-llama-bf16-checkpoint", 4, 256, 1024, 8, 2752, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1,
                   ln_eps=1e-6, arch=W.LLAMA, config_id=54),
+    W.LayerConfig("graph-forked-postln-bf16", 5, 1000, 512, 8, 1024, causal=0, dropout_p=0.1, dtype=W.BF16, len_lo=300, len_hi=1000, config_id=55),
+    W.LayerConfig("graph-forked-preln-bf16-checkpoint", 5, 1000, 256, 4, 512, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, config_id=56),
 ], ids=lambda c: c.name)
 def test_captured_step_on_two_streams_replays_to_the_same_bits(cfg):
     test_captured_step_replays_to_the_same_bits(cfg)

@@ -6,7 +6,7 @@ import torch
 import workloads as W
 from oracle import layer as L
 from paper_2302_08005_amd import binding as B
-from gpu_util import DEV, TOL, captured, err, forks, to_np
+from gpu_util import DEV, TOL, branches, captured, err, forks, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -254,7 +254,7 @@ def test_layer_parity_on_either_side_of_the_stream_rule(seq):
 
 
 def test_two_host_threads_share_the_helper_stream(monkeypatch):
-    """The test above at sizes whose backward forks."""
+    """The test above at sizes whose backward forks once (all weight gradients: test_two_host_threads_share_several_forks)."""
     big = [W.LayerConfig("threads-%d" % b, b, 200, 1024, 16, 4096, causal=0, dropout_p=0.1, dtype=W.BF16, config_id=62 + b) for b in (3, 4)]
     monkeypatch.setitem(globals(), "SMALL", [None] * 4 + big)
     test_backward_from_two_host_threads_on_one_device()
@@ -275,7 +275,8 @@ def test_which_calls_fork_onto_the_helper_stream(batch, seq, hidden, heads, dtyp
     assert forks(lambda: B.slapo_layer_bwd(layer.desc, layer.params, x, None, dy, layer.saved, dx, layer.grads, layer.scratch)) == two
 
 
-# the same checks at sizes whose backward forks: gradient accumulation, and checkpoint against plain for either wiring
+# the same checks at sizes whose backward forks (here the gradient of the output projection only; all of them: FORKED below):
+# gradient accumulation, and checkpoint against plain for either wiring
 FORKING = [
     W.LayerConfig("two-streams-postln-bf16", 4, 512, 512, 8, 1024, causal=0, dropout_p=0.1, dtype=W.BF16, len_lo=200, len_hi=512, config_id=72),
     W.LayerConfig("two-streams-preln-fp16-d128", 4, 512, 512, 4, 1024, causal=1, dropout_p=0.1, dtype=W.FP16, pre_ln=1, config_id=73),
@@ -308,3 +309,32 @@ def test_backward_attention_beside_weight_gradients_in_k_ranges(batch, seq, two)
     layer.forward(x)
     assert forks(step)
     assert captured(step, grids=True).count((seq // 128, 4, batch)) == (2 if two else 0)
+
+
+# beyond the size up to which weight gradients share the launches of the data gradients: four forks per backward
+FORKED = [
+    W.LayerConfig("forked-postln-bf16", 5, 1000, 512, 8, 1024, causal=0, dropout_p=0.1, dtype=W.BF16, len_lo=300, len_hi=1000, config_id=76),
+    W.LayerConfig("forked-preln-fp16-d128", 5, 1000, 512, 4, 1024, causal=1, dropout_p=0.1, dtype=W.FP16, pre_ln=1, config_id=77),
+]
+
+
+def backward_branches(cfg):
+    layer = B.Layer(cfg, W.make_params(cfg))
+    x = torch.zeros(cfg.batch, cfg.seq, cfg.hidden, dtype=layer.dt, device=DEV)
+    layer.forward(x, None)
+    dx = torch.empty_like(x)
+    return branches(lambda: B.slapo_layer_bwd(layer.desc, layer.params, x, None, x, layer.saved, dx, layer.grads, layer.scratch))
+
+
+@pytest.mark.parametrize("cfg", FORKED, ids=lambda c: c.name)
+def test_every_weight_gradient_forked_accumulates_and_recomputes(cfg, monkeypatch):
+    assert backward_branches(cfg) == 3
+    assert backward_branches(FORKING[0]) == 1
+    monkeypatch.setitem(globals(), "SMALL", [cfg] * 5)
+    test_layer_is_deterministic_and_accumulates()
+    test_checkpoint_mode_recomputes_to_the_same_bits(0)
+
+
+def test_two_host_threads_share_several_forks(monkeypatch):
+    monkeypatch.setitem(globals(), "SMALL", [None] * 4 + FORKED)
+    test_backward_from_two_host_threads_on_one_device()

@@ -13,7 +13,7 @@ import workloads as W
 from oracle import layer as L
 from oracle import llama_layer as LL
 from paper_2302_08005_amd import binding as B
-from gpu_util import DEV, TOL, err, forks
+from gpu_util import DEV, TOL, branches, err, forks
 
 pytestmark = pytest.mark.gpu
 
@@ -194,8 +194,8 @@ def test_full_size_24_layer_stack_layers_0_1_12_23():
         assert not bad, (l, bad, errs)
 
 
-# Stacks whose backward forks: each pre-LN layer then hands the branch gradient of the layer below over from one stream to
-# the other (two alternating buffers that the weight gradients of the helper stream read too).
+# Stacks whose backward forks: the gated one with every weight gradient, the classic ones with that of the output projection
+# only (their others share the launches of the data gradients).
 @pytest.mark.parametrize("cfg", [
     W.LayerConfig("two-streams-stack-preln-bf16", 4, 512, 512, 8, 1024, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, config_id=25),
     W.LayerConfig("two-streams-stack-llama-bf16", 4, 512, 256, 2, 688, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, ln_eps=1e-6,
@@ -207,4 +207,15 @@ def test_stack_on_two_streams(cfg):
     x = torch.zeros(cfg.batch, cfg.seq, cfg.hidden, dtype=st.dt, device=DEV)
     st.forward(x, None)
     assert forks(lambda: st.backward(x, None, x))
+    test_stack_matches_oracle_chain_and_single_layer_calls(cfg)
+
+
+def test_stack_with_every_weight_gradient_forked():
+    """Each pre-LN layer hands the dropped branch gradient of the layer below, with its b2 sums, over from one stream to the
+    other (two alternating buffers that the weight gradients of the helper stream read too)."""
+    cfg = W.LayerConfig("forked-stack-preln-bf16", 5, 1000, 256, 4, 512, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, config_id=28)
+    st = B.Stack(cfg, [W.make_params(cfg, layer_id=l) for l in range(N_LAYERS)])
+    x = torch.zeros(cfg.batch, cfg.seq, cfg.hidden, dtype=st.dt, device=DEV)
+    st.forward(x, None)
+    assert branches(lambda: st.backward(x, None, x)) >= 3 * N_LAYERS
     test_stack_matches_oracle_chain_and_single_layer_calls(cfg)
