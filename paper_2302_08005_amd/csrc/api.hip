@@ -32,7 +32,7 @@ int check_desc(const slapo_layer_desc* d) {
   const int hd = attn_width(d) / d->heads;
   if (hd != 64 && hd != 128) return SLAPO_ERR_UNSUPPORTED;
   if (d->hidden > 8192) return SLAPO_ERR_UNSUPPORTED;   // the row kernels hold a row per wavefront / per block
-  // the fp32 (correctness-mode) attention keeps two score rows per wavefront in LDS: 16 (2 d + 2 seq) bytes per block
+  // fp32 (correctness mode): beyond 1024 tokens dK/dV keeps two score rows per wavefront in LDS, 16 (2 d + 2 seq) bytes per block
   if (d->dtype == SLAPO_FP32 && (int64_t)16 * (2 * hd + 2 * (int64_t)d->seq) > 160 * 1024) return SLAPO_ERR_UNSUPPORTED;
   if (d->dtype != SLAPO_BF16 && d->dtype != SLAPO_FP32 && d->dtype != SLAPO_FP16) return SLAPO_ERR_UNSUPPORTED;
   if (d->act != SLAPO_GELU_ERF && d->act != SLAPO_RELU) return SLAPO_ERR_UNSUPPORTED;
@@ -171,8 +171,8 @@ SideStream* side_stream() {
 }
 
 // Small calls keep all of backward on the caller's stream. The forks and the join of two streams cost the host about as
-// much as the layer's 27 launches (a step's calls take 150-210 us instead of 85-130, by machine and moment), so two streams
-// pay where the step keeps the GPU busy for about that long and the weight gradients, whose few workgroups walk all tokens,
+// much as the launches of a layer that has one per product (a step's calls take 150-210 us instead of 85-130, by machine and
+// moment), so two streams pay where the step keeps the GPU busy for about that long and the weight gradients, whose few workgroups walk all tokens,
 // leave the chip to the data gradients beside them. The rule estimates the GPU's time for a step on one stream, in us:
 // launches; multiply-adds of the projections, with 300 tokens' worth for the weights that each call reads and writes
 // whatever its size (fp32 products take eight times as long); row work and the weight gradients' walk, per token, at a third
@@ -186,8 +186,9 @@ SideStream* side_stream() {
 //   hidden 512   1024 of 128: 156 / 161 (164); 1536 of 128: 177 / 159 (186); 2048 of 128: 194 / 165, 193 / 206 (208)
 //   hidden 768   512 of 128: 174 / 191 (155); 1024 of 128: 193 / 180 (186), of 1024: 242 / 227 (226)
 //   hidden 1024  128: 157 / 200 (142); 512 of 128: 185 / 201 (174); 1024 of 128: 230 / 218 (216)
-// These are figures of one product per launch. With paired launches (gradients_paired) one stream is the faster form beyond
-// the line too (hidden 1024, 600 tokens: 162 / 176 us; 512, 2048 159 / 170); which calls fork is kept as callers know it.
+// These figures, and the constants made from them, are of one product per launch. With paired launches (gradients_paired) a
+// step on one stream has 15 to 17 launches, and one stream is the faster form beyond the line too (hidden 1024, 600 tokens: 162 /
+// 176 us; 512, 2048 159 / 170); the line is kept where it was, and beyond it paired calls fork once.
 bool backward_on_one_stream(const slapo_layer_desc* d) {
   const double T = (double)d->batch * d->seq, H = d->hidden, F = d->ffn, A = attn_width(d);
   const double weights = 4.0 * H * A + (is_llama(d) ? 3.0 : 2.0) * H * F;
@@ -533,7 +534,8 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   auto reduce_rows = [&](void* dgamma, void* dbeta, void* dbias) {
     launch_colreduce3(dt, nrow, H, prow, dgamma, dbeta, dbias, acc, st);
   };
-  // Buffers: t0 dZ2 -> dY1/dN2 -> dA -> dN1; t1 dR2 (kept for dW2); t2 dZ1; t3 dR1 (kept for dWo).
+  // Buffers: t0 dZ2 -> dY1/dN2 -> dA -> dN1; t1 dR2 (kept for dW2); t2 dZ1; t3 dR1 (kept for dWo). Where nothing is dropped
+  // dR1 is t2, and dR2 is dy (pre-LN, dx elsewhere) or, in the paired post-LN launches, t0.
   void* dr1 = keeps_all ? t2 : t3;
 
   const bool llama = is_llama(d);

@@ -3,18 +3,20 @@
 // matched scaled-dot-product pattern). Works in place on the packed projection [B,S,3H] = Q | K | V,
 // so no head transposes are materialised.
 //
-// bf16 path. A workgroup of four wavefronts owns 128 query rows (forward, dQ) or 128 key rows (dK/dV)
-// of one (sample, head); each wavefront owns 32 of them and walks the other sequence dimension in
-// 64-row tiles brought into two LDS stages by direct global -> LDS loads (one barrier per tile). All products run on
+// 16-bit path. A workgroup of four wavefronts owns 128 query rows (forward, dQ) or 128 key rows (dK/dV) of one (sample,
+// head), or 64 in small grids, whose wavefronts then form two groups that share the walk (group_slot); each wavefront
+// owns 32 of them and walks the other sequence dimension in 64-row tiles brought into two LDS stages by direct global -> LDS loads (one barrier per tile). All products run on
 // v_mfma_f32_32x32x16_bf16 and are arranged "transposed" (S^T = K Q^T, O^T = V^T P^T, ...), because
 // then the accumulator layout of the score tile already is the B-operand layout of the next product
 // and the per-row softmax state (max, sum, logsumexp, delta) is one scalar per lane; a row's maximum
 // and sum need the lane's own 16..32 registers plus a single exchange with lane^32. The operand whose
 // contraction index is the strided one in LDS is fetched with the transposing ds_read_b64_tr_b16.
-// Backward recomputes the probabilities from the saved logsumexp and is split in two kernels (dK/dV
-// per key tile, dQ per query tile) so that no floating-point atomics are needed.
+// Backward recomputes the probabilities from the saved logsumexp and is split in two kinds of blocks (dK/dV
+// per key tile, dQ per query tile) so that no floating-point atomics are needed: two kernels, or one launch of both kinds
+// where neither fills the chip (attn_bwd_both_kernel).
 //
-// fp32 path: one wavefront per row, plain loops (correctness mode).
+// fp32 path (correctness mode): up to 1024 tokens fp32 MFMAs on 16 rows per workgroup, whose scores stay in LDS; longer
+// sequences one wavefront per row, plain loops.
 #include <type_traits>
 
 #include "common.h"
@@ -1120,6 +1122,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_both_kernel(Att
     attn_bwd_dkdv_block<D, DROP, F16, OWN_DELTAS<D, G>, G>(xcd_local_block(w, blocks_x, sh.heads, sh.batch, false, sh.lpt_heads), sh, qkv,
                                                            seqlens, out, dout, lse, delta, dqkv);
   else
+    // (with deltas of the other kind's own, `delta` is left filled all the same, as by the other forms)
     attn_bwd_dq_block<D, DROP, F16, G>(xcd_local_block(w - blocks, blocks_x, sh.heads, sh.batch, sh.causal != 0, sh.lpt_heads), sh, qkv,
                                        seqlens, out, dout, lse, OWN_DELTAS<D, G> ? delta : nullptr, dqkv);
 }
