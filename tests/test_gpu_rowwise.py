@@ -108,3 +108,35 @@ def test_column_sums(dtype, T, N):
     assert err(out, a.astype(np.float64).sum(0)) <= TOL[dtype]
     B.slapo_colreduce_partials(dtype, nblk, N, N, part, out, 1)     # accumulate on top
     assert err(out, 2 * a.astype(np.float64).sum(0)) <= 2 * TOL[dtype]
+
+
+# the instances that draw a mask and those that do not (4e-6 is below half a step of the draw: nothing is dropped, the scale
+# stays), at every kind of row kernel; dr_out on dz_out leaves the branch's gradient
+@pytest.mark.parametrize("dtype", [W.FP32, W.BF16, W.FP16])
+@pytest.mark.parametrize("p", [0.0, 4e-6, 0.25])
+@pytest.mark.parametrize("T,H", [(37, 256), (16, 512), (515, 1024), (19, 2560), (64, 4096), (70, 5120)])
+def test_rows_with_and_without_mask_draws(dtype, p, T, H):
+    gen = torch.Generator(device=DEV).manual_seed(T + H)
+    d = B.make_desc(batch=1, seq=T, hidden=H, heads=H // 64, ffn=64, dropout_p=p, seed=9, layer_id=2, dtype=dtype)
+    r, res, dy, dres = (torch.randn(T, H, device=DEV, generator=gen).to(tdtype(dtype)) for _ in range(4))
+    bias, gamma, beta = (torch.randn(H, device=DEV, generator=gen).to(tdtype(dtype)) for _ in range(3))
+    keep = torch.from_numpy(philox.keep_mask(T * H, p, 9, 0, 2).reshape(T, H)).to(DEV).double()
+    assert bool((keep == 1).all()) == (p < 0.1)
+    new = lambda: torch.empty_like(r)
+    z, y, dz, dr, one = new(), new(), new(), new(), new()
+    mu, rstd = (torch.empty(T, device=DEV) for _ in range(2))
+    B.slapo_bdrln_fwd(d, 0, T, r, bias, res, gamma, beta, z, y, mu, rstd)
+    want = res.double() + keep * (r.double() + bias.double()) / (1 - p)
+    norm = torch.nn.functional.layer_norm(want, (H,), gamma.double(), beta.double(), 1e-5)
+    assert err(z, want.cpu().numpy()) <= TOL[dtype] and err(y, norm.cpu().numpy()) <= TOL[dtype]
+    n = B.slapo_bdrln_bwd_blocks(T)
+    part, part2 = (torch.full((n, 3, H), 7.0, device=DEV) for _ in range(2))
+    B.slapo_bdrln_bwd(d, 0, T, dy, z, mu, rstd, gamma, dres, dz, dr, part)
+    zz = z.double().requires_grad_()
+    torch.nn.functional.layer_norm(zz, (H,), gamma.double(), beta.double(), 1e-5).backward(dy.double())
+    wz = zz.grad + dres.double()
+    wr = keep * wz / (1 - p)
+    assert err(dz, wz.cpu().numpy()) <= TOL[dtype] and err(dr, wr.cpu().numpy()) <= TOL[dtype]
+    assert err(part[:, 2].double().sum(0), wr.sum(0).cpu().numpy()) <= TOL[dtype]
+    B.slapo_bdrln_bwd(d, 0, T, dy, z, mu, rstd, gamma, dres, one, one, part2)
+    assert torch.equal(one, dr) and torch.equal(part, part2)
