@@ -288,6 +288,12 @@ ScratchLayout scratch_layout(const slapo_layer_desc* d) {
     upto(gemm_ws_bytes(d->dtype, GEMM_NN, EPI_NONE, Ti, Hi, F1));                             // gradient of the FFN input
     upto(gemm_ws_bytes(d->dtype, GEMM_NN, EPI_NONE, Ti, Ai, Hi));                             // gradient of the attention output
     upto(gemm_ws_bytes(d->dtype, GEMM_NN, EPI_NONE, Ti, Hi, 3 * Ai));                         // gradient of the attention input
+    // and for the products that the row kernels read in K ranges
+    auto ranges = [&](int K) {
+      const int r = product_ranges(d->dtype, Ti, Hi, K);
+      if (r > 1) upto((size_t)r * T * H * sizeof(float));
+    };
+    ranges(Ai); ranges(Fi); ranges(3 * Ai);
     L.gemm_ws = g ? take(g) : 0;
     L.gemm_ws_bytes = g;
   }
@@ -403,11 +409,23 @@ static void run_forward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   }
   launch_attn_fwd(dt, as, qkv, seqlens, attn, lse, st);
   float* gws = W.gemm_ws_bytes ? (float*)(sc + W.gemm_ws) : nullptr;   // for GEMMs whose tile grid ends in a thin round
-  launch_gemm(dt, GEMM_NT, EPI_NONE, d->act, T, H, A, attn, p->wo, r, nullptr, nullptr, nullptr, st, true, gws, W.gemm_ws_bytes);
+  // Output projections: the row kernel behind reads them, in K ranges where few tokens make few tiles.
+  int ranges = 0;
+  auto project = [&](int K, const void* a, const void* w) -> const void* {
+    ranges = product_ranges(dt, T, H, K);
+    if (ranges > 1) {
+      launch_gemm_ranges(dt, GEMM_NT, ranges, T, H, K, a, w, gws, st);
+      return gws;
+    }
+    ranges = 0;
+    launch_gemm(dt, GEMM_NT, EPI_NONE, d->act, T, H, K, a, w, r, nullptr, nullptr, nullptr, st, true, gws, W.gemm_ws_bytes);
+    return r;
+  };
+  const void* ro = project(A, attn, p->wo);
   const void* bo = llama ? nullptr : p->bo;
   const void* b2 = llama ? nullptr : p->b2;
-  if (d->pre_ln) launch_bdrln_fwd(dt, T, H, r, bo, x, p->ln2_g, p->ln2_b, z1, y1, mu2, rstd2, dp0, d->ln_eps, rms, st);
-  else launch_bdrln_fwd(dt, T, H, r, bo, x, p->ln1_g, p->ln1_b, z1, y1, mu1, rstd1, dp0, d->ln_eps, rms, st);
+  if (d->pre_ln) launch_bdrln_fwd(dt, T, H, ro, bo, x, p->ln2_g, p->ln2_b, z1, y1, mu2, rstd2, dp0, d->ln_eps, rms, st, ranges);
+  else launch_bdrln_fwd(dt, T, H, ro, bo, x, p->ln1_g, p->ln1_b, z1, y1, mu1, rstd1, dp0, d->ln_eps, rms, st, ranges);
   if (llama)   // w1 holds (gate, up) row pairs: one product, gated in the epilogue; `u` keeps the backward factors
     launch_gemm(dt, GEMM_NT, EPI_GATE, d->act, T, 2 * F, H, y1, p->w1, g, nullptr, nullptr, u, st, true);
   else
@@ -415,16 +433,16 @@ static void run_forward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   // Backward of a pre-LN layer reads nothing downstream of the activation output (its last step has no
   // LayerNorm whose input would have to be kept), so a recomputation stops here: one GEMM in six less.
   if (for_backward && d->pre_ln) return;
-  launch_gemm(dt, GEMM_NT, EPI_NONE, d->act, T, H, F, g, p->w2, r, nullptr, nullptr, nullptr, st, true, gws, W.gemm_ws_bytes);
+  const void* r2 = project(F, g, p->w2);
   if (d->pre_ln && link && link->above) {
     char* up = (char*)link->above_saved;
-    launch_bdrln_fwd(dt, T, H, r, b2, z1, link->above->ln1_g, llama ? nullptr : link->above->ln1_b, y, up + L.n1,
-                     (float*)(up + L.mu1), (float*)(up + L.rstd1), dp1, d->ln_eps, rms, st);
+    launch_bdrln_fwd(dt, T, H, r2, b2, z1, link->above->ln1_g, llama ? nullptr : link->above->ln1_b, y, up + L.n1,
+                     (float*)(up + L.mu1), (float*)(up + L.rstd1), dp1, d->ln_eps, rms, st, ranges);
   } else if (d->pre_ln) {
-    launch_bdrln_fwd(dt, T, H, r, b2, z1, nullptr, nullptr, y, nullptr, nullptr, nullptr, dp1, d->ln_eps, rms, st);
+    launch_bdrln_fwd(dt, T, H, r2, b2, z1, nullptr, nullptr, y, nullptr, nullptr, nullptr, dp1, d->ln_eps, rms, st, ranges);
   } else {
     void* z2 = sv + L.z2;
-    launch_bdrln_fwd(dt, T, H, r, b2, y1, p->ln2_g, p->ln2_b, z2, y, mu2, rstd2, dp1, d->ln_eps, rms, st);
+    launch_bdrln_fwd(dt, T, H, r2, b2, y1, p->ln2_g, p->ln2_b, z2, y, mu2, rstd2, dp1, d->ln_eps, rms, st, ranges);
   }
 }
 
@@ -534,6 +552,15 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   auto reduce_rows = [&](void* dgamma, void* dbeta, void* dbias) {
     launch_colreduce3(dt, nrow, H, prow, dgamma, dbeta, dbias, acc, st);
   };
+  // The gradient of a block's input, [T,H], which a row kernel reads next: t0, or K ranges in gws where few tokens make few tiles
+  // (`add`, what the product is added to, is then the row kernel's to add). Not the feed-forward block's of the gated layer, whose
+  // gradients are, bit for bit, those of the exported products, rotary turn and attention in a row (1024, 128 tokens: 2 us).
+  const int r_y1 = is_llama(d) ? 1 : product_ranges(dt, T, H, F), r_x = product_ranges(dt, T, H, 3 * A);
+  auto row_bwd = [&](int ranges, const void* add, const void* z, const float* mu, const float* rstd, const void* gamma, const void* dres,
+                     void* dz, void* dr, const DropoutParams& dp, int dr_from_stored) {
+    launch_bdrln_bwd(dt, T, H, ranges > 1 ? gws : t0, z, mu, rstd, gamma, dres, dz, dr, prow, dp, is_llama(d) ? 1 : 0, st, dr_from_stored, nrow,
+                     ranges > 1 ? ranges : 0, ranges > 1 ? add : nullptr);
+  };
   // Buffers: t0 dZ2 -> dY1/dN2 -> dA -> dN1; t1 dR2 (kept for dW2); t2 dZ1; t3 dR1 (kept for dWo). Where nothing is dropped
   // dR1 is t2, and dR2 is dy (pre-LN, dx elsewhere) or, in the paired post-LN launches, t0.
   void* dr1 = keeps_all ? t2 : t3;
@@ -584,14 +611,15 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     weight(H, F, dr2, g, gr->w2, db2);
     launch();
     data(EPI_ADD, T, H, F1, du, p->w1, t0, d->pre_ln ? nullptr : t0);
+    if (r_y1 > 1) { pr.parts = gws; pr.ranges = r_y1; }
     weight(F1, H, du, y1, gr->w1, llama ? nullptr : gr->b1);
     launch();
     // ---- attention block ----
     if (d->pre_ln) {
-      launch_bdrln_bwd(dt, T, H, t0, z1, mu2, rstd2, p->ln2_g, dy, t2, dr1, prow, dp0, rms, st, 0, nrow);
+      row_bwd(r_y1, nullptr, z1, mu2, rstd2, p->ln2_g, dy, t2, dr1, dp0, 0);
       take_sums(gr->ln2_g, g_ln2_b, g_bo);
     } else {
-      launch_bdrln_bwd(dt, T, H, t0, z1, mu1, rstd1, p->ln1_g, nullptr, t2, dr1, prow, dp0, rms, st, 0, nrow);
+      row_bwd(r_y1, t0, z1, mu1, rstd1, p->ln1_g, nullptr, t2, dr1, dp0, 0);
       take_sums(gr->ln1_g, g_ln1_b, g_bo);
     }
     data(EPI_ADD, T, A, H, dr1, p->wo, t0, nullptr);
@@ -605,16 +633,18 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     launch_attn_bwd(dt, as, qkv, seqlens, attn, t0, lse, delta, dqkv, st);
     if (side) side->order(side->join, ws, st);   // the gradient of the output projection has long been there
     data(EPI_ADD, T, H, 3 * A, dqkv, p->wqkv, d->pre_ln ? t0 : dx, d->pre_ln ? nullptr : t2);
+    if (r_x > 1) { pr.parts = gws; pr.ranges = r_x; }
     weight(3 * A, H, dqkv, d->pre_ln ? sv + L.n1 : x, gr->wqkv, llama ? nullptr : gr->bqkv);
     launch();
+    if (!d->pre_ln && r_x > 1) launch_add_ranges(dt, (int64_t)T * H, r_x, gws, t2, dx, st);
     if (d->pre_ln && keeps_all && link && link->below) {
-      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, prow, dp0, rms, st, 0, nrow);
+      row_bwd(r_x, nullptr, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, dp0, 0);
       link->sums[0] = gr->ln1_g; link->sums[1] = g_ln1_b; link->sums[2] = nullptr;
     } else if (d->pre_ln && link && link->dr2_below) {
-      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, link->dr2_below, prow, link->dp_below, rms, st, 1, nrow);
+      row_bwd(r_x, nullptr, x, mu1, rstd1, p->ln1_g, t2, dx, link->dr2_below, link->dp_below, 1);
       link->sums[0] = gr->ln1_g; link->sums[1] = g_ln1_b; link->sums[2] = link->db2_below;
     } else if (d->pre_ln) {
-      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, prow, dp0, rms, st, 0, nrow);
+      row_bwd(r_x, nullptr, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, dp0, 0);
       reduce_rows(gr->ln1_g, g_ln1_b, nullptr);
     }
     return finish();
@@ -641,21 +671,23 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     launch_gemm(dt, GEMM_NN, EPI_DGATE, d->act, T, F, H, dr2, p->w2, du, nullptr, u, nullptr, st, solo);
     fork(1);
     dweight(2 * F, H, du, y1, gr->w1);
-    launch_gemm(dt, GEMM_NN, EPI_NONE, d->act, T, H, 2 * F, du, p->w1, t0, nullptr, nullptr, nullptr, st, solo, gws, gwb);
+    if (r_y1 > 1) launch_gemm_ranges(dt, GEMM_NN, r_y1, T, H, 2 * F, du, p->w1, gws, st);
+    else launch_gemm(dt, GEMM_NN, EPI_NONE, d->act, T, H, 2 * F, du, p->w1, t0, nullptr, nullptr, nullptr, st, solo, gws, gwb);
   } else {
     launch_gemm(dt, GEMM_NN, EPI_DACT, d->act, T, F, H, dr2, p->w2, du, nullptr, u, nullptr, st, solo);
     fork(1);
     colsum(du, F, gr->b1, ws);
     dweight(F, H, du, y1, gr->w1);
-    if (d->pre_ln) launch_gemm(dt, GEMM_NN, EPI_NONE, d->act, T, H, F, du, p->w1, t0, nullptr, nullptr, nullptr, st, solo, gws, gwb);
+    if (r_y1 > 1) launch_gemm_ranges(dt, GEMM_NN, r_y1, T, H, F, du, p->w1, gws, st);
+    else if (d->pre_ln) launch_gemm(dt, GEMM_NN, EPI_NONE, d->act, T, H, F, du, p->w1, t0, nullptr, nullptr, nullptr, st, solo, gws, gwb);
     else launch_gemm(dt, GEMM_NN, EPI_ADD, d->act, T, H, F, du, p->w1, t0, nullptr, t0, nullptr, st, solo, gws, gwb);
   }
   // ---- attention block ----
   if (d->pre_ln) {
-    launch_bdrln_bwd(dt, T, H, t0, z1, mu2, rstd2, p->ln2_g, dy, t2, dr1, prow, dp0, rms, st, 0, nrow);
+    row_bwd(r_y1, nullptr, z1, mu2, rstd2, p->ln2_g, dy, t2, dr1, dp0, 0);
     reduce_rows(gr->ln2_g, g_ln2_b, g_bo);
   } else {
-    launch_bdrln_bwd(dt, T, H, t0, z1, mu1, rstd1, p->ln1_g, nullptr, t2, dr1, prow, dp0, rms, st, 0, nrow);
+    row_bwd(r_y1, t0, z1, mu1, rstd1, p->ln1_g, nullptr, t2, dr1, dp0, 0);
     reduce_rows(gr->ln1_g, g_ln1_b, g_bo);
   }
   fork(2);
@@ -666,13 +698,14 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   fork(3);
   if (d->pre_ln) {
     dweight(3 * A, H, dqkv, sv + L.n1, gr->wqkv);
-    launch_gemm(dt, GEMM_NN, EPI_NONE, d->act, T, H, 3 * A, dqkv, p->wqkv, t0, nullptr, nullptr, nullptr, st, solo, gws, gwb);
+    if (r_x > 1) launch_gemm_ranges(dt, GEMM_NN, r_x, T, H, 3 * A, dqkv, p->wqkv, gws, st);
+    else launch_gemm(dt, GEMM_NN, EPI_NONE, d->act, T, H, 3 * A, dqkv, p->wqkv, t0, nullptr, nullptr, nullptr, st, solo, gws, gwb);
     if (link && link->dr2_below) {
       // (from the stored dx, so that the layer below sees what it would compute from dx itself, bit for bit)
-      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, link->dr2_below, prow, link->dp_below, rms, st, 1, nrow);
+      row_bwd(r_x, nullptr, x, mu1, rstd1, p->ln1_g, t2, dx, link->dr2_below, link->dp_below, 1);
       reduce_rows(gr->ln1_g, g_ln1_b, link->db2_below);
     } else {
-      launch_bdrln_bwd(dt, T, H, t0, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, prow, dp0, rms, st, 0, nrow);
+      row_bwd(r_x, nullptr, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, dp0, 0);
       reduce_rows(gr->ln1_g, g_ln1_b, nullptr);
     }
   } else {

@@ -282,11 +282,11 @@ static void launch_bf16(int epi, int act, int M, int N, int K, const void* A, co
 }
 
 // ---- weight gradients with few output tiles: several K ranges per tile ---------------------------------
-// C (+)= sum over the ranges of the fp32 partial tiles, added in range order (so the result does not depend on
-// which workgroup finished first), eight columns per thread.
+// C = sum over the ranges of the fp32 partial products, added in range order (so the result does not depend on
+// which workgroup finished first), + addend (may be C itself), eight columns per thread.
 template <typename T>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(int64_t chunks, int64_t mn, int splits,
-                                                            const float* __restrict__ ws, T* C, int accumulate) {
+                                                            const float* __restrict__ ws, T* C, const T* addend) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= chunks) return;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -296,13 +296,21 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(int64_t chunks, int6
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] += v[e];
   }
-  if (accumulate) {
+  if (addend) {
     float v[8];
-    load8(C + i * 8, v);
+    load8(addend + i * 8, v);
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] += v[e];
   }
   store8(C + i * 8, acc);
+}
+
+void launch_add_ranges(int dtype, int64_t mn, int ranges, const float* parts, const void* addend, void* out, hipStream_t st) {
+  const int64_t chunks = mn / 8;
+  const dim3 grid((unsigned)((chunks + 255) / 256));
+  if (dtype == DT_FP32) hipLaunchKernelGGL(splitk_reduce_kernel<float>, grid, dim3(256), 0, st, chunks, mn, ranges, parts, (float*)out, (const float*)addend);
+  else if (dtype == DT_FP16) hipLaunchKernelGGL(splitk_reduce_kernel<f16_t>, grid, dim3(256), 0, st, chunks, mn, ranges, parts, (f16_t*)out, (const f16_t*)addend);
+  else hipLaunchKernelGGL(splitk_reduce_kernel<bf16_t>, grid, dim3(256), 0, st, chunks, mn, ranges, parts, (bf16_t*)out, (const bf16_t*)addend);
 }
 
 // Number of K ranges for a weight gradient: 1 (plain GEMM) unless the 128x128 tiles leave most of the chip idle
@@ -353,10 +361,52 @@ static void launch_splitk(int splits, int accumulate, int M, int N, int K, const
   hipLaunchKernelGGL(kern, dim3(tiles * splits), dim3((2 * 2 * 2 + 4) * 64), lds, st, M, N, K, (const bf16_t*)A,
                      (const bf16_t*)B, (bf16_t*)C, (const bf16_t*)nullptr, (const bf16_t*)nullptr,
                      reinterpret_cast<bf16_t*>(ws), splits, tiles * splits, 1, (float*)nullptr);
-  const int64_t mn = (int64_t)M * N, chunks = mn / 8;
-  const dim3 grid((unsigned)((chunks + 255) / 256));
-  if (F16) hipLaunchKernelGGL(splitk_reduce_kernel<f16_t>, grid, dim3(256), 0, st, chunks, mn, splits, ws, (f16_t*)C, accumulate);
-  else hipLaunchKernelGGL(splitk_reduce_kernel<bf16_t>, grid, dim3(256), 0, st, chunks, mn, splits, ws, (bf16_t*)C, accumulate);
+  launch_add_ranges(F16 ? DT_FP16 : DT_BF16, (int64_t)M * N, splits, ws, accumulate ? C : nullptr, C, st);
+}
+
+// ---- products of few tokens: K ranges that the reader adds up -----------------------------------------
+// A [T, hidden] product of few tokens is a handful of 64x64 tiles, each a chain of slabs that one workgroup fetches by itself
+// at 40 of the 64 bytes per clock its CU can load (128 x 1024 x 4096: 32 tiles of 64 slabs, 13-17 us). Four ranges of K bring
+// three more CUs per tile in, and the row kernel that reads the product adds them up on the way (rowwise.hip), so that no kernel
+// and no pass is added. Only the input gradient of a post-LN layer, which no row kernel reads, pays a kernel for the sum (4 us).
+// The line: the ranges cost the row kernel 1-2 us, and long chains of few tiles repay that; 64-tile products only from K = 6144
+// on, more tiles or shorter K nowhere. us, forward / backward of an encoder layer, plain -> ranges:
+//   inside   hidden 512, 128 tokens 36.7 -> 32.6 / 44.0 -> 40.5; 1024, 24 40.7 -> 36.6 / 57.4 -> 49.7, 128 43.9 -> 40.2 / 62.5 -> 55.3;
+//            2048, 64 57.5 -> 53.1 / 113.9 -> 93.4, 128 60.6 -> 57.0 / 117.2 -> 104.6; decoder 4096, 64 backward 263 -> 252
+//   outside  hidden 256, 1024 34.5 -> 36.4 / 48.6 -> 55.8; 512, 512 37.2 -> 37.9 / 52.5 -> 58.6; 1024, 256 45.5 -> 44.1 / 66.8 -> 67.9, 512
+//            51.7 -> 51.0 / 79.1 -> 83.6; 2048, 256 69.2 -> 68.9 / 126.9 -> 130.3; 4096, 128 168.6 -> 168.8 / 303.0 -> 310.6
+// (Up to eight ranges: the same within 2 %, the row kernels spill.)
+int product_ranges(int dtype, int M, int N, int K) {
+  if (dtype == DT_FP32 || N < 512 || N > 4096) return 1;   // (rows of other widths: no row kernel that adds ranges)
+  const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
+  const int slabs = (K + 127) / 128;
+  if (!((tiles <= 32 && K >= 2048) || (tiles <= 64 && K >= 6144))) return 1;
+  int s = 4;
+  while ((s - 1) * ((slabs + s - 1) / s) >= slabs) --s;   // every range non-empty
+  return s;
+}
+
+template <int LAYOUT, int BK, int NS, bool F16>
+static void launch_ranges(int ranges, int M, int N, int K, const void* A, const void* B, float* parts, hipStream_t st) {
+  const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
+  const size_t lds = gemm_lds_bytes<64, 64, BK, 2, 2, 1, NS>();
+  auto kern = K % BK == 0 ? gemm_bf16_kernel<LAYOUT, 64, 64, BK, 2, 2, 1, NS, 4, false, EPI_SPLITK, F16>
+                          : gemm_bf16_kernel<LAYOUT, 64, 64, BK, 2, 2, 1, NS, 4, true, EPI_SPLITK, F16>;
+  (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL(kern, dim3(tiles * ranges), dim3((2 * 2 + 4) * 64), lds, st, M, N, K, (const bf16_t*)A, (const bf16_t*)B,
+                     (bf16_t*)nullptr, (const bf16_t*)nullptr, (const bf16_t*)nullptr, reinterpret_cast<bf16_t*>(parts), ranges,
+                     tiles * ranges, 1, (float*)nullptr);
+}
+
+void launch_gemm_ranges(int dtype, int layout, int ranges, int M, int N, int K, const void* A, const void* B, float* parts,
+                        hipStream_t st) {
+#define SLAPO_RANGES(L)                                                                     \
+  do {                                                                                      \
+    if (dtype == DT_FP16) launch_ranges<L, 128, 3, true>(ranges, M, N, K, A, B, parts, st); \
+    else launch_ranges<L, 128, 3, false>(ranges, M, N, K, A, B, parts, st);                 \
+  } while (0)
+  if (layout == GEMM_NT) SLAPO_RANGES(GEMM_NT); else SLAPO_RANGES(GEMM_NN);
+#undef SLAPO_RANGES
 }
 
 void launch_weight_grad(int dtype, int accumulate, int M, int N, int K, const void* A, const void* B, void* C,

@@ -11,14 +11,38 @@
 
 namespace slapo {
 
+// K ranges of a product, fp32 arrays `stride` apart, added up in order: eight columns of a row per lane, all loads in flight
+// (product_ranges, gemm.hip, says which products of few tokens come that way; a kernel of its own for the sum of 128 x 1024
+// takes 3.6 us, the row kernels 1 us more).
+struct Ranges4 {
+  static constexpr int MAX_RANGES = 4;
+  float v[MAX_RANGES][8];
+  __device__ __forceinline__ void load(const float* p, int64_t stride, int ranges) {
+#pragma unroll
+    for (int r = 0; r < MAX_RANGES; ++r)
+      if (r < ranges) load8(p + r * stride, v[r]);   // (uniform)
+  }
+  __device__ __forceinline__ void get(float (&a)[8], int ranges) const {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) a[e] = v[0][e];
+#pragma unroll
+    for (int r = 1; r < MAX_RANGES; ++r)
+      if (r < ranges) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a[e] += v[r][e];
+      }
+  }
+};
+
+// RANGES: r is fp32 K ranges of the branch's output (`ranges` of them).
 // DRAW: elements are dropped. An instance each, here and in backward: a test of the threshold inside the row loop, where the
 // compiler cannot mix the draw's integer multiplies with the loads and sums around it, cost rows with dropout 3-7 % (16384
 // rows of 8192 forward 375 -> 390 us, 4096 of 5120 backward 38.3 -> 40.1).
-template <typename T, int NCH, bool BDR, bool LN, int WAVES, bool DRAW>
+template <typename T, int NCH, bool BDR, bool LN, int WAVES, bool DRAW, bool RANGES = false>
 __global__ __launch_bounds__(WAVES * 64) void bdrln_fwd_kernel(
-    int64_t rows, int H, const T* __restrict__ r, const T* __restrict__ bias, const T* __restrict__ res,
+    int64_t rows, int H, const std::conditional_t<RANGES, float, T>* __restrict__ r, const T* __restrict__ bias, const T* __restrict__ res,
     const T* __restrict__ gamma, const T* __restrict__ beta, T* __restrict__ z_out, T* __restrict__ out,
-    float* __restrict__ mu_out, float* __restrict__ rstd_out, DropoutParams dp, float eps, int rms) {
+    float* __restrict__ mu_out, float* __restrict__ rstd_out, DropoutParams dp, float eps, int rms, int ranges) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nchunk = H >> 3;
   const float inv_h = 1.0f / (float)H;
@@ -33,7 +57,13 @@ __global__ __launch_bounds__(WAVES * 64) void bdrln_fwd_kernel(
         load8(res + base + c * 8, v[i]);
         if (BDR) {
           float a[8], b[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-          load8(r + base + c * 8, a);
+          if constexpr (RANGES) {
+            Ranges4 q;
+            q.load(r + base + c * 8, rows * H, ranges);
+            q.get(a, ranges);
+          } else {
+            load8(r + base + c * 8, a);
+          }
           if (bias) load8(bias + c * 8, b);
           const uint32_t keep = DRAW ? dropout_keep8(dp, (uint64_t)(base >> 3) + (uint64_t)c) : 0xffu;
 #pragma unroll
@@ -247,12 +277,14 @@ __global__ __launch_bounds__(WAVES * 64) void bdrln_bwd_kernel(
 // two steps' worth of rows on their way from memory: with one block per CU (the partial sums it leaves are
 // [blocks, 3, H] floats, which bounds the block count) that is what keeps the memory pipeline full. At the end
 // the groups' column sums are added in group order through LDS: one partial row per block, as above.
-template <typename T, bool LN, int R, int MAXT, bool DRAW, bool ONE = false>
+// RANGES: dout is fp32 K ranges of the gradient (`ranges` of them), to which dadd is added if there is one; a step's loads
+// go out at its beginning (few rows: there is no next step).
+template <typename T, bool LN, int R, int MAXT, bool DRAW, bool ONE = false, bool RANGES = false>
 __global__ __launch_bounds__(MAXT) void bdrln_bwd_wide_kernel(
-    int64_t rows, int H, const T* __restrict__ dout, const T* __restrict__ z, const float* __restrict__ mu,
+    int64_t rows, int H, const std::conditional_t<RANGES, float, T>* __restrict__ dout, const T* __restrict__ z, const float* __restrict__ mu,
     const float* __restrict__ rstd, const T* __restrict__ gamma, const T* __restrict__ dres_in,
     T* __restrict__ dz_out, T* __restrict__ dr_out, float* __restrict__ partials, DropoutParams dp, int dr_from_stored,
-    int NW, int G) {
+    int NW, int G, int ranges, const T* __restrict__ dadd) {
   extern __shared__ __attribute__((aligned(16))) float wsm[];   // per-row sums [2][G][R][NW][2]; at the end column sums [G-1][3][H]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int group = wave / NW, gw = wave - group * NW;
@@ -268,6 +300,7 @@ __global__ __launch_bounds__(MAXT) void bdrln_bwd_wide_kernel(
   const int64_t n_steps = ONE ? 1 : (rows + per_step - 1) / per_step;   // the same for every group: they share the barrier
   auto first_row = [&](int64_t step) { return ((step * gridDim.x + blockIdx.x) * G + group) * R; };
   Raw8<T> ndy[R], nz[R], nres[R];
+  std::conditional_t<RANGES, Ranges4, char> nq[R];
   float nm[R], nrs[R];
   auto fetch = [&](int64_t step) {   // all loads of a step go out before anything waits
     const int64_t row0 = first_row(step);
@@ -277,7 +310,12 @@ __global__ __launch_bounds__(MAXT) void bdrln_bwd_wide_kernel(
       nm[j] = 0.f; nrs[j] = 0.f;
       if (row < rows) {
         if (active) {
-          ndy[j].load(dout + row * H + c * 8);
+          if constexpr (RANGES) {
+            nq[j].load(dout + row * H + c * 8, rows * H, ranges);
+            if (dadd) ndy[j].load(dadd + row * H + c * 8);
+          } else {
+            ndy[j].load(dout + row * H + c * 8);
+          }
           if (LN) nz[j].load(z + row * H + c * 8);
           if (dres_in) nres[j].load(dres_in + row * H + c * 8);
         }
@@ -285,9 +323,10 @@ __global__ __launch_bounds__(MAXT) void bdrln_bwd_wide_kernel(
       }
     }
   };
-  if (n_steps > 0) fetch(0);
+  if (!RANGES && n_steps > 0) fetch(0);
   int par = 0;
   for (int64_t step = 0; step < n_steps; ++step, par ^= 1) {
+    if constexpr (RANGES) fetch(step);
     const int64_t row0 = first_row(step);
     float dy[R][8], xh[R][8], s1[R], s2[R], m[R], rs[R];
     Raw8<T> cres[R];
@@ -295,7 +334,17 @@ __global__ __launch_bounds__(MAXT) void bdrln_bwd_wide_kernel(
     for (int j = 0; j < R; ++j) {
       s1[j] = 0.f; s2[j] = 0.f; m[j] = nm[j]; rs[j] = nrs[j];
       if (row0 + j < rows && active) {
-        ndy[j].get(dy[j]);
+        if constexpr (RANGES) {
+          nq[j].get(dy[j], ranges);
+          if (dadd) {
+            float t[8];
+            ndy[j].get(t);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) dy[j][e] += t[e];
+          }
+        } else {
+          ndy[j].get(dy[j]);
+        }
         if (dres_in) cres[j] = nres[j];
         if (LN) {
           float zz[8];
@@ -312,7 +361,7 @@ __global__ __launch_bounds__(MAXT) void bdrln_bwd_wide_kernel(
         }
       }
     }
-    if (step + 1 < n_steps) fetch(step + 1);   // on their way during the rest of this step
+    if (!RANGES && step + 1 < n_steps) fetch(step + 1);   // on their way during the rest of this step
     if (LN) {
       float* xs = wsm + (size_t)((par * G + group) * R) * NW * 2;
 #pragma unroll
@@ -491,17 +540,18 @@ static int nch_for(int H) {
   return n <= 1 ? 1 : n <= 2 ? 2 : n <= 4 ? 4 : n <= 5 ? 5 : n <= 8 ? 8 : n <= 10 ? 10 : 16;
 }
 
-template <typename T, bool BDR, bool LN, bool DRAW>
+template <typename T, bool BDR, bool LN, bool DRAW, bool RANGES = false>
 static void launch_fwd(int64_t rows, int H, const void* r, const void* bias, const void* res, const void* gamma,
                        const void* beta, void* z_out, void* out, float* mu, float* rstd, const DropoutParams& dp,
-                       float eps, int rms, hipStream_t st) {
-  constexpr int WAVES = 4;
+                       float eps, int rms, int ranges, hipStream_t st) {
+  using R = std::conditional_t<RANGES, float, T>;
+  constexpr int WAVES = RANGES ? 1 : 4;   // (few rows: each on a CU of its own)
   int64_t blocks = (rows + WAVES - 1) / WAVES;
   if (blocks > 4096) blocks = 4096;
 #define SLAPO_FWD(N)                                                                                          \
-  hipLaunchKernelGGL((bdrln_fwd_kernel<T, N, BDR, LN, WAVES, DRAW>), dim3((unsigned)blocks), dim3(WAVES * 64), 0, st, \
-                     rows, H, (const T*)r, (const T*)bias, (const T*)res, (const T*)gamma, (const T*)beta,    \
-                     (T*)z_out, (T*)out, mu, rstd, dp, eps, rms)
+  hipLaunchKernelGGL((bdrln_fwd_kernel<T, N, BDR, LN, WAVES, DRAW, RANGES>), dim3((unsigned)blocks), dim3(WAVES * 64), 0, st, \
+                     rows, H, (const R*)r, (const T*)bias, (const T*)res, (const T*)gamma, (const T*)beta,    \
+                     (T*)z_out, (T*)out, mu, rstd, dp, eps, rms, ranges)
   switch (nch_for(H)) {
     case 1: SLAPO_FWD(1); break;
     case 2: SLAPO_FWD(2); break;
@@ -516,11 +566,15 @@ static void launch_fwd(int64_t rows, int H, const void* r, const void* bias, con
 
 void launch_bdrln_fwd(int dtype, int64_t rows, int H, const void* r, const void* bias, const void* res,
                       const void* gamma, const void* beta, void* z_out, void* out, float* mu, float* rstd,
-                      const DropoutParams& dp, float eps, int rms, hipStream_t st) {
+                      const DropoutParams& dp, float eps, int rms, hipStream_t st, int r_ranges) {
   const bool bdr = r != nullptr, ln = gamma != nullptr;
   if (rms) { beta = nullptr; mu = nullptr; }
   const bool draw = dp.thr != 0;
-#define SLAPO_PICK_AS(T, BDR, LN, DRAW) launch_fwd<T, BDR, LN, DRAW>(rows, H, r, bias, res, gamma, beta, z_out, out, mu, rstd, dp, eps, rms, st)
+#define SLAPO_PICK_AS(T, BDR, LN, DRAW)                                                                       \
+  do {                                                                                                        \
+    if (BDR && r_ranges) launch_fwd<T, BDR, LN, DRAW, BDR && sizeof(T) == 2>(rows, H, r, bias, res, gamma, beta, z_out, out, mu, rstd, dp, eps, rms, r_ranges, st); \
+    else launch_fwd<T, BDR, LN, DRAW>(rows, H, r, bias, res, gamma, beta, z_out, out, mu, rstd, dp, eps, rms, 0, st); \
+  } while (0)
 #define SLAPO_PICK(T)                                                                                         \
   do {                                                                                                        \
     if (bdr && ln) { if (draw) SLAPO_PICK_AS(T, true, true, true); else SLAPO_PICK_AS(T, true, true, false); } \
@@ -543,17 +597,19 @@ int bdrln_bwd_blocks_wide(int64_t rows, int H) {
   return (int)(b > 256 ? 256 : b);
 }
 
-template <typename T, bool LN, bool DRAW>
+template <typename T, bool LN, bool DRAW, bool RANGES = false>
 static void launch_bwd(int64_t rows, int H, const void* dout, const void* z, const float* mu, const float* rstd,
                        const void* gamma, const void* dres_in, void* dz_out, void* dr_out, float* partials,
-                       const DropoutParams& dp, int dr_from_stored, int blocks, hipStream_t st) {
+                       const DropoutParams& dp, int dr_from_stored, int blocks, int ranges, const void* dadd, hipStream_t st) {
+  using D = std::conditional_t<RANGES, float, T>;
   if (H >= 512) {
     // Groups of NW wavefronts that split the columns. Up to hidden 3072 as many groups as fit 12 wavefronts (the
     // register budget of three wavefronts per SIMD holds two rows per group and their prefetch without spilling);
     // wider rows fill the block with one group, four rows at a time up to 4096, one above.
     const int nw = (H / 8 + 63) / 64;
-    int groups = nw <= 6 ? (12 / nw > 8 ? 8 : 12 / nw) : 1;
-    const int rows_per_group = nw <= 6 ? 2 : nw <= 8 ? 4 : 1;
+    // (two also where the blocks then hold all rows, whichever of the kernels: the sums over the rows keep their order)
+    int groups = RANGES ? 8 / nw : nw <= 6 ? (12 / nw > 8 ? 8 : 12 / nw) : 1;
+    const int rows_per_group = nw <= 6 || (nw <= 8 && rows <= 2 * (int64_t)blocks) ? 2 : nw <= 8 ? 4 : 1;
     // (no group without a row: each adds a round of column sums through LDS)
     const int64_t useful = (rows + (int64_t)blocks * rows_per_group - 1) / ((int64_t)blocks * rows_per_group);
     if (groups > useful) groups = (int)useful;
@@ -562,17 +618,19 @@ static void launch_bwd(int64_t rows, int H, const void* dout, const void* z, con
     const size_t lds = xs_bytes > col_bytes ? xs_bytes : col_bytes;
 #define SLAPO_WIDE(R, MAXT, ...)                                                                                     \
   do {                                                                                                               \
-    auto kern = bdrln_bwd_wide_kernel<T, LN, R, MAXT, DRAW, ##__VA_ARGS__>;                                                \
+    auto kern = bdrln_bwd_wide_kernel<T, LN, R, MAXT, DRAW, __VA_ARGS__, RANGES>;                                       \
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);             \
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(groups * nw * 64), lds, st, rows, H, (const T*)dout, (const T*)z, mu, \
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(groups * nw * 64), lds, st, rows, H, (const D*)dout, (const T*)z, mu, \
                        rstd, (const T*)gamma, (const T*)dres_in, (T*)dz_out, (T*)dr_out, partials, dp,              \
-                       dr_from_stored, nw, groups);                                                                  \
+                       dr_from_stored, nw, groups, ranges, (const T*)dadd);                                                  \
   } while (0)
     // (three rows per group where that takes all rows in ONE step instead of a full and a thin one: 4096 rows of 1024)
-    if (nw <= 6 && rows > (int64_t)blocks * groups * 2 && rows <= (int64_t)blocks * groups * 3) SLAPO_WIDE(3, 768, true);
-    else if (nw <= 6) SLAPO_WIDE(2, 768);
-    else if (nw <= 8) SLAPO_WIDE(4, 512);
-    else SLAPO_WIDE(1, 1024);
+    if constexpr (RANGES) {   // (few rows: blocks of at most eight wavefronts, whose registers hold the ranges of two rows)
+      SLAPO_WIDE(2, 512, false);
+    } else if (nw <= 6 && rows > (int64_t)blocks * groups * 2 && rows <= (int64_t)blocks * groups * 3) SLAPO_WIDE(3, 768, true);
+    else if (rows_per_group == 2) SLAPO_WIDE(2, 768, false);
+    else if (nw <= 8) SLAPO_WIDE(4, 512, false);
+    else SLAPO_WIDE(1, 1024, false);
 #undef SLAPO_WIDE
     return;
   }
@@ -585,6 +643,7 @@ static void launch_bwd(int64_t rows, int H, const void* dout, const void* z, con
                        rstd, (const T*)gamma, (const T*)dres_in, (T*)dz_out, (T*)dr_out, partials, dp,       \
                        dr_from_stored);                                                                      \
   } while (0)
+  if constexpr (!RANGES)
   switch (nch_for(H)) {
     case 1: SLAPO_BWD(1, 8); break;
     default: SLAPO_BWD(2, 8); break;
@@ -594,13 +653,17 @@ static void launch_bwd(int64_t rows, int H, const void* dout, const void* z, con
 
 void launch_bdrln_bwd(int dtype, int64_t rows, int H, const void* dout, const void* z, const float* mu,
                       const float* rstd, const void* gamma, const void* dres_in, void* dz_out, void* dr_out,
-                      float* partials, const DropoutParams& dp, int rms, hipStream_t st, int dr_from_stored, int blocks) {
+                      float* partials, const DropoutParams& dp, int rms, hipStream_t st, int dr_from_stored, int blocks,
+                      int dout_ranges, const void* dout_add) {
   if (blocks == 0) blocks = bdrln_bwd_blocks(rows);
   if (rms) mu = nullptr;   // the kernel reads a missing mean as RMSNorm (mean 0, no mean-of-gradient term)
   if (dr_out == dz_out) dz_out = nullptr;   // one array for both (nothing is dropped): stored once, and summed as dr
   const bool ln = gamma != nullptr, draw = dp.thr != 0;
-#define SLAPO_PICK_AS(T, LN, DRAW) \
-  launch_bwd<T, LN, DRAW>(rows, H, dout, z, mu, rstd, gamma, dres_in, dz_out, dr_out, partials, dp, dr_from_stored, blocks, st)
+#define SLAPO_PICK_AS(T, LN, DRAW)                                                          \
+  do {                                                                                      \
+    if (LN && dout_ranges) launch_bwd<T, LN, DRAW, LN && sizeof(T) == 2>(rows, H, dout, z, mu, rstd, gamma, dres_in, dz_out, dr_out, partials, dp, dr_from_stored, blocks, dout_ranges, dout_add, st); \
+    else launch_bwd<T, LN, DRAW>(rows, H, dout, z, mu, rstd, gamma, dres_in, dz_out, dr_out, partials, dp, dr_from_stored, blocks, 0, nullptr, st); \
+  } while (0)
 #define SLAPO_PICK(T)                                                                       \
   do {                                                                                      \
     if (ln) { if (draw) SLAPO_PICK_AS(T, true, true); else SLAPO_PICK_AS(T, true, false); } \
