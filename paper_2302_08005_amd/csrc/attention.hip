@@ -91,8 +91,8 @@ __device__ __forceinline__ bf16x8_t pack8(const f32x16_t& v, int h) {
 __device__ __forceinline__ void pin_here(f32x16_t& v) { asm volatile("" : "+v"(v)); }
 // Backward of the rotary embedding on four consecutive columns (two pairs) of a head of width d: turned by the negative
 // angles of the row's position. (16-bit gradients are rounded first, like the array that a pass of its own would read.)
-// The table loads at the end of a block cost what the pass saves where a block has few steps (98 x 66 tokens, 3 heads of 128:
-// dQ and dK/dV 38 -> 44 us, the pass 5 us), and a fraction of it elsewhere (4 x 1024 tokens, 32 heads of 128: 53 us saved with the forward pass).
+// The table loads at the end of a block cost a fraction of what the pass would (4 x 1024 tokens, 32 heads of 128: 53 us saved
+// with the forward pass); read by lanes of 32 rows, before the rows left through LDS, they cost as much where a block has few steps.
 __device__ __forceinline__ void rope_back(float (&v)[4], const float* __restrict__ table, int pos, int d, int col) {
   const float4 w = *reinterpret_cast<const float4*>(table + (int64_t)pos * d + col);
   turn_pair(v[0], v[1], w.x, -w.y);
@@ -168,6 +168,49 @@ template <int G, int REGS>
 __device__ __forceinline__ float* group_slot(void* smem, int grp, int row_wave, int lane) {
   return reinterpret_cast<float*>(smem) + ((grp - 1) * (4 / G) + row_wave) * (REGS * 64) + lane;
 }
+
+// A wavefront's 32 rows of output, [32][D], on their way out. A lane's accumulators are four columns of one row at a time, 8 bytes:
+// stored as they are, an instruction touches 32 rows with 16 bytes each, and the L2 sees every 128-byte line eight times. Through
+// LDS (the stages are free by then) each 8 bytes of a lane join those of its neighbours to whole rows. Rows are padded by 8
+// bytes, so that the 8-byte writes of 32 rows meet every bank once. us, 8-byte stores -> whole rows, forward / backward (samples x
+// tokens, heads): 64-wide 128 x 128, 16 26.5 -> 24.0 / 88.9 -> 76.1; 16 x 256, 16 11.1 -> 10.4 / 31.5 -> 27.0; 32 x 512, 16 45.7 -> 43.3 /
+// 150 -> 141; 8 x 1024, 32 causal 55.3 -> 52.7 / 170 -> 161; 128-wide causal 4 x 1024, 32 55.5 -> 52.8 / 178 -> 163; 4 x 2048, 20 108 ->
+// 104 / 350 -> 332; the longer the walk the less: 1 x 8192, 20 437 / 1238 -> 1222.
+template <int D, bool F16>
+struct RowsOut {
+  static constexpr int P = D + 4;          // row pitch in elements
+  static constexpr int ELEMS = 32 * P;
+  bf16_t* stage;                           // of this wavefront
+  int lane;
+  // columns 32 t + 8 g + 4 (lane / 32) .. + 3 of row lane % 32
+  __device__ __forceinline__ void put(int t, int g, float a, float b, float c, float d) const {
+    *reinterpret_cast<uint2*>(stage + (lane & 31) * P + t * 32 + g * 8 + 4 * (lane >> 5)) = make_uint2(pack2<F16>(a, b), pack2<F16>(c, d));
+  }
+  // rows 0 .. rows - 1 to out + row * stride. table: the rows are turned back by the rotary angles of the positions pos0 + row.
+  __device__ __forceinline__ void flush(bf16_t* out, int64_t stride, int rows, const float* __restrict__ table = nullptr, int pos0 = 0) const {
+    constexpr int CPR = D / 8, RPI = 64 / CPR;   // 16-byte chunks per row, rows per access
+    const int c = (lane % CPR) * 8;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < 32 / RPI; ++i) {
+      const int row = i * RPI + lane / CPR;
+      const uint2* p = reinterpret_cast<const uint2*>(stage + row * P + c);
+      uint2 w0 = p[0], w1 = p[1];
+      if (row < rows) {
+        if (table) {   // (uniform)
+          float v[4] = {unpack_lo<F16>(w0.x), unpack_hi<F16>(w0.x), unpack_lo<F16>(w0.y), unpack_hi<F16>(w0.y)};
+          rope_back(v, table, pos0 + row, D, c);
+          w0 = make_uint2(pack2<F16>(v[0], v[1]), pack2<F16>(v[2], v[3]));
+          float u[4] = {unpack_lo<F16>(w1.x), unpack_hi<F16>(w1.x), unpack_lo<F16>(w1.y), unpack_hi<F16>(w1.y)};
+          rope_back(u, table, pos0 + row, D, c + 4);
+          w1 = make_uint2(pack2<F16>(u[0], u[1]), pack2<F16>(u[2], u[3]));
+        }
+        *reinterpret_cast<uint4*>(out + row * stride + c) = make_uint4(w0.x, w0.y, w1.x, w1.y);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();   // (the next rows overwrite these)
+  }
+};
 
 __device__ __forceinline__ int visible_keys(const AttnShape& sh, const int32_t* seqlens, int b) {
   int n = sh.seq;
@@ -455,17 +498,14 @@ __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const 
 
   const float l_tot = l + __shfl_xor(l, 32, 64);
   const float inv = l_tot > 0.f ? (DROP ? sh.drop.scale : 1.f) / l_tot : 0.f;
+  // (a group's wavefront writes over its own slot of what the groups handed it)
+  const RowsOut<D, F16> rows = {smem + row_wave * (G > 1 ? (NT * 16 + 2) * 128 : RowsOut<D, F16>::ELEMS), lane};
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) rows.put(t, g, o[t][4 * g] * inv, o[t][4 * g + 1] * inv, o[t][4 * g + 2] * inv, o[t][4 * g + 3] * inv);
+  rows.flush(out + ((int64_t)b * S + wave_q_min) * H + a * D, H, S - wave_q_min);
   if (my_q < S) {
-    bf16_t* orow = out + ((int64_t)b * S + my_q) * H + a * D;
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        uint2 w;
-        w.x = pack2<F16>(o[t][4 * g] * inv, o[t][4 * g + 1] * inv);
-        w.y = pack2<F16>(o[t][4 * g + 2] * inv, o[t][4 * g + 3] * inv);
-        *reinterpret_cast<uint2*>(orow + t * 32 + g * 8 + 4 * kc) = w;
-      }
     if (kc == 0) lse[((int64_t)b * sh.heads + a) * S + my_q] = l_tot > 0.f ? m * scale + __logf(l_tot) : -INFINITY;
   }
 }
@@ -918,24 +958,18 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(const BlockId blk, const Att
         for (int r = 0; r < 16; ++r) { dk[t][r] += p[(t * 16 + r) * 64]; dv[t][r] += p[((NT + t) * 16 + r) * 64]; }
     }
   }
-  if (my_kv < S) {
-    bf16_t* krow = dqkv + ((int64_t)b * S + my_kv) * rs + H + a * D;
-    bf16_t* vrow = krow + H;
+  const RowsOut<D, F16> rows = {smem + row_wave * (G > 1 ? 2 * NT * 16 * 128 : RowsOut<D, F16>::ELEMS), lane};
+  bf16_t* krow = dqkv + ((int64_t)b * S + wave_kv_min) * rs + H + a * D;
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        uint2 w;
-        float v[4] = {dk[t][4 * g] * scale, dk[t][4 * g + 1] * scale, dk[t][4 * g + 2] * scale, dk[t][4 * g + 3] * scale};
-        if (sh.rope) { round_pairs<F16>(v); rope_back(v, sh.rope, my_kv, D, t * 32 + g * 8 + 4 * kc); }   // (uniform)
-        w.x = pack2<F16>(v[0], v[1]);
-        w.y = pack2<F16>(v[2], v[3]);
-        *reinterpret_cast<uint2*>(krow + t * 32 + g * 8 + 4 * kc) = w;
-        w.x = pack2<F16>(dv[t][4 * g], dv[t][4 * g + 1]);
-        w.y = pack2<F16>(dv[t][4 * g + 2], dv[t][4 * g + 3]);
-        *reinterpret_cast<uint2*>(vrow + t * 32 + g * 8 + 4 * kc) = w;
-      }
-  }
+    for (int g = 0; g < 4; ++g) rows.put(t, g, dk[t][4 * g] * scale, dk[t][4 * g + 1] * scale, dk[t][4 * g + 2] * scale, dk[t][4 * g + 3] * scale);
+  rows.flush(krow, rs, S - wave_kv_min, sh.rope, wave_kv_min);
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) rows.put(t, g, dv[t][4 * g], dv[t][4 * g + 1], dv[t][4 * g + 2], dv[t][4 * g + 3]);
+  rows.flush(krow + H, rs, S - wave_kv_min);
 }
 
 // ============================ backward: dQ per query tile ========================================
@@ -1076,20 +1110,12 @@ __device__ __forceinline__ void attn_bwd_dq_block(const BlockId blk, const AttnS
     }
   }
 
-  if (my_q < S) {
-    bf16_t* qrow = dqkv + ((int64_t)b * S + my_q) * rs + a * D;
+  const RowsOut<D, F16> rows = {smem + row_wave * (G > 1 ? NT * 16 * 128 : RowsOut<D, F16>::ELEMS), lane};
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        uint2 w;
-        float v[4] = {dq[t][4 * g] * scale, dq[t][4 * g + 1] * scale, dq[t][4 * g + 2] * scale, dq[t][4 * g + 3] * scale};
-        if (sh.rope) { round_pairs<F16>(v); rope_back(v, sh.rope, my_q, D, t * 32 + g * 8 + 4 * kc); }   // (uniform)
-        w.x = pack2<F16>(v[0], v[1]);
-        w.y = pack2<F16>(v[2], v[3]);
-        *reinterpret_cast<uint2*>(qrow + t * 32 + g * 8 + 4 * kc) = w;
-      }
-  }
+    for (int g = 0; g < 4; ++g) rows.put(t, g, dq[t][4 * g] * scale, dq[t][4 * g + 1] * scale, dq[t][4 * g + 2] * scale, dq[t][4 * g + 3] * scale);
+  rows.flush(dqkv + ((int64_t)b * S + wave_q_min) * rs + a * D, rs, S - wave_q_min, sh.rope, wave_q_min);
 }
 
 // ============================ backward: the launches =============================================

@@ -238,3 +238,31 @@ def test_which_backward_grids_are_one_launch(batch, seq, pd, one):
     grids = captured(lambda: B.slapo_attn_bwd(desc, qkv, None, out, out, lse, delta, dqkv), grids=True)
     x = (seq + 127) // 128
     assert grids == ([(2 * x * heads * batch, 1, 1)] if one else [(x, heads, batch)] * 2)
+
+
+# outputs leave as whole rows of a wavefront's 32: sequences that end inside one (one row, one short of and one beyond 32, 64 and
+# 128), each form of the kernels; nothing behind the last row is touched
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads", [2, 600])   # small grids (groups of wavefronts, one launch) and large ones
+@pytest.mark.parametrize("S", [1, 31, 33, 63, 65, 95, 127, 129])
+def test_attention_writes_its_rows_only(S, heads, d):
+    H, guard = heads * d, 40
+    cfg = W.LayerConfig("t", 1, S, H, heads, 64, causal=1, dtype=W.BF16)
+    few = min(heads, 8)   # heads that are compared
+    rng = np.random.default_rng(S + d)
+    qkv, dout = store(rng.standard_normal((S, 3, H)), W.BF16), store(rng.standard_normal((S, H)), W.BF16)
+    part = W.LayerConfig("t", 1, S, few * d, few, 64, causal=1, dtype=W.BF16)
+    qkv_part = np.ascontiguousarray(qkv[:, :, :few * d]).reshape(S, -1).astype(np.float64)
+    A_ref, P, _ = L.attention_fwd(part, qkv_part, None)
+    ref = L.attention_bwd(part, qkv_part, P, dout[:, :few * d].astype(np.float64)).reshape(S, 3, few * d)
+    out = torch.full((S + guard, H), 7.0, dtype=torch.bfloat16, device=DEV)
+    dqkv = torch.full((S + guard, 3 * H), 7.0, dtype=torch.bfloat16, device=DEV)
+    lse, delta = (torch.empty(heads, S, device=DEV) for _ in range(2))
+    desc, qkv_d = B.make_desc(cfg, hidden=64, attn_dim=H), to_dev(qkv.reshape(S, -1), W.BF16)
+    B.slapo_attn_fwd(desc, qkv_d, None, out, lse)
+    B.slapo_attn_bwd(desc, qkv_d, None, out, to_dev(dout, W.BF16), lse, delta, dqkv)
+    assert (out[S:] == 7).all() and (dqkv[S:] == 7).all()
+    assert err(out[:S, :few * d], A_ref) <= TOL[W.BF16]
+    got = dqkv[:S].reshape(S, 3, H)
+    for i in range(3):
+        assert err(got[:, i, :few * d], ref[:, i]) <= TOL[W.BF16], i
