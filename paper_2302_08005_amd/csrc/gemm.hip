@@ -33,6 +33,26 @@ void gemm_bf16_kernel(int M, int N, int K, const bf16_t* __restrict__ A, const b
       blockIdx.x, M, N, K, A, B, C, bias, aux_in, aux_out, act, tail_begin, tail_splits, hyb_ws);
 }
 
+// The whole rounds of a grid of 256x256 tiles, and the tiles of a thin last one in quarters (quarter_tiles): 128x128 tiles of the
+// same eight wavefronts, 128-deep slabs in two stages (the bytes in flight of the large tile). The quarters of a tile go to one XCD.
+template <int LAYOUT, bool KTAIL, int EPI, bool F16>
+__global__ __launch_bounds__(512, 1) void gemm_bf16_quarters_kernel(int M, int N, int K, const bf16_t* __restrict__ A,
+                                                                    const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
+                                                                    const bf16_t* __restrict__ bias, const bf16_t* aux_in,
+                                                                    bf16_t* __restrict__ aux_out, int act, int whole) {
+  if ((int)blockIdx.x < whole) {
+    gemm_bf16_tile<LAYOUT, 256, 256, 64, 2, 4, 1, 2, 0, KTAIL, EPI, F16>(blockIdx.x, M, N, K, A, B, C, bias, aux_in, aux_out, act, 0, 1, nullptr);
+    return;
+  }
+  const int tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256;
+  const int u = blockIdx.x - whole, tile = whole + (u >> 5) * 8 + (u & 7), quarter = (u >> 3) & 3;
+  if (tile >= tiles_m * tiles_n) return;
+  const TilePos pos = tile_position(tile, tiles_m, tiles_n, 1);
+  const int m0 = pos.tile_m * 256 + (quarter >> 1) * 128, n0 = pos.tile_n * 256 + (quarter & 1) * 128;
+  if (m0 >= M || n0 >= N) return;
+  gemm_bf16_tile<LAYOUT, 128, 128, 128, 2, 4, 1, 2, 0, KTAIL, EPI, F16>(0, M, N, K, A, B, C, bias, aux_in, aux_out, act, 0, 1, nullptr, m0, n0);
+}
+
 template <int LAYOUT, int W>
 __global__ __launch_bounds__(F32_WAVES * 64) void gemm_f32_kernel(int M, int N, int K, const float* __restrict__ A,
                                                                   const float* __restrict__ B, float* __restrict__ C,
@@ -246,6 +266,51 @@ static void launch_hybrid(const HybridPlan& hp, int epi, int M, int N, int K, co
   launch_hybrid_tile<LAYOUT, 256, 256, 2, 4, 2, 0, F16>(hp, epi, M, N, K, A, B, C, aux_in, ws, st);
 }
 
+// Thin last rounds without K ranges. A product that has the chip to itself runs the tiles of its whole rounds as 256x256 ones and
+// cuts each tile beyond them into four 128x128 ones, in the same launch: up to half a round of tiles makes at most two rounds of
+// quarters, which take a third of a round each. Every sum keeps its order, so the bits are those of whole tiles. us, the form
+// taken before (two rounds, or 128x128 tiles from K = 2048 on) / quarters:
+//   NT with GeLU  2331 x 8192 x 2560 (320 tiles) 113.4 / 95.2, x 1024 67.3 / 51.2, x 512 49.3 / 39.0; 4352 x 4096 x 2560 (272) 111.6 / 91.5;
+//                 2600 x 8192 x 4096 (352) 183.3 / 166.6, x 2560 119.5 / 116.9; 3072 x 8192 x 1024 (384) 68.9 / 65.1
+//   NT with bias  8192 x 2064 x 2560 (288) 100.6 / 77.8; 8192 x 2560 x 2560 (320) 107 / 84.7; 16384 x 1536 x 4096 (384) 174.6 / 159.5
+// K ranges (hybrid_plan) come first where a workspace is at hand and K is long enough for them (8192 x 2560 x 10240: 328 us, quarters 315;
+// beside its neighbours in a step level). Not on the two streams of backward, whose kernels fill a thin round from both sides:
+// steps of whole rounds and thin ones / quarters there too, 4 x 1024 tokens of width 2560 2123 / 2165 us, 1 x 8192 backward 3377 / 3413.
+// Steps with them in forward alone: 2 x 1000 tokens of width 2560, checkpointed 2988 -> 2866; 10 x 500 of 1024 606 -> 589; forward
+// of 2 x 1024 of 3072 635 -> 572, of 3 x 777 of 2048 302 -> 293.
+static int quarter_tiles(int layout, int M, int N, int K, bool solo) {
+  const int64_t t256 = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
+  const int rem = (int)(t256 % 256);
+  return solo && layout != GEMM_TN && t256 > 256 && rem > 0 && rem <= 128 && K >= 256 ? rem : 0;
+}
+
+template <int LAYOUT, bool F16>
+static void launch_quarters(int rem, int epi, int act, int M, int N, int K, const void* A, const void* B, void* C,
+                            const void* bias, const void* aux_in, void* aux_out, hipStream_t st) {
+  const int whole = ((M + 255) / 256) * ((N + 255) / 256) - rem;
+  constexpr size_t l0 = gemm_lds_bytes<256, 256, 64, 2, 4, 1, 2>(), l1 = gemm_lds_bytes<128, 128, 128, 2, 4, 1, 2>(), lds = l0 > l1 ? l0 : l1;
+#define SLAPO_QUARTERS(E)                                                                                               \
+  do {                                                                                                                  \
+    if constexpr (epi_used(LAYOUT, E)) {                                                                                \
+      auto kern = K % 128 == 0 ? gemm_bf16_quarters_kernel<LAYOUT, false, E, F16> : gemm_bf16_quarters_kernel<LAYOUT, true, E, F16>; \
+      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);               \
+      hipLaunchKernelGGL(kern, dim3(whole + (rem + 7) / 8 * 32), dim3(512), lds, st, M, N, K, (const bf16_t*)A, (const bf16_t*)B, \
+                         (bf16_t*)C, (const bf16_t*)bias, (const bf16_t*)aux_in, (bf16_t*)aux_out, act, whole);         \
+    }                                                                                                                   \
+  } while (0)
+  switch (epi) {
+    case EPI_NONE: SLAPO_QUARTERS(EPI_NONE); break;
+    case EPI_BIAS: SLAPO_QUARTERS(EPI_BIAS); break;
+    case EPI_BIAS_ACT: SLAPO_QUARTERS(EPI_BIAS_ACT); break;
+    case EPI_DACT: SLAPO_QUARTERS(EPI_DACT); break;
+    case EPI_GATE: SLAPO_QUARTERS(EPI_GATE); break;
+    case EPI_DGATE: SLAPO_QUARTERS(EPI_DGATE); break;
+    case EPI_ROPE: SLAPO_QUARTERS(EPI_ROPE); break;
+    default: SLAPO_QUARTERS(EPI_ADD); break;
+  }
+#undef SLAPO_QUARTERS
+}
+
 template <int LAYOUT, bool F16>
 static void launch_bf16(int epi, int act, int M, int N, int K, const void* A, const void* B, void* C,
                         const void* bias, const void* aux_in, void* aux_out, hipStream_t st, bool solo, float* ws,
@@ -256,6 +321,13 @@ static void launch_bf16(int epi, int act, int M, int N, int K, const void* A, co
     const HybridPlan hp = hybrid_plan(LAYOUT, epi, M, N, K);
     if (hp.ws_bytes && hp.ws_bytes <= ws_bytes) {
       launch_hybrid<LAYOUT, F16>(hp, epi, M, N, K, A, B, C, aux_in, ws, st);
+      return;
+    }
+  }
+  if constexpr (LAYOUT != GEMM_TN) {
+    const int rem = quarter_tiles(LAYOUT, M, N, K, solo);
+    if (rem && epi_used(LAYOUT, epi)) {
+      launch_quarters<LAYOUT, F16>(rem, epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
       return;
     }
   }
@@ -446,6 +518,10 @@ void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool sol
       snprintf(buf, len, "gemm_bf16_kernel<2, 128, 128, 64, 2, 2, 2, 4, 4, false, %d, %s, false> in %d K ranges + splitk_reduce_kernel", EPI_SPLITK, b, splits);
       return;
     }
+  }
+  if (const int rem = quarter_tiles(layout, M, N, K, solo); rem && epi_used(layout, epi)) {
+    snprintf(buf, len, "gemm_bf16_quarters_kernel<%d, %s, %d, %s>", layout, K % 128 != 0 ? "true" : "false", epi, b);
+    return;
   }
   const TileKind k = epi_used(layout, epi) ? select_tile(layout, M, N, K, solo) : TILE_128_LOADERS;
   if (k == TILE_128_LOADERS && two_per_cu(M, N, K)) {

@@ -155,13 +155,14 @@ constexpr unsigned BEYOND_OPERANDS = 0xfffffff0u;
 // order and applies the epilogue. Plain launches pass tail_begin = number of tiles.
 // BY_AUX (EPI_ADD): whether there is a sum to add to is told by aux_in, not by the instance.
 // `block`: this workgroup's position in the grid of the product (not blockIdx.x where a launch holds several products).
+// m_at >= 0: the tile's origin (m_at, n_at) in place of a position.
 template <int LAYOUT, int BM, int BN, int BK, int WGM, int WGN, int KS, int NS, int PW, bool KTAIL, int EPI,
           bool F16 = false, bool HYB = false, bool BY_AUX = false>
 __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, const bf16_t* __restrict__ A,
                                                const bf16_t* __restrict__ B, bf16_t* __restrict__ C,
                                                const bf16_t* __restrict__ bias, const bf16_t* aux_in,
                                                bf16_t* __restrict__ aux_out, int act, int tail_begin, int tail_splits,
-                                               float* __restrict__ hyb_ws) {
+                                               float* __restrict__ hyb_ws, int m_at = -1, int n_at = 0) {
   constexpr bool A_KC = (LAYOUT != GEMM_TN);  // A operand contiguous along K
   constexpr bool B_KC = (LAYOUT == GEMM_NT);
   // KS == 2: two sets of WGM x WGN wavefronts share the output tile; set g multiplies the g-th half of
@@ -215,7 +216,7 @@ __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, c
   const int splits = SPLITK ? act : (is_tail ? tail_splits : 1);
   const int split = SPLITK ? pos.copy : tail_range;
   const int tile_m = pos.tile_m, tile_n = pos.tile_n;
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  const int m0 = m_at >= 0 ? m_at : tile_m * BM, n0 = m_at >= 0 ? n_at : tile_n * BN;
 
   const int lane = threadIdx.x & 63;
   const bool is_loader = PW ? threadIdx.x >= NCOMP : true;
@@ -370,7 +371,8 @@ __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, c
     // Epilogues that move two values per product element put bursts of stores between the other workgroups' loads: the
     // earlier request pays there (4096 x 22016 x 4096 gated: 574 us at a gap of 2, 598 at 4, 627 at 6), the even spread
     // everywhere else (8192 x 2048 x 8192: 187.7 / 182.5 / 186.2).
-    constexpr int LOAD_GAP = EPI == EPI_GATE || EPI == EPI_DGATE || EPI == EPI_BIAS_ACT ? 2 : 4;
+    // (Tiles of 128x128 have half the MFMAs per load.)
+    constexpr int LOAD_GAP = BM == 128 || EPI == EPI_GATE || EPI == EPI_DGATE || EPI == EPI_BIAS_ACT ? 2 : 4;
     static_assert(LOAD_GAP * (LPS - 1) < NPAIR * MPP - MPP, "all loads issued in front of the wait");
     constexpr int EARLY = (MPP + LOAD_GAP - 1) / LOAD_GAP;   // loads issued in the last pair of the slab before
 #pragma unroll

@@ -6,7 +6,7 @@ import torch
 import workloads as W
 from oracle import layer as L
 from paper_2302_08005_amd import binding as B
-from gpu_util import DEV, TOL, err, store, to_dev, to_np
+from gpu_util import DEV, TOL, err, store, tdtype, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -385,3 +385,37 @@ def test_epilogues_of_64x64_tiles(layout, dtype):
             errs = {"add": err(run(B.EPI_ADD, aux_in=aux1), acc + aux[:, :N]), "dgelu": err(run(B.EPI_DACT, aux_in=aux1), acc * aux[:, :N]),
                     "dgate": err(run(B.EPI_DGATE, width=2 * N, aux_in=to_dev(aux, dtype)), np.repeat(acc, 2, 1) * aux)}
         assert all(v <= {W.BF16: 4e-3, W.FP16: 5e-4}[dtype] for v in errs.values()), (K, errs)
+
+
+# a thin last round in quarters of tiles (a product that has the chip to itself): the bits of whole tiles (GEMM_SHARED). One row or
+# eight columns beyond whole tiles (quarters without rows or columns), 1 to 128 tiles beyond a round, partial slabs of 128 and of 64.
+@pytest.mark.parametrize("M,N,K", [(4097, 4096, 256), (4096, 4104, 264), (65700, 240, 320), (4200, 4200, 392), (2331, 8192, 512), (4096, 6144, 1032)])
+@pytest.mark.parametrize("layout,epi", [(B.NT, B.EPI_NONE), (B.NT, B.EPI_BIAS), (B.NT, B.EPI_BIAS_ACT), (B.NT, B.EPI_GATE), (B.NN, B.EPI_NONE), (B.NN, B.EPI_DACT),
+                                        (B.NN, B.EPI_ADD), (B.NN, B.EPI_DGATE)])
+def test_gemm_thin_round_in_quarters(layout, epi, M, N, K):
+    dtype = W.FP16 if K % 16 else W.BF16
+    if epi == B.EPI_GATE:
+        N = (N + 15) // 16 * 16   # (pairs in whole 16-byte pieces of the gated output: other N are refused)
+    name = B.slapo_gemm_kernel_name(dtype, layout, epi, M, N, K)
+    assert "quarters" in name and "quarters" not in B.slapo_gemm_kernel_name(dtype, layout, epi, M, N, K, flags=B.GEMM_SHARED)
+    g = torch.Generator(device=DEV).manual_seed(M + K)
+    rnd = lambda *s: torch.randn(*s, device=DEV, generator=g).mul_(0.25).to(tdtype(dtype))
+    a, b = rnd(M, K), rnd(N, K) if layout == B.NT else rnd(K, N)
+    kw = {}
+    if epi in (B.EPI_BIAS, B.EPI_BIAS_ACT):
+        kw["bias"] = rnd(N)
+    if epi in (B.EPI_DACT, B.EPI_ADD, B.EPI_DGATE):
+        kw["aux_in"] = rnd(M, N * (2 if epi == B.EPI_DGATE else 1))
+    got = []
+    for flags in (0, B.GEMM_SHARED):
+        c = torch.full((M, 2 * N if epi == B.EPI_DGATE else N // 2 if epi == B.EPI_GATE else N), float("nan"), dtype=a.dtype, device=DEV)
+        aux = torch.full((M, N), float("nan"), dtype=a.dtype, device=DEV) if epi in (B.EPI_BIAS_ACT, B.EPI_GATE) else None
+        B.slapo_gemm_ex(dtype, layout, epi, W.GELU, M, N, K, a, b, c, aux_out=aux, flags=flags, **kw)
+        got.append((c, aux))
+    assert torch.isfinite(got[0][0]).all() and torch.equal(got[0][0], got[1][0])
+    assert got[0][1] is None or torch.equal(got[0][1], got[1][1])
+    if epi in (B.EPI_NONE, B.EPI_ADD):   # one in 16 rows against a product of its own
+        rows = torch.arange((M - 1) % 16, M, 16, device=DEV)
+        bt = b.float().t().contiguous() if layout == B.NT else b.float()
+        ref = a[rows].float() @ bt + (kw["aux_in"][rows].float() if epi == B.EPI_ADD else 0)
+        assert err(got[0][0][rows], to_np(ref)) <= TOL[dtype]
