@@ -418,7 +418,8 @@ static void run_forward(const slapo_layer_desc* d, const slapo_layer_params* p, 
       return gws;
     }
     ranges = 0;
-    launch_gemm(dt, GEMM_NT, EPI_NONE, d->act, T, H, K, a, w, r, nullptr, nullptr, nullptr, st, true, gws, W.gemm_ws_bytes);
+    const bool whole = gemm_in_one_round(dt, GEMM_NT, T, H, K);
+    launch_gemm(dt, GEMM_NT, EPI_NONE, d->act, T, H, K, a, w, r, nullptr, nullptr, nullptr, st, true, whole ? nullptr : gws, whole ? 0 : W.gemm_ws_bytes);
     return r;
   };
   const void* ro = project(A, attn, p->wo);
@@ -543,6 +544,11 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   const size_t gwb = W.gemm_ws_bytes;
   auto dweight = [&](int M, int N, const void* a, const void* b, void* c) {
     launch_weight_grad(dt, acc, M, N, T, a, b, c, splitk_ws, ws, solo);
+  };
+  // data gradient: C = A B (+ aux)
+  auto dgrad = [&](int epi, int N, int K, const void* a, const void* b, void* c, const void* aux) {
+    const bool whole = gemm_in_one_round(dt, GEMM_NN, T, N, K);
+    launch_gemm(dt, GEMM_NN, epi, d->act, T, N, K, a, b, c, nullptr, aux, nullptr, st, solo, whole ? nullptr : gws, whole ? 0 : gwb);
   };
   auto colsum = [&](const void* a, int N, void* out, hipStream_t s) {
     float* part = s == st ? pcol2 : pcol;   // per stream, so that the two sums may run at the same time
@@ -672,15 +678,15 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     fork(1);
     dweight(2 * F, H, du, y1, gr->w1);
     if (r_y1 > 1) launch_gemm_ranges(dt, GEMM_NN, r_y1, T, H, 2 * F, du, p->w1, gws, st);
-    else launch_gemm(dt, GEMM_NN, EPI_NONE, d->act, T, H, 2 * F, du, p->w1, t0, nullptr, nullptr, nullptr, st, solo, gws, gwb);
+    else dgrad(EPI_NONE, H, 2 * F, du, p->w1, t0, nullptr);
   } else {
     launch_gemm(dt, GEMM_NN, EPI_DACT, d->act, T, F, H, dr2, p->w2, du, nullptr, u, nullptr, st, solo);
     fork(1);
     colsum(du, F, gr->b1, ws);
     dweight(F, H, du, y1, gr->w1);
     if (r_y1 > 1) launch_gemm_ranges(dt, GEMM_NN, r_y1, T, H, F, du, p->w1, gws, st);
-    else if (d->pre_ln) launch_gemm(dt, GEMM_NN, EPI_NONE, d->act, T, H, F, du, p->w1, t0, nullptr, nullptr, nullptr, st, solo, gws, gwb);
-    else launch_gemm(dt, GEMM_NN, EPI_ADD, d->act, T, H, F, du, p->w1, t0, nullptr, t0, nullptr, st, solo, gws, gwb);
+    else if (d->pre_ln) dgrad(EPI_NONE, H, F, du, p->w1, t0, nullptr);
+    else dgrad(EPI_ADD, H, F, du, p->w1, t0, t0);
   }
   // ---- attention block ----
   if (d->pre_ln) {
@@ -692,14 +698,14 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   }
   fork(2);
   dweight(H, A, dr1, attn, gr->wo);
-  launch_gemm(dt, GEMM_NN, EPI_NONE, d->act, T, A, H, dr1, p->wo, t0, nullptr, nullptr, nullptr, st, solo, gws, gwb);
+  dgrad(EPI_NONE, A, H, dr1, p->wo, t0, nullptr);
   as.beside = side && splitk_ws;
   launch_attn_bwd(dt, as, qkv, seqlens, attn, t0, lse, delta, dqkv, st);
   fork(3);
   if (d->pre_ln) {
     dweight(3 * A, H, dqkv, sv + L.n1, gr->wqkv);
     if (r_x > 1) launch_gemm_ranges(dt, GEMM_NN, r_x, T, H, 3 * A, dqkv, p->wqkv, gws, st);
-    else launch_gemm(dt, GEMM_NN, EPI_NONE, d->act, T, H, 3 * A, dqkv, p->wqkv, t0, nullptr, nullptr, nullptr, st, solo, gws, gwb);
+    else dgrad(EPI_NONE, H, 3 * A, dqkv, p->wqkv, t0, nullptr);
     if (link && link->dr2_below) {
       // (from the stored dx, so that the layer below sees what it would compute from dx itself, bit for bit)
       row_bwd(r_x, nullptr, x, mu1, rstd1, p->ln1_g, t2, dx, link->dr2_below, link->dp_below, 1);
@@ -711,7 +717,7 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   } else {
     dweight(3 * A, H, dqkv, x, gr->wqkv);
     if (side && dx_on_x) side->order(side->join, ws, st);   // the helper stream has read x before dx is written there
-    launch_gemm(dt, GEMM_NN, EPI_ADD, d->act, T, H, 3 * A, dqkv, p->wqkv, dx, nullptr, t2, nullptr, st, solo, gws, gwb);
+    dgrad(EPI_ADD, H, 3 * A, dqkv, p->wqkv, dx, t2);
   }
   // the last bias gradient goes behind the data gradient on the caller's stream: the helper stream's last
   // product is the longer one, and this way the two streams end at about the same time

@@ -113,8 +113,35 @@ static void launch_bf16_tile(int epi, int act, int M, int N, int K, const void* 
 // us; 512, 512 48.9 / 43.2 / 42.4; 1024, 128 47.7 / 43.5 / 42.7; 2048, 128 68.7 / 62.0 / 60.9 (deeper rings, or eight
 // computing wavefronts instead of four: nothing or 1-3 % more). K needs no particular multiple: TN products with K = 2286 tokens and 768 x 3072 outputs take 18.7 us
 // (41.7 with the register-staged kernel that such K used to go to), K = 2000 and 10240 x 2560 take 107 us (170 before).
-enum TileKind { TILE_256, TILE_128_SPLITSLAB, TILE_128_LOADERS, TILE_128x64_LOADERS, TILE_64_LOADERS };
-static TileKind select_tile(int layout, int M, int N, int K, bool solo) {
+enum TileKind { TILE_256, TILE_128_SPLITSLAB, TILE_128_LOADERS, TILE_128x64_LOADERS, TILE_64_LOADERS, TILE_192x128_LOADERS, TILE_256x128_LOADERS,
+                TILE_192x256, TILE_NONE };
+
+// Products that one size of tile would finish in a round and a bit: the smallest tile that makes it exactly one round (one
+// workgroup per CU). 192x128 and 256x128 as the 128x128 form (eight computing wavefronts, four loaders, three stages), 192x256 as the
+// 256x256 form. Larger tiles read fewer bytes from LDS per MFMA, and nothing is left over; a slab of 192x128 takes 0.47 us against
+// 0.37 of 128x128, of 192x256 0.95 against 1.15 of 256x256. us, the form taken before (128x128 tiles, in K ranges where a workspace allows,
+// or two per CU) / one round:
+//   192x128  2331 x 2048 x 768 13.9 / 11.5, x 2048 25.8 / 21.3, x 8192 82.7 / 66.5 (0.95 -> 1.18 PFLOP/s); 2000 x 2560 x 8192 81.1 / 69.9; NN
+//            2000 x 2560 x 4096 52.4 / 40.0; with GeLU 2331 x 2048 x 2048 30.4 / 25.1
+//   256x128  2048 x 4096 x 768 17.4 / 16.9 (with GeLU 21.2 / 21.1), x 4096 57.4 / 52.8; NN 3000 x 2560 x 2048 32.7 / 29.8, x 4096 58.4 / 51.7
+//   192x256  3500 x 2560 x 768 24.3 / 18.1, x 2048 49.7 / 37.1, x 4096 78.7 / 67.1; NN 2048 x 5504 x 4096 93.4 / 72.9 (256x256 tiles 75.9)
+// Steps: 2 x 1024 tokens of width 3072 1507 -> 1375 us, 3 x 777 of 2048 834 -> 769, 10 x 500 of 1024 613 -> 573, gated 2 x 1100 of 4096 2760 -> 2479.
+// 192x256 loses to two 128x128 workgroups per CU where those are all resident (2600 x 3072 x 768 with GeLU: 504 tiles of 128x128, forward of
+// the layer 91 / 95), and at K = 512 192x128 gains nothing (a gated layer's 2048 x 2736 x 512: forward 57.5 / 58.0). Layout TN has no
+// such tiles (the chunk permutation of rows along M needs a power of two).
+static TileKind one_round_tile(int layout, int M, int N, int K) {
+  auto count = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  const int64_t t128 = count(128, 128);
+  if (layout == GEMM_TN || K < 768 || t128 <= 256) return TILE_NONE;
+  if (count(192, 128) <= 256) return TILE_192x128_LOADERS;
+  if (count(256, 128) <= 256) return TILE_256x128_LOADERS;
+  return t128 > 512 && count(192, 256) <= 256 ? TILE_192x256 : TILE_NONE;
+}
+bool gemm_in_one_round(int dtype, int layout, int M, int N, int K) {
+  return dtype != DT_FP32 && one_round_tile(layout, M, N, K) != TILE_NONE;
+}
+
+static TileKind tile_by_count(int layout, int M, int N, int K, bool solo) {
   const int64_t t256 = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
   const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
   // A grid of 256x256 tiles runs in rounds of 256 (one workgroup per CU) and a thin last round costs a full one:
@@ -142,6 +169,11 @@ static TileKind select_tile(int layout, int M, int N, int K, bool solo) {
   return layout == GEMM_TN && K > 1024 ? TILE_128_SPLITSLAB : TILE_128_LOADERS;
 }
 
+static TileKind select_tile(int layout, int M, int N, int K, bool solo) {
+  const TileKind one = one_round_tile(layout, M, N, K);
+  return one != TILE_NONE ? one : tile_by_count(layout, M, N, K, solo);
+}
+
 // Several rounds of 128x128 tiles: two LDS stages instead of four, so that two workgroups fit a CU and one's first loads and
 // epilogue run beside the other's products. Four / two stages, same card: NT 2286 x 3072 x 768 with GeLU 24.1 / 20.7
 // us, 2331 x 8192 x 2048 101 / 93.5, 2000 x 2560 x 2560 39.2 / 34.7; NN 2048 x 4096 x 2752 44.6 / 41.9, 2331 x 2752 x
@@ -166,7 +198,7 @@ static HybridPlan hybrid_plan(int layout, int epi, int M, int N, int K) {
   HybridPlan none = {TILE_256, 0, 0, 1, 0}, p = none;
   static const bool disabled = debug_flag("no-hybrid");
   if (disabled || (epi != EPI_NONE && epi != EPI_ADD)) return none;
-  p.tile = select_tile(layout, M, N, K, false);
+  p.tile = tile_by_count(layout, M, N, K, false);
   if (p.tile == TILE_64_LOADERS) p.tile = TILE_128x64_LOADERS;   // (K ranges bring the workgroups that the smaller tiles would)
   if (layout == GEMM_TN && p.tile != TILE_256) return none;   // (K ranges of their own: weight_grad_splits)
   const int bm = p.tile == TILE_256 ? 256 : 128, bn = p.tile == TILE_256 ? 256 : p.tile == TILE_128x64_LOADERS ? 64 : 128;
@@ -347,6 +379,16 @@ static void launch_bf16(int epi, int act, int M, int N, int K, const void* A, co
       launch_bf16_tile<LAYOUT, 128, 128, 2, 4, 1, 4, 4, F16, true>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st); break;
     case TILE_128x64_LOADERS:
       launch_bf16_tile<LAYOUT, 128, 64, 2, 2, 1, 4, 4, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st); break;
+    case TILE_192x128_LOADERS:
+      if constexpr (LAYOUT != GEMM_TN) launch_bf16_tile<LAYOUT, 192, 128, 2, 4, 1, 3, 4, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
+      break;
+    case TILE_256x128_LOADERS:
+      if constexpr (LAYOUT != GEMM_TN) launch_bf16_tile<LAYOUT, 256, 128, 2, 4, 1, 3, 4, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
+      break;
+    case TILE_192x256:
+      if constexpr (LAYOUT != GEMM_TN) launch_bf16_tile<LAYOUT, 192, 256, 2, 4, 1, 2, 0, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
+      break;
+    case TILE_NONE: break;
     case TILE_64_LOADERS:
       if constexpr (LAYOUT != GEMM_TN) launch_bf16_tile<LAYOUT, 64, 64, 2, 2, 1, 3, 4, F16, false, 128>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
       break;
@@ -503,7 +545,8 @@ void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool sol
   const char* b = f16 ? "true" : "false";
   const char* kt = layout != GEMM_TN && K % 64 != 0 ? "true" : "false";
   static const char* const shape[] = {"256, 256, 64, 2, 4, 1, 2, 0", "128, 128, 64, 2, 2, 2, 4, 4", "128, 128, 64, 2, 4, 1, 4, 4",
-                                      "128, 64, 64, 2, 2, 1, 4, 4", "64, 64, 128, 2, 2, 1, 3, 4"};
+                                      "128, 64, 64, 2, 2, 1, 4, 4", "64, 64, 128, 2, 2, 1, 3, 4", "192, 128, 64, 2, 4, 1, 3, 4",
+                                      "256, 128, 64, 2, 4, 1, 3, 4", "192, 256, 64, 2, 4, 1, 2, 0"};
   if (with_ws && !(weight_grad && weight_grad_splits(M, N, K) > 1)) {
     const HybridPlan hp = hybrid_plan(layout, weight_grad ? EPI_NONE : epi, M, N, K);
     if (hp.ws_bytes) {

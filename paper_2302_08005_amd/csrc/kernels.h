@@ -27,6 +27,8 @@ void launch_gemm(int dtype, int layout, int epi, int act, int M, int N, int K, c
                  void* C, const void* bias, const void* aux_in, void* aux_out, hipStream_t st, bool solo = false,
                  float* ws = nullptr, size_t ws_bytes = 0);
 size_t gemm_ws_bytes(int dtype, int layout, int epi, int M, int N, int K);
+// tiles that make the product exactly one round, which is faster than K ranges: launch_gemm without a workspace takes them
+bool gemm_in_one_round(int dtype, int layout, int M, int N, int K);
 // Products whose reader adds up K ranges itself (the row kernels, launch_add_ranges): product_ranges says in how many ranges a
 // product of this shape is worth computing (1: not at all), launch_gemm_ranges leaves them as fp32 arrays [ranges][M][N].
 int product_ranges(int dtype, int M, int N, int K);

@@ -419,3 +419,37 @@ def test_gemm_thin_round_in_quarters(layout, epi, M, N, K):
         bt = b.float().t().contiguous() if layout == B.NT else b.float()
         ref = a[rows].float() @ bt + (kw["aux_in"][rows].float() if epi == B.EPI_ADD else 0)
         assert err(got[0][0][rows], to_np(ref)) <= TOL[dtype]
+
+
+# tiles that make the product one round: two rows and eight columns beyond whole tiles, partial slabs
+@pytest.mark.parametrize("dtype", [W.BF16, W.FP16])
+@pytest.mark.parametrize("layout", [B.NT, B.NN])
+@pytest.mark.parametrize("M,N,name", [(2306, 2192, "192, 128, 64, 2, 4, 1, 3, 4"), (2050, 3472, "256, 128, 64, 2, 4, 1, 3, 4"), (3266, 3344, "192, 256, 64, 2, 4, 1, 2, 0")])
+def test_epilogues_of_one_round_tiles(M, N, name, layout, dtype):
+    """The bound of test_epilogues_of_every_tile_form."""
+    for K in (768, 840):
+        rng = np.random.default_rng(K + layout + M)
+        a, b = store(rng.standard_normal((M, K)), dtype), store(rng.standard_normal((K, N)) * K ** -0.5, dtype)
+        bias, aux = store(rng.standard_normal(N), dtype), store(rng.standard_normal((M, 2 * N)), dtype)
+        acc = (torch.from_numpy(a) @ torch.from_numpy(b)).double().numpy()
+        A, Bm = to_dev(a, dtype), to_dev(b.T.copy() if layout == B.NT else b, dtype)
+        keep = torch.empty(M, N, dtype=A.dtype, device=DEV)
+
+        def run(epi, act=W.GELU, width=N, aux_in=None, aux_out=None):
+            assert name in B.slapo_gemm_kernel_name(dtype, layout, epi, M, N, K)
+            out = torch.full((M + 1, width), 7.0, dtype=A.dtype, device=DEV)
+            B.slapo_gemm(dtype, layout, epi, act, M, N, K, A, Bm, out[:M], bias=to_dev(bias, dtype), aux_in=aux_in, aux_out=aux_out)
+            assert (out[M] == 7).all()
+            return out[:M]
+
+        errs = {"none": err(run(B.EPI_NONE), acc)}
+        if layout == B.NT:
+            gate, up = acc[:, ::2], acc[:, 1::2]
+            errs.update({"bias": err(run(B.EPI_BIAS), acc + bias), "gelu": err(run(B.EPI_BIAS_ACT, aux_out=keep), _act(acc + bias, W.GELU))})
+            errs["gelu'"] = err(keep, _dact(acc + bias, W.GELU))
+            errs["gate"] = err(run(B.EPI_GATE, width=N // 2, aux_out=keep), gate / (1 + np.exp(-gate)) * up)
+        else:
+            aux1 = to_dev(aux[:, :N].copy(), dtype)
+            errs.update({"add": err(run(B.EPI_ADD, aux_in=aux1), acc + aux[:, :N]), "dgelu": err(run(B.EPI_DACT, aux_in=aux1), acc * aux[:, :N]),
+                         "dgate": err(run(B.EPI_DGATE, width=2 * N, aux_in=to_dev(aux, dtype)), np.repeat(acc, 2, 1) * aux)})
+        assert all(v <= {W.BF16: 4e-3, W.FP16: 5e-4}[dtype] for v in errs.values()), (K, errs)
