@@ -1119,8 +1119,15 @@ __device__ __forceinline__ void attn_bwd_dq_block(const BlockId blk, const AttnS
 }
 
 // ============================ backward: the launches =============================================
-template <int D, bool DROP, bool F16>
-__global__ __launch_bounds__(256) void attn_bwd_dq_bf16_kernel(AttnShape sh, const bf16_t* __restrict__ qkv,
+// OCC: wavefronts per SIMD. 128-wide heads: two, in 230 (mask draws) or 244 registers; left to itself the kernel with mask draws takes
+// 257 and runs one. dQ and dK/dV with mask draws, us, one / two: 64 x 64 tokens, 16 heads 72.2 / 64.5, 128 x 32, 8 62.5 / 54.6, 32 x 520, 5
+// 254 / 225, causal 4 x 504, 26 86 / 80, 3 x 1000, 20 210 / 187, 2 x 2048, 20 310 / 278. One where that is faster: causal grids of 300 to 384 blocks,
+// a round of the chip and a bit, whose last and shortest blocks then start behind the first that end instead of beside long ones: 2 x
+// 1000, 20 (320 blocks) 108 / 114, 1 x 1800, 20 (300) 210 / 225, 2 x 1504, 16 (384) 153 / 161, 1 x 4096, 10 (320) 432 / 479, 10 x 504, 8 (320) 64.6
+// / 67.0, but 3 x 896, 15 (315) 131 / 128. Not below (3 x 264, 32, 288 blocks 49.2 / 46.6; 2 x 1000, 18 162 / 157), above (18 x 384, 8, 432 74.7 /
+// 69.2; 2 x 1000, 28, 448 131 / 127) or with short walks (7 x 384, 16, 336 63.4 / 60.7).
+template <int D, bool DROP, bool F16, int OCC>
+__global__ __launch_bounds__(256, OCC) void attn_bwd_dq_bf16_kernel(AttnShape sh, const bf16_t* __restrict__ qkv,
                                                                const int32_t* __restrict__ seqlens, const bf16_t* __restrict__ out,
                                                                const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                                                                float* __restrict__ delta, bf16_t* __restrict__ dqkv) {
@@ -1686,8 +1693,8 @@ static void bwd_bf16(const AttnShape& s, const void* qkv, const int32_t* seqlens
   // 48.5 / 45.3 / 54, 1536 (6 x 1024, causal) 132 / 141; 128-wide 64 (2 x 1024, causal) 68 / 44.5 / 29, 128 (2 x 512) 44 / 29 / 34.5,
   // 192 (3 x 1024, causal) 73 / 46 / 57, 256 (4 x 1024, causal) 74 / 56 / 68, 384 80 / 85; not causal 216 (24 x 1032) 84 / 77,
   // 255 (15 x 2056) 159 / 166. With mask draws, 64-wide 16 blocks 18.7 / - / 9.2, 128 (1024, causal) 85 / - / 43, 256 (4 x 512) 48.5 /
-  // 34.8, 512 (8 x 512) 70.5 / 65.3; 128-wide causal 256 116 / 85, not causal 160 (32 x 520) 69 / 61, 189 (21 x 1032) 122 / 130, 256
-  // (4 x 512) 69.2 / 71.5.
+  // 34.8, 512 (8 x 512) 70.5 / 65.3; 128-wide causal 256 116 / 85, not causal 144 (16 x 1032) 123 / 99, 160
+  // (4 x 512) 61 / 54, 176 (4 x 512) 61 / 64, 256 (4 x 512) 62.6 / 66.9.
   // Beside weight gradients in K ranges (s.beside) two launches again from 129 to 256 blocks of 64-wide heads: one at a time
   // they leave the half of every CU's LDS that a workgroup of those needs. Steps at hidden 256, two launches / one: 52 x 128 tokens
   // 215 / 217 us, 10 x 670 234 / 246, 16 x 512 245 / 255, 7 x 1024 229 / 253, 8 x 1024 262 / 271; up to 6143 tokens, without K
@@ -1698,7 +1705,11 @@ static void bwd_bf16(const AttnShape& s, const void* qkv, const int32_t* seqlens
   if (blocks <= room && !make_way) return bwd_both<D, F16, 1>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
   {  // dQ first: it also produces delta = rowsum(dO * O), which the dK/dV kernel reads
     const size_t lds = lds_dq;
-    auto kern = s.drop.thr ? attn_bwd_dq_bf16_kernel<D, true, F16> : attn_bwd_dq_bf16_kernel<D, false, F16>;
+    constexpr int OCC = D == 128 ? 2 : 1;
+    const bool alone = D == 128 && s.causal && s.seq >= 504 && blocks >= 300 && blocks <= 384;
+    auto kern = !s.drop.thr ? attn_bwd_dq_bf16_kernel<D, false, F16, OCC>
+                : alone     ? attn_bwd_dq_bf16_kernel<D, true, F16, 1>
+                            : attn_bwd_dq_bf16_kernel<D, true, F16, OCC>;
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, s, (const bf16_t*)qkv, seqlens, (const bf16_t*)out,
                        (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv);

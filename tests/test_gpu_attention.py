@@ -266,3 +266,26 @@ def test_attention_writes_its_rows_only(S, heads, d):
     got = dqkv[:S].reshape(S, 3, H)
     for i in range(3):
         assert err(got[:, i, :few * d], ref[:, i]) <= TOL[W.BF16], i
+
+
+# 128-wide heads with mask draws: 300 to 384 blocks of a causal grid run one per CU, fewer and more two
+@pytest.mark.parametrize("heads", [74, 75, 96, 97])
+def test_dq_with_draws_by_grid(heads):
+    S, d, few = 504, 128, 2
+    H = heads * d
+    cfg = W.LayerConfig("t", 1, S, H, heads, 64, causal=1, dtype=W.FP16, attn_dropout_p=0.1, seed=7, layer_id=1)
+    part = cfg.replace(hidden=few * d, heads=few)   # (a mask element's index counts the heads before it, not all of them)
+    rng = np.random.default_rng(heads)
+    qkv, dout = store(rng.standard_normal((S, 3, H)), W.FP16), store(rng.standard_normal((S, H)), W.FP16)
+    qkv_part = np.ascontiguousarray(qkv[:, :, :few * d]).reshape(S, -1).astype(np.float64)
+    A_ref, P, _ = L.attention_fwd(part, qkv_part, None)
+    ref = L.attention_bwd(part, qkv_part, P, dout[:, :few * d].astype(np.float64)).reshape(S, 3, few * d)
+    desc, qkv_d = B.make_desc(cfg, hidden=64, attn_dim=H), to_dev(qkv.reshape(S, -1), W.FP16)
+    out, dqkv = torch.empty(S, H, dtype=torch.float16, device=DEV), torch.empty_like(qkv_d)
+    lse, delta = (torch.empty(heads, S, device=DEV) for _ in range(2))
+    B.slapo_attn_fwd(desc, qkv_d, None, out, lse)
+    B.slapo_attn_bwd(desc, qkv_d, None, out, to_dev(dout, W.FP16), lse, delta, dqkv)
+    assert err(out[:, :few * d], A_ref) <= TOL[W.FP16]
+    got = dqkv.reshape(S, 3, H)
+    for i in range(3):
+        assert err(got[:, i, :few * d], ref[:, i]) <= TOL[W.FP16], i
