@@ -169,46 +169,72 @@ __device__ __forceinline__ float* group_slot(void* smem, int grp, int row_wave, 
   return reinterpret_cast<float*>(smem) + ((grp - 1) * (4 / G) + row_wave) * (REGS * 64) + lane;
 }
 
-// A wavefront's 32 rows of output, [32][D], on their way out. A lane's accumulators are four columns of one row at a time, 8 bytes:
-// stored as they are, an instruction touches 32 rows with 16 bytes each, and the L2 sees every 128-byte line eight times. Through
-// LDS (the stages are free by then) each 8 bytes of a lane join those of its neighbours to whole rows. Rows are padded by 8
-// bytes, so that the 8-byte writes of 32 rows meet every bank once. us, 8-byte stores -> whole rows, forward / backward (samples x
-// tokens, heads): 64-wide 128 x 128, 16 26.5 -> 24.0 / 88.9 -> 76.1; 16 x 256, 16 11.1 -> 10.4 / 31.5 -> 27.0; 32 x 512, 16 45.7 -> 43.3 /
-// 150 -> 141; 8 x 1024, 32 causal 55.3 -> 52.7 / 170 -> 161; 128-wide causal 4 x 1024, 32 55.5 -> 52.8 / 178 -> 163; 4 x 2048, 20 108 ->
-// 104 / 350 -> 332; the longer the walk the less: 1 x 8192, 20 437 / 1238 -> 1222.
-template <int D, bool F16>
+// A wavefront's 32 rows of output, [32][D] in its accumulators, on their way out. A lane has four columns of one row at a time, 8
+// bytes: stored as they are, an instruction touches 32 rows with 16 bytes each, and the L2 sees every 128-byte line eight times.
+// Through LDS (the stages are free by then) each 8 bytes of a lane join those of its neighbours to whole rows. us, as they are ->
+// whole rows, forward / backward (samples x tokens, heads): 64-wide 64 x 64, 16 7.8 -> 7.3 / 29.3 -> 26.9; 6 x 381, 12 9.5 -> 9.4 / 20.0 -> 18.9; 8 x
+// 512, 16 16.4 -> 15.2 / 43.5 -> 40.0; 8 x 1024, 32 causal 57.6 -> 55.4 / 174 -> 162; 128-wide causal 4 x 1024, 32 56.4 -> 53.4 / 184 -> 166; 4 x 2048, 20
+// 111 -> 107 / 360 -> 338; the longer the walk the less: 1 x 8192, 20 451 -> 449 / 1277 -> 1274.
+// As they are where that is faster: where a wavefront has fewer than 32 rows (the last, and in causal grids longest, block of 1 x 152, 19,
+// causal, forward 64-wide 5.8 / 6.0, 128-wide 7.2 / 7.6), and where no other wavefront of the block has any (SHORT, sequences up to 32:
+// 16 x 32, 8 forward 64-wide 4.1 / 4.3, 128-wide 5.0 / 5.5, backward 5.4 / 5.6, 8.1 / 8.3; 8 x 64, 8 3.9 / 3.9, 6.0 / 5.6). Those
+// have instances of their own, in which nothing is left of the other way: it costs their launches of 4-8 us 1-2 %.
+template <int D, bool F16, bool SHORT>
 struct RowsOut {
-  static constexpr int P = D + 4;          // row pitch in elements
+  static constexpr int P = D + 4;          // row pitch in elements: 8 bytes more, so that the 8-byte writes of 32 rows meet every bank once
   static constexpr int ELEMS = 32 * P;
   bf16_t* stage;                           // of this wavefront
-  int lane;
-  // columns 32 t + 8 g + 4 (lane / 32) .. + 3 of row lane % 32
-  __device__ __forceinline__ void put(int t, int g, float a, float b, float c, float d) const {
-    *reinterpret_cast<uint2*>(stage + (lane & 31) * P + t * 32 + g * 8 + 4 * (lane >> 5)) = make_uint2(pack2<F16>(a, b), pack2<F16>(c, d));
-  }
-  // rows 0 .. rows - 1 to out + row * stride. table: the rows are turned back by the rotary angles of the positions pos0 + row.
-  __device__ __forceinline__ void flush(bf16_t* out, int64_t stride, int rows, const float* __restrict__ table = nullptr, int pos0 = 0) const {
-    constexpr int CPR = D / 8, RPI = 64 / CPR;   // 16-byte chunks per row, rows per access
-    const int c = (lane % CPR) * 8;
+  int lane, first, rows;                   // first row; of the 32 from there on, so many exist
+  __device__ __forceinline__ RowsOut(bf16_t* stage, int lane, int first, int seq) : stage(stage), lane(lane), first(first), rows(seq - first) {}
+  // What the lanes of this wavefront have written is there for its other lanes, and they are done with what was there before
+  // (its LDS accesses are executed in order; this binds the compiler).
+  static __device__ __forceinline__ void meet() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int i = 0; i < 32 / RPI; ++i) {
-      const int row = i * RPI + lane / CPR;
-      const uint2* p = reinterpret_cast<const uint2*>(stage + row * P + c);
-      uint2 w0 = p[0], w1 = p[1];
+  }
+  static __device__ __forceinline__ uint2 turned(uint2 w, const float* __restrict__ table, int pos, int col) {
+    float v[4] = {unpack_lo<F16>(w.x), unpack_hi<F16>(w.x), unpack_lo<F16>(w.y), unpack_hi<F16>(w.y)};
+    rope_back(v, table, pos, D, col);
+    return make_uint2(pack2<F16>(v[0], v[1]), pack2<F16>(v[2], v[3]));
+  }
+  // value(t, e): column 32 t + 8 (e / 4) + 4 (lane / 32) + e % 4 of row lane % 32. out: the first row, the others `stride` apart.
+  // table: the rows are turned back by the rotary angles of their positions.
+  template <class Value>
+  __device__ __forceinline__ void store(Value&& value, bf16_t* out, int64_t stride, const float* __restrict__ table = nullptr) const {
+    const int row = lane & 31, col = 4 * (lane >> 5);
+    if (SHORT || rows < 32) {
       if (row < rows) {
-        if (table) {   // (uniform)
-          float v[4] = {unpack_lo<F16>(w0.x), unpack_hi<F16>(w0.x), unpack_lo<F16>(w0.y), unpack_hi<F16>(w0.y)};
-          rope_back(v, table, pos0 + row, D, c);
-          w0 = make_uint2(pack2<F16>(v[0], v[1]), pack2<F16>(v[2], v[3]));
-          float u[4] = {unpack_lo<F16>(w1.x), unpack_hi<F16>(w1.x), unpack_lo<F16>(w1.y), unpack_hi<F16>(w1.y)};
-          rope_back(u, table, pos0 + row, D, c + 4);
-          w1 = make_uint2(pack2<F16>(u[0], u[1]), pack2<F16>(u[2], u[3]));
-        }
-        *reinterpret_cast<uint4*>(out + row * stride + c) = make_uint4(w0.x, w0.y, w1.x, w1.y);
+#pragma unroll
+        for (int t = 0; t < D / 32; ++t)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            uint2 w = make_uint2(pack2<F16>(value(t, 4 * g), value(t, 4 * g + 1)), pack2<F16>(value(t, 4 * g + 2), value(t, 4 * g + 3)));
+            if (table) w = turned(w, table, first + row, t * 32 + g * 8 + col);   // (uniform)
+            *reinterpret_cast<uint2*>(out + (row * stride + t * 32 + g * 8 + col)) = w;
+          }
+      }
+      return;
+    }
+    if constexpr (!SHORT) {
+      meet();
+#pragma unroll
+      for (int t = 0; t < D / 32; ++t)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *reinterpret_cast<uint2*>(stage + row * P + t * 32 + g * 8 + col) =
+              make_uint2(pack2<F16>(value(t, 4 * g), value(t, 4 * g + 1)), pack2<F16>(value(t, 4 * g + 2), value(t, 4 * g + 3)));
+      meet();
+      constexpr int CPR = D / 8, RPI = 64 / CPR;   // 16-byte chunks per row, rows per access
+      const int c = (lane % CPR) * 8;
+#pragma unroll
+      for (int i = 0; i < 32 / RPI; ++i) {
+        const int r = i * RPI + lane / CPR;
+        const uint2* p = reinterpret_cast<const uint2*>(stage + r * P + c);
+        uint2 w0 = p[0], w1 = p[1];
+        if (table) { w0 = turned(w0, table, first + r, c); w1 = turned(w1, table, first + r, c + 4); }   // (uniform)
+        *reinterpret_cast<uint4*>(out + (r * stride + c)) = make_uint4(w0.x, w0.y, w1.x, w1.y);
       }
     }
-    __builtin_amdgcn_wave_barrier();   // (the next rows overwrite these)
   }
 };
 
@@ -324,7 +350,7 @@ __device__ __forceinline__ BlockId xcd_local_block(bool descending, int lpt_head
 // not the depth of the prefetch, are what hides the latencies here) and unchanged on the others.
 template <int D> constexpr int FWD_STAGES = 2;
 
-template <int D, bool DROP, bool F16, int G>
+template <int D, bool DROP, bool F16, int G, bool SHORT>
 __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const bf16_t* __restrict__ qkv,
                                                             const int32_t* __restrict__ seqlens,
                                                             bf16_t* __restrict__ out, float* __restrict__ lse) {
@@ -499,12 +525,9 @@ __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const 
   const float l_tot = l + __shfl_xor(l, 32, 64);
   const float inv = l_tot > 0.f ? (DROP ? sh.drop.scale : 1.f) / l_tot : 0.f;
   // (a group's wavefront writes over its own slot of what the groups handed it)
-  const RowsOut<D, F16> rows = {smem + row_wave * (G > 1 ? (NT * 16 + 2) * 128 : RowsOut<D, F16>::ELEMS), lane};
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) rows.put(t, g, o[t][4 * g] * inv, o[t][4 * g + 1] * inv, o[t][4 * g + 2] * inv, o[t][4 * g + 3] * inv);
-  rows.flush(out + ((int64_t)b * S + wave_q_min) * H + a * D, H, S - wave_q_min);
+  const RowsOut<D, F16, SHORT> rows(smem + row_wave * (G > 1 ? (NT * 16 + 2) * 128 : RowsOut<D, F16, SHORT>::ELEMS), lane, wave_q_min, S);
+  if (rows.rows <= 0) return;
+  rows.store([&](int t, int e) { return o[t][e] * inv; }, out + ((int64_t)b * S + rows.first) * H + a * D, H);
   if (my_q < S) {
     if (kc == 0) lse[((int64_t)b * sh.heads + a) * S + my_q] = l_tot > 0.f ? m * scale + __logf(l_tot) : -INFINITY;
   }
@@ -552,7 +575,7 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(AttnShape sh, const T* 
 template <int D> constexpr int DKDV_STAGES = 2;
 
 // OWN_DELTA: delta = rowsum(dO * O) of each query tile is computed here (see attn_bwd_both_kernel) instead of read.
-template <int D, bool DROP, bool F16, bool OWN_DELTA, int G>
+template <int D, bool DROP, bool F16, bool OWN_DELTA, int G, bool SHORT>
 __device__ __forceinline__ void attn_bwd_dkdv_block(const BlockId blk, const AttnShape& sh, const bf16_t* __restrict__ qkv,
                                                     const int32_t* __restrict__ seqlens, const bf16_t* __restrict__ out,
                                                     const bf16_t* __restrict__ dout, const float* __restrict__ lse,
@@ -958,22 +981,16 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(const BlockId blk, const Att
         for (int r = 0; r < 16; ++r) { dk[t][r] += p[(t * 16 + r) * 64]; dv[t][r] += p[((NT + t) * 16 + r) * 64]; }
     }
   }
-  const RowsOut<D, F16> rows = {smem + row_wave * (G > 1 ? 2 * NT * 16 * 128 : RowsOut<D, F16>::ELEMS), lane};
-  bf16_t* krow = dqkv + ((int64_t)b * S + wave_kv_min) * rs + H + a * D;
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) rows.put(t, g, dk[t][4 * g] * scale, dk[t][4 * g + 1] * scale, dk[t][4 * g + 2] * scale, dk[t][4 * g + 3] * scale);
-  rows.flush(krow, rs, S - wave_kv_min, sh.rope, wave_kv_min);
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) rows.put(t, g, dv[t][4 * g], dv[t][4 * g + 1], dv[t][4 * g + 2], dv[t][4 * g + 3]);
-  rows.flush(krow + H, rs, S - wave_kv_min);
+  const RowsOut<D, F16, SHORT> rows(smem + row_wave * (G > 1 ? 2 * NT * 16 * 128 : RowsOut<D, F16, SHORT>::ELEMS), lane,
+                                    SHORT ? wave_kv_min : __builtin_amdgcn_readfirstlane(wave_kv_min), S);
+  if (rows.rows <= 0) return;
+  bf16_t* krow = dqkv + ((int64_t)b * S + rows.first) * rs + H + a * D;
+  rows.store([&](int t, int e) { return dk[t][e] * scale; }, krow, rs, sh.rope);
+  rows.store([&](int t, int e) { return dv[t][e]; }, krow + H, rs);
 }
 
 // ============================ backward: dQ per query tile ========================================
-template <int D, bool DROP, bool F16, int G>
+template <int D, bool DROP, bool F16, int G, bool SHORT>
 __device__ __forceinline__ void attn_bwd_dq_block(const BlockId blk, const AttnShape& sh, const bf16_t* __restrict__ qkv,
                                                   const int32_t* __restrict__ seqlens, const bf16_t* __restrict__ out,
                                                   const bf16_t* __restrict__ dout, const float* __restrict__ lse,
@@ -1110,53 +1127,51 @@ __device__ __forceinline__ void attn_bwd_dq_block(const BlockId blk, const AttnS
     }
   }
 
-  const RowsOut<D, F16> rows = {smem + row_wave * (G > 1 ? NT * 16 * 128 : RowsOut<D, F16>::ELEMS), lane};
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) rows.put(t, g, dq[t][4 * g] * scale, dq[t][4 * g + 1] * scale, dq[t][4 * g + 2] * scale, dq[t][4 * g + 3] * scale);
-  rows.flush(dqkv + ((int64_t)b * S + wave_q_min) * rs + a * D, rs, S - wave_q_min, sh.rope, wave_q_min);
+  const RowsOut<D, F16, SHORT> rows(smem + row_wave * (G > 1 ? NT * 16 * 128 : RowsOut<D, F16, SHORT>::ELEMS), lane,
+                                    SHORT ? wave_q_min : __builtin_amdgcn_readfirstlane(wave_q_min), S);
+  if (rows.rows <= 0) return;
+  rows.store([&](int t, int e) { return dq[t][e] * scale; }, dqkv + ((int64_t)b * S + rows.first) * rs + a * D, rs, sh.rope);
 }
 
 // ============================ backward: the launches =============================================
-// OCC: wavefronts per SIMD. 128-wide heads: two, in 230 (mask draws) or 244 registers; left to itself the kernel with mask draws takes
-// 257 and runs one. dQ and dK/dV with mask draws, us, one / two: 64 x 64 tokens, 16 heads 72.2 / 64.5, 128 x 32, 8 62.5 / 54.6, 32 x 520, 5
+// OCC: wavefronts per SIMD at least. 128-wide heads with mask draws: two, in 230 registers; left to itself the kernel takes 257 and runs
+// one (without mask draws it takes 248, and is 1 % slower in the 244 that a bound brings: 1 x 8192 tokens, 20 heads 1261 / 1272). dQ and dK/dV with mask draws, us, one / two: 64 x 64 tokens, 16 heads 72.2 / 64.5, 128 x 32, 8 62.5 / 54.6, 32 x 520, 5
 // 254 / 225, causal 4 x 504, 26 86 / 80, 3 x 1000, 20 210 / 187, 2 x 2048, 20 310 / 278. One where that is faster: causal grids of 300 to 384 blocks,
 // a round of the chip and a bit, whose last and shortest blocks then start behind the first that end instead of beside long ones: 2 x
 // 1000, 20 (320 blocks) 108 / 114, 1 x 1800, 20 (300) 210 / 225, 2 x 1504, 16 (384) 153 / 161, 1 x 4096, 10 (320) 432 / 479, 10 x 504, 8 (320) 64.6
 // / 67.0, but 3 x 896, 15 (315) 131 / 128. Not below (3 x 264, 32, 288 blocks 49.2 / 46.6; 2 x 1000, 18 162 / 157), above (18 x 384, 8, 432 74.7 /
 // 69.2; 2 x 1000, 28, 448 131 / 127) or with short walks (7 x 384, 16, 336 63.4 / 60.7).
-template <int D, bool DROP, bool F16, int OCC>
+template <int D, bool DROP, bool F16, bool SHORT, int OCC>
 __global__ __launch_bounds__(256, OCC) void attn_bwd_dq_bf16_kernel(AttnShape sh, const bf16_t* __restrict__ qkv,
                                                                const int32_t* __restrict__ seqlens, const bf16_t* __restrict__ out,
                                                                const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                                                                float* __restrict__ delta, bf16_t* __restrict__ dqkv) {
-  attn_bwd_dq_block<D, DROP, F16, 1>(xcd_local_block(sh.causal != 0, sh.lpt_heads), sh, qkv, seqlens, out, dout, lse, delta, dqkv);
+  attn_bwd_dq_block<D, DROP, F16, 1, SHORT>(xcd_local_block(sh.causal != 0, sh.lpt_heads), sh, qkv, seqlens, out, dout, lse, delta, dqkv);
 }
-template <int D, bool DROP, bool F16>
+template <int D, bool DROP, bool F16, bool SHORT>
 __global__ __launch_bounds__(256) void attn_bwd_dkdv_bf16_kernel(AttnShape sh, const bf16_t* __restrict__ qkv,
                                                                  const int32_t* __restrict__ seqlens, const bf16_t* __restrict__ dout,
                                                                  const float* __restrict__ lse, const float* __restrict__ delta,
                                                                  bf16_t* __restrict__ dqkv) {
-  attn_bwd_dkdv_block<D, DROP, F16, false, 1>(xcd_local_block(false, sh.lpt_heads), sh, qkv, seqlens, nullptr, dout, lse, delta, dqkv);
+  attn_bwd_dkdv_block<D, DROP, F16, false, 1, SHORT>(xcd_local_block(false, sh.lpt_heads), sh, qkv, seqlens, nullptr, dout, lse, delta, dqkv);
 }
 // Both in one launch, for grids so small that the blocks of the two find room side by side: the dK/dV blocks first (they
 // take longer), each with its own delta of every query tile (O is read once more, which a chip that is mostly idle does
 // not notice), so that neither kind waits for the other. Two groups at 128-wide heads have no registers left for that:
 // delta comes from a kernel in front.
 template <int D, int G> constexpr bool OWN_DELTAS = D == 64 || G == 1;
-template <int D, bool DROP, bool F16, int G>
+template <int D, bool DROP, bool F16, int G, bool SHORT>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_bwd_both_kernel(AttnShape sh, int blocks_x, const bf16_t* __restrict__ qkv,
                                                             const int32_t* __restrict__ seqlens, const bf16_t* __restrict__ out,
                                                             const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                                                             float* delta, bf16_t* __restrict__ dqkv) {
   const int blocks = blocks_x * sh.heads * sh.batch, w = blockIdx.x;
   if (w < blocks)
-    attn_bwd_dkdv_block<D, DROP, F16, OWN_DELTAS<D, G>, G>(xcd_local_block(w, blocks_x, sh.heads, sh.batch, false, sh.lpt_heads), sh, qkv,
+    attn_bwd_dkdv_block<D, DROP, F16, OWN_DELTAS<D, G>, G, SHORT>(xcd_local_block(w, blocks_x, sh.heads, sh.batch, false, sh.lpt_heads), sh, qkv,
                                                            seqlens, out, dout, lse, delta, dqkv);
   else
     // (with deltas of the other kind's own, `delta` is left filled all the same, as by the other forms)
-    attn_bwd_dq_block<D, DROP, F16, G>(xcd_local_block(w - blocks, blocks_x, sh.heads, sh.batch, sh.causal != 0, sh.lpt_heads), sh, qkv,
+    attn_bwd_dq_block<D, DROP, F16, G, SHORT>(xcd_local_block(w - blocks, blocks_x, sh.heads, sh.batch, sh.causal != 0, sh.lpt_heads), sh, qkv,
                                        seqlens, out, dout, lse, OWN_DELTAS<D, G> ? delta : nullptr, dqkv);
 }
 
@@ -1585,13 +1600,14 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_simple_kernel(AttnShape sh,
 // =================================== launchers ===================================================
 // Blocks of 128 rows that the chip runs at a time where they fit a CU twice (64-wide heads) or once.
 template <int D> constexpr int64_t ONE_ROUND = D == 64 ? 512 : 256;
+constexpr int SHORT_SEQ = 32;   // (RowsOut)
 static int64_t attn_blocks(const AttnShape& s) { return (int64_t)((s.seq + 127) / 128) * s.heads * s.batch; }
 
-template <int D, bool F16, int G>
+template <int D, bool F16, int G, bool SHORT = false>
 static void fwd_bf16_groups(const AttnShape& s, const void* qkv, const int32_t* seqlens, void* out, float* lse, hipStream_t st) {
   constexpr size_t tiles = (size_t)FWD_STAGES<D> * G * 2 * Tile<D>::ELEMS * sizeof(bf16_t) + (G > 1 ? 128 * sizeof(float) : 0);
   constexpr size_t meet = (size_t)(G - 1) * (4 / G) * (D / 2 + 2) * 64 * sizeof(float), lds = tiles > meet ? tiles : meet;
-  auto kern = s.drop.thr ? attn_fwd_bf16_kernel<D, true, F16, G> : attn_fwd_bf16_kernel<D, false, F16, G>;
+  auto kern = s.drop.thr ? attn_fwd_bf16_kernel<D, true, F16, G, SHORT> : attn_fwd_bf16_kernel<D, false, F16, G, SHORT>;
   (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   constexpr int rows = 128 / G;
   hipLaunchKernelGGL(kern, dim3((s.seq + rows - 1) / rows, s.heads, s.batch), dim3(256), lds, st, s, (const bf16_t*)qkv,
@@ -1624,7 +1640,8 @@ static bool fwd_two_groups(const AttnShape& s) {
 }
 template <int D, bool F16>
 static void fwd_bf16(const AttnShape& s, const void* qkv, const int32_t* seqlens, void* out, float* lse, hipStream_t st) {
-  if (fwd_two_groups<D>(s)) fwd_bf16_groups<D, F16, 2>(s, qkv, seqlens, out, lse, st);
+  if (s.seq <= SHORT_SEQ) fwd_bf16_groups<D, F16, 1, true>(s, qkv, seqlens, out, lse, st);
+  else if (fwd_two_groups<D>(s)) fwd_bf16_groups<D, F16, 2>(s, qkv, seqlens, out, lse, st);
   else fwd_bf16_groups<D, F16, 1>(s, qkv, seqlens, out, lse, st);
 }
 template <int D>
@@ -1660,13 +1677,13 @@ void launch_attn_fwd(int dtype, const AttnShape& s0, const void* qkv, const int3
   else { if (D == 64) fwd_bf16<64, false>(s, qkv, seqlens, out, lse, st); else fwd_bf16<128, false>(s, qkv, seqlens, out, lse, st); }
 }
 
-template <int D, bool F16, int G>
+template <int D, bool F16, int G, bool SHORT = false>
 static void bwd_both(const AttnShape& s, const void* qkv, const int32_t* seqlens, const void* out, const void* dout,
                      const float* lse, float* delta, void* dqkv, hipStream_t st) {
   constexpr size_t tiles = (size_t)DKDV_STAGES<D> * G * (2 * Tile<D>::ELEMS + 256) * sizeof(bf16_t);
   constexpr size_t meet = (size_t)(G - 1) * (4 / G) * D * 64 * sizeof(float);
   const size_t main = tiles + (s.drop.thr ? 4 * 2048 : 0), lds = main > meet ? main : meet;
-  auto kern = s.drop.thr ? attn_bwd_both_kernel<D, true, F16, G> : attn_bwd_both_kernel<D, false, F16, G>;
+  auto kern = s.drop.thr ? attn_bwd_both_kernel<D, true, F16, G, SHORT> : attn_bwd_both_kernel<D, false, F16, G, SHORT>;
   (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (!OWN_DELTAS<D, G>) {
     using T = std::conditional_t<F16, f16_t, bf16_t>;
@@ -1678,13 +1695,35 @@ static void bwd_both(const AttnShape& s, const void* qkv, const int32_t* seqlens
   hipLaunchKernelGGL(kern, dim3(2 * blocks_x * s.heads * s.batch), dim3(256), lds, st, s, blocks_x, (const bf16_t*)qkv, seqlens,
                      (const bf16_t*)out, (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv);
 }
+// dQ first: it also produces delta = rowsum(dO * O), which the dK/dV kernel reads
+template <int D, bool F16, bool SHORT>
+static void bwd_two_launches(const AttnShape& s, const void* qkv, const int32_t* seqlens, const void* out, const void* dout,
+                             const float* lse, float* delta, void* dqkv, hipStream_t st) {
+  const dim3 grid((s.seq + 127) / 128, s.heads, s.batch);
+  const int64_t blocks = attn_blocks(s);
+  {
+    const size_t lds = (size_t)4 * Tile<D>::ELEMS * sizeof(bf16_t);
+    constexpr int OCC = D == 128 ? 2 : 1;
+    const bool alone = !SHORT && D == 128 && s.causal && s.seq >= 504 && blocks >= 300 && blocks <= 384;
+    auto kern = !s.drop.thr ? attn_bwd_dq_bf16_kernel<D, false, F16, SHORT, 1>
+                : alone     ? attn_bwd_dq_bf16_kernel<D, true, F16, SHORT, SHORT ? OCC : 1>
+                            : attn_bwd_dq_bf16_kernel<D, true, F16, SHORT, OCC>;
+    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, s, (const bf16_t*)qkv, seqlens, (const bf16_t*)out,
+                       (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv);
+  }
+  {
+    // with dropout: 2 KB per wavefront behind the stages for the exchange of mask draws
+    const size_t lds = (size_t)DKDV_STAGES<D> * (2 * Tile<D>::ELEMS + 256) * sizeof(bf16_t) + (s.drop.thr ? 4 * 2048 : 0);
+    auto kern = s.drop.thr ? attn_bwd_dkdv_bf16_kernel<D, true, F16, SHORT> : attn_bwd_dkdv_bf16_kernel<D, false, F16, SHORT>;
+    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, s, (const bf16_t*)qkv, seqlens, (const bf16_t*)dout, lse,
+                       (const float*)delta, (bf16_t*)dqkv);
+  }
+}
 template <int D, bool F16>
 static void bwd_bf16(const AttnShape& s, const void* qkv, const int32_t* seqlens, const void* out, const void* dout,
                      const float* lse, float* delta, void* dqkv, hipStream_t st) {
-  dim3 grid((s.seq + 127) / 128, s.heads, s.batch);
-  const size_t lds_dq = (size_t)4 * Tile<D>::ELEMS * sizeof(bf16_t);
-  // with dropout: 2 KB per wavefront behind the stages for the exchange of mask draws
-  const size_t lds_dkdv = (size_t)DKDV_STAGES<D> * (2 * Tile<D>::ELEMS + 256) * sizeof(bf16_t) + (s.drop.thr ? 4 * 2048 : 0);
   // One launch while either kind's blocks alone fit one round (128-wide blocks that do not differ in length: while they
   // leave an eighth of the chip free, with mask draws three eighths); two groups per block while the four times as many
   // blocks do.
@@ -1702,24 +1741,13 @@ static void bwd_bf16(const AttnShape& s, const void* qkv, const int32_t* seqlens
   const int64_t blocks = attn_blocks(s), room = D == 64 || s.causal ? ONE_ROUND<D> : s.drop.thr ? 160 : 224;
   if (blocks <= ONE_ROUND<D> / (s.causal ? 2 : 4) && s.seq > 64) return bwd_both<D, F16, 2>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
   const bool make_way = D == 64 && s.beside && blocks > 128 && blocks <= 256;
-  if (blocks <= room && !make_way) return bwd_both<D, F16, 1>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
-  {  // dQ first: it also produces delta = rowsum(dO * O), which the dK/dV kernel reads
-    const size_t lds = lds_dq;
-    constexpr int OCC = D == 128 ? 2 : 1;
-    const bool alone = D == 128 && s.causal && s.seq >= 504 && blocks >= 300 && blocks <= 384;
-    auto kern = !s.drop.thr ? attn_bwd_dq_bf16_kernel<D, false, F16, OCC>
-                : alone     ? attn_bwd_dq_bf16_kernel<D, true, F16, 1>
-                            : attn_bwd_dq_bf16_kernel<D, true, F16, OCC>;
-    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, s, (const bf16_t*)qkv, seqlens, (const bf16_t*)out,
-                       (const bf16_t*)dout, lse, delta, (bf16_t*)dqkv);
-  }
-  {
-    const size_t lds = lds_dkdv;
-    auto kern = s.drop.thr ? attn_bwd_dkdv_bf16_kernel<D, true, F16> : attn_bwd_dkdv_bf16_kernel<D, false, F16>;
-    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, s, (const bf16_t*)qkv, seqlens, (const bf16_t*)dout, lse,
-                       (const float*)delta, (bf16_t*)dqkv);
+  const bool is_short = s.seq <= SHORT_SEQ;
+  if (blocks <= room && !make_way) {
+    if (is_short) bwd_both<D, F16, 1, true>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
+    else bwd_both<D, F16, 1>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
+  } else {
+    if (is_short) bwd_two_launches<D, F16, true>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
+    else bwd_two_launches<D, F16, false>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
   }
 }
 template <int D>
