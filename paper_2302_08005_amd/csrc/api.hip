@@ -247,6 +247,12 @@ SavedLayout saved_layout(const slapo_layer_desc* d) {
   return L;
 }
 
+// Workspace of a layer's product with a plain or add epilogue: K ranges of the tiles of a thin last round, but none where tiles of
+// another size make the product exactly one round, which is faster (the exported products keep the K ranges that they offer).
+static size_t product_ws_bytes(int dtype, int layout, int M, int N, int K) {
+  return gemm_in_one_round(dtype, layout, M, N, K) ? 0 : gemm_ws_bytes(dtype, layout, EPI_NONE, M, N, K);
+}
+
 struct ScratchLayout {
   size_t t0, t1, t2, t3, du, dqkv, delta, part_row, part_col, part_col2, rope, splitk, gemm_ws, gemm_ws_bytes, splitk_bytes, acts, total;
 };
@@ -282,12 +288,12 @@ ScratchLayout scratch_layout(const slapo_layer_desc* d) {
     // the same kind of workspace for the GEMMs of the forward pass and of the data-gradient chain whose tile grid
     // would end in a thin round (their last tiles are then computed in K ranges); a region of its own, because
     // the chain runs while the helper stream's weight gradients use the one above
-    size_t g = gemm_ws_bytes(d->dtype, GEMM_NT, EPI_NONE, Ti, Hi, Ai);                       // attention output projection
+    size_t g = product_ws_bytes(d->dtype, GEMM_NT, Ti, Hi, Ai);                    // attention output projection
     auto upto = [&](size_t v) { g = g > v ? g : v; };
-    upto(gemm_ws_bytes(d->dtype, GEMM_NT, EPI_NONE, Ti, Hi, Fi));                             // second FFN product
-    upto(gemm_ws_bytes(d->dtype, GEMM_NN, EPI_NONE, Ti, Hi, F1));                             // gradient of the FFN input
-    upto(gemm_ws_bytes(d->dtype, GEMM_NN, EPI_NONE, Ti, Ai, Hi));                             // gradient of the attention output
-    upto(gemm_ws_bytes(d->dtype, GEMM_NN, EPI_NONE, Ti, Hi, 3 * Ai));                         // gradient of the attention input
+    upto(product_ws_bytes(d->dtype, GEMM_NT, Ti, Hi, Fi));                         // second FFN product
+    upto(product_ws_bytes(d->dtype, GEMM_NN, Ti, Hi, F1));                         // gradient of the FFN input
+    upto(product_ws_bytes(d->dtype, GEMM_NN, Ti, Ai, Hi));                         // gradient of the attention output
+    upto(product_ws_bytes(d->dtype, GEMM_NN, Ti, Hi, 3 * Ai));                     // gradient of the attention input
     // and for the products that the row kernels read in K ranges
     auto ranges = [&](int K) {
       const int r = product_ranges(d->dtype, Ti, Hi, K);
@@ -418,8 +424,8 @@ static void run_forward(const slapo_layer_desc* d, const slapo_layer_params* p, 
       return gws;
     }
     ranges = 0;
-    const bool whole = gemm_in_one_round(dt, GEMM_NT, T, H, K);
-    launch_gemm(dt, GEMM_NT, EPI_NONE, d->act, T, H, K, a, w, r, nullptr, nullptr, nullptr, st, true, whole ? nullptr : gws, whole ? 0 : W.gemm_ws_bytes);
+    const size_t need = product_ws_bytes(dt, GEMM_NT, T, H, K);
+    launch_gemm(dt, GEMM_NT, EPI_NONE, d->act, T, H, K, a, w, r, nullptr, nullptr, nullptr, st, true, need ? gws : nullptr, need);
     return r;
   };
   const void* ro = project(A, attn, p->wo);
@@ -541,14 +547,13 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   // weight gradient: C (+)= A^T B
   float* splitk_ws = W.splitk_bytes ? (float*)(sc + W.splitk) : nullptr;
   float* gws = W.gemm_ws_bytes ? (float*)(sc + W.gemm_ws) : nullptr;
-  const size_t gwb = W.gemm_ws_bytes;
   auto dweight = [&](int M, int N, const void* a, const void* b, void* c) {
     launch_weight_grad(dt, acc, M, N, T, a, b, c, splitk_ws, ws, solo);
   };
   // data gradient: C = A B (+ aux)
   auto dgrad = [&](int epi, int N, int K, const void* a, const void* b, void* c, const void* aux) {
-    const bool whole = gemm_in_one_round(dt, GEMM_NN, T, N, K);
-    launch_gemm(dt, GEMM_NN, epi, d->act, T, N, K, a, b, c, nullptr, aux, nullptr, st, solo, whole ? nullptr : gws, whole ? 0 : gwb);
+    const size_t need = product_ws_bytes(dt, GEMM_NN, T, N, K);
+    launch_gemm(dt, GEMM_NN, epi, d->act, T, N, K, a, b, c, nullptr, aux, nullptr, st, solo, need ? gws : nullptr, need);
   };
   auto colsum = [&](const void* a, int N, void* out, hipStream_t s) {
     float* part = s == st ? pcol2 : pcol;   // per stream, so that the two sums may run at the same time

@@ -209,6 +209,15 @@ def test_gemm_workspace_rules_on_the_host():
     assert B.status_string(-5).startswith("shape needs more workspace")
 
 
+def test_layers_reserve_no_k_ranges_for_one_round_products():
+    """Scratch per token where every long product is a full round of 128x128 tiles, and a few rows beyond it, where tiles of another
+    size make it one round (K ranges of 128x128 tiles would need 16 MB)."""
+    per_token = [B.slapo_layer_workspace(B.make_desc(batch=1, seq=seq, hidden=2048, heads=32, ffn=8192, causal=1, pre_ln=1, dtype=B.BF16))[1] / seq
+                 for seq in (2048, 2200, 2331)]
+    assert max(per_token) <= 1.02 * per_token[0], per_token
+    assert B.slapo_gemm_workspace(B.BF16, B.NT, B.EPI_NONE, 2200, 2048, 8192) > 0   # the exported product still has them
+
+
 def test_weight_gradient_plans_are_for_the_tiles_that_have_them():
     """Layout TN has K-range forms of 256x256 tiles (thin last rounds) and of split-slab 128x128 tiles (few tiles) only."""
     forms = set()
