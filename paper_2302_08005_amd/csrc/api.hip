@@ -295,11 +295,8 @@ ScratchLayout scratch_layout(const slapo_layer_desc* d) {
     upto(product_ws_bytes(d->dtype, GEMM_NN, Ti, Ai, Hi));                         // gradient of the attention output
     upto(product_ws_bytes(d->dtype, GEMM_NN, Ti, Hi, 3 * Ai));                     // gradient of the attention input
     // and for the products that the row kernels read in K ranges
-    auto ranges = [&](int K) {
-      const int r = product_ranges(d->dtype, Ti, Hi, K);
-      if (r > 1) upto((size_t)r * T * H * sizeof(float));
-    };
-    ranges(Ai); ranges(Fi); ranges(3 * Ai);
+    for (const int K : {Ai, Fi, 3 * Ai})
+      if (product_in_ranges(d->dtype, Ti, Hi, K)) upto(K_RANGES * T * H * sizeof(float));
     L.gemm_ws = g ? take(g) : 0;
     L.gemm_ws_bytes = g;
   }
@@ -416,14 +413,13 @@ static void run_forward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   launch_attn_fwd(dt, as, qkv, seqlens, attn, lse, st);
   float* gws = W.gemm_ws_bytes ? (float*)(sc + W.gemm_ws) : nullptr;   // for GEMMs whose tile grid ends in a thin round
   // Output projections: the row kernel behind reads them, in K ranges where few tokens make few tiles.
-  int ranges = 0;
+  bool ranges = false;
   auto project = [&](int K, const void* a, const void* w) -> const void* {
-    ranges = product_ranges(dt, T, H, K);
-    if (ranges > 1) {
-      launch_gemm_ranges(dt, GEMM_NT, ranges, T, H, K, a, w, gws, st);
+    ranges = product_in_ranges(dt, T, H, K);
+    if (ranges) {
+      launch_gemm_ranges(dt, GEMM_NT, T, H, K, a, w, gws, st);
       return gws;
     }
-    ranges = 0;
     const size_t need = product_ws_bytes(dt, GEMM_NT, T, H, K);
     launch_gemm(dt, GEMM_NT, EPI_NONE, d->act, T, H, K, a, w, r, nullptr, nullptr, nullptr, st, true, need ? gws : nullptr, need);
     return r;
@@ -566,11 +562,11 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   // The gradient of a block's input, [T,H], which a row kernel reads next: t0, or K ranges in gws where few tokens make few tiles
   // (`add`, what the product is added to, is then the row kernel's to add). Not the feed-forward block's of the gated layer, whose
   // gradients are, bit for bit, those of the exported products, rotary turn and attention in a row (1024, 128 tokens: 2 us).
-  const int r_y1 = is_llama(d) ? 1 : product_ranges(dt, T, H, F), r_x = product_ranges(dt, T, H, 3 * A);
-  auto row_bwd = [&](int ranges, const void* add, const void* z, const float* mu, const float* rstd, const void* gamma, const void* dres,
+  const bool r_y1 = !is_llama(d) && product_in_ranges(dt, T, H, F), r_x = product_in_ranges(dt, T, H, 3 * A);
+  auto row_bwd = [&](bool ranges, const void* add, const void* z, const float* mu, const float* rstd, const void* gamma, const void* dres,
                      void* dz, void* dr, const DropoutParams& dp, int dr_from_stored) {
-    launch_bdrln_bwd(dt, T, H, ranges > 1 ? gws : t0, z, mu, rstd, gamma, dres, dz, dr, prow, dp, is_llama(d) ? 1 : 0, st, dr_from_stored, nrow,
-                     ranges > 1 ? ranges : 0, ranges > 1 ? add : nullptr);
+    launch_bdrln_bwd(dt, T, H, ranges ? gws : t0, z, mu, rstd, gamma, dres, dz, dr, prow, dp, is_llama(d) ? 1 : 0, st, dr_from_stored, nrow,
+                     ranges, ranges ? add : nullptr);
   };
   // Buffers: t0 dZ2 -> dY1/dN2 -> dA -> dN1; t1 dR2 (kept for dW2); t2 dZ1; t3 dR1 (kept for dWo). Where nothing is dropped
   // dR1 is t2, and dR2 is dy (pre-LN, dx elsewhere) or, in the paired post-LN launches, t0.
@@ -622,7 +618,7 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     weight(H, F, dr2, g, gr->w2, db2);
     launch();
     data(EPI_ADD, T, H, F1, du, p->w1, t0, d->pre_ln ? nullptr : t0);
-    if (r_y1 > 1) { pr.parts = gws; pr.ranges = r_y1; }
+    if (r_y1) pr.parts = gws;
     weight(F1, H, du, y1, gr->w1, llama ? nullptr : gr->b1);
     launch();
     // ---- attention block ----
@@ -644,10 +640,10 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     launch_attn_bwd(dt, as, qkv, seqlens, attn, t0, lse, delta, dqkv, st);
     if (side) side->order(side->join, ws, st);   // the gradient of the output projection has long been there
     data(EPI_ADD, T, H, 3 * A, dqkv, p->wqkv, d->pre_ln ? t0 : dx, d->pre_ln ? nullptr : t2);
-    if (r_x > 1) { pr.parts = gws; pr.ranges = r_x; }
+    if (r_x) pr.parts = gws;
     weight(3 * A, H, dqkv, d->pre_ln ? sv + L.n1 : x, gr->wqkv, llama ? nullptr : gr->bqkv);
     launch();
-    if (!d->pre_ln && r_x > 1) launch_add_ranges(dt, (int64_t)T * H, r_x, gws, t2, dx, st);
+    if (!d->pre_ln && r_x) launch_add_ranges(dt, (int64_t)T * H, K_RANGES, gws, t2, dx, st);
     if (d->pre_ln && keeps_all && link && link->below) {
       row_bwd(r_x, nullptr, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, dp0, 0);
       link->sums[0] = gr->ln1_g; link->sums[1] = g_ln1_b; link->sums[2] = nullptr;
@@ -682,14 +678,13 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     launch_gemm(dt, GEMM_NN, EPI_DGATE, d->act, T, F, H, dr2, p->w2, du, nullptr, u, nullptr, st, solo);
     fork(1);
     dweight(2 * F, H, du, y1, gr->w1);
-    if (r_y1 > 1) launch_gemm_ranges(dt, GEMM_NN, r_y1, T, H, 2 * F, du, p->w1, gws, st);
-    else dgrad(EPI_NONE, H, 2 * F, du, p->w1, t0, nullptr);
+    dgrad(EPI_NONE, H, 2 * F, du, p->w1, t0, nullptr);
   } else {
     launch_gemm(dt, GEMM_NN, EPI_DACT, d->act, T, F, H, dr2, p->w2, du, nullptr, u, nullptr, st, solo);
     fork(1);
     colsum(du, F, gr->b1, ws);
     dweight(F, H, du, y1, gr->w1);
-    if (r_y1 > 1) launch_gemm_ranges(dt, GEMM_NN, r_y1, T, H, F, du, p->w1, gws, st);
+    if (r_y1) launch_gemm_ranges(dt, GEMM_NN, T, H, F, du, p->w1, gws, st);
     else if (d->pre_ln) dgrad(EPI_NONE, H, F, du, p->w1, t0, nullptr);
     else dgrad(EPI_ADD, H, F, du, p->w1, t0, t0);
   }
@@ -709,7 +704,7 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   fork(3);
   if (d->pre_ln) {
     dweight(3 * A, H, dqkv, sv + L.n1, gr->wqkv);
-    if (r_x > 1) launch_gemm_ranges(dt, GEMM_NN, r_x, T, H, 3 * A, dqkv, p->wqkv, gws, st);
+    if (r_x) launch_gemm_ranges(dt, GEMM_NN, T, H, 3 * A, dqkv, p->wqkv, gws, st);
     else dgrad(EPI_NONE, H, 3 * A, dqkv, p->wqkv, t0, nullptr);
     if (link && link->dr2_below) {
       // (from the stored dx, so that the layer below sees what it would compute from dx itself, bit for bit)

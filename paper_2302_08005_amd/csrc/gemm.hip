@@ -422,8 +422,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(int64_t chunks, int6
 void launch_add_ranges(int dtype, int64_t mn, int ranges, const float* parts, const void* addend, void* out, hipStream_t st) {
   const int64_t chunks = mn / 8;
   const dim3 grid((unsigned)((chunks + 255) / 256));
-  if (dtype == DT_FP32) hipLaunchKernelGGL(splitk_reduce_kernel<float>, grid, dim3(256), 0, st, chunks, mn, ranges, parts, (float*)out, (const float*)addend);
-  else if (dtype == DT_FP16) hipLaunchKernelGGL(splitk_reduce_kernel<f16_t>, grid, dim3(256), 0, st, chunks, mn, ranges, parts, (f16_t*)out, (const f16_t*)addend);
+  if (dtype == DT_FP16) hipLaunchKernelGGL(splitk_reduce_kernel<f16_t>, grid, dim3(256), 0, st, chunks, mn, ranges, parts, (f16_t*)out, (const f16_t*)addend);
   else hipLaunchKernelGGL(splitk_reduce_kernel<bf16_t>, grid, dim3(256), 0, st, chunks, mn, ranges, parts, (bf16_t*)out, (const bf16_t*)addend);
 }
 
@@ -489,35 +488,31 @@ static void launch_splitk(int splits, int accumulate, int M, int N, int K, const
 //            2048, 64 57.5 -> 53.1 / 113.9 -> 93.4, 128 60.6 -> 57.0 / 117.2 -> 104.6; decoder 4096, 64 backward 263 -> 252
 //   outside  hidden 256, 1024 34.5 -> 36.4 / 48.6 -> 55.8; 512, 512 37.2 -> 37.9 / 52.5 -> 58.6; 1024, 256 45.5 -> 44.1 / 66.8 -> 67.9, 512
 //            51.7 -> 51.0 / 79.1 -> 83.6; 2048, 256 69.2 -> 68.9 / 126.9 -> 130.3; 4096, 128 168.6 -> 168.8 / 303.0 -> 310.6
-// (Up to eight ranges: the same within 2 %, the row kernels spill.)
-int product_ranges(int dtype, int M, int N, int K) {
-  if (dtype == DT_FP32 || N < 512 || N > 4096) return 1;   // (rows of other widths: no row kernel that adds ranges)
+// (Up to eight ranges: the same within 2 %, the row kernels spill. 16 slabs or more: none of four ranges is empty.)
+bool product_in_ranges(int dtype, int M, int N, int K) {
+  if (dtype == DT_FP32 || N < RANGES_MIN_N || N > RANGES_MAX_N) return false;
   const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
-  const int slabs = (K + 127) / 128;
-  if (!((tiles <= 32 && K >= 2048) || (tiles <= 64 && K >= 6144))) return 1;
-  int s = 4;
-  while ((s - 1) * ((slabs + s - 1) / s) >= slabs) --s;   // every range non-empty
-  return s;
+  return (tiles <= 32 && K >= 2048) || (tiles <= 64 && K >= 6144);
 }
 
-template <int LAYOUT, int BK, int NS, bool F16>
-static void launch_ranges(int ranges, int M, int N, int K, const void* A, const void* B, float* parts, hipStream_t st) {
+template <int LAYOUT, bool F16>
+static void launch_ranges(int M, int N, int K, const void* A, const void* B, float* parts, hipStream_t st) {
+  constexpr int BK = 128, NS = 3;
   const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
   const size_t lds = gemm_lds_bytes<64, 64, BK, 2, 2, 1, NS>();
   auto kern = K % BK == 0 ? gemm_bf16_kernel<LAYOUT, 64, 64, BK, 2, 2, 1, NS, 4, false, EPI_SPLITK, F16>
                           : gemm_bf16_kernel<LAYOUT, 64, 64, BK, 2, 2, 1, NS, 4, true, EPI_SPLITK, F16>;
   (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL(kern, dim3(tiles * ranges), dim3((2 * 2 + 4) * 64), lds, st, M, N, K, (const bf16_t*)A, (const bf16_t*)B,
-                     (bf16_t*)nullptr, (const bf16_t*)nullptr, (const bf16_t*)nullptr, reinterpret_cast<bf16_t*>(parts), ranges,
-                     tiles * ranges, 1, (float*)nullptr);
+  hipLaunchKernelGGL(kern, dim3(tiles * K_RANGES), dim3((2 * 2 + 4) * 64), lds, st, M, N, K, (const bf16_t*)A, (const bf16_t*)B,
+                     (bf16_t*)nullptr, (const bf16_t*)nullptr, (const bf16_t*)nullptr, reinterpret_cast<bf16_t*>(parts), K_RANGES,
+                     tiles * K_RANGES, 1, (float*)nullptr);
 }
 
-void launch_gemm_ranges(int dtype, int layout, int ranges, int M, int N, int K, const void* A, const void* B, float* parts,
-                        hipStream_t st) {
-#define SLAPO_RANGES(L)                                                                     \
-  do {                                                                                      \
-    if (dtype == DT_FP16) launch_ranges<L, 128, 3, true>(ranges, M, N, K, A, B, parts, st); \
-    else launch_ranges<L, 128, 3, false>(ranges, M, N, K, A, B, parts, st);                 \
+void launch_gemm_ranges(int dtype, int layout, int M, int N, int K, const void* A, const void* B, float* parts, hipStream_t st) {
+#define SLAPO_RANGES(L)                                                         \
+  do {                                                                          \
+    if (dtype == DT_FP16) launch_ranges<L, true>(M, N, K, A, B, parts, st);     \
+    else launch_ranges<L, false>(M, N, K, A, B, parts, st);                     \
   } while (0)
   if (layout == GEMM_NT) SLAPO_RANGES(GEMM_NT); else SLAPO_RANGES(GEMM_NN);
 #undef SLAPO_RANGES

@@ -141,7 +141,7 @@ __global__ __launch_bounds__(PAIR_THREADS, 4) void grad_pair_kernel(PairArgs a) 
   if (nn) {
     gemm_bf16_tile<GEMM_NN, X::BM, X::BN, 64, 2, 2, 1, X::NS, PAIR_LOADERS, KTAIL, EPI, F16, false, EPI == EPI_ADD>(
         a.nn_first ? block : block - a.tn_blocks, p.M, p.N, p.K, (const bf16_t*)p.A, (const bf16_t*)p.B, (bf16_t*)p.C, nullptr,
-        (const bf16_t*)p.aux, reinterpret_cast<bf16_t*>(p.parts), EPI == EPI_SPLITK ? p.ranges : p.act, 0, 1, nullptr);
+        (const bf16_t*)p.aux, reinterpret_cast<bf16_t*>(p.parts), EPI == EPI_SPLITK ? K_RANGES : p.act, 0, 1, nullptr);
   } else {
     gemm_bf16_tile<GEMM_TN, W::BM, W::BN, 64, 2, 2, 1, W::NS, PAIR_LOADERS, false, EPI_ADD, F16, false, true>(
         a.nn_first ? block - a.nn_blocks : block, p.wM, p.wN, p.wK, (const bf16_t*)p.wA, (const bf16_t*)p.wB, (bf16_t*)p.dW, nullptr,
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(F32_WAVES * 64) void grad_pair_f32_kernel(PairArgs 
 
 template <class X, class W, bool F16>
 void launch_pair_tiles(PairArgs a, hipStream_t st) {
-  a.nn_blocks = X::count(a.p.M, a.p.N) * (a.p.parts ? a.p.ranges : 1);
+  a.nn_blocks = X::count(a.p.M, a.p.N) * (a.p.parts ? K_RANGES : 1);
   a.tn_blocks = a.p.dW ? W::count(a.p.wM, a.p.wN) : 0;
   constexpr size_t lds = max_lds(max_lds(X::LDS, W::LDS), PAIR_THREADS * 8 * sizeof(float));
   const dim3 grid(a.red_blocks + a.cs_blocks + a.nn_blocks + a.tn_blocks);
@@ -226,7 +226,7 @@ void launch_grad_pair(int dtype, const GradPair& p, hipStream_t st) {
   a.p = p;
   a.red_blocks = p.partials ? 3 * ((p.H + 63) / 64) : 0;
   a.cs_blocks = p.dW && p.colsum ? (p.wM + 127) / 128 : 0;
-  a.nn_first = p.K / (p.parts ? p.ranges : 1) >= p.wK;   // the longer tiles start first
+  a.nn_first = p.K / (p.parts ? K_RANGES : 1) >= p.wK;   // the longer tiles start first
   if (dtype == DT_FP32) {
     auto count = [](int M, int N, int t) { return ((M + t - 1) / t) * ((N + t - 1) / t); };
     // (as for one product: 16x16 tiles where the larger ones would leave half of the CUs idle)

@@ -29,11 +29,13 @@ void launch_gemm(int dtype, int layout, int epi, int act, int M, int N, int K, c
 size_t gemm_ws_bytes(int dtype, int layout, int epi, int M, int N, int K);
 // tiles that make the product exactly one round, which is faster than K ranges: launch_gemm without a workspace takes them
 bool gemm_in_one_round(int dtype, int layout, int M, int N, int K);
-// Products whose reader adds up K ranges itself (the row kernels, launch_add_ranges): product_ranges says in how many ranges a
-// product of this shape is worth computing (1: not at all), launch_gemm_ranges leaves them as fp32 arrays [ranges][M][N].
-int product_ranges(int dtype, int M, int N, int K);
-void launch_gemm_ranges(int dtype, int layout, int ranges, int M, int N, int K, const void* A, const void* B, float* parts, hipStream_t st);
-// out [mn] = sum of the ranges, in order, + addend (NULL: nothing)
+// Products whose reader adds up K ranges itself (the row kernels, launch_add_ranges): product_in_ranges says whether a product of
+// this shape is worth computing so (N then is a width of rows that the row kernels have such forms for), launch_gemm_ranges
+// leaves the ranges as fp32 arrays [K_RANGES][M][N].
+constexpr int K_RANGES = 4, RANGES_MIN_N = 512, RANGES_MAX_N = 4096;
+bool product_in_ranges(int dtype, int M, int N, int K);
+void launch_gemm_ranges(int dtype, int layout, int M, int N, int K, const void* A, const void* B, float* parts, hipStream_t st);
+// out [mn] = sum of the ranges, in order, + addend (NULL: nothing); 16-bit storage
 void launch_add_ranges(int dtype, int64_t mn, int ranges, const float* parts, const void* addend, void* out, hipStream_t st);
 // the smallest workspace that a caller who passes one may pass: 256x256 grids whose K is a multiple of 128 have always
 // asked for all that they can use; other K and grids of smaller tiles do without one that is too small for them
@@ -68,9 +70,8 @@ struct GradPair {
   int nblk, H;
   void* sums[3];
   int accumulate;
-  // the data gradient in K ranges (product_ranges), left as fp32 arrays [ranges][M][N] in place of C; NULL: C
+  // the data gradient in K ranges (product_in_ranges), left as fp32 arrays [K_RANGES][M][N] in place of C; NULL: C
   float* parts;
-  int ranges;
 };
 void launch_grad_pair(int dtype, const GradPair& p, hipStream_t st);
 
@@ -89,16 +90,16 @@ void launch_attn_bwd(int dtype, const AttnShape& s, const void* qkv, const int32
                      const void* dout, const float* lse, float* delta, void* dqkv, hipStream_t st);
 
 // rms: the normalisation is RMSNorm (no mean subtraction, no offset; beta, mu unused). bias may be null.
-// r_ranges > 0: r is that many fp32 arrays [rows, H], which add up to the branch's output (launch_gemm_ranges).
+// r_in_ranges: r is fp32 arrays [K_RANGES][rows][H], which add up to the branch's output (launch_gemm_ranges).
 void launch_bdrln_fwd(int dtype, int64_t rows, int H, const void* r, const void* bias, const void* res,
                       const void* gamma, const void* beta, void* z_out, void* out, float* mu, float* rstd,
-                      const DropoutParams& dp, float eps, int rms, hipStream_t st, int r_ranges = 0);
-// dout_ranges > 0: dout is that many fp32 arrays [rows, H], which add up, with dout_add (NULL: nothing), to the gradient.
+                      const DropoutParams& dp, float eps, int rms, hipStream_t st, bool r_in_ranges = false);
+// dout_in_ranges: dout is fp32 arrays [K_RANGES][rows][H], which add up, with dout_add (NULL: nothing), to the gradient.
 int bdrln_bwd_blocks(int64_t rows);
 void launch_bdrln_bwd(int dtype, int64_t rows, int H, const void* dout, const void* z, const float* mu,
                       const float* rstd, const void* gamma, const void* dres_in, void* dz_out, void* dr_out,
                       float* partials, const DropoutParams& dp, int rms, hipStream_t st, int dr_from_stored = 0, int blocks = 0,
-                      int dout_ranges = 0, const void* dout_add = nullptr);
+                      bool dout_in_ranges = false, const void* dout_add = nullptr);
 // Blocks (and partial rows) for launch_bdrln_bwd inside a layer (blocks = 0: bdrln_bwd_blocks, which the exported kernel has):
 // few rows go to more blocks of fewer, because a launch that short is its latency chain, of which the column sums across a
 // block's groups are a part: 16 blocks of 8 rows -> 64 of 2 at 128 rows of 1024, 7.2 -> 5.4 us; steps of 128 tokens at hidden 1024

@@ -12,29 +12,25 @@
 namespace slapo {
 
 // K ranges of a product, fp32 arrays `stride` apart, added up in order: eight columns of a row per lane, all loads in flight
-// (product_ranges, gemm.hip, says which products of few tokens come that way; a kernel of its own for the sum of 128 x 1024
+// (product_in_ranges, gemm.hip, says which products of few tokens come that way; a kernel of its own for the sum of 128 x 1024
 // takes 3.6 us, the row kernels 1 us more).
-struct Ranges4 {
-  static constexpr int MAX_RANGES = 4;
-  float v[MAX_RANGES][8];
-  __device__ __forceinline__ void load(const float* p, int64_t stride, int ranges) {
+struct Ranges {
+  float v[K_RANGES][8];
+  __device__ __forceinline__ void load(const float* p, int64_t stride) {
 #pragma unroll
-    for (int r = 0; r < MAX_RANGES; ++r)
-      if (r < ranges) load8(p + r * stride, v[r]);   // (uniform)
+    for (int r = 0; r < K_RANGES; ++r) load8(p + r * stride, v[r]);
   }
-  __device__ __forceinline__ void get(float (&a)[8], int ranges) const {
+  __device__ __forceinline__ void get(float (&a)[8]) const {
 #pragma unroll
     for (int e = 0; e < 8; ++e) a[e] = v[0][e];
 #pragma unroll
-    for (int r = 1; r < MAX_RANGES; ++r)
-      if (r < ranges) {
+    for (int r = 1; r < K_RANGES; ++r)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) a[e] += v[r][e];
-      }
+      for (int e = 0; e < 8; ++e) a[e] += v[r][e];
   }
 };
 
-// RANGES: r is fp32 K ranges of the branch's output (`ranges` of them).
+// RANGES: r is fp32 K ranges of the branch's output.
 // DRAW: elements are dropped. An instance each, here and in backward: a test of the threshold inside the row loop, where the
 // compiler cannot mix the draw's integer multiplies with the loads and sums around it, cost rows with dropout 3-7 % (16384
 // rows of 8192 forward 375 -> 390 us, 4096 of 5120 backward 38.3 -> 40.1).
@@ -42,7 +38,7 @@ template <typename T, int NCH, bool BDR, bool LN, int WAVES, bool DRAW, bool RAN
 __global__ __launch_bounds__(WAVES * 64) void bdrln_fwd_kernel(
     int64_t rows, int H, const std::conditional_t<RANGES, float, T>* __restrict__ r, const T* __restrict__ bias, const T* __restrict__ res,
     const T* __restrict__ gamma, const T* __restrict__ beta, T* __restrict__ z_out, T* __restrict__ out,
-    float* __restrict__ mu_out, float* __restrict__ rstd_out, DropoutParams dp, float eps, int rms, int ranges) {
+    float* __restrict__ mu_out, float* __restrict__ rstd_out, DropoutParams dp, float eps, int rms) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nchunk = H >> 3;
   const float inv_h = 1.0f / (float)H;
@@ -58,9 +54,9 @@ __global__ __launch_bounds__(WAVES * 64) void bdrln_fwd_kernel(
         if (BDR) {
           float a[8], b[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
           if constexpr (RANGES) {
-            Ranges4 q;
-            q.load(r + base + c * 8, rows * H, ranges);
-            q.get(a, ranges);
+            Ranges q;
+            q.load(r + base + c * 8, rows * H);
+            q.get(a);
           } else {
             load8(r + base + c * 8, a);
           }
@@ -277,14 +273,14 @@ __global__ __launch_bounds__(WAVES * 64) void bdrln_bwd_kernel(
 // two steps' worth of rows on their way from memory: with one block per CU (the partial sums it leaves are
 // [blocks, 3, H] floats, which bounds the block count) that is what keeps the memory pipeline full. At the end
 // the groups' column sums are added in group order through LDS: one partial row per block, as above.
-// RANGES: dout is fp32 K ranges of the gradient (`ranges` of them), to which dadd is added if there is one; a step's loads
+// RANGES: dout is fp32 K ranges of the gradient, to which dadd is added if there is one; a step's loads
 // go out at its beginning (few rows: there is no next step).
 template <typename T, bool LN, int R, int MAXT, bool DRAW, bool ONE = false, bool RANGES = false>
 __global__ __launch_bounds__(MAXT) void bdrln_bwd_wide_kernel(
     int64_t rows, int H, const std::conditional_t<RANGES, float, T>* __restrict__ dout, const T* __restrict__ z, const float* __restrict__ mu,
     const float* __restrict__ rstd, const T* __restrict__ gamma, const T* __restrict__ dres_in,
     T* __restrict__ dz_out, T* __restrict__ dr_out, float* __restrict__ partials, DropoutParams dp, int dr_from_stored,
-    int NW, int G, int ranges, const T* __restrict__ dadd) {
+    int NW, int G, const T* __restrict__ dadd) {
   extern __shared__ __attribute__((aligned(16))) float wsm[];   // per-row sums [2][G][R][NW][2]; at the end column sums [G-1][3][H]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int group = wave / NW, gw = wave - group * NW;
@@ -300,7 +296,7 @@ __global__ __launch_bounds__(MAXT) void bdrln_bwd_wide_kernel(
   const int64_t n_steps = ONE ? 1 : (rows + per_step - 1) / per_step;   // the same for every group: they share the barrier
   auto first_row = [&](int64_t step) { return ((step * gridDim.x + blockIdx.x) * G + group) * R; };
   Raw8<T> ndy[R], nz[R], nres[R];
-  std::conditional_t<RANGES, Ranges4, char> nq[R];
+  std::conditional_t<RANGES, Ranges, char> nq[R];
   float nm[R], nrs[R];
   auto fetch = [&](int64_t step) {   // all loads of a step go out before anything waits
     const int64_t row0 = first_row(step);
@@ -311,7 +307,7 @@ __global__ __launch_bounds__(MAXT) void bdrln_bwd_wide_kernel(
       if (row < rows) {
         if (active) {
           if constexpr (RANGES) {
-            nq[j].load(dout + row * H + c * 8, rows * H, ranges);
+            nq[j].load(dout + row * H + c * 8, rows * H);
             if (dadd) ndy[j].load(dadd + row * H + c * 8);
           } else {
             ndy[j].load(dout + row * H + c * 8);
@@ -335,7 +331,7 @@ __global__ __launch_bounds__(MAXT) void bdrln_bwd_wide_kernel(
       s1[j] = 0.f; s2[j] = 0.f; m[j] = nm[j]; rs[j] = nrs[j];
       if (row0 + j < rows && active) {
         if constexpr (RANGES) {
-          nq[j].get(dy[j], ranges);
+          nq[j].get(dy[j]);
           if (dadd) {
             float t[8];
             ndy[j].get(t);
@@ -543,7 +539,7 @@ static int nch_for(int H) {
 template <typename T, bool BDR, bool LN, bool DRAW, bool RANGES = false>
 static void launch_fwd(int64_t rows, int H, const void* r, const void* bias, const void* res, const void* gamma,
                        const void* beta, void* z_out, void* out, float* mu, float* rstd, const DropoutParams& dp,
-                       float eps, int rms, int ranges, hipStream_t st) {
+                       float eps, int rms, hipStream_t st) {
   using R = std::conditional_t<RANGES, float, T>;
   constexpr int WAVES = RANGES ? 1 : 4;   // (few rows: each on a CU of its own)
   int64_t blocks = (rows + WAVES - 1) / WAVES;
@@ -551,29 +547,32 @@ static void launch_fwd(int64_t rows, int H, const void* r, const void* bias, con
 #define SLAPO_FWD(N)                                                                                          \
   hipLaunchKernelGGL((bdrln_fwd_kernel<T, N, BDR, LN, WAVES, DRAW, RANGES>), dim3((unsigned)blocks), dim3(WAVES * 64), 0, st, \
                      rows, H, (const R*)r, (const T*)bias, (const T*)res, (const T*)gamma, (const T*)beta,    \
-                     (T*)z_out, (T*)out, mu, rstd, dp, eps, rms, ranges)
+                     (T*)z_out, (T*)out, mu, rstd, dp, eps, rms)
   switch (nch_for(H)) {
     case 1: SLAPO_FWD(1); break;
     case 2: SLAPO_FWD(2); break;
     case 4: SLAPO_FWD(4); break;
     case 5: SLAPO_FWD(5); break;
     case 8: SLAPO_FWD(8); break;
-    case 10: SLAPO_FWD(10); break;
-    default: SLAPO_FWD(16); break;
+    default:
+      static_assert(RANGES_MAX_N <= 8 * 512, "no wider rows come in ranges");
+      if constexpr (!RANGES) {
+        if (nch_for(H) == 10) SLAPO_FWD(10); else SLAPO_FWD(16);
+      }
   }
 #undef SLAPO_FWD
 }
 
 void launch_bdrln_fwd(int dtype, int64_t rows, int H, const void* r, const void* bias, const void* res,
                       const void* gamma, const void* beta, void* z_out, void* out, float* mu, float* rstd,
-                      const DropoutParams& dp, float eps, int rms, hipStream_t st, int r_ranges) {
+                      const DropoutParams& dp, float eps, int rms, hipStream_t st, bool r_in_ranges) {
   const bool bdr = r != nullptr, ln = gamma != nullptr;
   if (rms) { beta = nullptr; mu = nullptr; }
   const bool draw = dp.thr != 0;
 #define SLAPO_PICK_AS(T, BDR, LN, DRAW)                                                                       \
   do {                                                                                                        \
-    if (BDR && r_ranges) launch_fwd<T, BDR, LN, DRAW, BDR && sizeof(T) == 2>(rows, H, r, bias, res, gamma, beta, z_out, out, mu, rstd, dp, eps, rms, r_ranges, st); \
-    else launch_fwd<T, BDR, LN, DRAW>(rows, H, r, bias, res, gamma, beta, z_out, out, mu, rstd, dp, eps, rms, 0, st); \
+    if (BDR && r_in_ranges) launch_fwd<T, BDR, LN, DRAW, BDR && sizeof(T) == 2>(rows, H, r, bias, res, gamma, beta, z_out, out, mu, rstd, dp, eps, rms, st); \
+    else launch_fwd<T, BDR, LN, DRAW>(rows, H, r, bias, res, gamma, beta, z_out, out, mu, rstd, dp, eps, rms, st); \
   } while (0)
 #define SLAPO_PICK(T)                                                                                         \
   do {                                                                                                        \
@@ -600,16 +599,17 @@ int bdrln_bwd_blocks_wide(int64_t rows, int H) {
 template <typename T, bool LN, bool DRAW, bool RANGES = false>
 static void launch_bwd(int64_t rows, int H, const void* dout, const void* z, const float* mu, const float* rstd,
                        const void* gamma, const void* dres_in, void* dz_out, void* dr_out, float* partials,
-                       const DropoutParams& dp, int dr_from_stored, int blocks, int ranges, const void* dadd, hipStream_t st) {
+                       const DropoutParams& dp, int dr_from_stored, int blocks, const void* dadd, hipStream_t st) {
   using D = std::conditional_t<RANGES, float, T>;
-  if (H >= 512) {
+  if (RANGES || H >= 512) {
     // Groups of NW wavefronts that split the columns. Up to hidden 3072 as many groups as fit 12 wavefronts (the
     // register budget of three wavefronts per SIMD holds two rows per group and their prefetch without spilling);
-    // wider rows fill the block with one group, four rows at a time up to 4096, one above.
+    // wider rows fill the block with one group, four rows at a time up to 4096, one above. Rows of 3080 to 4096 too go two at a
+    // time where the blocks then hold them all, up to 512 in a layer: backward of 16 to 256 tokens 0-2 % faster (128 tokens, hidden 3328 231 -> 226
+    // us, gated 242 -> 238), at 512 level.
     const int nw = (H / 8 + 63) / 64;
-    // (two also where the blocks then hold all rows, whichever of the kernels: the sums over the rows keep their order)
     int groups = RANGES ? 8 / nw : nw <= 6 ? (12 / nw > 8 ? 8 : 12 / nw) : 1;
-    const int rows_per_group = nw <= 6 || (nw <= 8 && rows <= 2 * (int64_t)blocks) ? 2 : nw <= 8 ? 4 : 1;
+    const int rows_per_group = RANGES || nw <= 6 || (nw <= 8 && rows <= 2 * (int64_t)blocks) ? 2 : nw <= 8 ? 4 : 1;
     // (no group without a row: each adds a round of column sums through LDS)
     const int64_t useful = (rows + (int64_t)blocks * rows_per_group - 1) / ((int64_t)blocks * rows_per_group);
     if (groups > useful) groups = (int)useful;
@@ -622,7 +622,7 @@ static void launch_bwd(int64_t rows, int H, const void* dout, const void* z, con
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);             \
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(groups * nw * 64), lds, st, rows, H, (const D*)dout, (const T*)z, mu, \
                        rstd, (const T*)gamma, (const T*)dres_in, (T*)dz_out, (T*)dr_out, partials, dp,              \
-                       dr_from_stored, nw, groups, ranges, (const T*)dadd);                                                  \
+                       dr_from_stored, nw, groups, (const T*)dadd);                                                  \
   } while (0)
     // (three rows per group where that takes all rows in ONE step instead of a full and a thin one: 4096 rows of 1024)
     if constexpr (RANGES) {   // (few rows: blocks of at most eight wavefronts, whose registers hold the ranges of two rows)
@@ -654,15 +654,15 @@ static void launch_bwd(int64_t rows, int H, const void* dout, const void* z, con
 void launch_bdrln_bwd(int dtype, int64_t rows, int H, const void* dout, const void* z, const float* mu,
                       const float* rstd, const void* gamma, const void* dres_in, void* dz_out, void* dr_out,
                       float* partials, const DropoutParams& dp, int rms, hipStream_t st, int dr_from_stored, int blocks,
-                      int dout_ranges, const void* dout_add) {
+                      bool dout_in_ranges, const void* dout_add) {
   if (blocks == 0) blocks = bdrln_bwd_blocks(rows);
   if (rms) mu = nullptr;   // the kernel reads a missing mean as RMSNorm (mean 0, no mean-of-gradient term)
   if (dr_out == dz_out) dz_out = nullptr;   // one array for both (nothing is dropped): stored once, and summed as dr
   const bool ln = gamma != nullptr, draw = dp.thr != 0;
 #define SLAPO_PICK_AS(T, LN, DRAW)                                                          \
   do {                                                                                      \
-    if (LN && dout_ranges) launch_bwd<T, LN, DRAW, LN && sizeof(T) == 2>(rows, H, dout, z, mu, rstd, gamma, dres_in, dz_out, dr_out, partials, dp, dr_from_stored, blocks, dout_ranges, dout_add, st); \
-    else launch_bwd<T, LN, DRAW>(rows, H, dout, z, mu, rstd, gamma, dres_in, dz_out, dr_out, partials, dp, dr_from_stored, blocks, 0, nullptr, st); \
+    if (LN && dout_in_ranges) launch_bwd<T, LN, DRAW, LN && sizeof(T) == 2>(rows, H, dout, z, mu, rstd, gamma, dres_in, dz_out, dr_out, partials, dp, dr_from_stored, blocks, dout_add, st); \
+    else launch_bwd<T, LN, DRAW>(rows, H, dout, z, mu, rstd, gamma, dres_in, dz_out, dr_out, partials, dp, dr_from_stored, blocks, nullptr, st); \
   } while (0)
 #define SLAPO_PICK(T)                                                                       \
   do {                                                                                      \
