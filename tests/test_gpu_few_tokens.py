@@ -28,6 +28,8 @@ CASES = [
     W.LayerConfig("64-tiles-short", 2, 64, 2048, 16, 6136, dropout_p=0.0, dtype=W.BF16, config_id=69),
     # the widest rows that have ranges (whole blocks of eight wavefronts in backward)
     W.LayerConfig("widest", 1, 60, 4096, 32, 6200, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, config_id=70),
+    # the same as a post-LN layer: the residual gradient is the row kernel's to add, outside of the paired launches (more than 64 M weights)
+    W.LayerConfig("widest-postln", 1, 60, 4096, 32, 6200, dropout_p=0.1, dtype=W.BF16, config_id=72),
     W.LayerConfig("gated", 1, 100, 1024, 8, 2048, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, ln_eps=1e-6, arch=W.LLAMA, config_id=71),
 ]
 
@@ -62,3 +64,20 @@ def test_layer_of_few_tokens(cfg):
         for l in range(n):
             for k in W.param_names(cfg):
                 assert torch.equal(st.grads[l][k], layers[l].grads[k]), (checkpoint, l, k)
+
+
+# dx written over x: products and gradients in launches of their own, sums in another order than with dx elsewhere
+@pytest.mark.parametrize("cfg", [c for c in CASES if c.name in ("postln-short-last-range", "postln-all", "widest-postln")], ids=lambda c: c.name)
+def test_input_gradient_on_top_of_the_input(cfg):
+    params = W.make_params(cfg, perturbed=True)
+    x, dy, sl = W.make_inputs(cfg)
+    ref = L.layer_forward(cfg, params, x, sl)
+    gref = L.layer_backward(cfg, params, ref, dy)
+    layer = B.Layer(cfg, params)
+    xd, dyd = layer.to_device(x), layer.to_device(dy)
+    sld = None if sl is None else torch.from_numpy(sl).to(DEV)
+    layer.forward(xd, sld)
+    B.slapo_layer_bwd(layer.desc, layer.params, xd, sld, dyd, layer.saved, xd, layer.grads, layer.scratch)
+    errs = {"dx": err(xd, gref["dx"]), **{"d" + k: err(layer.grads[k], gref[k]) for k in W.param_names(cfg)}}
+    bad = {k: v for k, v in errs.items() if not v <= TOL[cfg.dtype]}
+    assert not bad, (bad, errs)

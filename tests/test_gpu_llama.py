@@ -238,3 +238,22 @@ def test_rotary_turn_inside_the_layer_has_the_bits_of_the_kernel(dtype, batch, s
     B.slapo_weight_grad(dtype, 0, 3 * H, H, T, dqkv, n1, dw, ws)
     torch.cuda.synchronize()
     assert torch.equal(dw, layer.grads["wqkv"])
+
+
+# Projections of packed queries, keys and values that come as one-round tiles or with quarters: the turn in their epilogues. Sequences
+# end inside tiles.
+@pytest.mark.parametrize("dtype,batch,seq,heads,tiles", [
+    (W.BF16, 3, 500, 8, "<0, 192, 128, 64,"), (W.FP16, 4, 510, 16, "<0, 256, 128, 64,"), (W.BF16, 7, 500, 8, "<0, 192, 256, 64,"),
+    (W.FP16, 6, 950, 16, "quarters_kernel<0, false")])
+def test_rotary_turn_of_one_round_tiles_and_quarters(dtype, batch, seq, heads, tiles):
+    H, T = 1024, batch * seq
+    assert tiles in B.slapo_gemm_kernel_name(dtype, B.NT, B.EPI_NONE, T, 3 * H, H)
+    cfg = W.LayerConfig("turn", batch, seq, H, heads, 512, causal=1, dropout_p=0.0, dtype=dtype, pre_ln=1, ln_eps=1e-6, arch=W.LLAMA,
+                        config_id=52)
+    layer = B.Layer(cfg, W.make_params(cfg))
+    gen = torch.Generator(device=DEV).manual_seed(8)
+    layer.forward(torch.randn(T, H, device=DEV, generator=gen).to(layer.dt))
+    qkv = torch.empty(T, 3 * H, dtype=layer.dt, device=DEV)
+    B.slapo_gemm(dtype, B.NT, B.EPI_NONE, 0, T, 3 * H, H, layer.saved_tensor("n1"), layer.params["wqkv"], qkv)
+    B.slapo_rope(layer.desc, qkv, torch.empty(seq, H // heads // 2, 2, device=DEV), 0)
+    assert torch.equal(qkv.view(-1), layer.saved_tensor("qkv"))
