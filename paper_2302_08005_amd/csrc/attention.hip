@@ -178,7 +178,9 @@ __device__ __forceinline__ float* group_slot(void* smem, int grp, int row_wave, 
 // As they are where that is faster: where a wavefront has fewer than 32 rows (the last, and in causal grids longest, block of 1 x 152, 19,
 // causal, forward 64-wide 5.8 / 6.0, 128-wide 7.2 / 7.6), and where no other wavefront of the block has any (SHORT, sequences up to 32:
 // 16 x 32, 8 forward 64-wide 4.1 / 4.3, 128-wide 5.0 / 5.5, backward 5.4 / 5.6, 8.1 / 8.3; 8 x 64, 8 3.9 / 3.9, 6.0 / 5.6). Those
-// have instances of their own, in which nothing is left of the other way: it costs their launches of 4-8 us 1-2 %.
+// have instances of their own, in which nothing is left of the other way: it costs their launches of 4-8 us 1-2 %. Gradients that are
+// turned on the way always take their rows through LDS, because the table then is read in whole rows too (backward of a gated layer,
+// 16 x 16 tokens, hidden 768: 128-wide 64.5 / 63.2; 6 x 40, hidden 512 61.2 / 59.9).
 template <int D, bool F16, bool SHORT>
 struct RowsOut {
   static constexpr int P = D + 4;          // row pitch in elements: 8 bytes more, so that the 8-byte writes of 32 rows meet every bank once
@@ -202,16 +204,14 @@ struct RowsOut {
   template <class Value>
   __device__ __forceinline__ void store(Value&& value, bf16_t* out, int64_t stride, const float* __restrict__ table = nullptr) const {
     const int row = lane & 31, col = 4 * (lane >> 5);
-    if (SHORT || rows < 32) {
+    if (SHORT || (rows < 32 && !table)) {   // (uniform)
       if (row < rows) {
 #pragma unroll
         for (int t = 0; t < D / 32; ++t)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            uint2 w = make_uint2(pack2<F16>(value(t, 4 * g), value(t, 4 * g + 1)), pack2<F16>(value(t, 4 * g + 2), value(t, 4 * g + 3)));
-            if (table) w = turned(w, table, first + row, t * 32 + g * 8 + col);   // (uniform)
-            *reinterpret_cast<uint2*>(out + (row * stride + t * 32 + g * 8 + col)) = w;
-          }
+          for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<uint2*>(out + (row * stride + t * 32 + g * 8 + col)) =
+                make_uint2(pack2<F16>(value(t, 4 * g), value(t, 4 * g + 1)), pack2<F16>(value(t, 4 * g + 2), value(t, 4 * g + 3)));
       }
       return;
     }
@@ -226,13 +226,18 @@ struct RowsOut {
       meet();
       constexpr int CPR = D / 8, RPI = 64 / CPR;   // 16-byte chunks per row, rows per access
       const int c = (lane % CPR) * 8;
-#pragma unroll
-      for (int i = 0; i < 32 / RPI; ++i) {
-        const int r = i * RPI + lane / CPR;
+      const auto move = [&](int r) {
         const uint2* p = reinterpret_cast<const uint2*>(stage + r * P + c);
         uint2 w0 = p[0], w1 = p[1];
         if (table) { w0 = turned(w0, table, first + r, c); w1 = turned(w1, table, first + r, c + 4); }   // (uniform)
         *reinterpret_cast<uint4*>(out + (r * stride + c)) = make_uint4(w0.x, w0.y, w1.x, w1.y);
+      };
+      if (rows >= 32) {   // (uniform)
+#pragma unroll
+        for (int i = 0; i < 32 / RPI; ++i) move(i * RPI + lane / CPR);
+      } else {
+#pragma unroll 1
+        for (int r = lane / CPR; r < rows; r += RPI) move(r);
       }
     }
   }
@@ -1600,7 +1605,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_simple_kernel(AttnShape sh,
 // =================================== launchers ===================================================
 // Blocks of 128 rows that the chip runs at a time where they fit a CU twice (64-wide heads) or once.
 template <int D> constexpr int64_t ONE_ROUND = D == 64 ? 512 : 256;
-constexpr int SHORT_SEQ = 32;   // (RowsOut)
+constexpr int SHORT_SEQ = 32;   // (RowsOut; not where gradients are turned)
 static int64_t attn_blocks(const AttnShape& s) { return (int64_t)((s.seq + 127) / 128) * s.heads * s.batch; }
 
 template <int D, bool F16, int G, bool SHORT = false>
@@ -1741,7 +1746,7 @@ static void bwd_bf16(const AttnShape& s, const void* qkv, const int32_t* seqlens
   const int64_t blocks = attn_blocks(s), room = D == 64 || s.causal ? ONE_ROUND<D> : s.drop.thr ? 160 : 224;
   if (blocks <= ONE_ROUND<D> / (s.causal ? 2 : 4) && s.seq > 64) return bwd_both<D, F16, 2>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
   const bool make_way = D == 64 && s.beside && blocks > 128 && blocks <= 256;
-  const bool is_short = s.seq <= SHORT_SEQ;
+  const bool is_short = s.seq <= SHORT_SEQ && !s.rope;
   if (blocks <= room && !make_way) {
     if (is_short) bwd_both<D, F16, 1, true>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
     else bwd_both<D, F16, 1>(s, qkv, seqlens, out, dout, lse, delta, dqkv, st);
