@@ -160,6 +160,16 @@ __device__ __forceinline__ void tile_ring(int n_tiles, Issue&& issue_tile, Compu
   }
 }
 
+// The walk of a sequence that is one tile (SHORT): nothing is on its way during anything.
+template <typename Issue, typename Compute>
+__device__ __forceinline__ void one_tile(int n_tiles, Issue&& issue_tile, Compute&& compute) {
+  if (n_tiles <= 0) return;
+  issue_tile(0, 0);
+  wait_loads_and_lds<0>();
+  block_barrier();
+  compute(0, 0);
+}
+
 // Small grids (few heads, few rows) leave most of the chip idle while each block walks its tiles one after the other. Their
 // blocks own 128 / G rows instead of 128 and their wavefronts form G groups that take every G-th tile of the walk (a step
 // brings in G tiles); the groups' results meet in LDS. G = 2: twice the blocks, half the steps.
@@ -177,10 +187,12 @@ __device__ __forceinline__ float* group_slot(void* smem, int grp, int row_wave, 
 // 111 -> 107 / 360 -> 338; the longer the walk the less: 1 x 8192, 20 451 -> 449 / 1277 -> 1274.
 // As they are where that is faster: where a wavefront has fewer than 32 rows (the last, and in causal grids longest, block of 1 x 152, 19,
 // causal, forward 64-wide 5.8 / 6.0, 128-wide 7.2 / 7.6), and where no other wavefront of the block has any (SHORT, sequences up to 32:
-// 16 x 32, 8 forward 64-wide 4.1 / 4.3, 128-wide 5.0 / 5.5, backward 5.4 / 5.6, 8.1 / 8.3; 8 x 64, 8 3.9 / 3.9, 6.0 / 5.6). Those
-// have instances of their own, in which nothing is left of the other way: it costs their launches of 4-8 us 1-2 %. Gradients that are
-// turned on the way always take their rows through LDS, because the table then is read in whole rows too (backward of a gated layer,
-// 16 x 16 tokens, hidden 768: 128-wide 64.5 / 63.2; 6 x 40, hidden 512 61.2 / 59.9).
+// 16 x 32, 8 forward 64-wide 4.1 / 4.4, 128-wide 5.0 / 5.5, backward 5.4 / 5.6, 8.1 / 8.3; 8 x 64, 8 3.9 / 3.9, 6.0 / 5.6).
+// Gradients that are turned on the way always take their rows through LDS, because the table then is read in whole rows too
+// (backward of a gated layer, 16 x 16 tokens, hidden 768: 128-wide 64.5 / 63.2; 6 x 40, hidden 512 61.2 / 59.9).
+// SHORT instances hold what one tile with one sub-tile of keys and of queries needs and nothing else (62-143 registers where the others
+// take 118-256). Against both sub-tiles and the ring of tiles, forward / backward: 64-wide 16 x 32, 8 4.1 -> 3.5 / 5.4 -> 4.3, 128 x 32, 8 6.7
+// -> 5.4 / 20.7 -> 14.4; 128-wide 64 x 16, 8 6.1 -> 4.9 / 19.8 -> 13.3. All attention kernels together 2.0 -> 1.65 MB of code.
 template <int D, bool F16, bool SHORT>
 struct RowsOut {
   static constexpr int P = D + 4;          // row pitch in elements: 8 bytes more, so that the 8-byte writes of 32 rows meet every bank once
@@ -362,6 +374,7 @@ __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const 
   constexpr int NS = D / 16, NT = D / 32;
   constexpr int TE = Tile<D>::ELEMS;
   constexpr int RB = 128 / G;   // rows of the block
+  constexpr int SUBS = SHORT ? 1 : 2;   // sub-tiles of 32 keys that hold any
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];  // [2][G][K tile | V tile]
   const int S = sh.seq, H = sh.hidden;
   const BlockId blk = xcd_local_block(sh.causal != 0, sh.lpt_heads);
@@ -419,11 +432,11 @@ __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const 
     if (G == 1 && !mine) return;
     const bf16_t* kt = smem + (stage * G + grp) * 2 * TE;
     const bf16_t* vt = kt + TE;
-    f32x16_t sc[2];
+    f32x16_t sc[SUBS];
     float mx = -INFINITY;
     if (mine) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < SUBS; ++i) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) sc[i][r] = 0.f;
 #pragma unroll
@@ -432,7 +445,7 @@ __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const 
       }
       if ((kv0 + 64 > kv_len) || (sh.causal && kv0 + 63 > wave_q_min)) {   // tile crosses a mask boundary
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < SUBS; ++i)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int kv = kv0 + i * 32 + acc_row(r, lane);
@@ -441,7 +454,7 @@ __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const 
           }
       }
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < SUBS; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[i][r]);
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
@@ -473,7 +486,7 @@ __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const 
     }
     const float mb = (m == -INFINITY) ? 0.f : m * sl2;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < SUBS; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float p = __builtin_amdgcn_exp2f(fmaf(sc[i][r], sl2, -mb));
@@ -482,14 +495,14 @@ __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const 
       }
     if (DROP) {   // the row sum above is the softmax denominator: dropout acts on the normalised probabilities
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < SUBS; ++i) {
         const uint32_t keep = keep16_query_lane(sh.drop, row_blk, kv0 + 32 * i, kc);
 #pragma unroll
         for (int r = 0; r < 16; ++r) sc[i][r] = ((keep >> r) & 1u) ? sc[i][r] : 0.f;
       }
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < SUBS; ++i)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const bf16x8_t pf = pack8<F16>(sc[i], h);
@@ -498,7 +511,8 @@ __global__ __launch_bounds__(256) void attn_fwd_bf16_kernel(AttnShape sh, const 
           o[t] = mfma16<F16>(frag_tr<D>(vt, ft_base, i * 32 + 16 * h, t), pf, o[t]);
       }
   };
-  tile_ring<FWD_STAGES<D>, G * 2 * TileDirect<D>::MINE>((n_tiles + G - 1) / G, issue_step, compute);
+  if constexpr (SHORT) one_tile(n_tiles, issue_step, compute);
+  else tile_ring<FWD_STAGES<D>, G * 2 * TileDirect<D>::MINE>((n_tiles + G - 1) / G, issue_step, compute);
   if constexpr (G > 1) {   // (the ring ends behind a barrier: the stages are free)
     static_assert(FWD_STAGES<D> == 2, "partly filled steps are waited for as a whole");
     constexpr int REGS = NT * 16 + 2;
@@ -592,7 +606,7 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(const BlockId blk, const Att
   constexpr int FB = 4;                 // k-steps of fragment prefetch (register budget: 8 FB registers)
   constexpr int NSTG = DKDV_STAGES<D>;
   constexpr bool ACC_A = (D == 128);    // dK/dV accumulators in AGPRs (see mfma16_agpr)
-  constexpr bool PIPE = ACC_A && !DROP; // hand-pipelined sub-tiles for tiles without a mask boundary (see compute)
+  constexpr bool PIPE = ACC_A && !DROP && !SHORT; // hand-pipelined sub-tiles for tiles without a mask boundary (see compute)
   static_assert(!PIPE || (NS == 8 && NT == 4), "the pipelined rounds are written for D = 128");
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
   const int S = sh.seq, H = sh.hidden;
@@ -818,7 +832,7 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(const BlockId blk, const Att
       }
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < (SHORT ? 1 : 2); ++i) {   // (SHORT: the second 32 queries do not exist)
       const int qs = q0 + i * 32;
       if (sh.causal && qs + 31 < wave_kv_min) continue;  // every query of this sub-tile precedes my keys
       f32x16_t sc, dp;
@@ -916,7 +930,16 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(const BlockId blk, const Att
   // them (loads complete in issue order) leaves the younger tile loads in flight. LPT = tile loads per step
   // that every wavefront issues.
   const int n_steps = (n_tiles + G - 1) / G;
-  if (n_steps > 0) {
+  if constexpr (SHORT) {
+    DeltaRows rows;
+    if (OWN_DELTA && n_tiles > 0) load_delta_rows(0, rows);
+    const float stat = load_stats(0);
+    one_tile(n_tiles, [&](int, int) {
+      issue_step(0, 0);
+      store_stats(0, stat);
+      if constexpr (OWN_DELTA) store_delta(0, 0, rows);
+    }, compute);
+  } else if (n_steps > 0) {
     constexpr int LPT = G * 2 * TileDirect<D>::MINE;
     static_assert(G == 1 || NSTG == 2, "partly filled steps are waited for as a whole");
     DeltaRows rows[G];
@@ -1075,7 +1098,7 @@ __device__ __forceinline__ void attn_bwd_dq_block(const BlockId blk, const AttnS
     const bf16_t* vt = kt + TE;
     const bool edge = (kv0 + 64 > kv_len) || (sh.causal && kv0 + 63 > wave_q_min);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < (SHORT ? 1 : 2); ++i) {
       f32x16_t sc, dp;
 #pragma unroll
       for (int r = 0; r < 16; ++r) sc[r] = dp[r] = 0.f;
@@ -1111,7 +1134,8 @@ __device__ __forceinline__ void attn_bwd_dq_block(const BlockId blk, const AttnS
       }
     }
   };
-  tile_ring<2, G * 2 * TileDirect<D>::MINE>((n_tiles + G - 1) / G, issue_step, compute);
+  if constexpr (SHORT) one_tile(n_tiles, issue_step, compute);
+  else tile_ring<2, G * 2 * TileDirect<D>::MINE>((n_tiles + G - 1) / G, issue_step, compute);
   if constexpr (G > 1) {
     constexpr int REGS = NT * 16;
     if (grp > 0) {

@@ -60,7 +60,7 @@ def test_dq_of_128_wide_heads_runs_two_wavefronts_per_simd(kernels, draws):
 
 
 # dQ and dK/dV with mask draws in one launch, 64-wide heads: all 256 registers of two wavefronts per SIMD, and as few more as can be
-@pytest.mark.parametrize("groups,most", [(1, 3), (2, 13)])
+@pytest.mark.parametrize("groups,most", [(1, 2), (2, 13)])
 def test_spills_of_the_one_launch_backward(kernels, groups, most):
     for name, k in _named(kernels, rf"attn_bwd_both_kernelILi64ELb1ELb[01]ELi{groups}E").items():
         assert k[".vgpr_count"] <= 256 and k[".vgpr_spill_count"] <= most, (name, k[".vgpr_spill_count"])
