@@ -22,12 +22,17 @@ def _code_objects(blob):
         at = blob.find(magic, at + 24)
 
 
-def _notes(elf):
+def _sections(elf):
+    """(type, offset, size) of each."""
     shoff, = struct.unpack_from("<Q", elf, 40)
     shentsize, shnum = struct.unpack_from("<HH", elf, 58)
     for i in range(shnum):
         kind, = struct.unpack_from("<I", elf, shoff + i * shentsize + 4)
-        offset, size = struct.unpack_from("<QQ", elf, shoff + i * shentsize + 24)
+        yield kind, *struct.unpack_from("<QQ", elf, shoff + i * shentsize + 24)
+
+
+def _notes(elf):
+    for kind, offset, size in _sections(elf):
         if kind == 7:   # SHT_NOTE
             namesz, descsz, note = struct.unpack_from("<III", elf, offset)
             if note == 32:   # NT_AMDGPU_METADATA
@@ -64,3 +69,19 @@ def test_dq_of_128_wide_heads_runs_two_wavefronts_per_simd(kernels, draws):
 def test_spills_of_the_one_launch_backward(kernels, groups, most):
     for name, k in _named(kernels, rf"attn_bwd_both_kernelILi64ELb1ELb[01]ELi{groups}E").items():
         assert k[".vgpr_count"] <= 256 and k[".vgpr_spill_count"] <= most, (name, k[".vgpr_spill_count"])
+
+
+def test_kernels_start_on_pages():
+    """Addresses of the functions in every code object (a step fetches each kernel's code anew, page by page)."""
+    with open(B.LIB_PATH, "rb") as f:
+        objects = list(_code_objects(f.read()))
+    seen = 0
+    for elf in objects:
+        for kind, offset, size in _sections(elf):
+            if kind == 11:   # SHT_DYNSYM
+                for at in range(offset, offset + size, 24):
+                    info, value = elf[at + 4], struct.unpack_from("<Q", elf, at + 8)[0]
+                    if info & 15 == 2:   # STT_FUNC
+                        seen += 1
+                        assert value % 4096 == 0, hex(value)
+    assert seen > 300
