@@ -150,6 +150,7 @@ int slapo_layer_fwd(const slapo_layer_desc *desc, const slapo_layer_params *para
 /* Backward: given dy = dL/dy [B,S,H] and the `saved` buffer of the matching forward, writes
  * dx [B,S,H] and the parameter gradients (twelve; six for SLAPO_ARCH_LLAMA; same shapes and element type as
  * the parameters). dx may be the array x itself and may lie on dy in any way; it overlaps nothing else.
+ * (On top of x, gradients of a post-LN layer are sums in another order: the last bits differ from those with dx elsewhere.)
  * The dropout masks are regenerated from (seed, layer_id, site, element index), never stored. */
 int slapo_layer_bwd(const slapo_layer_desc *desc, const slapo_layer_params *params, const void *x,
                     const int32_t *seqlens, const void *dy, const void *saved, void *dx,

@@ -128,7 +128,7 @@ enum TileKind { TILE_256, TILE_128_SPLITSLAB, TILE_128_LOADERS, TILE_128x64_LOAD
 // Steps: 2 x 1024 tokens of width 3072 1507 -> 1375 us, 3 x 777 of 2048 834 -> 769, 10 x 500 of 1024 613 -> 573, gated 2 x 1100 of 4096 2760 -> 2479.
 // 192x256 loses to two 128x128 workgroups per CU where those are all resident (2600 x 3072 x 768 with GeLU: 504 tiles of 128x128, forward of
 // the layer 91 / 95), and at K = 512 192x128 gains nothing (a gated layer's 2048 x 2736 x 512: forward 57.5 / 58.0). Layout TN has no
-// such tiles (the chunk permutation of rows along M needs a power of two).
+// such tiles: the chunk permutation of rows along M needs a power of two, and 256x128 ones have not been built for it.
 static TileKind one_round_tile(int layout, int M, int N, int K) {
   auto count = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   const int64_t t128 = count(128, 128);
@@ -175,9 +175,10 @@ static TileKind select_tile(int layout, int M, int N, int K, bool solo) {
 }
 
 // Several rounds of 128x128 tiles: two LDS stages instead of four, so that two workgroups fit a CU and one's first loads and
-// epilogue run beside the other's products. Four / two stages, same card: NT 2286 x 3072 x 768 with GeLU 24.1 / 20.7
-// us, 2331 x 8192 x 2048 101 / 93.5, 2000 x 2560 x 2560 39.2 / 34.7; NN 2048 x 4096 x 2752 44.6 / 41.9, 2331 x 2752 x
-// 4096 gated 62.9 / 57.0. Many rounds of long K gain nothing (700 x 16384 x 4096 101.6 / 104.2).
+// epilogue run beside the other's products. For K below 768, layout TN, and grids that no tile makes one round. Four / two stages, us:
+// NT 3000 x 1536 x 512 12.8 / 11.0, with GeLU 18.3 / 15.4, 4096 x 2048 x 512 with GeLU 22.9 / 19.2, 640 x 12000 x 1024 with GeLU 29.0 / 24.7, x 4096
+// 62.2 / 60.8; NN 3000 x 2048 x 512 with GeLU' 15.9 / 13.4, 640 x 12000 x 2048 37.8 / 34.9; TN 1536 x 4096 x 512 14.2 / 12.5, x 1024 20.4 / 19.1; more
+// rounds gain less (NT 7000 x 1536 x 512 19.0 / 18.8).
 static bool two_per_cu(int M, int N, int K) {
   const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
   return t128 > 256 && (t128 <= 512 || K <= 3072);
@@ -189,10 +190,11 @@ static bool two_per_cu(int M, int N, int K) {
 // of 1/s the length, and a second kernel adds the ranges in order (bitwise reproducible) and applies the
 // epilogue. Worth it when the saved (1 - 1/s) of a round outweighs writing and re-reading the partial tiles,
 // i.e. for long K; plain and add epilogues only (the others have so many tiles that a thin round matters little).
-// A grid with fewer tiles than half the CUs is all tail: 128 x 1024 outputs are 16 tiles of 128x64.
-// Same card, without / with: NT 2331 x 2048 x 8192 (304 tiles of 128x128) 98 / 83 us, 2000 x 2560 x 10240 (320) 125 / 102,
-// NN 2000 x 2560 x 7680 101 / 84; 128 x 1024 x 4096 16.3 / 10.8, K = 3072 12.9 / 10.7. Below those lengths the second
-// kernel costs what the ranges save (2331 x 2048 x 2048: 29 us either way).
+// A grid with fewer tiles than half the CUs is all tail: 300 x 2048 outputs are 96 tiles of 128x64.
+// Without / with, us: 8192 x 2560 x 10240 397 / 359 (whole tiles), 336 / 330 (quarters); 300 x 2048 x 8192 24.4 / 23.4. Three kinds of plan
+// are older than what the product takes without a workspace now, and slower: 128x128 tiles where others make one round (2331 x 2048 x
+// 8192 73 / 83; the layers pass no workspace there), few 128x64 tiles where 64x64 ones have 128-deep slabs (256 x 1024 x 4096 10.2 / 13.5)
+// and where the reader adds ranges itself (product_in_ranges). Exported calls that bring a workspace get what they ask for.
 struct HybridPlan { TileKind tile; int tail_begin, tail_tiles, splits; size_t ws_bytes; };
 static HybridPlan hybrid_plan(int layout, int epi, int M, int N, int K) {
   HybridPlan none = {TILE_256, 0, 0, 1, 0}, p = none;
