@@ -6,7 +6,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libslapo_mi355x.so")
-SOURCES = ("api.hip", "gemm.hip", "grads.hip", "attention.hip", "rowwise.hip")
+SOURCES = ("api.hip", "gemm.hip", "grads.hip", "products.hip", "attention.hip", "rowwise.hip")
 # per-file extra flags: the attention kernels alternate MFMA and vector work on the same tiles, so their MFMA
 # results are kept in ordinary VGPRs (the default puts them in accumulation registers and copies them back
 # and forth for every softmax)

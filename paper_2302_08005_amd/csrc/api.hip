@@ -218,6 +218,37 @@ bool gradients_paired(const slapo_layer_desc* d) {
   return !is_llama(d) && T <= 4096.0 && weights * T <= 3.2e10 && (weights <= 6.4e7 || d->dtype == SLAPO_FP32);
 }
 
+// Whether the weight gradients of backward share launches of 256x256 tiles with each other and with data gradients (launch_products),
+// all on the caller's stream, and which: the gradient of the layer's input and all four behind the attention kernels (BEHIND), or those
+// of each block with the gradient of the block's input (BLOCKS). Decided by what either form takes in slabs of such a tile
+// (products_slabs), against the work itself. Where the gradient of the second feed-forward weight alone has tiles for three
+// quarters of the chip, two streams run the same large tiles and fill each other's thin rounds: only nearly full launches beat
+// them, by 0 to 5 %. Elsewhere they run 128x128 ones, at 1.3 times the work, and pay about 22 slabs for forks and launches.
+// BLOCKS are the better form at equal slabs (by 4 % of them: fewer tiles drift apart). Backward, us, two streams / together:
+//   hidden 1024, tokens 1500 157 / 176 (apart), 2000 196 / 189, 3000 251 / 225, 4000 315 / 287, 8000 597 / 514, 16000 1067 / 926
+//   hidden 1536, 2000 337 / 335, 4000 587 / 560 (BLOCKS), 8000 1092 / 1003, 16000 2212 / 1853
+//   hidden 768, 2000 136 / 150, 4000 239 / 225, 8000 424 / 433, 16000 733 / 771; 512, 8000 245 / 292 (all apart)
+//   hidden 2048, 4000 829 / 810, 12000 2275 / 2219; 2560, 2000 690 / 714 (apart), 8000 2372 / 2272; 3072, 4096 1663 / 1766 (BEHIND), 1662 (BLOCKS)
+//   gated, hidden 2048, FFN 5504, 2000 519 / 481, 4000 890 / 857; 4096, attention 2048, FFN 5504, 4096 1424 / 1464 (apart); 4096, 512, 1376,
+//   4096 527 / 489; 4096, FFN 11008, 4000 2733 / 2689
+enum Together { APART, BEHIND, BLOCKS };
+Together products_together(const slapo_layer_desc* d) {
+  if (d->dtype == SLAPO_FP32) return APART;
+  const int T = d->batch * d->seq, H = d->hidden, F = d->ffn, A = attn_width(d), F1 = is_llama(d) ? 2 * F : F;
+  const auto sizes = [](int layout, int M, int N, int K) { return Product{layout, M, N, K, nullptr, nullptr, nullptr, nullptr}; };
+  const Product x = sizes(GEMM_NN, T, H, 3 * A), y = sizes(GEMM_NN, T, H, F1), w2 = sizes(GEMM_TN, H, F, T), w1 = sizes(GEMM_TN, F1, H, T),
+                wo = sizes(GEMM_TN, H, A, T), wqkv = sizes(GEMM_TN, 3 * A, H, T);
+  const Product behind[] = {x, w2, w1, wo, wqkv}, first[] = {y, w2, w1}, second[] = {x, wo, wqkv};
+  int64_t total = 0, ignored = 0;
+  const int in_blocks = products_slabs(3, first, &total) + products_slabs(3, second, &total);
+  const int at_end = products_slabs(5, behind, &ignored) + gemm_slabs(GEMM_NN, T, H, F1);
+  const bool blocks = in_blocks <= 1.04 * at_end;
+  const double slabs = blocks ? in_blocks : at_end, work = (double)total / 256.0;
+  const bool large_alone = (int64_t)((H + 255) / 256) * ((F + 255) / 256) >= 192;
+  if (slabs > (large_alone ? 1.065 * work : 1.3 * work + 22.0)) return APART;
+  return blocks ? BLOCKS : BEHIND;
+}
+
 // byte offsets of the regions of `saved`
 struct SavedLayout {
   size_t qkv, attn, lse, z1, n1, y1, u, g, z2, mu1, rstd1, mu2, rstd2, total;
@@ -534,22 +565,33 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   const bool dy_is_dr2 = d->pre_ln && keeps_all && !overlap(dx, dy, array);   // (a dx on top of dy is written while the helper stream reads dr2)
   const bool dx_on_x = !d->pre_ln && overlap(dx, x, array);   // (a pre-LN layer's dx is written row by row behind the read, and no weight gradient reads x)
   // `st` carries the data-gradient chain; `ws` the weight / bias gradients that hang off it
-  SideStream* side = backward_on_one_stream(d) ? nullptr : side_stream();
-  const bool solo = side == nullptr;   // one stream: every GEMM has the chip to itself
+  const Together together = dx_on_x ? APART : products_together(d);   // (dx would be written while a tile beside it still reads x)
+  // (beside products that share launches only the column sums behind the bias gradients run on the helper stream)
+  SideStream* side = (together != APART ? is_llama(d) : backward_on_one_stream(d)) ? nullptr : side_stream();
+  const bool solo = side == nullptr || together != APART;   // every GEMM has the chip to itself
   hipStream_t ws = side ? side->stream : st;
   auto fork = [&](int i) {   // everything issued on st so far happens before what follows on ws
-    if (side) side->order(side->fork[i], st, ws);
+    if (side && (together == APART || i == 1 || i == 3)) side->order(side->fork[i], st, ws);
   };
   // weight gradient: C (+)= A^T B
   float* splitk_ws = W.splitk_bytes ? (float*)(sc + W.splitk) : nullptr;
   float* gws = W.gemm_ws_bytes ? (float*)(sc + W.gemm_ws) : nullptr;
+  Product waiting[MAX_PRODUCTS];   // for the next launch of several
+  int n_waiting = 0;
   auto dweight = [&](int M, int N, const void* a, const void* b, void* c) {
-    launch_weight_grad(dt, acc, M, N, T, a, b, c, splitk_ws, ws, solo);
+    if (together != APART) waiting[n_waiting++] = {GEMM_TN, M, N, T, a, b, c, acc ? c : nullptr};
+    else launch_weight_grad(dt, acc, M, N, T, a, b, c, splitk_ws, ws, solo);
   };
   // data gradient: C = A B (+ aux)
   auto dgrad = [&](int epi, int N, int K, const void* a, const void* b, void* c, const void* aux) {
     const size_t need = product_ws_bytes(dt, GEMM_NN, T, N, K);
     launch_gemm(dt, GEMM_NN, epi, d->act, T, N, K, a, b, c, nullptr, aux, nullptr, st, solo, need ? gws : nullptr, need);
+  };
+  // the same, with the weight gradients that wait
+  auto dgrad_with_weights = [&](int N, int K, const void* a, const void* b, void* c, const void* aux) {
+    waiting[n_waiting++] = {GEMM_NN, T, N, K, a, b, c, aux};
+    launch_products(dt, n_waiting, waiting, st);
+    n_waiting = 0;
   };
   auto colsum = [&](const void* a, int N, void* out, hipStream_t s) {
     float* part = s == st ? pcol2 : pcol;   // per stream, so that the two sums may run at the same time
@@ -562,7 +604,7 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   // The gradient of a block's input, [T,H], which a row kernel reads next: t0, or K ranges in gws where few tokens make few tiles
   // (`add`, what the product is added to, is then the row kernel's to add). Not the feed-forward block's of the gated layer, whose
   // gradients are, bit for bit, those of the exported products, rotary turn and attention in a row (1024, 128 tokens: 2 us).
-  const bool r_y1 = !is_llama(d) && product_in_ranges(dt, T, H, F), r_x = product_in_ranges(dt, T, H, 3 * A);
+  const bool r_y1 = together != BLOCKS && !is_llama(d) && product_in_ranges(dt, T, H, F), r_x = together == APART && product_in_ranges(dt, T, H, 3 * A);
   auto row_bwd = [&](bool ranges, const void* add, const void* z, const float* mu, const float* rstd, const void* gamma, const void* dres,
                      void* dz, void* dr, const DropoutParams& dp, int dr_from_stored) {
     launch_bdrln_bwd(dt, T, H, ranges ? gws : t0, z, mu, rstd, gamma, dres, dz, dr, prow, dp, is_llama(d) ? 1 : 0, st, dr_from_stored, nrow,
@@ -583,7 +625,7 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   void *g_b2 = llama ? nullptr : gr->b2, *g_bo = llama ? nullptr : gr->bo;
   void *g_ln1_b = llama ? nullptr : gr->ln1_b, *g_ln2_b = llama ? nullptr : gr->ln2_b;
 
-  if (gradients_paired(d) && !dx_on_x) {   // (it would be written while the weight gradient beside it still reads x)
+  if (together == APART && gradients_paired(d) && !dx_on_x) {   // (it would be written while the weight gradient beside it still reads x)
     // The weight gradients share the launches of the data gradients (GradPair), and the sums behind the row kernels and
     // the biases ride on them.
     GradPair pr = {};
@@ -671,20 +713,23 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     reduce_rows(gr->ln2_g, g_ln2_b, g_b2);
   }
   fork(0);
-  if (dy_is_dr2 && !llama) colsum(dr2, H, g_b2, ws);
+  if (dy_is_dr2 && !llama && together == APART) colsum(dr2, H, g_b2, ws);
   dweight(H, F, dr2, g, gr->w2);
   if (llama) {
     // dG = dR2 W2, turned into the (gate, up) gradient pairs [T,2F] by the two saved factors in the epilogue
     launch_gemm(dt, GEMM_NN, EPI_DGATE, d->act, T, F, H, dr2, p->w2, du, nullptr, u, nullptr, st, solo);
     fork(1);
     dweight(2 * F, H, du, y1, gr->w1);
-    dgrad(EPI_NONE, H, 2 * F, du, p->w1, t0, nullptr);
+    if (together == BLOCKS) dgrad_with_weights(H, 2 * F, du, p->w1, t0, nullptr);
+    else dgrad(EPI_NONE, H, 2 * F, du, p->w1, t0, nullptr);
   } else {
     launch_gemm(dt, GEMM_NN, EPI_DACT, d->act, T, F, H, dr2, p->w2, du, nullptr, u, nullptr, st, solo);
     fork(1);
+    if (dy_is_dr2 && together != APART) colsum(dr2, H, g_b2, ws);
     colsum(du, F, gr->b1, ws);
     dweight(F, H, du, y1, gr->w1);
-    if (r_y1) launch_gemm_ranges(dt, GEMM_NN, T, H, F, du, p->w1, gws, st);
+    if (together == BLOCKS) dgrad_with_weights(H, F, du, p->w1, t0, d->pre_ln ? nullptr : t0);
+    else if (r_y1) launch_gemm_ranges(dt, GEMM_NN, T, H, F, du, p->w1, gws, st);
     else if (d->pre_ln) dgrad(EPI_NONE, H, F, du, p->w1, t0, nullptr);
     else dgrad(EPI_ADD, H, F, du, p->w1, t0, t0);
   }
@@ -699,12 +744,14 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   fork(2);
   dweight(H, A, dr1, attn, gr->wo);
   dgrad(EPI_NONE, A, H, dr1, p->wo, t0, nullptr);
-  as.beside = side && splitk_ws;
+  as.beside = side && splitk_ws && together == APART;
   launch_attn_bwd(dt, as, qkv, seqlens, attn, t0, lse, delta, dqkv, st);
   fork(3);
+  if (!llama && together != APART) colsum(dqkv, 3 * A, gr->bqkv, ws);
   if (d->pre_ln) {
     dweight(3 * A, H, dqkv, sv + L.n1, gr->wqkv);
-    if (r_x) launch_gemm_ranges(dt, GEMM_NN, T, H, 3 * A, dqkv, p->wqkv, gws, st);
+    if (together != APART) dgrad_with_weights(H, 3 * A, dqkv, p->wqkv, t0, nullptr);
+    else if (r_x) launch_gemm_ranges(dt, GEMM_NN, T, H, 3 * A, dqkv, p->wqkv, gws, st);
     else dgrad(EPI_NONE, H, 3 * A, dqkv, p->wqkv, t0, nullptr);
     if (link && link->dr2_below) {
       // (from the stored dx, so that the layer below sees what it would compute from dx itself, bit for bit)
@@ -717,11 +764,12 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   } else {
     dweight(3 * A, H, dqkv, x, gr->wqkv);
     if (side && dx_on_x) side->order(side->join, ws, st);   // the helper stream has read x before dx is written there
-    dgrad(EPI_ADD, H, 3 * A, dqkv, p->wqkv, dx, t2);
+    if (together != APART) dgrad_with_weights(H, 3 * A, dqkv, p->wqkv, dx, t2);
+    else dgrad(EPI_ADD, H, 3 * A, dqkv, p->wqkv, dx, t2);
   }
   // the last bias gradient goes behind the data gradient on the caller's stream: the helper stream's last
   // product is the longer one, and this way the two streams end at about the same time
-  if (!llama) colsum(dqkv, 3 * A, gr->bqkv, st);
+  if (!llama && together == APART) colsum(dqkv, 3 * A, gr->bqkv, st);
   if (side) side->order(side->join, ws, st);   // join: the caller's stream continues only after the weight gradients are complete
   return finish();
 }

@@ -397,6 +397,20 @@ static void launch_bf16(int epi, int act, int M, int N, int K, const void* A, co
   }
 }
 
+// Rates of the other tiles in slabs of a 256x256 one (1.33 us): their rules have the times.
+int gemm_slabs(int layout, int M, int N, int K) {
+  const int nk = (K + 63) / 64, t256 = ((M + 255) / 256) * ((N + 255) / 256), t128 = ((M + 127) / 128) * ((N + 127) / 128);
+  const int rem = quarter_tiles(layout, M, N, K, true), rounds = t256 / 256;
+  if (rem) return rounds * (nk + TILE_SLABS) + ((rem + 63) / 64) * (nk + TILE_SLABS) / 4 + nk / 10;
+  switch (select_tile(layout, M, N, K, true)) {
+    case TILE_256: return ((t256 + 255) / 256) * (nk + TILE_SLABS);
+    case TILE_192x128_LOADERS: return nk * 36 / 100 + TILE_SLABS;
+    case TILE_256x128_LOADERS: return nk * 46 / 100 + TILE_SLABS;
+    case TILE_192x256: return nk * 70 / 100 + TILE_SLABS;
+    default: return ((t128 + 255) / 256) * (nk * 29 / 100 + TILE_SLABS);
+  }
+}
+
 // ---- weight gradients with few output tiles: several K ranges per tile ---------------------------------
 // C = sum over the ranges of the fp32 partial products, added in range order (so the result does not depend on
 // which workgroup finished first), + addend (may be C itself), eight columns per thread.

@@ -127,20 +127,25 @@ __device__ __forceinline__ GateTerms gate_terms(float u, float w) {
 // block: its workgroups walk K in step, and every A (B) slab that reaches the L2 is used by all tiles of its row
 // (column) in the block. `copies`: the grid holds that many copies of the tile set (K ranges), copy after copy.
 struct TilePos { int tile_m, tile_n, copy; };
+__device__ __forceinline__ TilePos tile_in_order(int id, int tiles_m, int tiles_n) {
+  TilePos t;
+  t.copy = 0;
+  constexpr int GROUP_M = 4;
+  const int group = id / (GROUP_M * tiles_n);
+  const int first_m = group * GROUP_M;
+  const int gsz = tiles_m - first_m < GROUP_M ? tiles_m - first_m : GROUP_M;
+  const int in_group = id - group * GROUP_M * tiles_n;
+  t.tile_m = first_m + in_group % gsz;
+  t.tile_n = in_group / gsz;
+  return t;
+}
 __device__ __forceinline__ TilePos tile_position(int bid, int tiles_m, int tiles_n, int copies) {
   const int nblk = tiles_m * tiles_n;
   const int per_xcd = (nblk * copies) / 8;
   if (bid < per_xcd * 8) bid = (bid & 7) * per_xcd + (bid >> 3);
-  TilePos t;
-  t.copy = bid / nblk;
-  bid -= t.copy * nblk;
-  constexpr int GROUP_M = 4;
-  const int group = bid / (GROUP_M * tiles_n);
-  const int first_m = group * GROUP_M;
-  const int gsz = tiles_m - first_m < GROUP_M ? tiles_m - first_m : GROUP_M;
-  const int in_group = bid - group * GROUP_M * tiles_n;
-  t.tile_m = first_m + in_group % gsz;
-  t.tile_n = in_group / gsz;
+  const int copy = bid / nblk;
+  TilePos t = tile_in_order(bid - copy * nblk, tiles_m, tiles_n);
+  t.copy = copy;
   return t;
 }
 

@@ -53,6 +53,16 @@ size_t weight_grad_ws_least_bytes(int dtype, int M, int N, int K);
 void launch_weight_grad(int dtype, int accumulate, int M, int N, int K, const void* A, const void* B, void* C,
                         float* ws, hipStream_t st, bool solo = false);
 
+// Independent products in one launch of 256x256 tiles, 16-bit storage (products.hip): C [M,N] = A B (layout GEMM_NN) or A^T B
+// (GEMM_TN), + aux (NULL: nothing; it may be C).
+constexpr int MAX_PRODUCTS = 5, TILE_SLABS = 6;   // TILE_SLABS: what a tile takes besides its 64-deep slabs, in such slabs
+struct Product { int layout, M, N, K; const void *A, *B; void* C; const void* aux; };
+void launch_products(int dtype, int n, const Product* products, hipStream_t st);
+// how long the launch takes, in 64-deep slabs of one tile; *work += the same summed over its tiles (sizes only, no pointers)
+int products_slabs(int n, const Product* products, int64_t* work);
+// the same for a product (NN, 16-bit) that has a launch of its own and the chip to itself
+int gemm_slabs(int layout, int M, int N, int K);
+
 // What backward computes from one gradient array, in one launch: the gradient that goes on (layout NN, C [M,N] = A [M,K]
 // B [K,N], epilogue EPI_DACT, EPI_DGATE or EPI_ADD; the latter adds nothing if aux is NULL), the weight gradient
 // dW [wM,wN] (+)= wA [wK,wM]^T wB [wK,wN] (NULL: none), the column sums of wA (a bias gradient; NULL: none) and the sums over the partial

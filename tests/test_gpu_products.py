@@ -1,0 +1,60 @@
+"""Backward whose weight gradients share launches of 256x256 tiles with each other and with data gradients: vs the fp64 oracle, and
+vs the same layer with a launch for each (dx on top of x). Ragged tokens, widths and K."""
+import pytest
+import torch
+
+import workloads as W
+from gpu_util import DEV, TOL, captured, err, to_np
+from paper_2302_08005_amd import binding as B
+from test_gpu_layer import run_case
+from test_gpu_llama import run_case as run_gated
+
+pytestmark = pytest.mark.gpu
+
+
+def cfg(name, batch, seq, hidden, heads, ffn, dtype=W.BF16, **kw):
+    return W.LayerConfig(name, batch, seq, hidden, heads, ffn, **{**dict(causal=0, dropout_p=0.1, dtype=dtype, config_id=96), **kw})
+
+
+def tiles(*products):
+    return sum(((m + 255) // 256) * ((n + 255) // 256) for m, n in products)
+
+
+def launches(layer, x, dy, dx):
+    return captured(lambda: B.slapo_layer_bwd(layer.desc, layer.params, x, None, dy, layer.saved, dx, layer.grads, layer.scratch), grids=True)
+
+
+# the input gradient and all weight gradients behind attention
+@pytest.mark.parametrize("c", [
+    cfg("postln-ragged", 4, 525, 1024, 16, 4104, len_lo=100, len_hi=525),
+    cfg("gated-half-ragged", 3, 700, 1024, 8, 2728, W.FP16, causal=1, pre_ln=1, dropout_p=0.0, ln_eps=1e-6, arch=W.LLAMA)], ids=lambda c: c.name)
+def test_gradients_behind_attention(c):
+    errs, layer, (x, sl, dy, _, dx) = (run_gated if c.arch == W.LLAMA else run_case)(c, check_saved=False)
+    assert all(v <= TOL[c.dtype] for v in errs.values()), errs
+    T, H, F, F1 = c.batch * c.seq, c.hidden, c.ffn, c.ffn * (2 if c.arch == W.LLAMA else 1)
+    assert launches(layer, x, dy, dx).count((tiles((T, H), (H, F), (F1, H), (H, H), (3 * H, H)), 1, 1)) == 1
+    first, dx = {k: v.clone() for k, v in layer.grads.items()}, dx.clone()
+    layer.desc.accumulate_grads = 1
+    assert torch.equal(layer.backward(x, sl, dy), dx)
+    for k in W.param_names(c):   # one rounding of the storage type more than twice the first result
+        assert err(layer.grads[k], 2 * to_np(first[k])) <= TOL[c.dtype] / 2, k
+
+
+# each block's with the gradient of its input
+def test_gradients_of_each_block():
+    c = cfg("blocks", 4, 1000, 1536, 24, 6152)
+    layer, T, H, F = B.Layer(c, W.make_params(c)), 4000, 1536, 6152
+    gen = torch.Generator(device=DEV).manual_seed(9)
+    x, dy = (torch.randn(c.batch, c.seq, H, device=DEV, generator=gen).to(layer.dt) for _ in range(2))
+    layer.forward(x)
+    dx = layer.backward(x, None, dy)
+    want = {k: v.clone() for k, v in layer.grads.items()}
+    grids = launches(layer, x, dy, dx)
+    assert (tiles((T, H), (H, F), (F, H)), 1, 1) in grids and (tiles((T, H), (H, H), (3 * H, H)), 1, 1) in grids
+    x2 = x.clone()   # dx on top of x: a launch for each
+    assert len(launches(layer, x2, dy, x2)) > len(grids)
+    B.slapo_layer_bwd(layer.desc, layer.params, x2, None, dy, layer.saved, x2, layer.grads, layer.scratch)
+    torch.cuda.synchronize()
+    assert err(x2, to_np(dx)) <= TOL[c.dtype]   # (the same sums in another order, rounded once more on the way)
+    for k in W.PARAM_NAMES:
+        assert err(layer.grads[k], to_np(want[k])) <= TOL[c.dtype], k
