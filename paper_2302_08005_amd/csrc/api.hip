@@ -284,8 +284,15 @@ static size_t product_ws_bytes(int dtype, int layout, int M, int N, int K) {
   return gemm_in_one_round(dtype, layout, M, N, K) ? 0 : gemm_ws_bytes(dtype, layout, EPI_NONE, M, N, K);
 }
 
+// The gradient of the first feed-forward bias: column sums that the product which computes the gradient of the activations leaves
+// behind (EPI_DACT), instead of another pass over that array (16384 tokens, 4096 columns: 27 us alone, 36 beside a product).
+// From 1024 tokens on: below, the pass is 5 us on the helper stream or rides on the next launch. fp32 products leave none.
+inline bool sums_with_du(const slapo_layer_desc* d) {
+  return !is_llama(d) && d->dtype != SLAPO_FP32 && (int64_t)d->batch * d->seq >= 1024;
+}
+
 struct ScratchLayout {
-  size_t t0, t1, t2, t3, du, dqkv, delta, part_row, part_col, part_col2, rope, splitk, gemm_ws, gemm_ws_bytes, splitk_bytes, acts, total;
+  size_t t0, t1, t2, t3, du, dqkv, delta, part_row[3], part_col, part_col2, part_du, rope, splitk, gemm_ws, gemm_ws_bytes, splitk_bytes, acts, total;
 };
 ScratchLayout scratch_layout(const slapo_layer_desc* d) {
   const size_t eb = d->dtype == SLAPO_FP32 ? 4 : 2;
@@ -300,11 +307,12 @@ ScratchLayout scratch_layout(const slapo_layer_desc* d) {
   L.du = take(T * F * eb * (is_llama(d) ? 2 : 1));
   L.dqkv = take(T * 3 * A * eb);
   L.delta = take((size_t)d->batch * d->heads * d->seq * 4);
-  L.part_row = take((size_t)bdrln_bwd_blocks_wide((int64_t)T, (int)H) * 3 * H * 4);
+  for (size_t& p : L.part_row) p = take((size_t)bdrln_bwd_blocks_wide((int64_t)T, (int)H) * 3 * H * 4);   // one per row kernel
   size_t widest = F > 3 * A ? F : 3 * A;
   widest = widest > H ? widest : H;
   L.part_col = take((size_t)colsum_blocks((int64_t)T) * widest * 4);
   L.part_col2 = take((size_t)colsum_blocks((int64_t)T) * widest * 4);   // the two streams of backward each own one
+  L.part_du = sums_with_du(d) ? take((T + DACT_SUM_ROWS - 1) / DACT_SUM_ROWS * F * 4) : 0;
   L.rope = is_llama(d) ? take((size_t)d->seq * (A / d->heads / 2) * 8) : 0;   // (cos, sin) table
   // fp32 partial tiles of the weight gradients that are computed in several K ranges (one at a time: all of them
   // run on the helper stream); 0 for shapes that fill the chip with plain tiles
@@ -554,7 +562,7 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   const float *lse = (const float*)(sv + L.lse), *mu1 = (const float*)(sv + L.mu1), *rstd1 = (const float*)(sv + L.rstd1);
   const float *mu2 = (const float*)(sv + L.mu2), *rstd2 = (const float*)(sv + L.rstd2);
   void *t0 = sc + W.t0, *t1 = sc + W.t1, *t2 = sc + W.t2, *t3 = sc + W.t3, *du = sc + W.du, *dqkv = sc + W.dqkv;
-  float *delta = (float*)(sc + W.delta), *prow = (float*)(sc + W.part_row), *pcol = (float*)(sc + W.part_col), *pcol2 = (float*)(sc + W.part_col2);
+  float *delta = (float*)(sc + W.delta), *prow = (float*)(sc + W.part_row[0]), *pcol = (float*)(sc + W.part_col), *pcol2 = (float*)(sc + W.part_col2);
   AttnShape as = make_attn_shape(d);
   const DropoutParams dp0 = make_dropout(d, 0), dp1 = make_dropout(d, 1);
   const int nrow = bdrln_bwd_blocks_wide(T, H), ncol = colsum_blocks(T);
@@ -598,16 +606,17 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     launch_colsum_partials(dt, T, N, a, part, s);
     launch_colreduce_partials(dt, ncol, N, N, part, out, acc, s);
   };
-  auto reduce_rows = [&](void* dgamma, void* dbeta, void* dbias) {
-    launch_colreduce3(dt, nrow, H, prow, dgamma, dbeta, dbias, acc, st);
+  // the sums over the partial rows that row kernel `k` (0 to 2, in their order) left
+  auto reduce_rows = [&](int k, void* dgamma, void* dbeta, void* dbias, hipStream_t s) {
+    launch_colreduce3(dt, nrow, H, (float*)(sc + W.part_row[k]), dgamma, dbeta, dbias, acc, s);
   };
   // The gradient of a block's input, [T,H], which a row kernel reads next: t0, or K ranges in gws where few tokens make few tiles
   // (`add`, what the product is added to, is then the row kernel's to add). Not the feed-forward block's of the gated layer, whose
   // gradients are, bit for bit, those of the exported products, rotary turn and attention in a row (1024, 128 tokens: 2 us).
   const bool r_y1 = together != BLOCKS && !is_llama(d) && product_in_ranges(dt, T, H, F), r_x = together == APART && product_in_ranges(dt, T, H, 3 * A);
   auto row_bwd = [&](bool ranges, const void* add, const void* z, const float* mu, const float* rstd, const void* gamma, const void* dres,
-                     void* dz, void* dr, const DropoutParams& dp, int dr_from_stored) {
-    launch_bdrln_bwd(dt, T, H, ranges ? gws : t0, z, mu, rstd, gamma, dres, dz, dr, prow, dp, is_llama(d) ? 1 : 0, st, dr_from_stored, nrow,
+                     void* dz, void* dr, const DropoutParams& dp, int dr_from_stored, int k = 0) {
+    launch_bdrln_bwd(dt, T, H, ranges ? gws : t0, z, mu, rstd, gamma, dres, dz, dr, (float*)(sc + W.part_row[k]), dp, is_llama(d) ? 1 : 0, st, dr_from_stored, nrow,
                      ranges, ranges ? add : nullptr);
   };
   // Buffers: t0 dZ2 -> dY1/dN2 -> dA -> dN1; t1 dR2 (kept for dW2); t2 dZ1; t3 dR1 (kept for dWo). Where nothing is dropped
@@ -694,80 +703,96 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
       link->sums[0] = gr->ln1_g; link->sums[1] = g_ln1_b; link->sums[2] = link->db2_below;
     } else if (d->pre_ln) {
       row_bwd(r_x, nullptr, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, dp0, 0);
-      reduce_rows(gr->ln1_g, g_ln1_b, nullptr);
+      reduce_rows(0, gr->ln1_g, g_ln1_b, nullptr, st);
     }
     return finish();
   }
 
   // ---- FFN block ----
+  // The sums over partial rows and the bias gradients leave the chain with the next fork: of every weight gradient, or of the two
+  // beside products that share launches (one, in front of the last launch, takes as long).
   const void* dr2 = t1;
+  bool rows2 = true;   // the first row kernel has left partial rows
   if (dy_is_dr2) {
     dr2 = dy;
+    rows2 = false;
   } else if (d->pre_ln && link && link->dr2_in) {
     dr2 = link->dr2_in;
+    rows2 = false;
   } else if (d->pre_ln) {
     launch_bdrln_bwd(dt, T, H, dy, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, t1, prow, dp1, rms, st, 0, nrow);
-    if (!llama) reduce_rows(nullptr, nullptr, g_b2);
+    rows2 = !llama;
   } else {
     launch_bdrln_bwd(dt, T, H, dy, sv + L.z2, mu2, rstd2, p->ln2_g, nullptr, t0, t1, prow, dp1, rms, st, 0, nrow);
-    reduce_rows(gr->ln2_g, g_ln2_b, g_b2);
   }
-  fork(0);
-  if (dy_is_dr2 && !llama && together == APART) colsum(dr2, H, g_b2, ws);
+  const bool with_du = sums_with_du(d);
+  float* pdu = (float*)(sc + W.part_du);
+  auto sums_of_ffn_output = [&] {
+    if (rows2) reduce_rows(0, d->pre_ln ? nullptr : gr->ln2_g, d->pre_ln ? nullptr : g_ln2_b, g_b2, ws);
+    if (dy_is_dr2 && !llama) colsum(dr2, H, g_b2, ws);
+  };
+  auto sums_of_du = [&] {
+    if (with_du) launch_colreduce_partials(dt, (T + DACT_SUM_ROWS - 1) / DACT_SUM_ROWS, F, F, pdu, gr->b1, acc, ws);
+    else if (!llama) colsum(du, F, gr->b1, ws);
+  };
+  auto sums_of_attention_output = [&] {
+    if (d->pre_ln) reduce_rows(1, gr->ln2_g, g_ln2_b, g_bo, ws);
+    else reduce_rows(1, gr->ln1_g, g_ln1_b, g_bo, ws);
+  };
+  if (together == APART) {
+    fork(0);
+    sums_of_ffn_output();
+  }
   dweight(H, F, dr2, g, gr->w2);
   if (llama) {
     // dG = dR2 W2, turned into the (gate, up) gradient pairs [T,2F] by the two saved factors in the epilogue
     launch_gemm(dt, GEMM_NN, EPI_DGATE, d->act, T, F, H, dr2, p->w2, du, nullptr, u, nullptr, st, solo);
-    fork(1);
-    dweight(2 * F, H, du, y1, gr->w1);
-    if (together == BLOCKS) dgrad_with_weights(H, 2 * F, du, p->w1, t0, nullptr);
-    else dgrad(EPI_NONE, H, 2 * F, du, p->w1, t0, nullptr);
   } else {
-    launch_gemm(dt, GEMM_NN, EPI_DACT, d->act, T, F, H, dr2, p->w2, du, nullptr, u, nullptr, st, solo);
-    fork(1);
-    if (dy_is_dr2 && together != APART) colsum(dr2, H, g_b2, ws);
-    colsum(du, F, gr->b1, ws);
-    dweight(F, H, du, y1, gr->w1);
-    if (together == BLOCKS) dgrad_with_weights(H, F, du, p->w1, t0, d->pre_ln ? nullptr : t0);
-    else if (r_y1) launch_gemm_ranges(dt, GEMM_NN, T, H, F, du, p->w1, gws, st);
-    else if (d->pre_ln) dgrad(EPI_NONE, H, F, du, p->w1, t0, nullptr);
-    else dgrad(EPI_ADD, H, F, du, p->w1, t0, t0);
+    launch_gemm(dt, GEMM_NN, EPI_DACT, d->act, T, F, H, dr2, p->w2, du, nullptr, u, with_du ? pdu : nullptr, st, solo);
   }
+  const int F1 = llama ? 2 * F : F;
+  fork(1);
+  if (together != APART) sums_of_ffn_output();
+  sums_of_du();
+  dweight(F1, H, du, y1, gr->w1);
+  if (together == BLOCKS) dgrad_with_weights(H, F1, du, p->w1, t0, d->pre_ln ? nullptr : t0);
+  else if (r_y1) launch_gemm_ranges(dt, GEMM_NN, T, H, F, du, p->w1, gws, st);
+  else dgrad(d->pre_ln ? EPI_NONE : EPI_ADD, H, F1, du, p->w1, t0, d->pre_ln ? nullptr : t0);
   // ---- attention block ----
-  if (d->pre_ln) {
-    row_bwd(r_y1, nullptr, z1, mu2, rstd2, p->ln2_g, dy, t2, dr1, dp0, 0);
-    reduce_rows(gr->ln2_g, g_ln2_b, g_bo);
-  } else {
-    row_bwd(r_y1, t0, z1, mu1, rstd1, p->ln1_g, nullptr, t2, dr1, dp0, 0);
-    reduce_rows(gr->ln1_g, g_ln1_b, g_bo);
+  if (d->pre_ln) row_bwd(r_y1, nullptr, z1, mu2, rstd2, p->ln2_g, dy, t2, dr1, dp0, 0, 1);
+  else row_bwd(r_y1, t0, z1, mu1, rstd1, p->ln1_g, nullptr, t2, dr1, dp0, 0, 1);
+  if (together == APART) {
+    fork(2);
+    sums_of_attention_output();
   }
-  fork(2);
   dweight(H, A, dr1, attn, gr->wo);
   dgrad(EPI_NONE, A, H, dr1, p->wo, t0, nullptr);
   as.beside = side && splitk_ws && together == APART;
   launch_attn_bwd(dt, as, qkv, seqlens, attn, t0, lse, delta, dqkv, st);
   fork(3);
-  if (!llama && together != APART) colsum(dqkv, 3 * A, gr->bqkv, ws);
+  if (together != APART) {
+    sums_of_attention_output();
+    if (!llama) colsum(dqkv, 3 * A, gr->bqkv, ws);
+  }
+  dweight(3 * A, H, dqkv, d->pre_ln ? sv + L.n1 : x, gr->wqkv);
   if (d->pre_ln) {
-    dweight(3 * A, H, dqkv, sv + L.n1, gr->wqkv);
     if (together != APART) dgrad_with_weights(H, 3 * A, dqkv, p->wqkv, t0, nullptr);
     else if (r_x) launch_gemm_ranges(dt, GEMM_NN, T, H, 3 * A, dqkv, p->wqkv, gws, st);
     else dgrad(EPI_NONE, H, 3 * A, dqkv, p->wqkv, t0, nullptr);
     if (link && link->dr2_below) {
       // (from the stored dx, so that the layer below sees what it would compute from dx itself, bit for bit)
-      row_bwd(r_x, nullptr, x, mu1, rstd1, p->ln1_g, t2, dx, link->dr2_below, link->dp_below, 1);
-      reduce_rows(gr->ln1_g, g_ln1_b, link->db2_below);
+      row_bwd(r_x, nullptr, x, mu1, rstd1, p->ln1_g, t2, dx, link->dr2_below, link->dp_below, 1, 2);
+      reduce_rows(2, gr->ln1_g, g_ln1_b, link->db2_below, st);
     } else {
-      row_bwd(r_x, nullptr, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, dp0, 0);
-      reduce_rows(gr->ln1_g, g_ln1_b, nullptr);
+      row_bwd(r_x, nullptr, x, mu1, rstd1, p->ln1_g, t2, dx, nullptr, dp0, 0, 2);
+      reduce_rows(2, gr->ln1_g, g_ln1_b, nullptr, st);
     }
   } else {
-    dweight(3 * A, H, dqkv, x, gr->wqkv);
     if (side && dx_on_x) side->order(side->join, ws, st);   // the helper stream has read x before dx is written there
     if (together != APART) dgrad_with_weights(H, 3 * A, dqkv, p->wqkv, dx, t2);
     else dgrad(EPI_ADD, H, 3 * A, dqkv, p->wqkv, dx, t2);
   }
-  // the last bias gradient goes behind the data gradient on the caller's stream: the helper stream's last
+  // apart, the last bias gradient goes behind the data gradient on the caller's stream: the helper stream's last
   // product is the longer one, and this way the two streams end at about the same time
   if (!llama && together == APART) colsum(dqkv, 3 * A, gr->bqkv, st);
   if (side) side->order(side->join, ws, st);   // join: the caller's stream continues only after the weight gradients are complete
@@ -903,7 +928,8 @@ static int gemm_entry(int dtype, int layout, int epilogue, int act, int64_t M, i
   // a workspace that is too small for what the shape can use is never half used: it is refused or left alone
   if (ws && ws_bytes < gemm_ws_least_bytes(dtype, layout, epilogue, (int)M, (int)N, (int)K)) return SLAPO_ERR_WORKSPACE;
   entry_error();
-  launch_gemm(dtype, layout, epilogue, act, (int)M, (int)N, (int)K, A, B, C, bias, aux_in, aux_out,
+  launch_gemm(dtype, layout, epilogue, act, (int)M, (int)N, (int)K, A, B, C, bias, aux_in,
+              epilogue == EPI_DACT ? nullptr : aux_out,   // (no output of this epilogue here)
               (hipStream_t)stream, solo, (float*)ws, ws ? ws_bytes : 0);
   return finish();
 }

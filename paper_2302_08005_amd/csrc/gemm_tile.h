@@ -90,6 +90,21 @@ __device__ __forceinline__ GateTerms gate_terms(float u, float w) {
   return g;
 }
 
+// Sum over the lanes whose number is the same modulo EVERY (4, 8 or 16), in all of them.
+template <int EVERY>
+__device__ __forceinline__ float sum_of_lanes(float x) {
+  auto rotated = [](float v, auto by) {   // within 16 lanes
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + decltype(by)::value, 0xf, 0xf, false));
+  };
+  if constexpr (EVERY <= 4) x += rotated(x, std::integral_constant<int, 4>{});
+  if constexpr (EVERY <= 8) x += rotated(x, std::integral_constant<int, 8>{});
+  const unsigned a = __builtin_bit_cast(unsigned, x);
+  const auto p = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+  const unsigned b = __builtin_bit_cast(unsigned, __builtin_bit_cast(float, (unsigned)p[0]) + __builtin_bit_cast(float, (unsigned)p[1]));
+  const auto q = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return __builtin_bit_cast(float, (unsigned)q[0]) + __builtin_bit_cast(float, (unsigned)q[1]);
+}
+
 // LDS layouts. Every tile sits in LDS unpadded and in memory order, 16 bytes of thread t of a slab at byte
 // 16 t of the stage, as the direct global -> LDS loads of gfx950 write it (one wave-level load fills 1 KB of
 // consecutive LDS, lane l at byte 16 l).
@@ -552,6 +567,9 @@ __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, c
 #pragma unroll
     for (int e = 0; e < 4; ++e) { u[2 * e] = unpack_lo<F16>(w[e]); u[2 * e + 1] = unpack_hi<F16>(w[e]); }
   };
+  // EPI_DACT: aux_out takes the column sums of every 32 rows of C, [M / 32 rounded up][N] floats (NULL: none), from which the bias
+  // gradient in front of the activation comes without another pass over C. The sums are of the unrounded values.
+  float* col_sums = EPI == EPI_DACT ? reinterpret_cast<float*>(aux_out) : nullptr;
   const bool aux_here = AUX && !is_tail && (!BY_AUX || aux_in != nullptr);   // (uniform)
   if (aux_here) aux_fetch(0, au[0]);
 #pragma unroll
@@ -564,6 +582,7 @@ __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, c
       for (int j = 0; j < TN; ++j)
         *reinterpret_cast<f32x4_t*>(stage + (h * 16 + (lane & 15)) * LDP + j * 16 + 4 * (lane >> 4)) = acc[2 * i + h][j];
     __builtin_amdgcn_wave_barrier();
+    float sums[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int pass = 0; pass < 32 / RPP; ++pass) {
       const int row = pass * RPP + rr;
@@ -609,6 +628,8 @@ __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, c
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] *= u[e];
           }
+#pragma unroll
+          for (int e = 0; e < 8; ++e) sums[e] += v[e];
         } else if (EPI == EPI_ADD) {
           if (!BY_AUX || aux_here) {
             float u[8];
@@ -654,6 +675,12 @@ __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, c
         }
         if (EPI != EPI_GATE && EPI != EPI_DGATE && EPI != EPI_SPLITK) store8h<F16>(C + idx, v);
       }
+    }
+    if (EPI == EPI_DACT && col_sums) {   // (uniform)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sums[e] = sum_of_lanes<CPR>(sums[e]);
+      const int first = m0 + wm0 + i * 32;
+      if (rr == 0 && first < M && n < N) store8(col_sums + (int64_t)(first / 32) * N + n, sums);
     }
   }
 }

@@ -12,12 +12,15 @@ bool debug_flag(const char* name);
 enum { GEMM_NT = 0, GEMM_NN = 1, GEMM_TN = 2 };
 // EPI_GATE: the product's columns are (gate, up) pairs; C [M,N/2] = silu(gate) * up, aux_out [M,N] = the pair
 //   (up * silu'(gate), silu(gate)), the two factors backward multiplies the gradient of C with.
+// EPI_DACT: C = acc * act'(aux_in); aux_out (16-bit storage; NULL: none) = column sums of every DACT_SUM_ROWS rows of C, as
+//   floats [M / DACT_SUM_ROWS rounded up][N], for launch_colreduce_partials.
 // EPI_DGATE: the product is that gradient [M,N]; C [M,2N] = (acc * aux_in[m,2n], acc * aux_in[m,2n+1]).
 // EPI_SPLITK (internal to the weight-gradient path): the workgroup covers one of `act` K ranges of its tile and
 //   writes the fp32 accumulators to aux_out (a float workspace [splits][M][N]); splitk_reduce sums them.
 // EPI_ROPE (internal to the gated layer's QKV projection): the first two thirds of the columns are heads whose adjacent
 //   pairs are turned by the angles of the row's position; bias = the (cos, sin) table (launch_rope_table), act = rope_act(...).
 enum { EPI_NONE = 0, EPI_BIAS = 1, EPI_BIAS_ACT = 2, EPI_DACT = 3, EPI_ADD = 4, EPI_GATE = 5, EPI_DGATE = 6, EPI_SPLITK = 7, EPI_ROPE = 8 };
+constexpr int DACT_SUM_ROWS = 32;
 inline int rope_act(int seq, int head_dim) { return 2 * seq + (head_dim == 128 ? 1 : 0); }
 
 // solo: nothing else runs beside this GEMM (it may then pick tiles by round count, see launch_bf16)

@@ -58,3 +58,19 @@ def test_gradients_of_each_block():
     assert err(x2, to_np(dx)) <= TOL[c.dtype]   # (the same sums in another order, rounded once more on the way)
     for k in W.PARAM_NAMES:
         assert err(layer.grads[k], to_np(want[k])) <= TOL[c.dtype], k
+
+
+# the first feed-forward bias's gradient: column sums that the product of the activation gradient leaves behind, by its tiles
+@pytest.mark.parametrize("hidden,heads,ffn,dtype,attn_dim,tile", [
+    (768, 1, 776, W.BF16, 64, "<1, 128, 128, 64, 2, 4, 1, 4,"), (768, 1, 1032, W.FP16, 64, "<1, 192, 128,"),
+    (768, 1, 1544, W.BF16, 64, "<1, 256, 128,"), (768, 1, 2056, W.BF16, 64, "<1, 192, 256,"),
+    (768, 1, 3080, W.FP16, 64, "<1, 256, 256,"), (1024, 16, 4104, W.BF16, 0, "quarters_kernel<1,")])
+def test_column_sums_of_the_activation_gradient(hidden, heads, ffn, dtype, attn_dim, tile):
+    c = cfg("sums", 3, 1391, hidden, heads, ffn, dtype, attn_dim=attn_dim)
+    T = c.batch * c.seq
+    assert tile in B.slapo_gemm_kernel_name(dtype, B.NN, B.EPI_DACT, T, ffn, hidden, flags=0 if "quarters" in tile else B.GEMM_SHARED)
+    errs, layer, (x, sl, dy, _, dx) = run_case(c, check_saved=False)
+    assert all(v <= TOL[dtype] for v in errs.values()), errs
+    grids = launches(layer, x, dy, dx)
+    assert ((ffn + 255) // 256, 64, 1) not in grids                                       # no pass over that array ...
+    assert ((3 * (attn_dim or hidden) + 255) // 256, 64, 1) in grids                      # ... as there is over the gradient of QKV
