@@ -223,14 +223,15 @@ bool gradients_paired(const slapo_layer_desc* d) {
 // of each block with the gradient of the block's input (BLOCKS). Decided by what either form takes in slabs of such a tile
 // (products_slabs), against the work itself. Where the gradient of the second feed-forward weight alone has tiles for three
 // quarters of the chip, two streams run the same large tiles and fill each other's thin rounds: only nearly full launches beat
-// them, by 0 to 5 %. Elsewhere they run 128x128 ones, at 1.3 times the work, and pay about 22 slabs for forks and launches.
-// BLOCKS are the better form at equal slabs (by 4 % of them: fewer tiles drift apart). Backward, us, two streams / together:
-//   hidden 1024, tokens 1500 157 / 176 (apart), 2000 196 / 189, 3000 251 / 225, 4000 315 / 287, 8000 597 / 514, 16000 1067 / 926
-//   hidden 1536, 2000 337 / 335, 4000 587 / 560 (BLOCKS), 8000 1092 / 1003, 16000 2212 / 1853
+// them, by 0 to 5 %. Elsewhere they run 128x128 ones, at 1.3 times the work, and pay about 22 slabs for forks and launches. The gated
+// layer gains less (it has no sums that would leave the chain, and wide products, which two streams overlap well): nearer lines.
+// BLOCKS are the better form at equal slabs (fewer tiles drift apart). Backward, us, two streams / together:
+//   hidden 1024, tokens 1500 157 / 176 (apart), 2000 196 / 173, 3000 251 / 212, 4000 315 / 271, 8000 597 / 494, 16000 1067 / 926
+//   hidden 1536, 2000 337 / 314, 4000 587 / 536, 8000 1092 / 976, 16000 2212 / 1842
 //   hidden 768, 2000 136 / 150, 4000 239 / 225, 8000 424 / 433, 16000 733 / 771; 512, 8000 245 / 292 (all apart)
-//   hidden 2048, 4000 829 / 810, 12000 2275 / 2219; 2560, 2000 690 / 714 (apart), 8000 2372 / 2272; 3072, 4096 1663 / 1766 (BEHIND), 1662 (BLOCKS)
-//   gated, hidden 2048, FFN 5504, 2000 519 / 481, 4000 890 / 857; 4096, attention 2048, FFN 5504, 4096 1424 / 1464 (apart); 4096, 512, 1376,
-//   4096 527 / 489; 4096, FFN 11008, 4000 2733 / 2689
+//   hidden 2048, 4000 820 / 781; 2560, 2000 690 / 714 (apart), 6000 1717 / 1704; 3072, 2048 884 / 895 (apart), 4096 1632 / 1610
+//   gated, hidden 1152, FFN 3072, 2400 (a step) 388 / 391 (apart); 1536, 4096, 2700 587 / 597 (apart); 2048, 5504, 4000 883 / 823; 4096, attention
+//   2048, FFN 5504, 4096 1410 / 1471 (apart); 4096, attention 512, FFN 1376, 4096 527 / 497; 4096, FFN 11008, 4096 (a step) 4176 / 4103
 enum Together { APART, BEHIND, BLOCKS };
 Together products_together(const slapo_layer_desc* d) {
   if (d->dtype == SLAPO_FP32) return APART;
@@ -242,10 +243,10 @@ Together products_together(const slapo_layer_desc* d) {
   int64_t total = 0, ignored = 0;
   const int in_blocks = products_slabs(3, first, &total) + products_slabs(3, second, &total);
   const int at_end = products_slabs(5, behind, &ignored) + gemm_slabs(GEMM_NN, T, H, F1);
-  const bool blocks = in_blocks <= 1.04 * at_end;
+  const bool blocks = in_blocks <= 1.02 * at_end;
   const double slabs = blocks ? in_blocks : at_end, work = (double)total / 256.0;
   const bool large_alone = (int64_t)((H + 255) / 256) * ((F + 255) / 256) >= 192;
-  if (slabs > (large_alone ? 1.065 * work : 1.3 * work + 22.0)) return APART;
+  if (slabs > (large_alone ? (is_llama(d) ? 1.025 : 1.06) * work : is_llama(d) ? 1.2 * work + 4.0 : 1.3 * work + 22.0)) return APART;
   return blocks ? BLOCKS : BEHIND;
 }
 
@@ -709,8 +710,8 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   }
 
   // ---- FFN block ----
-  // The sums over partial rows and the bias gradients leave the chain with the next fork: of every weight gradient, or of the two
-  // beside products that share launches (one, in front of the last launch, takes as long).
+  // The bias gradients leave the chain with the next fork: of every weight gradient, or of the two beside products that share
+  // launches, and there the sums over partial rows too (one fork, in front of the last launch, takes as long).
   const void* dr2 = t1;
   bool rows2 = true;   // the first row kernel has left partial rows
   if (dy_is_dr2) {
@@ -727,8 +728,11 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   }
   const bool with_du = sums_with_du(d);
   float* pdu = (float*)(sc + W.part_du);
+  hipStream_t rs = together != APART ? ws : st;   // (apart, the helper stream is the longer one where tokens are few)
+  auto sums_of_ffn_rows = [&] {
+    if (rows2) reduce_rows(0, d->pre_ln ? nullptr : gr->ln2_g, d->pre_ln ? nullptr : g_ln2_b, g_b2, rs);
+  };
   auto sums_of_ffn_output = [&] {
-    if (rows2) reduce_rows(0, d->pre_ln ? nullptr : gr->ln2_g, d->pre_ln ? nullptr : g_ln2_b, g_b2, ws);
     if (dy_is_dr2 && !llama) colsum(dr2, H, g_b2, ws);
   };
   auto sums_of_du = [&] {
@@ -736,10 +740,11 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     else if (!llama) colsum(du, F, gr->b1, ws);
   };
   auto sums_of_attention_output = [&] {
-    if (d->pre_ln) reduce_rows(1, gr->ln2_g, g_ln2_b, g_bo, ws);
-    else reduce_rows(1, gr->ln1_g, g_ln1_b, g_bo, ws);
+    if (d->pre_ln) reduce_rows(1, gr->ln2_g, g_ln2_b, g_bo, rs);
+    else reduce_rows(1, gr->ln1_g, g_ln1_b, g_bo, rs);
   };
   if (together == APART) {
+    sums_of_ffn_rows();
     fork(0);
     sums_of_ffn_output();
   }
@@ -752,7 +757,10 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   }
   const int F1 = llama ? 2 * F : F;
   fork(1);
-  if (together != APART) sums_of_ffn_output();
+  if (together != APART) {
+    sums_of_ffn_rows();
+    sums_of_ffn_output();
+  }
   sums_of_du();
   dweight(F1, H, du, y1, gr->w1);
   if (together == BLOCKS) dgrad_with_weights(H, F1, du, p->w1, t0, d->pre_ln ? nullptr : t0);
@@ -762,8 +770,8 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   if (d->pre_ln) row_bwd(r_y1, nullptr, z1, mu2, rstd2, p->ln2_g, dy, t2, dr1, dp0, 0, 1);
   else row_bwd(r_y1, t0, z1, mu1, rstd1, p->ln1_g, nullptr, t2, dr1, dp0, 0, 1);
   if (together == APART) {
-    fork(2);
     sums_of_attention_output();
+    fork(2);
   }
   dweight(H, A, dr1, attn, gr->wo);
   dgrad(EPI_NONE, A, H, dr1, p->wo, t0, nullptr);

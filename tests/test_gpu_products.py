@@ -20,19 +20,27 @@ def tiles(*products):
     return sum(((m + 255) // 256) * ((n + 255) // 256) for m, n in products)
 
 
+def with_quarters(whole, cut):
+    """The grid of a launch of `whole` tiles, `cut` of them in quarters."""
+    return whole - cut + (cut + 7) // 8 * 32, 1, 1
+
+
 def launches(layer, x, dy, dx):
     return captured(lambda: B.slapo_layer_bwd(layer.desc, layer.params, x, None, dy, layer.saved, dx, layer.grads, layer.scratch), grids=True)
 
 
-# the input gradient and all weight gradients behind attention
-@pytest.mark.parametrize("c", [
-    cfg("postln-ragged", 4, 525, 1024, 16, 4104, len_lo=100, len_hi=525),
-    cfg("gated-half-ragged", 3, 700, 1024, 8, 2728, W.FP16, causal=1, pre_ln=1, dropout_p=0.0, ln_eps=1e-6, arch=W.LLAMA)], ids=lambda c: c.name)
-def test_gradients_behind_attention(c):
+# the input gradient and all weight gradients behind attention; `cut`: tiles in quarters, of weight gradients, or of the input gradient
+# where that is the shortest (its K, 1344, is no multiple of a quarter's slabs)
+@pytest.mark.parametrize("c,cut", [
+    (cfg("postln-ragged", 4, 525, 1024, 16, 4104, len_lo=100, len_hi=525), 0),
+    (cfg("gated-half-ragged", 4, 775, 1024, 8, 2728, W.FP16, causal=1, pre_ln=1, dropout_p=0.0, ln_eps=1e-6, arch=W.LLAMA), 0),
+    (cfg("weights-in-quarters-half", 4, 525, 1024, 16, 6152, W.FP16), 44),
+    (cfg("input-in-quarters", 4, 650, 1536, 7, 4104, attn_dim=448, causal=1, pre_ln=1), 58)], ids=lambda v: getattr(v, "name", v))
+def test_gradients_behind_attention(c, cut):
     errs, layer, (x, sl, dy, _, dx) = (run_gated if c.arch == W.LLAMA else run_case)(c, check_saved=False)
     assert all(v <= TOL[c.dtype] for v in errs.values()), errs
-    T, H, F, F1 = c.batch * c.seq, c.hidden, c.ffn, c.ffn * (2 if c.arch == W.LLAMA else 1)
-    assert launches(layer, x, dy, dx).count((tiles((T, H), (H, F), (F1, H), (H, H), (3 * H, H)), 1, 1)) == 1
+    T, H, F, F1, A = c.batch * c.seq, c.hidden, c.ffn, c.ffn * (2 if c.arch == W.LLAMA else 1), c.attn_dim or c.hidden
+    assert launches(layer, x, dy, dx).count(with_quarters(tiles((T, H), (H, F), (F1, H), (H, A), (3 * A, H)), cut)) == 1
     first, dx = {k: v.clone() for k, v in layer.grads.items()}, dx.clone()
     layer.desc.accumulate_grads = 1
     assert torch.equal(layer.backward(x, sl, dy), dx)
@@ -42,15 +50,15 @@ def test_gradients_behind_attention(c):
 
 # each block's with the gradient of its input
 def test_gradients_of_each_block():
-    c = cfg("blocks", 4, 1000, 1536, 24, 6152)
-    layer, T, H, F = B.Layer(c, W.make_params(c)), 4000, 1536, 6152
+    c = cfg("blocks", 4, 750, 1536, 16, 4104, attn_dim=1024)
+    layer, T, H, F, A = B.Layer(c, W.make_params(c)), 3000, 1536, 4104, 1024
     gen = torch.Generator(device=DEV).manual_seed(9)
     x, dy = (torch.randn(c.batch, c.seq, H, device=DEV, generator=gen).to(layer.dt) for _ in range(2))
     layer.forward(x)
     dx = layer.backward(x, None, dy)
     want = {k: v.clone() for k, v in layer.grads.items()}
     grids = launches(layer, x, dy, dx)
-    assert (tiles((T, H), (H, F), (F, H)), 1, 1) in grids and (tiles((T, H), (H, H), (3 * H, H)), 1, 1) in grids
+    assert with_quarters(tiles((T, H), (H, F), (F, H)), 20) in grids and with_quarters(tiles((T, H), (H, A), (3 * A, H)), 0) in grids
     x2 = x.clone()   # dx on top of x: a launch for each
     assert len(launches(layer, x2, dy, x2)) > len(grids)
     B.slapo_layer_bwd(layer.desc, layer.params, x2, None, dy, layer.saved, x2, layer.grads, layer.scratch)
