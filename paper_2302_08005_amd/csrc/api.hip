@@ -223,15 +223,17 @@ bool gradients_paired(const slapo_layer_desc* d) {
 // of each block with the gradient of the block's input (BLOCKS). Decided by what either form takes in slabs of such a tile
 // (products_slabs), against the work itself. Where the gradient of the second feed-forward weight alone has tiles for three
 // quarters of the chip, two streams run the same large tiles and fill each other's thin rounds: only nearly full launches beat
-// them, by 0 to 5 %. Elsewhere they run 128x128 ones, at 1.3 times the work, and pay about 22 slabs for forks and launches. The gated
-// layer gains less (it has no sums that would leave the chain, and wide products, which two streams overlap well): nearer lines.
-// BLOCKS are the better form at equal slabs (fewer tiles drift apart). Backward, us, two streams / together:
-//   hidden 1024, tokens 1500 157 / 176 (apart), 2000 196 / 173, 3000 251 / 212, 4000 315 / 271, 8000 597 / 494, 16000 1067 / 926
-//   hidden 1536, 2000 337 / 314, 4000 587 / 536, 8000 1092 / 976, 16000 2212 / 1842
-//   hidden 768, 2000 136 / 150, 4000 239 / 225, 8000 424 / 433, 16000 733 / 771; 512, 8000 245 / 292 (all apart)
+// them, by 0 to 5 %. Elsewhere they run 128x128 ones, at 1.3 times the work, and pay about 28 slabs for forks and launches. From
+// 150 slabs of work on that counts for nothing beside what a half-empty round costs. The gated layer gains less (it has no sums that would
+// leave the chain, and wide products, which two streams overlap well): nearer lines, and only what the tiles save from 90 slabs on. BLOCKS are the better form at equal slabs (fewer tiles drift apart).
+// Backward, us, apart / together:
+//   hidden 640, tokens 5700 246 / 237 (apart); 832, FFN 3328, 13468 665 / 704 (apart); 1152, 4608, 6288 569 / 588 (apart); 768, 1900 133 / 134 (apart), 2280 147 / 138, 3800 226 / 191, 5700 296 / 302, 16000 733 / 771 (both apart)
+//   hidden 896, 1520 134 / 139 (apart), 1900 163 / 146; 1024, 1520 156 / 157 (apart), 1900 185 / 165, 3800 285 / 248, 8000 597 / 494
+//   hidden 1280, 1140 171 / 185 (apart), 1520 215 / 192, 5700 602 / 553; 1536, 4000 587 / 536, 16000 2212 / 1842; 512, 8000 245 / 292 (apart)
 //   hidden 2048, 4000 820 / 781; 2560, 2000 690 / 714 (apart), 6000 1717 / 1704; 3072, 2048 884 / 895 (apart), 4096 1632 / 1610
-//   gated, hidden 1152, FFN 3072, 2400 (a step) 388 / 391 (apart); 1536, 4096, 2700 587 / 597 (apart); 2048, 5504, 4000 883 / 823; 4096, attention
-//   2048, FFN 5504, 4096 1410 / 1471 (apart); 4096, attention 512, FFN 1376, 4096 527 / 497; 4096, FFN 11008, 4096 (a step) 4176 / 4103
+//   gated, hidden 768, 2500 161 / 153 (apart); 1024, FFN 2736, 2000 188 / 177 (apart), 2500 204 / 194, 4000 297 / 265; 1536, 4096, 2500 354 / 363,
+//   3000 413 / 411 (both apart), 4000 517 / 503; 2048, 5504, 1500 387 / 401 (apart), 2000 492 / 457, 4000 869 / 808; 4096, attention 2048, FFN
+//   5504, 4096 1410 / 1471 (apart); 4096, attention 512, FFN 1376, 4096 527 / 497; 4096, FFN 11008, 4096 (a step) 4176 / 4103
 enum Together { APART, BEHIND, BLOCKS };
 Together products_together(const slapo_layer_desc* d) {
   if (d->dtype == SLAPO_FP32) return APART;
@@ -246,7 +248,9 @@ Together products_together(const slapo_layer_desc* d) {
   const bool blocks = in_blocks <= 1.02 * at_end;
   const double slabs = blocks ? in_blocks : at_end, work = (double)total / 256.0;
   const bool large_alone = (int64_t)((H + 255) / 256) * ((F + 255) / 256) >= 192;
-  if (slabs > (large_alone ? (is_llama(d) ? 1.025 : 1.06) * work : is_llama(d) ? 1.2 * work + 4.0 : 1.3 * work + 22.0)) return APART;
+  const double line = is_llama(d) ? (large_alone ? 1.025 * work : work < 90.0 ? work + 27.0 : 1.13 * work)
+                                  : (large_alone ? 1.05 * work : work < 150.0 ? 1.3 * work + 28.0 : 1.22 * work);
+  if (slabs > line) return APART;
   return blocks ? BLOCKS : BEHIND;
 }
 

@@ -102,14 +102,15 @@ int slabs_of_launch(int n, const Product* p, int quarters, int* last) {
   return end;
 }
 
-// Quarters for the tiles that end with the launch if it then ends earlier, and they are at most a quarter of a round: more of
-// them run at a higher clock as they are (400 tiles of 8192 tokens, hidden 2560, whole / the last 144 in quarters: 340 / 379 us).
+// Quarters for the tiles that end with the launch if it then ends earlier, and they are at most an eighth of a round: more of
+// them run at a higher clock as they are (400 tiles of 8192 tokens, hidden 2560, whole / the last 144 in quarters: 340 / 379 us; a
+// decoder of 3696 tokens, hidden 3712, apart / a launch per block with the last 53 in quarters: 2845 / 2918).
 struct ProductPlan { int quarters, slabs; };
 ProductPlan plan_of(int n, const Product* p) {
   int last = 0, ignored = 0;
   const int whole = slabs_of_launch(n, p, 0, &last);
   last = std::min(last, tiles_of(p[n - 1]));
-  if (last > CUS / 4) return {0, whole};
+  if (last > CUS / 8) return {0, whole};
   const int cut = slabs_of_launch(n, p, last, &ignored);
   return cut < whole ? ProductPlan{last, cut} : ProductPlan{0, whole};
 }

@@ -30,12 +30,12 @@ def launches(layer, x, dy, dx):
 
 
 # the input gradient and all weight gradients behind attention; `cut`: tiles in quarters, of weight gradients, or of the input gradient
-# where that is the shortest (its K, 1344, is no multiple of a quarter's slabs)
+# where that is the shortest (its K, 960, is no multiple of a quarter's slabs)
 @pytest.mark.parametrize("c,cut", [
     (cfg("postln-ragged", 4, 525, 1024, 16, 4104, len_lo=100, len_hi=525), 0),
     (cfg("gated-half-ragged", 4, 775, 1024, 8, 2728, W.FP16, causal=1, pre_ln=1, dropout_p=0.0, ln_eps=1e-6, arch=W.LLAMA), 0),
-    (cfg("weights-in-quarters-half", 4, 525, 1024, 16, 6152, W.FP16), 44),
-    (cfg("input-in-quarters", 4, 650, 1536, 7, 4104, attn_dim=448, causal=1, pre_ln=1), 58)], ids=lambda v: getattr(v, "name", v))
+    (cfg("weights-in-quarters-half", 4, 500, 1536, 24, 6152, W.FP16), 28),
+    (cfg("input-in-quarters", 4, 650, 1536, 5, 4104, attn_dim=320, causal=1, pre_ln=1), 18)], ids=lambda v: getattr(v, "name", v))
 def test_gradients_behind_attention(c, cut):
     errs, layer, (x, sl, dy, _, dx) = (run_gated if c.arch == W.LLAMA else run_case)(c, check_saved=False)
     assert all(v <= TOL[c.dtype] for v in errs.values()), errs
