@@ -114,7 +114,7 @@ static void launch_bf16_tile(int epi, int act, int M, int N, int K, const void* 
 // computing wavefronts instead of four: nothing or 1-3 % more). K needs no particular multiple: TN products with K = 2286 tokens and 768 x 3072 outputs take 18.7 us
 // (41.7 with the register-staged kernel that such K used to go to), K = 2000 and 10240 x 2560 take 107 us (170 before).
 enum TileKind { TILE_256, TILE_128_SPLITSLAB, TILE_128_LOADERS, TILE_128x64_LOADERS, TILE_64_LOADERS, TILE_192x128_LOADERS, TILE_256x128_LOADERS,
-                TILE_192x256, TILE_NONE };
+                TILE_192x256, TILE_64x32_LOADERS, TILE_NONE };
 
 // Products that one size of tile would finish in a round and a bit: the smallest tile that makes it exactly one round (one
 // workgroup per CU). 192x128 and 256x128 as the 128x128 form (eight computing wavefronts, four loaders, three stages), 192x256 as the
@@ -141,6 +141,16 @@ bool gemm_in_one_round(int dtype, int layout, int M, int N, int K) {
   return dtype != DT_FP32 && one_round_tile(layout, M, N, K) != TILE_NONE;
 }
 
+// 64x32 tiles (four stages of 128-deep slabs) where 64x64 ones take at most half of the CUs: three quarters of the bytes per CU and slab.
+// Layout NT (rows of an operand that is not contiguous along K are 64 elements at least). us, 64x64 / 64x32, operands from memory:
+//   128 x 3072 x 1024 5.78 / 5.08, 128 x 4096 x 1024 with GeLU 6.53 / 5.67, 128 x 2304 x 768 5.29 / 4.62, 256 x 2048 x 512 with GeLU 5.27 / 4.69;
+//   more than 256 of them: 256 x 4096 x 1024 7.14 / 9.86, 128 x 6144 x 2048 12.2 / 16.6
+// Products of at most 32 tiles of 64x64 keep those (128 x 768 x 768 4.99 / 4.31): callers of the exported product are told so.
+static bool many_64x32(int M, int N) {
+  const int64_t rows = (M + 63) / 64;
+  return rows * ((N + 63) / 64) > 32 && rows * ((N + 31) / 32) <= 256;
+}
+
 static TileKind tile_by_count(int layout, int M, int N, int K, bool solo) {
   const int64_t t256 = (int64_t)((M + 255) / 256) * ((N + 255) / 256);
   const int64_t t128 = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
@@ -165,7 +175,10 @@ static TileKind tile_by_count(int layout, int M, int N, int K, bool solo) {
   // Two rounds of 128x64 tiles are slower than one of 128x128 (768 x 3072 outputs, K = 2286: 26.8 against 18.7 us), one
   // round is faster (2304 x 768: 14.9 against 17.4).
   const int64_t t128x64 = (int64_t)((M + 127) / 128) * ((N + 63) / 64);
-  if (t128x64 <= 256) return t128x64 <= 128 && layout != GEMM_TN && K >= 256 ? TILE_64_LOADERS : TILE_128x64_LOADERS;
+  if (t128x64 <= 256) {
+    if (t128x64 > 128 || layout == GEMM_TN || K < 256) return TILE_128x64_LOADERS;
+    return layout == GEMM_NT && many_64x32(M, N) ? TILE_64x32_LOADERS : TILE_64_LOADERS;
+  }
   return layout == GEMM_TN && K > 1024 ? TILE_128_SPLITSLAB : TILE_128_LOADERS;
 }
 
@@ -201,7 +214,7 @@ static HybridPlan hybrid_plan(int layout, int epi, int M, int N, int K) {
   static const bool disabled = debug_flag("no-hybrid");
   if (disabled || (epi != EPI_NONE && epi != EPI_ADD)) return none;
   p.tile = tile_by_count(layout, M, N, K, false);
-  if (p.tile == TILE_64_LOADERS) p.tile = TILE_128x64_LOADERS;   // (K ranges bring the workgroups that the smaller tiles would)
+  if (p.tile == TILE_64_LOADERS || p.tile == TILE_64x32_LOADERS) p.tile = TILE_128x64_LOADERS;   // (K ranges bring the workgroups that the smaller tiles would)
   if (layout == GEMM_TN && p.tile != TILE_256) return none;   // (K ranges of their own: weight_grad_splits)
   const int bm = p.tile == TILE_256 ? 256 : 128, bn = p.tile == TILE_256 ? 256 : p.tile == TILE_128x64_LOADERS ? 64 : 128;
   const int tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
@@ -391,6 +404,9 @@ static void launch_bf16(int epi, int act, int M, int N, int K, const void* A, co
       if constexpr (LAYOUT != GEMM_TN) launch_bf16_tile<LAYOUT, 192, 256, 2, 4, 1, 2, 0, F16>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
       break;
     case TILE_NONE: break;
+    case TILE_64x32_LOADERS:
+      if constexpr (LAYOUT == GEMM_NT) launch_bf16_tile<LAYOUT, 64, 32, 2, 2, 1, 4, 4, F16, false, 128>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
+      break;
     case TILE_64_LOADERS:
       if constexpr (LAYOUT != GEMM_TN) launch_bf16_tile<LAYOUT, 64, 64, 2, 2, 1, 3, 4, F16, false, 128>(epi, act, M, N, K, A, B, C, bias, aux_in, aux_out, st);
       break;
@@ -511,17 +527,29 @@ bool product_in_ranges(int dtype, int M, int N, int K) {
   return (tiles <= 32 && K >= 2048) || (tiles <= 64 && K >= 6144);
 }
 
-template <int LAYOUT, bool F16>
-static void launch_ranges(int M, int N, int K, const void* A, const void* B, float* parts, hipStream_t st) {
-  constexpr int BK = 128, NS = 3;
-  const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
-  const size_t lds = gemm_lds_bytes<64, 64, BK, 2, 2, 1, NS>();
-  auto kern = K % BK == 0 ? gemm_bf16_kernel<LAYOUT, 64, 64, BK, 2, 2, 1, NS, 4, false, EPI_SPLITK, F16>
-                          : gemm_bf16_kernel<LAYOUT, 64, 64, BK, 2, 2, 1, NS, 4, true, EPI_SPLITK, F16>;
+template <int LAYOUT, int BN, int NS, bool F16>
+static void launch_ranges_tile(int M, int N, int K, const void* A, const void* B, float* parts, hipStream_t st) {
+  constexpr int BK = 128;
+  const int tiles = ((M + 63) / 64) * ((N + BN - 1) / BN);
+  const size_t lds = gemm_lds_bytes<64, BN, BK, 2, 2, 1, NS>();
+  auto kern = K % BK == 0 ? gemm_bf16_kernel<LAYOUT, 64, BN, BK, 2, 2, 1, NS, 4, false, EPI_SPLITK, F16>
+                          : gemm_bf16_kernel<LAYOUT, 64, BN, BK, 2, 2, 1, NS, 4, true, EPI_SPLITK, F16>;
   (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(kern, dim3(tiles * K_RANGES), dim3((2 * 2 + 4) * 64), lds, st, M, N, K, (const bf16_t*)A, (const bf16_t*)B,
                      (bf16_t*)nullptr, (const bf16_t*)nullptr, (const bf16_t*)nullptr, reinterpret_cast<bf16_t*>(parts), K_RANGES,
                      tiles * K_RANGES, 1, (float*)nullptr);
+}
+
+// (64x32 tiles in layout NT where all ranges of them fit one round, as for whole products)
+template <int LAYOUT, bool F16>
+static void launch_ranges(int M, int N, int K, const void* A, const void* B, float* parts, hipStream_t st) {
+  if constexpr (LAYOUT == GEMM_NT) {
+    if (((M + 63) / 64) * ((N + 31) / 32) * K_RANGES <= 256) {
+      launch_ranges_tile<LAYOUT, 32, 4, F16>(M, N, K, A, B, parts, st);
+      return;
+    }
+  }
+  launch_ranges_tile<LAYOUT, 64, 3, F16>(M, N, K, A, B, parts, st);
 }
 
 void launch_gemm_ranges(int dtype, int layout, int M, int N, int K, const void* A, const void* B, float* parts, hipStream_t st) {
@@ -557,7 +585,7 @@ void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool sol
   const char* kt = layout != GEMM_TN && K % 64 != 0 ? "true" : "false";
   static const char* const shape[] = {"256, 256, 64, 2, 4, 1, 2, 0", "128, 128, 64, 2, 2, 2, 4, 4", "128, 128, 64, 2, 4, 1, 4, 4",
                                       "128, 64, 64, 2, 2, 1, 4, 4", "64, 64, 128, 2, 2, 1, 3, 4", "192, 128, 64, 2, 4, 1, 3, 4",
-                                      "256, 128, 64, 2, 4, 1, 3, 4", "192, 256, 64, 2, 4, 1, 2, 0"};
+                                      "256, 128, 64, 2, 4, 1, 3, 4", "192, 256, 64, 2, 4, 1, 2, 0", "64, 32, 128, 2, 2, 1, 4, 4"};
   if (with_ws && !(weight_grad && weight_grad_splits(M, N, K) > 1)) {
     const HybridPlan hp = hybrid_plan(layout, weight_grad ? EPI_NONE : epi, M, N, K);
     if (hp.ws_bytes) {
@@ -582,7 +610,7 @@ void describe_gemm(int dtype, int layout, int epi, int M, int N, int K, bool sol
     snprintf(buf, len, "gemm_bf16_kernel<%d, 128, 128, 64, 2, 4, 1, 2, 4, %s, %d, %s, false>", layout, kt, epi, b);
     return;
   }
-  if (k == TILE_64_LOADERS) kt = K % 128 != 0 ? "true" : "false";
+  if (k == TILE_64_LOADERS || k == TILE_64x32_LOADERS) kt = K % 128 != 0 ? "true" : "false";
   snprintf(buf, len, "gemm_bf16_kernel<%d, %s, %s, %d, %s, false>", layout, shape[(int)k], kt, epi, b);
 }
 

@@ -196,6 +196,7 @@ __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, c
   static_assert(A_LOADS >= 1 && B_LOADS >= 1, "tile too small for the thread count");
   static_assert(BK == 64 || BK == 128, "swizzles and fragment addresses written for 128- and 256-byte tile rows");
   static_assert(TM % 2 == 0, "tile rows are multiplied in pairs");
+  static_assert((A_KC || BM >= 64) && (B_KC || BN >= 64), "at least four 32-byte granules per row of an M-contiguous tile");
   static_assert(NS >= 2 && NS <= 10, "stage count");
   constexpr int PA = A_KC ? BK : BM;        // row pitch of the A tile in elements (unpadded)
   constexpr int PB = B_KC ? BK : BN;
@@ -203,7 +204,6 @@ __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, c
   auto swzK = [](int row) { return BK == 64 ? (row / 2) % 8 : row % 16; };
   auto swzM = [](int krow, auto width) {
     constexpr int W = decltype(width)::value;
-    static_assert(W >= 64, "at least four 32-byte granules per tile row");
     constexpr int RPM = W >= 128 ? 1 : 128 / W;   // k-rows per 256 bytes of LDS
     const int q = krow / RPM;
     // One transposing read covers, per group of 32 lanes, one granule of k-rows r..r+3 and r+8..r+11: eight 32-byte

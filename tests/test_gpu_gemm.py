@@ -453,3 +453,37 @@ def test_epilogues_of_one_round_tiles(M, N, name, layout, dtype):
             errs.update({"add": err(run(B.EPI_ADD, aux_in=aux1), acc + aux[:, :N]), "dgelu": err(run(B.EPI_DACT, aux_in=aux1), acc * aux[:, :N]),
                          "dgate": err(run(B.EPI_DGATE, width=2 * N, aux_in=to_dev(aux, dtype)), np.repeat(acc, 2, 1) * aux)})
         assert all(v <= {W.BF16: 4e-3, W.FP16: 5e-4}[dtype] for v in errs.values()), (K, errs)
+
+
+# 64x32 tiles: from 33 tiles of 64x64 to 256 of 64x32; ragged edges, partial slabs, one slab count more and less than the stages
+@pytest.mark.parametrize("M,N", [(64, 2056), (65, 1032), (129, 2608), (256, 2048)])
+def test_gemm_64x32_tiles(M, N):
+    Ks = (256, 264, 376, 504, 640, 1016)
+    for K in Ks:
+        assert "64, 32, 128, 2, 2, 1, 4, 4, " + ("false" if K % 128 == 0 else "true") in B.slapo_gemm_kernel_name(W.BF16, B.NT, B.EPI_NONE, M, N, K)
+    for M_, N_ in ((64, 2048), (257, 2048)):
+        assert "64, 32, " not in B.slapo_gemm_kernel_name(W.BF16, B.NT, B.EPI_NONE, M_, N_, 256)
+    test_gemm_partial_last_slab(B.NT, Ks, M, N)
+
+
+@pytest.mark.parametrize("dtype", [W.BF16, W.FP16])
+def test_epilogues_of_64x32_tiles(dtype):
+    """The bound of test_epilogues_of_every_tile_form, in the products that have these tiles."""
+    M, N = 130, 1040
+    for K in (256, 328):
+        rng = np.random.default_rng(K)
+        a, b, bias = store(rng.standard_normal((M, K)), dtype), store(rng.standard_normal((K, N)) * K ** -0.5, dtype), store(rng.standard_normal(N), dtype)
+        acc = a.astype(np.float64) @ b.astype(np.float64)
+        A, Bm, keep = to_dev(a, dtype), to_dev(b.T.copy(), dtype), torch.empty(M, N, dtype=to_dev(a, dtype).dtype, device=DEV)
+
+        def run(epi, act=W.GELU, width=N, aux_out=None):
+            assert "64, 32, 128" in B.slapo_gemm_kernel_name(dtype, B.NT, epi, M, N, K)
+            out = torch.full((M, width), 7.0, dtype=A.dtype, device=DEV)
+            B.slapo_gemm(dtype, B.NT, epi, act, M, N, K, A, Bm, out, bias=to_dev(bias, dtype), aux_out=aux_out)
+            return out
+
+        gate, up = acc[:, ::2], acc[:, 1::2]
+        errs = {"bias": err(run(B.EPI_BIAS), acc + bias), "gelu": err(run(B.EPI_BIAS_ACT, aux_out=keep), _act(acc + bias, W.GELU))}
+        errs["gelu'"] = err(keep, _dact(acc + bias, W.GELU))
+        errs["gate"] = err(run(B.EPI_GATE, width=N // 2, aux_out=keep), gate / (1 + np.exp(-gate)) * up)
+        assert all(v <= {W.BF16: 4e-3, W.FP16: 5e-4}[dtype] for v in errs.values()), (K, errs)
