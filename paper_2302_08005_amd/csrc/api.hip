@@ -250,7 +250,7 @@ Together products_together(const slapo_layer_desc* d) {
   const bool large_alone = (int64_t)((H + 255) / 256) * ((F + 255) / 256) >= 192;
   const double line = is_llama(d) ? (large_alone ? 1.025 * work : work < 90.0 ? work + 27.0 : 1.13 * work)
                                   : (large_alone ? 1.05 * work : work < 150.0 ? 1.3 * work + 28.0 : 1.22 * work);
-  if (slabs > line) return APART;
+  if (slabs > line || slabs > 2.25 * work) return APART;   // (not where the tiles of all products together leave most of the chip idle)
   return blocks ? BLOCKS : BEHIND;
 }
 
@@ -732,7 +732,9 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   }
   const bool with_du = sums_with_du(d);
   float* pdu = (float*)(sc + W.part_du);
-  hipStream_t rs = together != APART ? ws : st;   // (apart, the helper stream is the longer one where tokens are few)
+  // (apart, the helper stream is the longer one where tokens are few: gated, hidden 2688, 992 tokens 1362 / 1395 us with them there)
+  const bool rows_aside = together != APART || T >= 1536;
+  hipStream_t rs = rows_aside ? ws : st;
   auto sums_of_ffn_rows = [&] {
     if (rows2) reduce_rows(0, d->pre_ln ? nullptr : gr->ln2_g, d->pre_ln ? nullptr : g_ln2_b, g_b2, rs);
   };
@@ -748,8 +750,9 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     else reduce_rows(1, gr->ln1_g, g_ln1_b, g_bo, rs);
   };
   if (together == APART) {
-    sums_of_ffn_rows();
+    if (!rows_aside) sums_of_ffn_rows();
     fork(0);
+    if (rows_aside) sums_of_ffn_rows();
     sums_of_ffn_output();
   }
   dweight(H, F, dr2, g, gr->w2);
@@ -774,8 +777,9 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   if (d->pre_ln) row_bwd(r_y1, nullptr, z1, mu2, rstd2, p->ln2_g, dy, t2, dr1, dp0, 0, 1);
   else row_bwd(r_y1, t0, z1, mu1, rstd1, p->ln1_g, nullptr, t2, dr1, dp0, 0, 1);
   if (together == APART) {
-    sums_of_attention_output();
+    if (!rows_aside) sums_of_attention_output();
     fork(2);
+    if (rows_aside) sums_of_attention_output();
   }
   dweight(H, A, dr1, attn, gr->wo);
   dgrad(EPI_NONE, A, H, dr1, p->wo, t0, nullptr);

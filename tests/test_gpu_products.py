@@ -82,3 +82,15 @@ def test_column_sums_of_the_activation_gradient(hidden, heads, ffn, dtype, attn_
     grids = launches(layer, x, dy, dx)
     assert ((ffn + 255) // 256, 64, 1) not in grids                                       # no pass over that array ...
     assert ((3 * (attn_dim or hidden) + 255) // 256, 64, 1) in grids                      # ... as there is over the gradient of QKV
+
+
+# which layers share launches: small ones and those that leave most of the chip idle do not
+@pytest.mark.parametrize("batch,seq,hidden,together", [(12, 24, 256, False), (6, 200, 768, False), (6, 381, 768, True), (3, 500, 1024, False), (4, 500, 1024, True),
+                                                       (16, 500, 512, False)])
+def test_which_layers_share_launches(batch, seq, hidden, together):
+    c, T, H, F = cfg("lines", batch, seq, hidden, hidden // 64, 4 * hidden), batch * seq, hidden, 4 * hidden
+    layer = B.Layer(c, W.make_params(c))
+    x = torch.zeros(batch, seq, hidden, dtype=layer.dt, device=DEV)
+    layer.forward(x)
+    grids = launches(layer, x, x, torch.empty_like(x))
+    assert (with_quarters(tiles((T, H), (H, F), (F, H), (H, H), (3 * H, H)), 0) in grids) == together
