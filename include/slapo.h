@@ -18,8 +18,9 @@
  *   - `stream` is a hipStream_t passed as void*; all work is ordered after what was enqueued there
  *     before the call and before what is enqueued there afterwards; nothing synchronises with the host,
  *     no device memory is allocated or freed, no pointer is kept after the call returns.
- *     slapo_layer_bwd (but for small calls, which stay on `stream`) issues its weight-gradient GEMMs, of calls not much
- *     larger only that of the output projection, on one internal helper stream per device, created on first use and
+ *     slapo_layer_bwd (but for small calls, which stay on `stream`) issues part of its work - the weight-gradient GEMMs
+ *     or, where they share launches with the data gradients, only that of the output projection or the sums behind the
+ *     bias gradients - on one internal helper stream per device, created on first use and
  *     kept for the life of the process, forked from and joined back into `stream` with events (capturable in a HIP
  *     graph like any fork/join). This helper stream and its events are the only state the library holds besides the
  *     fixed scratch array of slapo_weight_grad_static.

@@ -126,7 +126,8 @@ int finish() {
 }
 
 // The weight-gradient GEMMs of the backward pass do not feed the data-gradient chain, and most kernels of
-// the chain leave half of each CU's LDS and wave slots free (one 128x128 tile per CU). They are therefore
+// the chain leave half of each CU's LDS and wave slots free (one 128x128 tile per CU). Where they do not share
+// launches with each other and the data gradients (products_together, grad pairs) they are therefore
 // issued on a helper stream that forks from and joins back into the caller's stream with events, so the
 // two kinds of GEMM share the CUs. One helper stream and a few events per device are created on first use
 // and kept for the life of the process (the only state the library holds). Host threads that call into the
@@ -236,7 +237,8 @@ bool gradients_paired(const slapo_layer_desc* d) {
 //   5504, 4096 1410 / 1471 (apart); 4096, attention 512, FFN 1376, 4096 527 / 497; 4096, FFN 11008, 4096 (a step) 4176 / 4103
 enum Together { APART, BEHIND, BLOCKS };
 Together products_together(const slapo_layer_desc* d) {
-  if (d->dtype == SLAPO_FP32) return APART;
+  // (fewer than 1024 tokens: a gated layer of 576, hidden 3072, attention 768, two layers 540 / 547; the others are far from the lines)
+  if (d->dtype == SLAPO_FP32 || (int64_t)d->batch * d->seq < 1024) return APART;
   const int T = d->batch * d->seq, H = d->hidden, F = d->ffn, A = attn_width(d), F1 = is_llama(d) ? 2 * F : F;
   const auto sizes = [](int layout, int M, int N, int K) { return Product{layout, M, N, K, nullptr, nullptr, nullptr, nullptr}; };
   const Product x = sizes(GEMM_NN, T, H, 3 * A), y = sizes(GEMM_NN, T, H, F1), w2 = sizes(GEMM_TN, H, F, T), w1 = sizes(GEMM_TN, F1, H, T),
