@@ -569,6 +569,7 @@ __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, c
   };
   // EPI_DACT: aux_out takes the column sums of every 32 rows of C, [M / 32 rounded up][N] floats (NULL: none), from which the bias
   // gradient in front of the activation comes without another pass over C. The sums are of the unrounded values.
+  static_assert(EPI != EPI_DACT || CPR == 4 || CPR == 8 || CPR == 16, "sum_of_lanes");
   float* col_sums = EPI == EPI_DACT ? reinterpret_cast<float*>(aux_out) : nullptr;
   const bool aux_here = AUX && !is_tail && (!BY_AUX || aux_in != nullptr);   // (uniform)
   if (aux_here) aux_fetch(0, au[0]);
