@@ -152,6 +152,8 @@ int slapo_layer_fwd(const slapo_layer_desc *desc, const slapo_layer_params *para
  * dx [B,S,H] and the parameter gradients (twelve; six for SLAPO_ARCH_LLAMA; same shapes and element type as
  * the parameters). dx may be the array x itself and may lie on dy in any way; it overlaps nothing else.
  * (On top of x, gradients of a post-LN layer are sums in another order: the last bits differ from those with dx elsewhere.)
+ * The gradient of b1 adds up the gradient of the pre-activation before it is rounded to a 16-bit element type or, by the size of
+ * the call, after; a value beyond that type's range is an infinity in it either way.
  * The dropout masks are regenerated from (seed, layer_id, site, element index), never stored. */
 int slapo_layer_bwd(const slapo_layer_desc *desc, const slapo_layer_params *params, const void *x,
                     const int32_t *seqlens, const void *dy, const void *saved, void *dx,

@@ -568,7 +568,8 @@ __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, c
     for (int e = 0; e < 4; ++e) { u[2 * e] = unpack_lo<F16>(w[e]); u[2 * e + 1] = unpack_hi<F16>(w[e]); }
   };
   // EPI_DACT: aux_out takes the column sums of every 32 rows of C, [M / 32 rounded up][N] floats (NULL: none), from which the bias
-  // gradient in front of the activation comes without another pass over C. The sums are of the unrounded values.
+  // gradient in front of the activation comes without another pass over C. The sums are of the unrounded values; a value that the
+  // storage type holds as an infinity counts as one (IEEE half, from 65520 on; bf16 reaches as far as the sums do).
   static_assert(EPI != EPI_DACT || CPR == 4 || CPR == 8 || CPR == 16, "sum_of_lanes");
   float* col_sums = EPI == EPI_DACT ? reinterpret_cast<float*>(aux_out) : nullptr;
   const bool aux_here = AUX && !is_tail && (!BY_AUX || aux_in != nullptr);   // (uniform)
@@ -630,7 +631,7 @@ __device__ __forceinline__ void gemm_bf16_tile(int block, int M, int N, int K, c
             for (int e = 0; e < 8; ++e) v[e] *= u[e];
           }
 #pragma unroll
-          for (int e = 0; e < 8; ++e) sums[e] += v[e];
+          for (int e = 0; e < 8; ++e) sums[e] += !F16 || fabsf(v[e]) < 65520.f ? v[e] : v[e] * __builtin_inff();
         } else if (EPI == EPI_ADD) {
           if (!BY_AUX || aux_here) {
             float u[8];

@@ -84,6 +84,22 @@ def test_column_sums_of_the_activation_gradient(hidden, heads, ffn, dtype, attn_
     assert ((3 * (attn_dim or hidden) + 255) // 256, 64, 1) in grids                      # ... as there is over the gradient of QKV
 
 
+# in IEEE half a gradient that overflows its storage is an infinity in the bias gradient too, whatever its column adds up to: gradients
+# in launches of their own, in shared ones, and beside data gradients (where the sums are a pass over the stored array)
+@pytest.mark.parametrize("batch,seq,hidden", [(16, 500, 512), (4, 500, 1024), (2, 200, 512)])
+def test_overflow_of_the_activation_gradient_shows_in_the_bias_gradient(batch, seq, hidden):
+    c = cfg("overflow", batch, seq, hidden, hidden // 64, 4 * hidden, W.FP16, pre_ln=1, causal=1, act=W.RELU, dropout_p=0.0)
+    params = W.make_params(c)
+    params["w2"][:, :2], params["b1"][:2] = (8.0, -8.0), 100.0   # (two gates that are always open)
+    layer = B.Layer(c, params)
+    x, dy = torch.randn(batch, seq, hidden, device=DEV).to(layer.dt), torch.zeros(batch, seq, hidden, dtype=layer.dt, device=DEV)
+    dy[0, 0], dy[0, 1] = 9216.0 / hidden, -4608.0 / hidden   # times 8 and summed: 73728, beyond the largest half, and half of that
+    layer.forward(x)
+    layer.backward(x, None, dy)
+    b1 = layer.grads["b1"].float()
+    assert b1[:2].tolist() == [float("inf"), -float("inf")] and bool(torch.isfinite(b1[2:]).all())
+
+
 # which layers share launches: small ones and those that leave most of the chip idle do not
 @pytest.mark.parametrize("batch,seq,hidden,together", [(12, 24, 256, False), (6, 200, 768, False), (6, 381, 768, True), (3, 500, 1024, False), (4, 500, 1024, True),
                                                        (16, 500, 512, False)])
