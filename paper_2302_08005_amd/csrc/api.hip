@@ -298,6 +298,16 @@ inline bool sums_with_du(const slapo_layer_desc* d) {
   return !is_llama(d) && d->dtype != SLAPO_FP32 && (int64_t)d->batch * d->seq >= 1024;
 }
 
+// The sums over the partial rows that the row kernels leave run on the helper stream beside launches that several products share
+// (classic layers of 1024 tokens and more), and from 1536 tokens on beside launches for each product. An array of partial rows per row
+// kernel is then in flight; on the chain one serves all three, and what the next kernel writes is what the last sum has just read.
+// us of backward, classic and gated layers, on the chain with an array for each / with one / on the helper stream:
+//   896 tokens, hidden 2048 272 / 263 / 267, gated (1024) 314 / 306 / 312; gated 1152, 2560 471 / 468 / 475; 1152, 2560 441 / 439 / 437
+//   1280, 1536 242 / 242 / 230; 1408, 2048 362 / 361 / 348; gated 1536, 1536 244 / 244 / 237; 5500, 768 295 / 295 / 283; 8000, 512 250 / 248 /
+//   236; 2000, 2048 463 / 460 / 450; 2000, 3072 866 / 865 / 878; 4000, 2560 1260 / 1260 / 1250
+constexpr int ROW_SUMS_ASIDE = 1536;
+inline size_t row_sums_aside_from(const slapo_layer_desc* d) { return is_llama(d) || d->dtype == SLAPO_FP32 ? ROW_SUMS_ASIDE : 1024; }
+
 struct ScratchLayout {
   size_t t0, t1, t2, t3, du, dqkv, delta, part_row[3], part_col, part_col2, part_du, rope, splitk, gemm_ws, gemm_ws_bytes, splitk_bytes, acts, total;
 };
@@ -314,7 +324,8 @@ ScratchLayout scratch_layout(const slapo_layer_desc* d) {
   L.du = take(T * F * eb * (is_llama(d) ? 2 : 1));
   L.dqkv = take(T * 3 * A * eb);
   L.delta = take((size_t)d->batch * d->heads * d->seq * 4);
-  for (size_t& p : L.part_row) p = take((size_t)bdrln_bwd_blocks_wide((int64_t)T, (int)H) * 3 * H * 4);   // one per row kernel
+  for (size_t& p : L.part_row)   // one per row kernel where sums over partial rows may leave the chain, else one for all
+    p = &p == L.part_row || T >= row_sums_aside_from(d) ? take((size_t)bdrln_bwd_blocks_wide((int64_t)T, (int)H) * 3 * H * 4) : L.part_row[0];
   size_t widest = F > 3 * A ? F : 3 * A;
   widest = widest > H ? widest : H;
   L.part_col = take((size_t)colsum_blocks((int64_t)T) * widest * 4);
@@ -588,6 +599,8 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   auto fork = [&](int i) {   // everything issued on st so far happens before what follows on ws
     if (side && (together == APART || i == 1 || i == 3)) side->order(side->fork[i], st, ws);
   };
+  const bool rows_aside = side && (together != APART || T >= ROW_SUMS_ASIDE);
+  auto partial_rows = [&](int k) { return (float*)(sc + W.part_row[rows_aside ? k : 0]); };   // of row kernel `k` (0 to 2, in their order)
   // weight gradient: C (+)= A^T B
   float* splitk_ws = W.splitk_bytes ? (float*)(sc + W.splitk) : nullptr;
   float* gws = W.gemm_ws_bytes ? (float*)(sc + W.gemm_ws) : nullptr;
@@ -613,9 +626,8 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
     launch_colsum_partials(dt, T, N, a, part, s);
     launch_colreduce_partials(dt, ncol, N, N, part, out, acc, s);
   };
-  // the sums over the partial rows that row kernel `k` (0 to 2, in their order) left
   auto reduce_rows = [&](int k, void* dgamma, void* dbeta, void* dbias, hipStream_t s) {
-    launch_colreduce3(dt, nrow, H, (float*)(sc + W.part_row[k]), dgamma, dbeta, dbias, acc, s);
+    launch_colreduce3(dt, nrow, H, partial_rows(k), dgamma, dbeta, dbias, acc, s);
   };
   // The gradient of a block's input, [T,H], which a row kernel reads next: t0, or K ranges in gws where few tokens make few tiles
   // (`add`, what the product is added to, is then the row kernel's to add). Not the feed-forward block's of the gated layer, whose
@@ -623,7 +635,7 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   const bool r_y1 = together != BLOCKS && !is_llama(d) && product_in_ranges(dt, T, H, F), r_x = together == APART && product_in_ranges(dt, T, H, 3 * A);
   auto row_bwd = [&](bool ranges, const void* add, const void* z, const float* mu, const float* rstd, const void* gamma, const void* dres,
                      void* dz, void* dr, const DropoutParams& dp, int dr_from_stored, int k = 0) {
-    launch_bdrln_bwd(dt, T, H, ranges ? gws : t0, z, mu, rstd, gamma, dres, dz, dr, (float*)(sc + W.part_row[k]), dp, is_llama(d) ? 1 : 0, st, dr_from_stored, nrow,
+    launch_bdrln_bwd(dt, T, H, ranges ? gws : t0, z, mu, rstd, gamma, dres, dz, dr, partial_rows(k), dp, is_llama(d) ? 1 : 0, st, dr_from_stored, nrow,
                      ranges, ranges ? add : nullptr);
   };
   // Buffers: t0 dZ2 -> dY1/dN2 -> dA -> dN1; t1 dR2 (kept for dW2); t2 dZ1; t3 dR1 (kept for dWo). Where nothing is dropped
@@ -734,8 +746,6 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   }
   const bool with_du = sums_with_du(d);
   float* pdu = (float*)(sc + W.part_du);
-  // (apart, the helper stream is the longer one where tokens are few: gated, hidden 2688, 992 tokens 1362 / 1395 us with them there)
-  const bool rows_aside = together != APART || T >= 1536;
   hipStream_t rs = rows_aside ? ws : st;
   auto sums_of_ffn_rows = [&] {
     if (rows2) reduce_rows(0, d->pre_ln ? nullptr : gr->ln2_g, d->pre_ln ? nullptr : g_ln2_b, g_b2, rs);

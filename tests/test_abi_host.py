@@ -41,6 +41,15 @@ def test_descriptor_validation():
         assert e.value.status == code, (kw, e.value.status)
 
 
+@pytest.mark.parametrize("arch,tokens", [(B.LLAMA, 1536), (B.CLASSIC, 1024)])
+def test_scratch_holds_partial_rows_for_each_row_kernel_only_where_their_sums_leave_the_chain(arch, tokens):
+    """Fewer tokens: one array for all three, which stays in the caches (256 partial rows of 3 x hidden floats)."""
+    def scratch(seq):
+        return B.slapo_layer_workspace(B.make_desc(batch=1, seq=seq, hidden=2048, heads=32, ffn=5504, causal=1, pre_ln=1, arch=arch))[1]
+    array = 256 * 3 * 2048 * 4
+    assert scratch(tokens) - scratch(tokens - 8) > 2 * array > scratch(tokens - 8) - scratch(tokens - 16)
+
+
 def test_null_and_alignment_errors_come_before_any_device_work():
     d = B.make_desc(batch=2, seq=128, hidden=256, heads=4, ffn=1024)
     lib = B.lib()
