@@ -219,22 +219,44 @@ bool gradients_paired(const slapo_layer_desc* d) {
   return !is_llama(d) && T <= 4096.0 && weights * T <= 3.2e10 && (weights <= 6.4e7 || d->dtype == SLAPO_FP32);
 }
 
+}  // namespace
+
+namespace slapo {
+
 // Whether the weight gradients of backward share launches of 256x256 tiles with each other and with data gradients (launch_products),
 // all on the caller's stream, and which: the gradient of the layer's input and all four behind the attention kernels (BEHIND), or those
-// of each block with the gradient of the block's input (BLOCKS). Decided by what either form takes in slabs of such a tile
-// (products_slabs), against the work itself. Where the gradient of the second feed-forward weight alone has tiles for three
-// quarters of the chip, two streams run the same large tiles and fill each other's thin rounds: only nearly full launches beat
-// them, by 0 to 5 %. Elsewhere they run 128x128 ones, at 1.3 times the work, and pay about 28 slabs for forks and launches. From
-// 150 slabs of work on that counts for nothing beside what a half-empty round costs. The gated layer gains less (it has no sums that would
-// leave the chain, and wide products, which two streams overlap well): nearer lines, and only what the tiles save from 90 slabs on. BLOCKS are the better form at equal slabs (fewer tiles drift apart).
-// Backward, us, apart / together:
-//   hidden 640, tokens 5700 246 / 237 (apart); 832, FFN 3328, 13468 665 / 704 (apart); 1152, 4608, 6288 569 / 588 (apart); 768, 1900 133 / 134 (apart), 2280 147 / 138, 3800 226 / 191, 5700 296 / 302, 16000 733 / 771 (both apart)
-//   hidden 896, 1520 134 / 139 (apart), 1900 163 / 146; 1024, 1520 156 / 157 (apart), 1900 185 / 165, 3800 285 / 248, 8000 597 / 494
-//   hidden 1280, 1140 171 / 185 (apart), 1520 215 / 192, 5700 602 / 553; 1536, 4000 587 / 536, 16000 2212 / 1842; 512, 8000 245 / 292 (apart)
-//   hidden 2048, 4000 820 / 781; 2560, 2000 690 / 714 (apart), 6000 1717 / 1704; 3072, 2048 884 / 895 (apart), 4096 1632 / 1610
-//   gated, hidden 768, 2500 161 / 153 (apart); 1024, FFN 2736, 2000 188 / 177 (apart), 2500 204 / 194, 4000 297 / 265; 1536, 4096, 2500 354 / 363,
-//   3000 413 / 411 (both apart), 4000 517 / 503; 2048, 5504, 1500 387 / 401 (apart), 2000 492 / 457, 4000 869 / 808; 4096, attention 2048, FFN
-//   5504, 4096 1410 / 1471 (apart); 4096, attention 512, FFN 1376, 4096 527 / 497; 4096, FFN 11008, 4096 (a step) 4176 / 4103
+// of each block with the gradient of the block's input (BLOCKS; the better form at equal slabs, fewer tiles drift apart). Classic layers:
+// decided by what either form takes in slabs of such a tile. Shared, the launches as they fill rounds (products_slabs) and the two products
+// that then have the chip to themselves; apart, the tiles of all products spread over the chip, because two streams fill each other's
+// thin rounds. Where the gradient of the second feed-forward weight alone has tiles for three quarters of the chip, the two streams run
+// the same large tiles and hide more behind each other: 7 % and 12 slabs between the estimates. Elsewhere they run 128x128 tiles and pay
+// for forks and launches: 12 % and 22 slabs the other way. The lines are those that cost least over 733 sizes (1024 to 16384 tokens,
+// hidden 512 to 4096, any feed-forward width): 33 are more than 1 % slower than apart (8 % at most), 81 would be that much faster
+// together; with the work in the shared launches in place of the second estimate it was 76 (13 %) and 142. The gated layer gains
+// less (it has no sums that would leave the chain, and wide products, which two streams overlap well) and has lines over that work.
+// Backward, us, apart / together; "hidden,FFN[,attention]: tokens"; "!": the slower one is taken:
+//   classic  576,2304: 1536 99/103!; 640,2560: 1408 114/116!, 2660 142/136!, 3800 188/184!, 5700 238/235!, 8000 337/387; 768,2048: 2700 173/177!;
+//     768,3072: 1520 120/127, 1900 133/135, 2280 146/139, 3072 202/188, 3800 225/191, 5700 283/298, 8000 394/414, 16000 705/745;
+//     832,3328: 13468 709/711; 896,2392: 6464 362/332!; 896,3584: 1520 133/140, 1900 163/148, 5700 362/347, 8000 493/456; 1024,4096: 1140 132/150,
+//     1520 152/158, 1900 183/165, 3800 281/248, 5700 420/374, 8000 582/489, 12000 816/694; 1088,4352: 1332 160/166, 8000 649/706, 8320 664/719!;
+//     1152,3072: 7168 552/541!; 1152,4520: 4096 367/378; 1152,4608: 4096 406/428, 6288 537/563, 8192 814/845!; 1280,5120: 1140 170/185,
+//     1520 215/194, 3800 426/392, 4560 511/469, 5700 593/551, 6840 677/681, 8000 827/783, 10240 1247/1205, 12000 1197/1087, 16000 1642/1416;
+//     1536,6144: 1520 257/255, 2280 364/350, 3000 442/442, 4000 580/528, 6000 816/757, 8000 1065/970, 12000 1641/1415, 16000 2174/1819;
+//     2048,6992: 9088 1551/1506; 2048,8192: 1520 385/378!, 2000 451/455, 3000 631/632, 4000 800/782!, 5000 1004/1014, 6000 1158/1138,
+//     8000 1475/1441, 12000 2272/2206, 13653 2520/2436; 2112,5800: 15300 3204/2978; 2432,8208: 13696 3394/3272!; 2560,10240: 2000 668/691,
+//     3000 918/903, 4000 1224/1248, 6000 1713/1699, 8192 2375/2264, 12000 3446/3412; 2688,10752: 4096 1461/1420; 2752,11008: 2048 772/790;
+//     2880,6272: 7168 2034/1965; 2880,11520: 1332 604/619; 2944,11776: 7168 2644/2596; 3072,12288: 1536 698/727, 2048 871/882, 3072 1247/1251,
+//     4096 1607/1598, 6144 2471/2341, 8192 3216/3116; 3392,9048: 8100 3454/3506!; 3392,11968: 3000 1522/1551!; 3456,13824: 4096 2046/2092;
+//     3520,9384: 4096 1846/1895; 3712,14848: 3696 2134/2192!; 3776,15104: 2000 1291/1249!; 3840,9736: 1024 658/644; 4096,16384: 1024 870/854,
+//     1536 1176/1160, 2048 1466/1411, 2560 1791/1750, 3072 2108/2033, 3584 2355/2385!, 4096 2668/2595;
+//   gated  512,1368: 2048 139/108!; 576,1536: 3072 145/156; 768,2048: 1500 136/129!, 2000 135/134, 2500 152/152, 3000 164/169, 4000 191/201;
+//     832,2216: 5500 325/337; 960,2560: 3072 214/201, 3584 227/214, 4000 294/271; 1024,2728: 5439 419/387; 1024,2736: 1500 158/162, 2000 182/176!,
+//     2500 194/193, 4000 293/264, 8000 537/514; 1216,400,128: 8192 198/243; 1536,4096: 1500 242/255, 2000 289/311, 2500 356/369, 3000 410/421,
+//     4000 512/489, 8000 968/957; 1728,2304,832: 4608 437/415!; 1856,4952: 4500 872/904!; 1920,1280,448: 2000 152/146; 1984,5288: 2664 612/585,
+//     11776 2294/2165, 14500 2932/2749; 2048,1360,512: 13500 839/787; 2048,5504: 1500 384/399, 2000 502/458, 4000 864/802, 8000 1556/1483;
+//     2112,2816,1024: 1024 187/202; 2368,784,256: 1024 145/113; 2496,6656: 4000 1174/1131!; 2560,3408,1280: 12800 2159/1898; 2624,7000: 2331 836/862;
+//     3072,2048,768: 7326 879/826; 3968,2640,960: 5661 1105/1058; 4096,1376,512: 2048 289/276, 4096 509/478; 4096,2752,1024: 2048 477/444,
+//     4096 819/774; 4096,5504,2048: 4096 1399/1415; 4096,11008: 2048 1450/1453, 3000 2075/2071, 4096 2683/2683.
 enum Together { APART, BEHIND, BLOCKS };
 Together products_together(const slapo_layer_desc* d) {
   // (fewer than 1024 tokens: a gated layer of 576, hidden 3072, attention 768, two layers 540 / 547; the others are far from the lines)
@@ -248,13 +270,23 @@ Together products_together(const slapo_layer_desc* d) {
   const int in_blocks = products_slabs(3, first, &total) + products_slabs(3, second, &total);
   const int at_end = products_slabs(5, behind, &ignored) + gemm_slabs(GEMM_NN, T, H, F1);
   const bool blocks = in_blocks <= 1.02 * at_end;
-  const double slabs = blocks ? in_blocks : at_end, work = (double)total / 256.0;
   const bool large_alone = (int64_t)((H + 255) / 256) * ((F + 255) / 256) >= 192;
-  const double line = is_llama(d) ? (large_alone ? 1.025 * work : work < 90.0 ? work + 27.0 : 1.13 * work)
-                                  : (large_alone ? 1.05 * work : work < 150.0 ? 1.3 * work + 28.0 : 1.22 * work);
-  if (slabs > line || slabs > 2.25 * work) return APART;   // (not where the tiles of all products together leave most of the chip idle)
+  if (is_llama(d)) {
+    const double slabs = blocks ? in_blocks : at_end, work = (double)total / 256.0;
+    if (slabs > (large_alone ? 1.025 * work : work < 90.0 ? work + 26.0 : 1.13 * work)) return APART;
+    if (slabs > 2.25 * work) return APART;   // (not where the tiles of all products together leave most of the chip idle)
+  } else {
+    const double shared = (blocks ? in_blocks : at_end) + gemm_slabs(GEMM_NN, T, F, H) + gemm_slabs(GEMM_NN, T, A, H);
+    double apart = gemm_slabs_beside(GEMM_NN, T, F, H) + gemm_slabs_beside(GEMM_NN, T, A, H);
+    for (const Product& p : {x, y, w2, w1, wo, wqkv}) apart += gemm_slabs_beside(p.layout, p.M, p.N, p.K);
+    if (shared > (large_alone ? 1.07 * apart - 12.0 : 1.12 * apart + 22.0)) return APART;
+  }
   return blocks ? BLOCKS : BEHIND;
 }
+
+}  // namespace slapo
+
+namespace {
 
 // byte offsets of the regions of `saved`
 struct SavedLayout {

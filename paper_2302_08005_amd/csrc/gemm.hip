@@ -413,6 +413,25 @@ static void launch_bf16(int epi, int act, int M, int N, int K, const void* A, co
   }
 }
 
+// What the tiles of a product take spread over all CUs, as they are where the tiles of another stream fill the rounds: at the rates of
+// each form (slabs of a 256x256 tile, 1.33 us), and what a tile takes besides its slabs, four such ones for the smaller forms.
+double gemm_slabs_beside(int layout, int M, int N, int K) {
+  const double nk = (K + 63) / 64;
+  const auto tiles = [&](int bm, int bn) { return (double)((M + bm - 1) / bm) * ((N + bn - 1) / bn) / 256.0; };
+  switch (select_tile(layout, M, N, K, false)) {
+    case TILE_256: return tiles(256, 256) * (nk + TILE_SLABS);
+    case TILE_192x256: return tiles(192, 256) * (0.70 * nk + TILE_SLABS);
+    case TILE_256x128_LOADERS: return tiles(256, 128) * (0.46 * nk + 4);
+    case TILE_192x128_LOADERS: return tiles(192, 128) * (0.36 * nk + 4);
+    case TILE_128x64_LOADERS: return tiles(128, 64) * (0.16 * nk + 4);
+    case TILE_64_LOADERS: return tiles(64, 64) * (0.13 * nk + 4);
+    case TILE_128_LOADERS:
+      if (two_per_cu(M, N, K)) return tiles(128, 128) * (0.55 * nk + 4) / 2;
+      [[fallthrough]];
+    default: return tiles(128, 128) * (0.29 * nk + 4);
+  }
+}
+
 // Rates of the other tiles in slabs of a 256x256 one (1.33 us): their rules have the times.
 int gemm_slabs(int layout, int M, int N, int K) {
   const int nk = (K + 63) / 64, t256 = ((M + 255) / 256) * ((N + 255) / 256), t128 = ((M + 127) / 128) * ((N + 127) / 128);

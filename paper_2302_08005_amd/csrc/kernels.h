@@ -65,6 +65,8 @@ void launch_products(int dtype, int n, const Product* products, hipStream_t st);
 int products_slabs(int n, const Product* products, int64_t* work);
 // the same for a product (NN, 16-bit) that has a launch of its own and the chip to itself
 int gemm_slabs(int layout, int M, int N, int K);
+// and for one that another stream's tiles run beside (backward with a launch for each product)
+double gemm_slabs_beside(int layout, int M, int N, int K);
 
 // What backward computes from one gradient array, in one launch: the gradient that goes on (layout NN, C [M,N] = A [M,K]
 // B [K,N], epilogue EPI_DACT, EPI_DGATE or EPI_ADD; the latter adds nothing if aux is NULL), the weight gradient
