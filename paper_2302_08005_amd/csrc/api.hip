@@ -259,7 +259,9 @@ namespace slapo {
 //     4096 819/774; 4096,5504,2048: 4096 1399/1415; 4096,11008: 2048 1450/1453, 3000 2075/2071, 4096 2683/2683.
 enum Together { APART, BEHIND, BLOCKS };
 Together products_together(const slapo_layer_desc* d) {
-  // (fewer than 1024 tokens: a gated layer of 576, hidden 3072, attention 768, two layers 540 / 547; the others are far from the lines)
+  // (Fewer than 1024 tokens: of 150 sizes measured there the lines below would have four share, us apart / together: gated, 512 tokens of
+  // width 3712, attention 896 170 / 177, 832 of 2240, 512 146 / 133, of 3264, 384 148 / 139; classic, 1016 of 3840 769 / 742; and 576 gated
+  // ones of 3072, 768 two layers 540 / 547. The others are up to twice as slow together. What the count takes is the host's, which small calls wait for.)
   if (d->dtype == SLAPO_FP32 || (int64_t)d->batch * d->seq < 1024) return APART;
   const int T = d->batch * d->seq, H = d->hidden, F = d->ffn, A = attn_width(d), F1 = is_llama(d) ? 2 * F : F;
   const auto sizes = [](int layout, int M, int N, int K) { return Product{layout, M, N, K, nullptr, nullptr, nullptr, nullptr}; };
@@ -325,7 +327,8 @@ static size_t product_ws_bytes(int dtype, int layout, int M, int N, int K) {
 
 // The gradient of the first feed-forward bias: column sums that the product which computes the gradient of the activations leaves
 // behind (EPI_DACT), instead of another pass over that array (16384 tokens, 4096 columns: 27 us alone, 36 beside a product).
-// From 1024 tokens on: below, the pass is 5 us on the helper stream or rides on the next launch. fp32 products leave none.
+// From 1024 tokens on: below, the pass is 5 us on the helper stream or rides on the next launch. fp32 products leave none, and paired
+// launches neither, but such layers come here too where dx lies on x.
 inline bool sums_with_du(const slapo_layer_desc* d) {
   return !is_llama(d) && d->dtype != SLAPO_FP32 && (int64_t)d->batch * d->seq >= 1024;
 }
@@ -664,7 +667,8 @@ static int run_backward(const slapo_layer_desc* d, const slapo_layer_params* p, 
   // The gradient of a block's input, [T,H], which a row kernel reads next: t0, or K ranges in gws where few tokens make few tiles
   // (`add`, what the product is added to, is then the row kernel's to add). Not the feed-forward block's of the gated layer, whose
   // gradients are, bit for bit, those of the exported products, rotary turn and attention in a row (1024, 128 tokens: 2 us).
-  const bool r_y1 = together != BLOCKS && !is_llama(d) && product_in_ranges(dt, T, H, F), r_x = together == APART && product_in_ranges(dt, T, H, 3 * A);
+  // (Never where launches are shared: 1024 tokens and more make more tiles.)
+  const bool r_y1 = !is_llama(d) && product_in_ranges(dt, T, H, F), r_x = product_in_ranges(dt, T, H, 3 * A);
   auto row_bwd = [&](bool ranges, const void* add, const void* z, const float* mu, const float* rstd, const void* gamma, const void* dres,
                      void* dz, void* dr, const DropoutParams& dp, int dr_from_stored, int k = 0) {
     launch_bdrln_bwd(dt, T, H, ranges ? gws : t0, z, mu, rstd, gamma, dres, dz, dr, partial_rows(k), dp, is_llama(d) ? 1 : 0, st, dr_from_stored, nrow,

@@ -53,18 +53,26 @@ def test_scratch_holds_partial_rows_for_each_row_kernel_only_where_their_sums_le
 def test_which_backward_form_is_taken_where_both_were_measured():
     """The times beside the rule, and the rule: the faster form is taken but where the comment says that it is not."""
     text = open(os.path.join(ROOT, "paper_2302_08005_amd", "csrc", "api.hip")).read()
-    together = B.lib()._ZN5slapo17products_togetherEPK16slapo_layer_desc
     comment, seen, arch = text[:text.index("enum Together")].rsplit("the slower one is taken:", 1)[1], 0, None
     for family, sizes, points in re.findall(r"(classic|gated)?\s+(\d+,[\d,]+): ([\d/!,\s]+)", comment.replace("//", " ")):
         arch = {"classic": B.CLASSIC, "gated": B.LLAMA, "": arch}[family]
         hidden, ffn, attn = ([int(v) for v in sizes.split(",")] + [0])[:3]
         for tokens, apart, shared, slower in re.findall(r"(\d+)\s+(\d+)/(\d+)(!?)", points):
             d = B.make_desc(batch=1, seq=int(tokens), hidden=hidden, heads=1, ffn=ffn, attn_dim=attn, arch=arch)
-            taken, other = (int(shared), int(apart)) if together(C.byref(d)) else (int(apart), int(shared))
+            taken, other = (int(shared), int(apart)) if B.backward_form(d) else (int(apart), int(shared))
             seen += 1
             # (times are given in whole us)
             assert taken - 0.5 > 1.01 * (other - 0.5) if slower else taken - 0.5 < 1.01 * (other + 0.5), (arch, hidden, ffn, attn, tokens)
     assert seen > 130
+
+
+def test_products_of_layers_that_share_launches_come_in_no_k_ranges():
+    """Backward reads a block's input gradient as K ranges by that rule alone; layers of fewer than 1024 tokens share no launches."""
+    ranges = lambda *a: B.lib()._ZN5slapo17product_in_rangesEiiii(B.BF16, *a) & 1
+    assert ranges(128, 512, 2048) and not any(ranges(t, h, k) for t in (1024, 1025, 4096) for h in range(8, 8200, 8) for k in (2048, 1 << 20))
+    for arch in (B.CLASSIC, B.LLAMA):
+        assert not any(B.backward_form(B.make_desc(batch=1, seq=t, hidden=h, heads=1, ffn=f, attn_dim=a, arch=arch))
+                       for t in (64, 512, 1023) for h in (512, 2304, 4096) for f in (h // 2, 4 * h) for a in (h // 4, h))
 
 
 def test_null_and_alignment_errors_come_before_any_device_work():
