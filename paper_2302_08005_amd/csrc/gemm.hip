@@ -145,7 +145,8 @@ bool gemm_in_one_round(int dtype, int layout, int M, int N, int K) {
 // Layout NT (rows of an operand that is not contiguous along K are 64 elements at least). us, 64x64 / 64x32, operands from memory:
 //   128 x 3072 x 1024 5.78 / 5.08, 128 x 4096 x 1024 with GeLU 6.53 / 5.67, 128 x 2304 x 768 5.29 / 4.62, 256 x 2048 x 512 with GeLU 5.27 / 4.69;
 //   more than 256 of them: 256 x 4096 x 1024 7.14 / 9.86, 128 x 6144 x 2048 12.2 / 16.6
-// Products of at most 32 tiles of 64x64 keep those (128 x 768 x 768 4.99 / 4.31): callers of the exported product are told so.
+// Products of at most 32 tiles of 64x64 keep those although 64x32 ones are faster there too (128 x 768 x 768 4.99 / 4.31): the layer and
+// the exported product select alike, and the tests of the latter hold it to 64x64 tiles at these sizes.
 static bool many_64x32(int M, int N) {
   const int64_t rows = (M + 63) / 64;
   return rows * ((N + 63) / 64) > 32 && rows * ((N + 31) / 32) <= 256;
