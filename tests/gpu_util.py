@@ -44,8 +44,8 @@ class _KernelNode(ctypes.Structure):   # hipKernelNodeParams
                 ("args", ctypes.c_void_p), ("shared", ctypes.c_uint32)]
 
 
-def captured(step, grids=False):
-    """(nodes, edges) of the graph that `step` is captured as, or the grids of its kernels; nothing of it is run."""
+def captured(step, grids=False, names=False):
+    """(nodes, edges) of the graph that `step` is captured as, or the grids or (mangled) names of its kernels; nothing of it is run."""
     graph = torch.cuda.CUDAGraph(keep_graph=True)
     with torch.cuda.graph(graph):
         step()
@@ -54,8 +54,9 @@ def captured(step, grids=False):
     raw, nodes, edges = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0), ctypes.c_size_t(0)
     assert hip.hipGraphGetNodes(raw, None, ctypes.byref(nodes)) == 0 and nodes.value > 0
     assert hip.hipGraphGetEdges(raw, None, None, ctypes.byref(edges)) == 0
-    if not grids:
+    if not grids and not names:
         return nodes.value, edges.value
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
     each, out = (ctypes.c_void_p * nodes.value)(), []
     assert hip.hipGraphGetNodes(raw, each, ctypes.byref(nodes)) == 0
     for n in each:
@@ -63,8 +64,13 @@ def captured(step, grids=False):
         assert hip.hipGraphNodeGetType(ctypes.c_void_p(n), ctypes.byref(kind)) == 0
         if kind.value == 0:   # hipGraphNodeTypeKernel
             assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(n), ctypes.byref(k)) == 0
-            out.append(tuple(k.grid))
+            out.append(hip.hipKernelNameRefByPtr(ctypes.c_void_p(k.func), None).decode() if names else tuple(k.grid))
     return out
+
+
+def shared_launches(step):
+    """How many launches of several products of 256x256 tiles `step` makes."""
+    return sum("gemm_bf16_products_kernel" in name for name in captured(step, names=True))
 
 
 def branches(step):

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import workloads as W
+from gpu_util import branches, forks, shared_launches
 from paper_2302_08005_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -54,13 +55,23 @@ def test_captured_step_replays_to_the_same_bits(cfg):
             assert torch.equal(g, w), (replay, i)
 
 
-# above the size from which backward forks onto the helper stream (CASES stay below it): once, and with every weight gradient
-@pytest.mark.parametrize("cfg", [
-    W.LayerConfig("graph-two-streams-postln-bf16", 6, 381, 768, 12, 3072, causal=0, dropout_p=0.1, dtype=W.BF16, len_lo=50, len_hi=381, config_id=53),
-    W.LayerConfig("graph-two-streams-llama-bf16-checkpoint", 4, 256, 1024, 8, 2752, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1,
-                  ln_eps=1e-6, arch=W.LLAMA, config_id=54),
-    W.LayerConfig("graph-forked-postln-bf16", 5, 1000, 512, 8, 1024, causal=0, dropout_p=0.1, dtype=W.BF16, len_lo=300, len_hi=1000, config_id=55),
-    W.LayerConfig("graph-forked-preln-bf16-checkpoint", 5, 1000, 256, 4, 512, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, config_id=56),
-], ids=lambda c: c.name)
-def test_captured_step_on_two_streams_replays_to_the_same_bits(cfg):
+# above the size from which backward forks onto the helper stream (CASES stay below it): once beside paired launches, twice beside launches
+# of several products, and with every weight gradient; the gated layer that shares launches does not fork
+@pytest.mark.parametrize("cfg,forked,shared", [
+    (W.LayerConfig("graph-paired-postln-bf16", 4, 512, 512, 8, 1024, causal=0, dropout_p=0.1, dtype=W.BF16, len_lo=50, len_hi=512, config_id=57), 1, 0),
+    (W.LayerConfig("graph-two-streams-postln-bf16", 6, 381, 768, 12, 3072, causal=0, dropout_p=0.1, dtype=W.BF16, len_lo=50, len_hi=381, config_id=53), None, 1),
+    (W.LayerConfig("graph-shared-llama-bf16", 4, 300, 2048, 4, 1360, causal=1, dropout_p=0.0, dtype=W.BF16, pre_ln=1,
+                   ln_eps=1e-6, arch=W.LLAMA, attn_dim=512, config_id=58), 0, 1),
+    (W.LayerConfig("graph-two-streams-llama-bf16-checkpoint", 4, 256, 1024, 8, 2752, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1,
+                   ln_eps=1e-6, arch=W.LLAMA, config_id=54), 3, 0),
+    (W.LayerConfig("graph-forked-postln-bf16", 5, 1000, 512, 8, 1024, causal=0, dropout_p=0.1, dtype=W.BF16, len_lo=300, len_hi=1000, config_id=55), 3, 0),
+    (W.LayerConfig("graph-forked-preln-bf16-checkpoint", 5, 1000, 256, 4, 512, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, config_id=56), 3, 0),
+], ids=lambda c: getattr(c, "name", c))
+def test_captured_step_on_two_streams_replays_to_the_same_bits(cfg, forked, shared):
+    layer = B.Layer(cfg, W.make_params(cfg))
+    x = torch.zeros(cfg.batch, cfg.seq, cfg.hidden, dtype=layer.dt, device="cuda:0")
+    layer.forward(x)
+    dx = torch.empty_like(x)
+    back = lambda: B.slapo_layer_bwd(layer.desc, layer.params, x, None, x, layer.saved, dx, layer.grads, layer.scratch)
+    assert shared_launches(back) == shared and (branches(back) == forked if forked is not None else forks(back))
     test_captured_step_replays_to_the_same_bits(cfg)

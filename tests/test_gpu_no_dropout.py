@@ -21,6 +21,7 @@ CASES = [
     cfg("postln", 3, 67, 256, 4, 520, pre_ln=0, causal=0, len_lo=20, len_hi=67), cfg("preln-fp32", 2, 33, 320, 5, 328, dtype=W.FP32),
     cfg("preln-two-streams", 4, 523, 512, 8, 2048), cfg("postln-two-streams-forked", 5, 1000, 512, 8, 1024, pre_ln=0, causal=0),
     cfg("preln-two-streams-forked", 5, 1000, 512, 8, 1024),
+    cfg("preln-shared", 4, 500, 1024, 16, 4096), cfg("postln-shared-blocks-fp16", 4, 756, 1152, 18, 3456, pre_ln=0, causal=0, dtype=W.FP16),
 ]
 
 
@@ -45,7 +46,8 @@ def test_stacks_without_dropout(c):
     stack_matches(c)
 
 
-@pytest.mark.parametrize("c", [cfg("one-stream", 2, 67, 256, 4, 1000), cfg("forked", 5, 1000, 512, 8, 1024)], ids=lambda c: c.name)
+@pytest.mark.parametrize("c", [cfg("one-stream", 2, 67, 256, 4, 1000), cfg("forked", 5, 1000, 512, 8, 1024),
+                               cfg("shared", 4, 500, 1024, 16, 4096)], ids=lambda c: c.name)
 def test_input_gradient_partly_on_top_of_dy(c):
     """dx from 40 rows into dy on: as with dx on dy, no launch beside the one that writes dx reads dy."""
     layer, T = B.Layer(c, W.make_params(c)), c.batch * c.seq

@@ -3,8 +3,9 @@ vs the same layer with a launch for each (dx on top of x). Ragged tokens, widths
 import pytest
 import torch
 
+import test_gpu_layer
 import workloads as W
-from gpu_util import DEV, TOL, captured, err, to_np
+from gpu_util import DEV, TOL, captured, err, shared_launches, to_np
 from paper_2302_08005_amd import binding as B
 from test_gpu_layer import run_case
 from test_gpu_llama import run_case as run_gated
@@ -49,8 +50,9 @@ def test_gradients_behind_attention(c, cut):
 
 
 # each block's with the gradient of its input
-def test_gradients_of_each_block():
-    c = cfg("blocks", 4, 750, 1536, 16, 4104, attn_dim=1024)
+@pytest.mark.parametrize("dtype", [W.BF16, W.FP16])
+def test_gradients_of_each_block(dtype):
+    c = cfg("blocks", 4, 750, 1536, 16, 4104, dtype, attn_dim=1024)
     layer, T, H, F, A = B.Layer(c, W.make_params(c)), 3000, 1536, 4104, 1024
     gen = torch.Generator(device=DEV).manual_seed(9)
     x, dy = (torch.randn(c.batch, c.seq, H, device=DEV, generator=gen).to(layer.dt) for _ in range(2))
@@ -66,6 +68,11 @@ def test_gradients_of_each_block():
     assert err(x2, to_np(dx)) <= TOL[c.dtype]   # (the same sums in another order, rounded once more on the way)
     for k in W.PARAM_NAMES:
         assert err(layer.grads[k], to_np(want[k])) <= TOL[c.dtype], k
+        layer.grads[k].copy_(want[k])
+    layer.desc.accumulate_grads = 1
+    assert torch.equal(layer.backward(x, None, dy), dx)
+    for k in W.PARAM_NAMES:   # one rounding of the storage type more than twice the first result
+        assert err(layer.grads[k], 2 * to_np(want[k])) <= TOL[c.dtype] / 2, k
 
 
 # the first feed-forward bias's gradient: column sums that the product of the activation gradient leaves behind, by its tiles
@@ -108,5 +115,27 @@ def test_which_layers_share_launches(batch, seq, hidden, together):
     layer = B.Layer(c, W.make_params(c))
     x = torch.zeros(batch, seq, hidden, dtype=layer.dt, device=DEV)
     layer.forward(x)
-    grids = launches(layer, x, x, torch.empty_like(x))
-    assert (with_quarters(tiles((T, H), (H, F), (F, H), (H, H), (3 * H, H)), 0) in grids) == together
+    dx = torch.empty_like(x)
+    assert shared_launches(lambda: B.slapo_layer_bwd(layer.desc, layer.params, x, None, x, layer.saved, dx, layer.grads, layer.scratch)) == together
+    assert (with_quarters(tiles((T, H), (H, F), (F, H), (H, H), (3 * H, H)), 0) in launches(layer, x, x, dx)) == together
+
+
+# checkpointing, and two host threads with a helper stream between them, at sizes that share launches behind attention and by block
+SHARING = [cfg("threads-behind", 4, 500, 1024, 16, 4096, causal=1, pre_ln=1), cfg("threads-blocks", 4, 756, 1152, 18, 3456)]
+
+
+@pytest.mark.parametrize("c,n", list(zip(SHARING, (1, 2))), ids=lambda v: getattr(v, "name", v))
+def test_shared_launches_accumulate_and_recompute(c, n, monkeypatch):
+    layer = B.Layer(c, W.make_params(c))
+    x = torch.zeros(c.batch, c.seq, c.hidden, dtype=layer.dt, device=DEV)
+    layer.forward(x)
+    dx = torch.empty_like(x)
+    assert shared_launches(lambda: B.slapo_layer_bwd(layer.desc, layer.params, x, None, x, layer.saved, dx, layer.grads, layer.scratch)) == n
+    monkeypatch.setattr(test_gpu_layer, "SMALL", [c] * 5)
+    test_gpu_layer.test_layer_is_deterministic_and_accumulates()
+    test_gpu_layer.test_checkpoint_mode_recomputes_to_the_same_bits(0)
+
+
+def test_two_host_threads_with_shared_launches(monkeypatch):
+    monkeypatch.setattr(test_gpu_layer, "SMALL", [None] * 4 + SHARING)
+    test_gpu_layer.test_backward_from_two_host_threads_on_one_device()

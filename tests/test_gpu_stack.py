@@ -13,7 +13,7 @@ import workloads as W
 from oracle import layer as L
 from oracle import llama_layer as LL
 from paper_2302_08005_amd import binding as B
-from gpu_util import DEV, TOL, branches, err, forks
+from gpu_util import DEV, TOL, branches, err, forks, shared_launches
 
 pytestmark = pytest.mark.gpu
 
@@ -218,4 +218,23 @@ def test_stack_with_every_weight_gradient_forked():
     x = torch.zeros(cfg.batch, cfg.seq, cfg.hidden, dtype=st.dt, device=DEV)
     st.forward(x, None)
     assert branches(lambda: st.backward(x, None, x)) >= 3 * N_LAYERS
+    test_stack_matches_oracle_chain_and_single_layer_calls(cfg)
+
+
+# Stacks whose layers share launches of several products: all behind attention (one per layer) or by block (two). The gradients that
+# a pre-LN layer hands down, dropped or not, wait there for the last launch while the helper stream adds up partial rows.
+@pytest.mark.parametrize("cfg,each", [
+    (W.LayerConfig("shared-stack-preln-bf16", 4, 500, 1024, 16, 4096, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, config_id=101), 1),
+    (W.LayerConfig("shared-stack-preln-kept-fp16", 4, 500, 1024, 8, 4096, causal=1, dropout_p=0.0, dtype=W.FP16, pre_ln=1, config_id=102), 1),
+    (W.LayerConfig("shared-stack-preln-blocks-bf16", 4, 756, 1152, 18, 3456, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, config_id=103), 2),
+    (W.LayerConfig("shared-stack-llama-bf16", 4, 300, 2048, 4, 1360, causal=1, dropout_p=0.0, dtype=W.BF16, pre_ln=1, ln_eps=1e-6,
+                   arch=W.LLAMA, attn_dim=512, config_id=104), 1),
+    (W.LayerConfig("shared-stack-llama-blocks-bf16", 4, 706, 2048, 16, 2048, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, ln_eps=1e-6,
+                   arch=W.LLAMA, config_id=105), 2),
+], ids=lambda c: getattr(c, "name", c))
+def test_stack_with_shared_launches(cfg, each):
+    st = B.Stack(cfg, [W.make_params(cfg, layer_id=l) for l in range(N_LAYERS)])
+    x = torch.zeros(cfg.batch, cfg.seq, cfg.hidden, dtype=st.dt, device=DEV)
+    st.forward(x, None)
+    assert shared_launches(lambda: st.backward(x, None, x)) == each * N_LAYERS
     test_stack_matches_oracle_chain_and_single_layer_calls(cfg)
