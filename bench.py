@@ -7,7 +7,8 @@ the CPU oracle timed on the host cores, and under extra.configs the same step fi
 configurations (C3, C4, C5), each with
   - the whole step: ms, samples/s, algorithmic TFLOP/s and the fraction of the bf16 MFMA peak,
   - the GEMM + attention kernels alone: every one of the 12 GEMMs (with its fused epilogue and the tile
-    selection the step uses) and the attention forward / backward launched in isolation; their summed time
+    selection the step uses; those that share a launch in the step as that launch) and the attention forward / backward launched
+    in isolation; their summed time
     against the step's algorithmic GEMM + attention work is the joint MFMA fraction of the kernels' own time,
   - the HBM-bound fused row kernels (forward and backward) over a rotation of disjoint buffer sets of at least
     1 GiB in total, so that no launch finds its operands in the 256 MB last-level cache.
@@ -35,10 +36,10 @@ ROTATE_BYTES = 1 << 30           # the HBM-bound loops walk through at least thi
 # script (figures, scale factors and commands in profiles/), keyed by workload and kernel instance; None where
 # no counter run covers the pair.
 TRAFFIC_BYTES_PER_LAUNCH = {
-    # profiles/layer_step_C2_bert_large_hbm_traffic.txt: 100.77 MB fetched + 7.69 MB written
-    ("C2-bert-large-layer-bf16", "gemm_bf16_kernel<2, 128, 128, 64, 2, 2, 2, 4, 4, false, 0, false, false>"): 108.46e6,
-    # profiles/layer_step_C4_gptneo_2p7b_hbm_traffic.txt: 825.65 MB fetched + 52.43 MB written
-    ("C4-gptneo-2.7b-layer-bf16", "gemm_bf16_kernel<2, 256, 256, 64, 2, 4, 1, 2, 0, false, 0, false, false>"): 878.07e6,
+    # profiles/layer_step_C2_bert_large_hbm_traffic.txt: 285.55 MB fetched + 33.55 MB written
+    ("C2-bert-large-layer-bf16", "gemm_bf16_products_kernel<false, false>"): 319.11e6,
+    # profiles/layer_step_C4_gptneo_2p7b_hbm_traffic.txt: 3683.36 MB fetched + 199.23 MB written
+    ("C4-gptneo-2.7b-layer-bf16", "gemm_bf16_products_kernel<false, false>"): 3882.59e6,
 }
 
 
@@ -181,6 +182,7 @@ def kernel_figures(B, cfg, layer, xd, dyd, sld, seqlens, reps, stream, verbose=F
     res = rnd(T, H)
 
     rows = []   # (name, algorithmic flop, fn, kernel instance)
+    form = B.backward_form(layer.desc)   # which products of backward share launches
 
     def gemm(name, shared, layout, epi, M, N, K, a, b, c, **kw):
         flags = B.GEMM_SHARED if shared else 0
@@ -196,6 +198,12 @@ def kernel_figures(B, cfg, layer, xd, dyd, sld, seqlens, reps, stream, verbose=F
         rows.append((name, 2.0 * M * N * K, lambda: B.slapo_weight_grad(dt, 0, M, N, K, a, b, c, ws),
                      B.slapo_gemm_kernel_name(dt, B.TN, B.EPI_NONE, M, N, K, flags=B.GEMM_SHARED, weight_grad=1, with_ws=1)))
 
+    def shared(*products):
+        ktail = any(p[1] == B.NN and p[4] % 128 for p in products)
+        rows.append(("+".join(p[0] for p in products), sum(2.0 * p[2] * p[3] * p[4] for p in products),
+                     lambda: B.launch_products(dt, [p[1:] for p in products]),
+                     f"gemm_bf16_products_kernel<{str(ktail).lower()}, {str(dt == W.FP16).lower()}>"))
+
     # forward: the GEMM has the chip to itself
     if llama:
         gemm("qkv", False, B.NT, B.EPI_NONE, T, 3 * A, H, n_in, P["wqkv"], ot3a)
@@ -208,24 +216,38 @@ def kernel_figures(B, cfg, layer, xd, dyd, sld, seqlens, reps, stream, verbose=F
         gemm("ffn1+bias+act", False, B.NT, B.EPI_BIAS_ACT, T, F, H, n_in, P["w1"], og, bias=P["b1"],
              aux_out=(otf if act == W.GELU else None))
     gemm("ffn2", False, B.NT, B.EPI_NONE, T, H, F, g, P["w2"], oth)
-    # backward: the data-gradient chain shares the chip with the weight gradients of the helper stream
+    # backward: with a launch per product the data-gradient chain shares the chip with the weight gradients of the helper stream
+    beside = form == B.APART
     if llama:
-        gemm("dG+dgate", True, B.NN, B.EPI_DGATE, T, F, H, th, P["w2"], otf, aux_in=u)
+        gemm("dG+dgate", beside, B.NN, B.EPI_DGATE, T, F, H, th, P["w2"], otf, aux_in=u)
     else:
-        gemm("dG+dact", True, B.NN, B.EPI_DACT, T, F, H, th, P["w2"], otf, aux_in=(u if u is not None else g))
-    if post:
-        gemm("dY1+add", True, B.NN, B.EPI_ADD, T, H, F1, tf, P["w1"], oth, aux_in=res)
+        gemm("dG+dact", beside, B.NN, B.EPI_DACT, T, F, H, th, P["w2"], otf, aux_in=(u if u is not None else g))
+    if form != B.BLOCKS:
+        if post:
+            gemm("dY1+add", beside, B.NN, B.EPI_ADD, T, H, F1, tf, P["w1"], oth, aux_in=res)
+        else:
+            gemm("dN2", beside, B.NN, B.EPI_NONE, T, H, F1, tf, P["w1"], oth)
+    gemm("dA", beside, B.NN, B.EPI_NONE, T, A, H, th, P["wo"], ota)
+    if form == B.APART:
+        if post:
+            gemm("dX+add", beside, B.NN, B.EPI_ADD, T, H, 3 * A, t3a, P["wqkv"], oth, aux_in=res)
+        else:
+            gemm("dN1", beside, B.NN, B.EPI_NONE, T, H, 3 * A, t3a, P["wqkv"], oth)
+        wgrad("dW2", H, F, T, th, g)
+        wgrad("dW1", F1, H, T, tf, n_in)
+        wgrad("dWo", H, A, T, th, attn)
+        wgrad("dWqkv", 3 * A, H, T, t3a, n_in)
     else:
-        gemm("dN2", True, B.NN, B.EPI_NONE, T, H, F1, tf, P["w1"], oth)
-    gemm("dA", True, B.NN, B.EPI_NONE, T, A, H, th, P["wo"], ota)
-    if post:
-        gemm("dX+add", True, B.NN, B.EPI_ADD, T, H, 3 * A, t3a, P["wqkv"], oth, aux_in=res)
-    else:
-        gemm("dN1", True, B.NN, B.EPI_NONE, T, H, 3 * A, t3a, P["wqkv"], oth)
-    wgrad("dW2", H, F, T, th, g)
-    wgrad("dW1", F1, H, T, tf, n_in)
-    wgrad("dWo", H, A, T, th, attn)
-    wgrad("dWqkv", 3 * A, H, T, t3a, n_in)
+        aux = res if post else None
+        ow = [torch.empty(m, n, device="cuda", dtype=tdt) for m, n in ((H, F), (F1, H), (H, A), (3 * A, H))]
+        ffn_weights = [("dW2", B.TN, H, F, T, th, g, ow[0], None), ("dW1", B.TN, F1, H, T, tf, n_in, ow[1], None)]
+        attn_weights = [("dWo", B.TN, H, A, T, th, attn, ow[2], None), ("dWqkv", B.TN, 3 * A, H, T, t3a, n_in, ow[3], None)]
+        of_attn = ("dX+add" if post else "dN1", B.NN, T, H, 3 * A, t3a, P["wqkv"], oth, aux)
+        if form == B.BLOCKS:
+            shared(*ffn_weights, ("dY1+add" if post else "dN2", B.NN, T, H, F1, tf, P["w1"], oth, aux))
+            shared(*attn_weights, of_attn)
+        else:
+            shared(*ffn_weights, *attn_weights, of_attn)
     n_gemm = len(rows)
     lse_o, delta, dqkv = torch.empty_like(lse), torch.empty_like(lse), torch.empty_like(qkv)
     _, gemm_fwd, att_fwd = layer_flops(cfg, seqlens)
@@ -253,11 +275,12 @@ def kernel_figures(B, cfg, layer, xd, dyd, sld, seqlens, reps, stream, verbose=F
              "attention_bwd_tflops": kernels["attention bwd"]["tflops"],
              "gemm_attention_tflops": joint_tf, "gemm_attention_frac_of_mfma_peak": joint_tf / MFMA_BF16_PEAK_TFLOPS}
 
-    # Dominant kernel: the weight-gradient (TN) GEMM instance that takes the most time per step (dW2, dW1, dWqkv and,
-    # where it is the same instance, dWo), launched through slapo_weight_grad exactly as the layer's backward does.
+    # Dominant kernel: the instance with weight gradients that takes the most time per step: a launch of several products where the
+    # layer shares launches, else the (TN) instance of dW2, dW1, dWqkv and, where it is the same one, dWo, launched through
+    # slapo_weight_grad as the layer's backward does.
     symbol, (flop, ms, n, names) = max(by_symbol.items(), key=lambda kv: kv[1][1])
     achieved = flop / (ms * 1e-3) / 1e12
-    roofline = {"bound": "mfma", "kernel": f"{symbol} (weight gradients {', '.join(names)})",
+    roofline = {"bound": "mfma", "kernel": f"{symbol} ({'weight gradients ' if form == B.APART else ''}{', '.join(names)})",
                 "achieved": achieved, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / MFMA_BF16_PEAK_TFLOPS, "traffic": TRAFFIC_BYTES_PER_LAUNCH.get((cfg.name, symbol)),
                 "avg_launch_us": ms * 1e3 / n, "flop_per_launch": flop / n}

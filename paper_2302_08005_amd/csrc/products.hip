@@ -3,9 +3,10 @@
 // ones, which read twice the bytes from LDS per multiply. Together they fill rounds of the large tiles. Which calls: products_together
 // (api.hip). What bounds it: the matrix cores under the chip's power limit (1.3 us per 64-deep slab with all CUs busy, 1.0 with a
 // quarter of them) and 8-10 us per tile of first loads and last stores.
-// us, alone / together (operands in the last-level cache):
-//   T = 4096, hidden 1024, FFN 4096: dX (NN, K = 3072) and the four weight gradients, 256 tiles 139 / 95; T = 16384 of it, 448 tiles
-//   435 / 390; T = 2048, hidden 4096, attention 512, FFN 1376: 158 / 119; T = 8192, hidden 2560, FFN 10240, 1520 tiles 1210 / 1170;
+// us, alone / together (the same operands again and again, so that the last-level cache holds those of the smaller ones):
+//   T = 4096, hidden 1024, FFN 4096: dX (NN, K = 3072) and the four weight gradients, 256 tiles 139 / 95 (in the step, with operands from
+//   memory and a pass over dQKV beside it, the launch takes 113-130); T = 16384 of it, 448 tiles 435 / 390 (375-385 in the step); T = 2048,
+//   hidden 4096, attention 512, FFN 1376, 528 tiles: 158 / 105-109 (122 in the step); T = 8192, hidden 2560, FFN 10240, 1520 tiles 1210 / 1170;
 //   whole rounds by themselves gain nothing (8192, hidden 2048, FFN 8192: 707 / 733; the tiles of several rounds drift apart).
 #include <algorithm>
 
@@ -34,8 +35,9 @@ struct ProductArgs {
 // tiles (192 tiles of three products: 367 / 350); longer ones go by product (1200 tiles, K = 8192: 990 / 957).
 //
 // The tiles that would end alone come in quarters, 128x128 tiles of the same eight wavefronts on 128-deep slabs, which take a third of
-// a tile's time (gemm.hip has them for single products): 400 tiles of 2048 tokens, hidden 4096, FFN 1376, end on 16 that start when
-// the others are through their second; 117 -> 99 us. The quarters of a tile go to one XCD.
+// a tile's time (gemm.hip has them for single products): 528 tiles of 2048 tokens, hidden 4096, attention 512, FFN 1376, end on 16 that
+// start when the others are through their second; 126 -> 105 us, 138 -> 148 with all operands from memory, backward 290 -> 275. Over 45
+// layers that cut 1 to 32 tiles backward takes 0.90 to 1.01 of what it takes with whole ones. The quarters of a tile go to one XCD.
 template <int LAYOUT, bool KTAIL, bool F16>
 __device__ __forceinline__ void product_tile(bool quarter, int m0, int n0, int M, int N, int K, const bf16_t* A, const bf16_t* B, bf16_t* C,
                                              const bf16_t* aux) {
