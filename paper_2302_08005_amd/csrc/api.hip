@@ -225,15 +225,20 @@ namespace slapo {
 
 // Whether the weight gradients of backward share launches of 256x256 tiles with each other and with data gradients (launch_products),
 // all on the caller's stream, and which: the gradient of the layer's input and all four behind the attention kernels (BEHIND), or those
-// of each block with the gradient of the block's input (BLOCKS; the better form at equal slabs, fewer tiles drift apart). Classic layers:
-// decided by what either form takes in slabs of such a tile. Shared, the launches as they fill rounds (products_slabs) and the two products
+// of each block with the gradient of the block's input (BLOCKS; the better form at equal slabs, fewer tiles drift apart). Decided
+// by what either form takes in slabs of such a tile. Shared, the launches as they fill rounds (products_slabs) and the two products
 // that then have the chip to themselves; apart, the tiles of all products spread over the chip, because two streams fill each other's
 // thin rounds. Where the gradient of the second feed-forward weight alone has tiles for three quarters of the chip, the two streams run
-// the same large tiles and hide more behind each other: 7 % and 12 slabs between the estimates. Elsewhere they run 128x128 tiles and pay
-// for forks and launches: 12 % and 22 slabs the other way. The lines are those that cost least over 733 sizes (1024 to 16384 tokens,
-// hidden 512 to 4096, any feed-forward width): 33 are more than 1 % slower than apart (8 % at most), 81 would be that much faster
-// together; with the work in the shared launches in place of the second estimate it was 76 (13 %) and 142. The gated layer gains
-// less (it has no sums that would leave the chain, and wide products, which two streams overlap well) and has lines over that work.
+// the same large tiles and hide more behind each other: 7 % and 12 slabs between the estimates (12 % where only the gradient of the gated
+// layer's first feed-forward weight, twice as wide, is as large). Elsewhere they run 128x128 tiles and pay for forks and launches: 12 % and 22
+// slabs the other way; the gated layer has no sums that would leave the chain: 10 % and 8 slabs, but where sharing takes at most
+// 76 slabs, the calls for two streams cost the host more than that (140 us; from hidden 512 on, where it was measured). Its calls on one
+// stream pair gradients, which is faster there (77 / 96).
+// Classic layers: the lines are those that cost least over 733 sizes (1024 to 16384 tokens, hidden 512 to 4096, any feed-forward width);
+// over 2367 others 74 are more than 1 % slower than apart (7 % at most), 202 would be that much faster together, and backward takes 0.4 %
+// more than with the faster form of each. Gated: over 3721 sizes 127 are more than 1 % slower than apart (12 % at most) and 478 would be that
+// much faster together; with lines over the work in the shared launches, as before, it was 111 and 741, and 1.7 % over the faster forms
+// where it is 0.8 now.
 // Backward, us, apart / together; "hidden,FFN[,attention]: tokens"; "!": the slower one is taken:
 //   classic  576,2304: 1536 99/103!; 640,2560: 1408 114/116!, 2660 142/136!, 3800 188/184!, 5700 238/235!, 8000 337/387; 768,2048: 2700 173/177!;
 //     768,3072: 1520 120/127, 1900 133/135, 2280 146/139, 3072 202/188, 3800 225/191, 5700 283/298, 8000 394/414, 16000 705/745;
@@ -249,41 +254,42 @@ namespace slapo {
 //     4096 1607/1598, 6144 2471/2341, 8192 3216/3116; 3392,9048: 8100 3454/3506!; 3392,11968: 3000 1522/1551!; 3456,13824: 4096 2046/2092;
 //     3520,9384: 4096 1846/1895; 3712,14848: 3696 2134/2192!; 3776,15104: 2000 1291/1249!; 3840,9736: 1024 658/644; 4096,16384: 1024 870/854,
 //     1536 1176/1160, 2048 1466/1411, 2560 1791/1750, 3072 2108/2033, 3584 2355/2385!, 4096 2668/2595;
-//   gated  512,1368: 2048 139/108!; 576,1536: 3072 145/156; 768,2048: 1500 136/129!, 2000 135/134, 2500 152/152, 3000 164/169, 4000 191/201;
-//     832,2216: 5500 325/337; 960,2560: 3072 214/201, 3584 227/214, 4000 294/271; 1024,2728: 5439 419/387; 1024,2736: 1500 158/162, 2000 182/176!,
-//     2500 194/193, 4000 293/264, 8000 537/514; 1216,400,128: 8192 198/243; 1536,4096: 1500 242/255, 2000 289/311, 2500 356/369, 3000 410/421,
-//     4000 512/489, 8000 968/957; 1728,2304,832: 4608 437/415!; 1856,4952: 4500 872/904!; 1920,1280,448: 2000 152/146; 1984,5288: 2664 612/585,
-//     11776 2294/2165, 14500 2932/2749; 2048,1360,512: 13500 839/787; 2048,5504: 1500 384/399, 2000 502/458, 4000 864/802, 8000 1556/1483;
-//     2112,2816,1024: 1024 187/202; 2368,784,256: 1024 145/113; 2496,6656: 4000 1174/1131!; 2560,3408,1280: 12800 2159/1898; 2624,7000: 2331 836/862;
-//     3072,2048,768: 7326 879/826; 3968,2640,960: 5661 1105/1058; 4096,1376,512: 2048 289/276, 4096 509/478; 4096,2752,1024: 2048 477/444,
-//     4096 819/774; 4096,5504,2048: 4096 1399/1415; 4096,11008: 2048 1450/1453, 3000 2075/2071, 4096 2683/2683.
+//   gated  512,1368: 2048 139/108; 576,1280: 16304 752/892; 576,1536: 3072 145/156, 10200 471/550; 768,1704: 9992 533/583; 768,2040: 2752
+//     183/186; 768,2048: 1192 149/127!, 1500 136/129!, 1552 135/138, 2000 135/134, 2500 152/152, 3000 164/169, 4000 191/201, 14816 858/917;
+//     832,2216: 5500 325/337; 896,2392: 10336 771/787; 960,2560: 2408 189/184!, 3072 214/201, 3584 227/214, 4000 294/271; 1024,2280: 6320
+//     463/445; 1024,2728: 1752 179/180, 5439 419/387, 6424 499/494, 7432 580/554, 11328 931/864; 1024,2736: 1500 158/162, 2000 182/176!, 2500
+//     194/193, 4000 293/264, 8000 537/514; 1024,3384: 1944 204/197; 1088,360,128: 4040 137/159; 1152,3728: 1312 198/201; 1152,4016: 2608
+//     297/310; 1216,400,128: 8192 198/243; 1280,2376,640: 1192 151/144!; 1472,488,128: 4416 169/201; 1536,4096: 1500 242/255, 2000 289/311,
+//     2500 356/369, 3000 410/421, 4000 512/489, 4488 578/618!, 8000 968/957, 14712 2251/2100; 1600,2888,768: 8288 825/832; 1664,4440: 2800
+//     492/485!, 3408 596/589; 1728,2304,832: 4608 437/415!; 1792,4776: 9168 1670/1558; 1856,4952: 4500 872/904!; 1920,1280,448: 2000 152/146;
+//     1920,6264: 9264 2161/2123!; 1984,5288: 2664 612/585, 5248 1147/1125, 11776 2294/2165, 14500 2932/2749; 2048,552,256: 3104 169/174;
+//     2048,1360,512: 13500 839/787; 2048,5504: 1500 384/399, 2000 502/458, 4000 864/802, 8000 1556/1483; 2112,2816,1024: 1024 187/202, 7488
+//     943/930!; 2176,5800: 1224 373/402, 11664 3215/3160!; 2240,5976: 3064 784/797; 2368,784,256: 1024 145/113; 2496,6656: 4000 1174/1131!,
+//     4088 1236/1194!; 2560,3408,1280: 12800 2159/1898; 2624,7000: 2331 836/862; 3072,2048,768: 7326 879/826; 3072,8192: 5816 2416/2390!;
+//     3584,9560: 1560 1024/1036; 3840,3768,960: 4288 980/988; 3904,5200,1920: 5248 1861/1848; 3968,2640,960: 5661 1105/1058; 4096,1376,512:
+//     2048 289/276, 4096 509/478; 4096,2752,1024: 2048 477/444, 4096 819/774; 4096,5504,2048: 4096 1399/1415!; 4096,11008: 2048 1450/1453,
+//     3000 2075/2071, 4096 2683/2683.
 enum Together { APART, BEHIND, BLOCKS };
 Together products_together(const slapo_layer_desc* d) {
-  // (Fewer than 1024 tokens: of 150 sizes measured there the lines below would have four share, us apart / together: gated, 512 tokens of
-  // width 3712, attention 896 170 / 177, 832 of 2240, 512 146 / 133, of 3264, 384 148 / 139; classic, 1016 of 3840 769 / 742; and 576 gated
-  // ones of 3072, 768 two layers 540 / 547. The others are up to twice as slow together. What the count takes is the host's, which small calls wait for.)
-  if (d->dtype == SLAPO_FP32 || (int64_t)d->batch * d->seq < 1024) return APART;
+  // (Fewer than 1024 tokens: of 150 sizes measured there the lines below would have two share: gated, 1016 tokens of width 640
+  // 150 / 109; classic, 1016 of 3840 769 / 742. The others are up to twice as slow together, products
+  // come in K ranges there, and what the count takes is the host's, which small calls wait for.)
+  if (d->dtype == SLAPO_FP32 || (int64_t)d->batch * d->seq < 1024 || (is_llama(d) && backward_on_one_stream(d))) return APART;
   const int T = d->batch * d->seq, H = d->hidden, F = d->ffn, A = attn_width(d), F1 = is_llama(d) ? 2 * F : F;
   const auto sizes = [](int layout, int M, int N, int K) { return Product{layout, M, N, K, nullptr, nullptr, nullptr, nullptr}; };
   const Product x = sizes(GEMM_NN, T, H, 3 * A), y = sizes(GEMM_NN, T, H, F1), w2 = sizes(GEMM_TN, H, F, T), w1 = sizes(GEMM_TN, F1, H, T),
                 wo = sizes(GEMM_TN, H, A, T), wqkv = sizes(GEMM_TN, 3 * A, H, T);
   const Product behind[] = {x, w2, w1, wo, wqkv}, first[] = {y, w2, w1}, second[] = {x, wo, wqkv};
-  int64_t total = 0, ignored = 0;
-  const int in_blocks = products_slabs(3, first, &total) + products_slabs(3, second, &total);
-  const int at_end = products_slabs(5, behind, &ignored) + gemm_slabs(GEMM_NN, T, H, F1);
+  const int in_blocks = products_slabs(3, first) + products_slabs(3, second);
+  const int at_end = products_slabs(5, behind) + gemm_slabs(GEMM_NN, T, H, F1);
   const bool blocks = in_blocks <= 1.02 * at_end;
-  const bool large_alone = (int64_t)((H + 255) / 256) * ((F + 255) / 256) >= 192;
-  if (is_llama(d)) {
-    const double slabs = blocks ? in_blocks : at_end, work = (double)total / 256.0;
-    if (slabs > (large_alone ? 1.025 * work : work < 90.0 ? work + 26.0 : 1.13 * work)) return APART;
-    if (slabs > 2.25 * work) return APART;   // (not where the tiles of all products together leave most of the chip idle)
-  } else {
-    const double shared = (blocks ? in_blocks : at_end) + gemm_slabs(GEMM_NN, T, F, H) + gemm_slabs(GEMM_NN, T, A, H);
-    double apart = gemm_slabs_beside(GEMM_NN, T, F, H) + gemm_slabs_beside(GEMM_NN, T, A, H);
-    for (const Product& p : {x, y, w2, w1, wo, wqkv}) apart += gemm_slabs_beside(p.layout, p.M, p.N, p.K);
-    if (shared > (large_alone ? 1.07 * apart - 12.0 : 1.12 * apart + 22.0)) return APART;
-  }
-  return blocks ? BLOCKS : BEHIND;
+  const auto large_alone = [&](int ffn) { return (int64_t)((H + 255) / 256) * ((ffn + 255) / 256) >= 192; };
+  const double shared = (blocks ? in_blocks : at_end) + gemm_slabs(GEMM_NN, T, F, H) + gemm_slabs(GEMM_NN, T, A, H);
+  double apart = gemm_slabs_beside(GEMM_NN, T, F, H) + gemm_slabs_beside(GEMM_NN, T, A, H);
+  for (const Product& p : {x, y, w2, w1, wo, wqkv}) apart += gemm_slabs_beside(p.layout, p.M, p.N, p.K);
+  const double line = large_alone(F) ? 1.07 * apart - 12.0 : large_alone(F1) ? 1.12 * apart - 12.0
+                      : is_llama(d) ? std::max(1.1 * apart + 8.0, H >= 512 ? 76.0 : 0.0) : 1.12 * apart + 22.0;
+  return shared > line ? APART : blocks ? BLOCKS : BEHIND;
 }
 
 }  // namespace slapo

@@ -61,8 +61,8 @@ void launch_weight_grad(int dtype, int accumulate, int M, int N, int K, const vo
 constexpr int MAX_PRODUCTS = 5, TILE_SLABS = 6;   // TILE_SLABS: what a tile takes besides its 64-deep slabs, in such slabs
 struct Product { int layout, M, N, K; const void *A, *B; void* C; const void* aux; };
 void launch_products(int dtype, int n, const Product* products, hipStream_t st);
-// how long the launch takes, in 64-deep slabs of one tile; *work += the same summed over its tiles (sizes only, no pointers)
-int products_slabs(int n, const Product* products, int64_t* work);
+// how long the launch takes, in 64-deep slabs of one tile (sizes only, no pointers)
+int products_slabs(int n, const Product* products);
 // the same for a product (NN, 16-bit) that has a launch of its own and the chip to itself
 int gemm_slabs(int layout, int M, int N, int K);
 // and for one that another stream's tiles run beside (backward with a launch for each product)

@@ -119,11 +119,10 @@ ProductPlan plan_of(int n, const Product* p) {
 
 }  // namespace
 
-int products_slabs(int n, const Product* products, int64_t* work) {
+int products_slabs(int n, const Product* products) {
   Product p[MAX_PRODUCTS];
   std::copy(products, products + n, p);
   longest_first(n, p);
-  for (int i = 0; i < n; ++i) *work += (int64_t)tiles_of(p[i]) * (slabs_of(p[i]) + TILE_SLABS);
   return plan_of(n, p).slabs;
 }
 
