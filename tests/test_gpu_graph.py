@@ -60,7 +60,7 @@ def test_captured_step_replays_to_the_same_bits(cfg):
 @pytest.mark.parametrize("cfg,forked,shared", [
     (W.LayerConfig("graph-paired-postln-bf16", 4, 512, 512, 8, 1024, causal=0, dropout_p=0.1, dtype=W.BF16, len_lo=50, len_hi=512, config_id=57), 1, 0),
     (W.LayerConfig("graph-two-streams-postln-bf16", 6, 381, 768, 12, 3072, causal=0, dropout_p=0.1, dtype=W.BF16, len_lo=50, len_hi=381, config_id=53), None, 1),
-    (W.LayerConfig("graph-shared-llama-bf16", 4, 300, 2048, 4, 1360, causal=1, dropout_p=0.0, dtype=W.BF16, pre_ln=1,
+    (W.LayerConfig("graph-shared-llama-bf16", 4, 375, 2048, 4, 1360, causal=1, dropout_p=0.0, dtype=W.BF16, pre_ln=1,
                    ln_eps=1e-6, arch=W.LLAMA, attn_dim=512, config_id=58), 0, 1),
     (W.LayerConfig("graph-two-streams-llama-bf16-checkpoint", 4, 256, 1024, 8, 2752, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1,
                    ln_eps=1e-6, arch=W.LLAMA, config_id=54), 3, 0),

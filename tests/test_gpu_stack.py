@@ -227,7 +227,7 @@ def test_stack_with_every_weight_gradient_forked():
     (W.LayerConfig("shared-stack-preln-bf16", 4, 500, 1024, 16, 4096, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, config_id=101), 1),
     (W.LayerConfig("shared-stack-preln-kept-fp16", 4, 500, 1024, 8, 4096, causal=1, dropout_p=0.0, dtype=W.FP16, pre_ln=1, config_id=102), 1),
     (W.LayerConfig("shared-stack-preln-blocks-bf16", 4, 756, 1152, 18, 3456, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, config_id=103), 2),
-    (W.LayerConfig("shared-stack-llama-bf16", 4, 300, 2048, 4, 1360, causal=1, dropout_p=0.0, dtype=W.BF16, pre_ln=1, ln_eps=1e-6,
+    (W.LayerConfig("shared-stack-llama-bf16", 4, 375, 2048, 4, 1360, causal=1, dropout_p=0.0, dtype=W.BF16, pre_ln=1, ln_eps=1e-6,
                    arch=W.LLAMA, attn_dim=512, config_id=104), 1),
     (W.LayerConfig("shared-stack-llama-blocks-bf16", 4, 706, 2048, 16, 2048, causal=1, dropout_p=0.1, dtype=W.BF16, pre_ln=1, ln_eps=1e-6,
                    arch=W.LLAMA, config_id=105), 2),
